@@ -50,6 +50,11 @@ constexpr int64_t LARGE_GRID_BYTES = 1LL << 30;   // grids from this size on get
 constexpr int64_t CACHED_GRID_BYTES = 124LL << 20;
 constexpr int64_t CACHED_CHUNK_BYTES = 24LL << 20;  // cache-resident 2-D grids from this size on: XCD chunks of 32
 
+// Scatter: consecutive workgroups one XCD takes (16384^2: 797 us in the hardware's order, 806 with 16, 765 with 32, 752
+// with 64; 1024 x 1024 x 768: 2463, 2382, 2399, 2422; small grids the same with all).  The x halo arrays fill in runs of
+// 16 cells and less per workgroup, which then meet in one L2.
+constexpr int SG_XCD_CHUNK = 32;
+
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -709,29 +714,71 @@ int launch_boundary_sync(jacobi_plan *p, const void *in, void *out, hipStream_t 
                                       : launch_boundary_t<float>(p, (const float *)in, (float *)out, st);
 }
 
-template <typename T, bool GATHER>
-int launch_sg_t(jacobi_plan *p, const T *from, T *to, hipStream_t st)
+template <typename T>
+int launch_scatter_t(jacobi_plan *p, const T *from, T *grid, hipStream_t st)
 {
     const Geo &g = p->geo;
-    const long long GP = p->lay.dims[2] + 2, GQ = (p->lay.dims[1] + 2) * GP;
-    const int64_t nrows = (int64_t)g.ntiles * g.nplanes * g.rows;
-    if (nrows > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many tile rows for one scatter / gather launch");
-    const int cols = g.tw + 2;
-    // a wavefront per row and chunk of up to 256 cells, four per lane in flight (fewer for narrower tiles)
-    const int q = (int)std::min<int64_t>(4, ceil_div(cols, jk::WAVE));
-    const int64_t nchunks = ceil_div(cols, q * jk::WAVE), nitems = nrows * nchunks;
-    const int64_t nwg = ceil_div(nitems, jk::WAVES_PER_WG);
-    if (nitems > 0xfffffff0LL) return fail(JACOBI_EINVAL, "too many row chunks for one scatter / gather launch");
-#define JK_SG(Q_) \
-    hipLaunchKernelGGL((jk::scatter_gather_kernel<T, GATHER, Q_>), dim3((unsigned)nwg), dim3(jk::WG), 0, st, g, from, to, \
-                       GP, GQ, (unsigned)nchunks, (unsigned)nitems)
+    const int nv = 16 / (int)sizeof(T);
+    if ((int64_t)g.ntiles * g.nplanes * g.rows > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many tile rows for one scatter / gather launch");
+    jk::ScatterParams sp;
+    sp.GP = p->lay.dims[2] + 2;
+    sp.GQ = (p->lay.dims[1] + 2) * sp.GP;
+    sp.vrow = (unsigned)ceil_div(g.tw, nv);
+    sp.nvec = (unsigned)g.nplanes * (unsigned)g.rows * sp.vrow;
+    sp.wg_per_tile = (unsigned)ceil_div(sp.nvec, jk::SG_UNIT);
+    sp.by_vrow.set(sp.vrow);
+    sp.by_rows.set((unsigned)g.rows);
+    sp.xcd_chunk = SG_XCD_CHUNK;
+    const int64_t nwg = (int64_t)g.ntiles * sp.wg_per_tile;
+    if (nwg > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many workgroups for one scatter / gather launch");
+    const dim3 blocks((unsigned)nwg), threads(jk::WG);
+    if (store_flavour(p)) hipLaunchKernelGGL((jk::scatter_kernel<T, true>), blocks, threads, 0, st, g, sp, from, grid);
+    else hipLaunchKernelGGL((jk::scatter_kernel<T, false>), blocks, threads, 0, st, g, sp, from, grid);
+    HIP_TRY(hipGetLastError());
+    return JACOBI_OK;
+}
+
+template <typename T>
+int launch_gather_t(jacobi_plan *p, const T *grid, T *to, hipStream_t st)
+{
+    const Geo &g = p->geo;
+    const int nv = 16 / (int)sizeof(T);
+    if ((int64_t)g.ntiles * g.nplanes * g.rows > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many tile rows for one scatter / gather launch");
+    jk::GatherParams gp;
+    gp.GP = (unsigned)(p->lay.dims[2] + 2);
+    gp.plane_rows = (unsigned)(p->lay.dims[1] + 2);
+    const int line = jk::LINE_BYTES / (int)sizeof(T);
+    gp.shift = (unsigned)((uintptr_t)to / sizeof(T) % line);
+    // a wavefront per row, up to four vectors per lane; several wavefronts for a longer row.  From 8 on the vectors
+    // of a workgroup's wavefronts alternate (16384^2: 834 us with 4 KiB per wavefront, 778 with 4 KiB per workgroup
+    // and step; shorter rows would leave more lanes without work).
+    const int64_t nrows = (int64_t)gp.plane_rows * (g.ndim == 3 ? p->lay.dims[0] + 2 : 1);
+    const int64_t vecs = ceil_div((int64_t)gp.GP + line - 1, nv);
+    const int q = (int)std::min<int64_t>(jk::SG_VECS, ceil_div(vecs, jk::WAVE));
+    gp.nchunks = (unsigned)ceil_div(vecs, q * jk::WAVE);
+    gp.together = gp.nchunks >= 2 * jk::WAVES_PER_WG ? jk::WAVES_PER_WG : 1;
+    if (gp.together > 1) gp.nchunks = (unsigned)round_up(gp.nchunks, jk::WAVES_PER_WG);
+    if (nrows * gp.nchunks > 0xfffffff0LL) return fail(JACOBI_EINVAL, "too many row chunks for one scatter / gather launch");
+    gp.nitems = (unsigned)(nrows * gp.nchunks);
+    gp.by_chunks.set(gp.nchunks);
+    gp.by_rows.set(gp.plane_rows);
+    gp.by_td.set((unsigned)g.td);
+    gp.by_th.set((unsigned)g.th);
+    gp.by_tw.set((unsigned)g.tw);
+    const dim3 blocks((unsigned)ceil_div(gp.nitems, jk::WAVES_PER_WG)), threads(jk::WG);
+    const bool stream = store_flavour(p) != 0;
+#define JK_GATHER(Q_)                                                                                                        \
+    do {                                                                                                                     \
+        if (stream) hipLaunchKernelGGL((jk::gather_kernel<T, true, Q_>), blocks, threads, 0, st, g, gp, grid, to);           \
+        else hipLaunchKernelGGL((jk::gather_kernel<T, false, Q_>), blocks, threads, 0, st, g, gp, grid, to);                 \
+    } while (0)
     switch (q) {
-    case 1: JK_SG(1); break;
-    case 2: JK_SG(2); break;
-    case 3: JK_SG(3); break;
-    default: JK_SG(4); break;
+    case 1: JK_GATHER(1); break;
+    case 2: JK_GATHER(2); break;
+    case 3: JK_GATHER(3); break;
+    default: JK_GATHER(4); break;
     }
-#undef JK_SG
+#undef JK_GATHER
     HIP_TRY(hipGetLastError());
     return JACOBI_OK;
 }
@@ -990,8 +1037,8 @@ int jacobi_scatter(jacobi_plan *plan, const void *global_padded_dev, void *grid,
     hipStream_t st = (hipStream_t)stream;
     if (int rc = prepare_plan(plan)) return rc;
     return plan->lay.dtype == JACOBI_F64
-               ? launch_sg_t<double, false>(plan, (const double *)global_padded_dev, (double *)grid, st)
-               : launch_sg_t<float, false>(plan, (const float *)global_padded_dev, (float *)grid, st);
+               ? launch_scatter_t<double>(plan, (const double *)global_padded_dev, (double *)grid, st)
+               : launch_scatter_t<float>(plan, (const float *)global_padded_dev, (float *)grid, st);
 }
 
 int jacobi_gather(jacobi_plan *plan, const void *grid, void *global_padded_dev, void *stream)
@@ -1000,8 +1047,8 @@ int jacobi_gather(jacobi_plan *plan, const void *grid, void *global_padded_dev, 
     if (misaligned(grid)) return fail(JACOBI_EINVAL, "grids must be 16-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     return plan->lay.dtype == JACOBI_F64
-               ? launch_sg_t<double, true>(plan, (const double *)grid, (double *)global_padded_dev, st)
-               : launch_sg_t<float, true>(plan, (const float *)grid, (float *)global_padded_dev, st);
+               ? launch_gather_t<double>(plan, (const double *)grid, (double *)global_padded_dev, st)
+               : launch_gather_t<float>(plan, (const float *)grid, (float *)global_padded_dev, st);
 }
 
 int halo_exchange(jacobi_plan *plan, void *grid, void *stream)
