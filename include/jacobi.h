@@ -118,7 +118,9 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * CU count and LDS size and allocates the plan-owned scratch of the residual reduction (one
  * double per workgroup of the largest launch ANY option setting can ask for, so it never has
  * to grow: 8 bytes per 4 one-row strips of about 100 cells at most, 5 MiB for 16384^2; behind
- * it the 16 bytes of the one-launch kernel's barrier words, set to zero here once).
+ * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
+ * blocks, their messages and words (16 to 32 bytes per border cell: 2 MB for 256^2, 37 MB for 1024^2), set
+ * to zero here once).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -376,8 +378,17 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    iterations (each holds that many ghost rows per side, which it recomputes), storing
  *                    their own rows to the other grid and re-reading only the ghost rows.  These phases
  *                    swap the two grids like passes do (jacobi_pass_schedule lists them; read *final).
- *                    The barrier's wait is bounded: if the workgroups cannot all be resident (the device
+ *                    The narrow grids' barrier's wait is bounded: if the workgroups cannot all be resident (the device
  *                    is busy with other work for seconds) the launch still ends and writes NaN.
+ *                    Mid-sized 2-D grids (wider than 64 cells, up to about 2000^2 in fp64, 2400^2 in fp32, also those above
+ *                    that "resident_depth" / "resident_rows" were not set for) run that way too, cut into blocks in
+ *                    both directions: a workgroup keeps a block in registers and exchanges its border with the
+ *                    neighbouring blocks alone, as messages in the plan's scratch (1024^2: 5.4 -> 1.2 us per
+ *                    iteration); jacobi_run is then ONE launch, norms included (128 of them per launch).  There
+ *                    jacobi_pass_schedule still lists the passes of the launch-per-pass path, as which the grids swap
+ *                    roles.  If not all of the launch's workgroups start within a few milliseconds (other work holds
+ *                    CUs), those that did do the work through memory: slower, the same result.  A call takes this path
+ *                    if a fixed estimate of both says it is faster (8 iterations and more of 1024^2).
  *                    The launch is the whole call: it carries the Dirichlet ring over itself, and in
  *                    jacobi_run it also delivers the residual norm of the grid it produced (NaN if the
  *                    barrier gave up).  Two launches of one plan must not overlap in time: they share
@@ -389,7 +400,8 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    registers - 4, or 3 where a lane holds two vectors of a row -, or just enough for a
  *                    grid that fits one workgroup)
  *   "resident_spin_limit"  0 | n  polls a workgroup waits at that barrier before giving up: n - 1
- *                    beyond the first (0 = default, about 4 million: seconds)
+ *                    beyond the first (0 = default, about 4 million: seconds); with blocks: polls before the
+ *                    workgroups that are there go on without the others (0 = default, 2048)
  *   "stack"          0 | 1 | 4 | 8  2-D stand-alone residual pass: wavefronts of a workgroup stacked over
  *                    the same columns, 8 rows each, passing each other their border rows through LDS
  *                    instead of loading them again (0 = choose: 8 on tiles of 1024 rows and more, else

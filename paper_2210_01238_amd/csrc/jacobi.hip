@@ -60,6 +60,18 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
+// How a mid-sized grid is cut into the blocks that one launch keeps in registers (blocks_common.h); fixed by the plan's
+// shape and type.
+struct BlockPlan {
+    bool ok = false;
+    int cells_per_lane = 0, rows_per_wave = 0;
+    jk::BlockCut x, y;
+    int workgroups = 0;
+    int64_t msg_bytes = 0;            // of one of the two message areas
+    int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
+    double us_per_iteration = 0;      // estimate
+};
+
 struct jacobi_plan {
     jacobi_layout lay;
     Geo geo;
@@ -78,6 +90,8 @@ struct jacobi_plan {
     // ask for, plus one slot for the value residual_norm_host copies back.  Never reallocated.
     double *partial = nullptr;
     int64_t partial_cap = 0;
+    BlockPlan blocks;
+    char *block_scratch = nullptr;    // behind those
     unsigned *sync_words = nullptr;   // behind the partial sums: arrival counter and failure flag of the resident kernel
     // profiling events around update launches
     std::vector<hipEvent_t> ev;   // pairs: 2*i start, 2*i+1 stop
@@ -604,6 +618,96 @@ int launch_resident(jacobi_plan *p, const ResidentChoice &c, void *in, void *out
     return launch_checked(jk::launch_resident(p->lay.dtype == JACOBI_F64, c.nseg, c.rw, a), "resident kernel launch");
 }
 
+// ---- mid-sized grids: a whole run in one launch, the grid in registers (blocks2d_kernel.h) -------------------------
+constexpr int BLOCK_NORMS = 128;                 // norms of one launch
+constexpr int BLOCK_MAX_ITERS = 1 << 28;         // iterations of one call (the tags of a launch have to fit 32 bits)
+constexpr int64_t BLOCK_SYNC_BYTES = 256;
+constexpr unsigned ROLL_DEFAULT_LIMIT = 1u << 11;        // polls of about a microsecond each
+
+// Cuts n cells into held ranges of `held`, starts at multiples of `unit`, `d` ghost cells; false if that cannot be done
+// with owned ranges of at least `least` cells.
+bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, jk::BlockCut *c)
+{
+    if (n < held || n % unit || held % unit || d % unit || held <= 2 * d) return false;
+    c->n = (int)n; c->held = held; c->d = d; c->unit = unit;
+    const int units = (int)(n - held) / unit;
+    c->nb = 1 + (int)ceil_div(units, (held - 2 * d) / unit);
+    c->step = c->nb > 1 ? units / (c->nb - 1) : 0;
+    c->longer = c->nb > 1 ? units % (c->nb - 1) : 0;
+    for (int b = 0; b < c->nb; ++b)
+        if (c->nb > 1 && c->own_hi(b) - c->own_lo(b) < least) return false;
+    return true;
+}
+
+// What the model below says a launch per iteration / passes of up to 12 iterations take (us per iteration), and what a
+// launch of a block kernel takes besides its iterations.
+constexpr double BLOCK_LAUNCH_US = 20.0;
+double launch_us_2d(int64_t cell_bytes) { return 3.0 + 0.25e-6 * cell_bytes; }
+double blocked_us_2d(int64_t cells) { return 1.8 + 0.7e-6 * cells; }
+
+// The cut of a 2-D grid with the least time per iteration, by a model fitted to 30 cuts of twelve grids between 300^2 and
+// 2400^2 (within 10 % of what they measured): 0.06 us for the border rows and the barrier, 2.05 ns for each of the
+// instructions a SIMD's two wavefronts issue (4 per cell, 4 or 2 lane shifts per row), and every d iterations an exchange of
+// 2.5 us plus 0.22 us per MB of messages.
+BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
+{
+    struct Variant { int c, rw; double extra64, extra32; bool f32_only; };
+    static const Variant variants[] = {
+#define JK_V(C_, RW_, E64_, E32_) {C_, RW_, E64_, E32_, false},
+        JK_BLOCKS2D_VARIANTS(JK_V)
+#undef JK_V
+#define JK_V(C_, RW_, E64_, E32_) {C_, RW_, E64_, E32_, true},
+        JK_BLOCKS2D_VARIANTS_F32(JK_V)
+#undef JK_V
+    };
+    BlockPlan best;
+    const bool f64 = dtype == JACOBI_F64;
+    const int64_t Nx = (int64_t)g.Tx * g.tw, Ny = (int64_t)g.Ty * g.th;
+    for (const Variant &v : variants) {
+        if (f64 && v.f32_only) continue;
+        const int HW = jk::WAVE * v.c, HH = jk::BLK_WAVES * v.rw;
+        if (Nx <= HW || Ny < HH) continue;
+        for (int d = 4; d <= 16; d += 4) {
+            jk::BlockCut x, y;
+            if (!cut_into_blocks(Nx, HW, d, v.c, 2 * d, &x) || !cut_into_blocks(Ny, HH, d, 1, 2 * d, &y)) continue;
+            if (x.nb < 2 || (int64_t)x.nb * y.nb > num_cu) continue;
+            const double msg = (double)x.nb * y.nb * jk::blocks2d_frame(x, y) * (f64 ? 16 : 8);
+            const double us = 0.06 + 2 * v.rw * (4 * v.c + (f64 ? 4 : 2)) * 0.00205 +
+                              (2.5 + 0.22e-6 * msg + (f64 ? v.extra64 : v.extra32)) / d;
+            if (best.ok && us >= best.us_per_iteration) continue;
+            best.ok = true;
+            best.us_per_iteration = us;
+            best.cells_per_lane = v.c;
+            best.rows_per_wave = v.rw;
+            best.x = x; best.y = y;
+            best.workgroups = x.nb * y.nb;
+            best.msg_bytes = round_up((int64_t)msg, 256);
+        }
+    }
+    // not for grids that the other paths run as fast
+    if (best.ok && best.us_per_iteration > 0.8 * launch_us_2d(Nx * Ny * (f64 ? 8 : 4))) best.ok = false;
+    if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
+    return best;
+}
+
+// Whether a call of so many iterations runs that way: what it saves per iteration has to pay for the launch (1024^2:
+// 3 iterations 20 us by launches against 32, 8 iterations 48 against 19).  `row`: what the kernel for narrow grids
+// (resident2d_kernel) would do with them - if it can run, it takes 0.95 us per iteration and about 6 us less per launch, and it
+// runs where its geometry was asked for by option.
+bool blocks_usable(const jacobi_plan *p, int iters, const ResidentChoice &row)
+{
+    const BlockPlan &b = p->blocks;
+    if (!p->resident || !b.ok || b.workgroups > p->num_cu || iters > BLOCK_MAX_ITERS) return false;
+    const jacobi_layout &L = p->lay;
+    const int64_t cells = L.dims[0] * L.dims[1] * L.dims[2];
+    if (row.ok) {
+        if (p->resident_depth > 0 || p->resident_rows > 0 || row.nwg == 1) return false;
+        return iters * (0.95 - b.us_per_iteration) > 6.0;
+    }
+    const double other = p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
+    return iters * (other - b.us_per_iteration) > BLOCK_LAUNCH_US;
+}
+
 // What the next pass does with `left` iterations to go.  The iterations are spread evenly over
 // few passes of equal depth (10 iterations at depth 8 run as 5 + 5, not 8 + 2: up to depth 8 a
 // pass costs no more for being deeper).  kernel: 0 single step (needs current
@@ -658,6 +762,63 @@ PassChoice choose_pass(const jacobi_plan *p, int left)
         if (t2_usable(p)) return {2, 1};
     }
     return {1, 0};
+}
+
+// Passes jacobi_sweep makes of `iters` iterations: as many as jacobi_pass_schedule lists.
+int64_t count_passes(const jacobi_plan *p, int64_t iters)
+{
+    if (const ResidentChoice row = resident_choice(p, (int)iters); row.ok) return row.nphase;
+    if (p->tblock == 1) return iters;
+    int64_t n = 0;
+    for (int64_t k = 0; k < iters; ++n) k += choose_pass(p, (int)(iters - k)).depth;
+    return n;
+}
+
+// One launch: `iters` iterations, norms of the grids after every `every`-th (0: none).  The result goes to `in` or
+// `out` as the passes of the launch-per-pass path would leave it.
+int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int norms, double *result, bool final_is_out, hipStream_t st)
+{
+    jk::BlockRun run;
+    run.iters = iters;
+    run.every = every;
+    run.norms = norms;
+    run.final_is_out = final_is_out ? 1 : 0;
+    run.roll_limit = p->resident_spin_limit > 0 ? (unsigned)(p->resident_spin_limit - 1) : ROLL_DEFAULT_LIMIT;
+    run.spin_limit = RESIDENT_DEFAULT_SPIN;
+    run.sync = (jk::BlockSync *)p->block_scratch;
+    run.partial = (double *)(p->block_scratch + BLOCK_SYNC_BYTES);
+    run.msg = p->block_scratch + p->blocks.scratch_bytes - 2 * p->blocks.msg_bytes;
+    run.msg_bytes = (unsigned)p->blocks.msg_bytes;
+    run.result = result;
+    jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, run}, in, out};
+    const int c = p->blocks.cells_per_lane, rw = p->blocks.rows_per_wave;
+    return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks2d_f64(c, rw, a) : jk::launch_blocks2d_f32(c, rw, a),
+                          "block kernel launch");
+}
+
+// `iters` iterations of jacobi_run that way, in launches of at most BLOCK_NORMS norms.  *final as jacobi_run leaves it.
+int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double *result, hipStream_t st, void **final)
+{
+    void *cur = in, *other = out;
+    const int64_t per_launch = every > 0 ? (int64_t)every * BLOCK_NORMS : iters;
+    for (int done = 0; done < iters;) {
+        const int n = (int)std::min<int64_t>(per_launch, iters - done);
+        const int norms = every > 0 ? n / every : 0;
+        const int64_t passes = every > 0 ? (int64_t)norms * count_passes(p, every) + count_passes(p, n % every) : count_passes(p, n);
+        const bool to_other = (passes & 1) != 0;
+        const bool timed = p->profile && p->ev_used < MAX_PROFILE_EVENTS;
+        if (timed) HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used], st));
+        const int rc = launch_blocks(p, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
+        if (rc) return rc;
+        if (timed) {
+            HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used + 1], st));
+            ++p->ev_used;
+        }
+        if (to_other) std::swap(cur, other);
+        done += n;
+    }
+    if (final) *final = cur;
+    return JACOBI_OK;
 }
 
 template <typename T>
@@ -828,7 +989,8 @@ int prepare_plan(jacobi_plan *p)
     else (void)hipGetLastError();
     const int64_t need = max_partials(p) + 1;      // + the slot residual_norm_host reads back
     // behind them: two doubles' worth of words for the resident kernel's grid barrier
-    hipError_t e = hipMalloc((void **)&p->partial, (size_t)(need + 2) * sizeof(double));
+    const size_t words_end = (size_t)round_up((need + 2) * (int64_t)sizeof(double), 256);
+    hipError_t e = hipMalloc((void **)&p->partial, p->blocks.ok ? words_end + (size_t)p->blocks.scratch_bytes : (size_t)(need + 2) * sizeof(double));
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         return fail(JACOBI_ENOMEM, "device allocation of residual scratch failed");
@@ -837,10 +999,17 @@ int prepare_plan(jacobi_plan *p)
     p->partial_cap = need;
     p->sync_words = (unsigned *)(p->partial + need);
     // the resident kernel's barrier words are zero between launches: it clears them itself when it finishes
-    e = hipMemset(p->sync_words, 0, 2 * sizeof(double));
+    // so are the block kernels' words, and no message carries a tag yet
+    size_t clear = 2 * sizeof(double);
+    if (p->blocks.ok) {
+        p->block_scratch = (char *)p->partial + words_end;
+        clear = (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words);
+    }
+    e = hipMemset(p->sync_words, 0, clear);
     if (e != hipSuccess) {
         (void)hipFree(p->partial);
         p->partial = nullptr;
+        p->block_scratch = nullptr;
         return fail_hip(e, "hipMemset(barrier words)");
     }
     p->prepared = true;
@@ -990,6 +1159,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
     g.hpitch = L.xhalo_pitch;
     g.xsend = L.xsend_offset;
     g.tile_stride = L.tile_stride;
+    if (ndim == 2) p->blocks = plan_blocks2d(g, dtype, jk::NUM_CU);
     *plan = p;
     return JACOBI_OK;
 }
@@ -1018,7 +1188,9 @@ int jacobi_prepare(jacobi_plan *plan)
 
 size_t jacobi_scratch_bytes(const jacobi_plan *plan)
 {
-    return plan ? (size_t)(max_partials(const_cast<jacobi_plan *>(plan)) + 1 + 2) * sizeof(double) : 0;
+    if (!plan) return 0;
+    const int64_t bytes = (max_partials(const_cast<jacobi_plan *>(plan)) + 1 + 2) * (int64_t)sizeof(double);
+    return (size_t)(plan->blocks.ok ? round_up(bytes, 256) + plan->blocks.scratch_bytes : bytes);
 }
 
 size_t jacobi_grid_bytes(const jacobi_plan *plan) { return plan ? (size_t)plan->lay.grid_bytes : 0; }
@@ -1065,13 +1237,10 @@ struct RunCarry {
     bool x_packed = false;          // its x send arrays hold its first / last columns
 };
 
-// residual_in_dev: if not null, also the residual norm of `in`; residual_out_dev: if not null, also that of the
-// grid the iterations produce.
-static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipStream_t st, void **final,
-                        double *residual_in_dev, RunCarry *carry = nullptr, double *residual_out_dev = nullptr)
+// What has to be there before iterations are enqueued: the plan's device state and, with option profile, its events.
+static int prepare_run(jacobi_plan *plan)
 {
-    int rc = prepare_plan(plan);
-    if (rc) return rc;
+    if (int rc = prepare_plan(plan)) return rc;
     if (plan->profile && plan->ev.empty()) {
         plan->ev.reserve(2 * MAX_PROFILE_EVENTS);
         for (int i = 0; i < 2 * MAX_PROFILE_EVENTS; ++i) {
@@ -1080,10 +1249,21 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
             plan->ev.push_back(e);
         }
     }
+    return JACOBI_OK;
+}
+
+// residual_in_dev: if not null, also the residual norm of `in`; residual_out_dev: if not null, also that of the
+// grid the iterations produce.
+static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipStream_t st, void **final,
+                        double *residual_in_dev, RunCarry *carry = nullptr, double *residual_out_dev = nullptr)
+{
+    int rc = prepare_run(plan);
+    if (rc) return rc;
     ResidentChoice rc_res = resident_choice(plan, iters, residual_out_dev != nullptr);
     const bool norm_in_launch = rc_res.ok && residual_out_dev;
     if (!rc_res.ok && residual_out_dev) rc_res = resident_choice(plan, iters);
-    if (rc_res.ok) {
+    const bool blocks = blocks_usable(plan, iters, rc_res);
+    if (rc_res.ok && !blocks) {
         // small 2-D grid: every iteration inside one launch, which also carries the ring over and delivers the
         // residual of its result; the residual of `in`, if asked for, from the stand-alone reduction first
         if (residual_in_dev) {
@@ -1109,6 +1289,14 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
         if (final) *final = result;
         if (residual_out_dev && !norm_in_launch) return residual_common(plan, result, residual_out_dev, st);
         return JACOBI_OK;
+    }
+    if (blocks) {
+        if (residual_in_dev) {
+            rc = residual_common(plan, in, residual_in_dev, st);
+            if (rc) return rc;
+        }
+        if (carry) *carry = RunCarry{true, false, false};
+        return run_blocks(plan, in, out, iters, residual_out_dev ? iters : 0, residual_out_dev, st, final);
     }
     const PassChoice first = choose_pass(plan, iters);
     int64_t nwg_res = 0;
@@ -1348,6 +1536,11 @@ int jacobi_run(jacobi_plan *plan, void *in, void *out, int iters, int residual_e
     const int nres = residual_every > 0 ? iters / residual_every : 0;
     if (nres > 0 && !residuals_dev) return fail(JACOBI_EINVAL, "residuals_dev is NULL");
     hipStream_t st = (hipStream_t)stream;
+    if (iters > 0 && blocks_usable(plan, iters, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0))) {
+        int rc = prepare_run(plan);
+        if (rc) return rc;
+        return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);
+    }
     void *cur = in, *other = out;
     int done = 0, pending = -1;      // pending: index of a residual still owed for the grid in `cur`
     RunCarry carry;                  // blocks after the first start from what the one before left in the grids

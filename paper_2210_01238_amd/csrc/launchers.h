@@ -124,4 +124,62 @@ struct ResidentLaunch {
 };
 hipError_t launch_resident(bool f64, int nseg, int rows_per_wave, const ResidentLaunch &a);
 
+// ---- mid-sized grids: a whole run in one launch, the grid in the registers of the chip (blocks_common.h) ------------
+// Plan-owned words; all zero between launches except the epoch.
+struct BlockSync {
+    unsigned roll;            // workgroups counted in, ROLL_CLOSED
+    unsigned participants;    // workgroups counted when the roll was closed (0: not yet known)
+    unsigned done;            // workgroups that have finished
+    unsigned barrier;         // plain path: arrivals
+    unsigned failed;          // somebody gave up waiting: results are NaN
+    unsigned epoch;           // number of the last exchange of all launches so far
+};
+
+// What one launch does.
+struct BlockRun {
+    int iters;             // iterations of the launch
+    int every;             // norms of the grids after iterations every, 2*every, ... (0: none)
+    int norms;             // how many of them (iters / every, or 0)
+    int final_is_out;      // the result goes to the grid the launch does not start from
+    unsigned roll_limit, spin_limit;   // polls before the roll is closed / before a wait is given up
+    BlockSync *sync;
+    void *msg;             // two message areas
+    unsigned msg_bytes;    // of one of them
+    double *partial;       // one sum per norm and workgroup
+    double *result;        // the norms
+};
+
+// Cut of one dimension into blocks: held ranges of `held` cells start at start(b), multiples of `unit` evenly spread over
+// the n cells; a block owns what lies d behind the start of its range up to d behind the start of the next one.
+struct BlockCut {
+    int n, held, nb, d, unit, step, longer;        // steps between starts in units: the first `longer` ones step + 1
+    __host__ __device__ int start(int b) const { return (b * step + (b < longer ? b : longer)) * unit; }
+    __host__ __device__ int own_lo(int b) const { return b == 0 ? 0 : start(b) + d; }
+    __host__ __device__ int own_hi(int b) const { return b == nb - 1 ? n : start(b + 1) + d; }
+};
+
+struct Blocks2d {
+    BlockCut x, y;
+    BlockRun run;
+};
+
+constexpr int BLK_WAVES = 8;
+// cells of a block's message: the d first and last rows (full held width), the d first and last columns
+__host__ __device__ inline unsigned blocks2d_frame(const BlockCut &x, const BlockCut &y) { return 2u * x.d * (x.held + y.held); }
+
+// Compiled variants: cells per lane, rows per wavefront, and what an exchange takes longer in fp64 / fp32 because the
+// registers do not hold everything (us; measured; the cells themselves stay in registers).  0xff: not compiled.
+#define JK_BLOCKS2D_VARIANTS(X)                                                                                              \
+    X(1, 2, 0, 0) X(1, 4, 0, 0) X(1, 6, 0, 0) X(1, 8, 0, 0) X(1, 12, 0, 0) X(1, 16, 0, 0) X(2, 4, 0, 0) X(2, 6, 0, 0)        \
+    X(2, 8, 0, 0) X(2, 10, 0, 0) X(2, 12, 1.4, 0) X(2, 16, 20, 0) X(4, 8, 16, 1) X(4, 10, 25, 2) X(4, 12, 30, 5)
+#define JK_BLOCKS2D_VARIANTS_F32(X) X(1, 24, 0, 0) X(2, 24, 0, 10.6)
+struct Blocks2dLaunch {
+    hipStream_t st;
+    Geo g;
+    Blocks2d p;
+    void *in, *out;
+};
+hipError_t launch_blocks2d_f64(int c, int rw, const Blocks2dLaunch &a);
+hipError_t launch_blocks2d_f32(int c, int rw, const Blocks2dLaunch &a);
+
 }  // namespace jk

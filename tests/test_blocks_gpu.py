@@ -1,0 +1,153 @@
+"""The path that runs a whole jacobi_run of a mid-sized grid in one launch, the grid cut into blocks that workgroups keep in
+registers and whose borders they exchange as tagged messages.  fp64 grids bit for bit against the CPU oracle, fp32 within
+1e-5*max|u|, norms within 1e-12 / 1e-5 (the bars of the other suites).  Shapes at the edges of the cut: one cell more than
+a block, odd sizes, widths that only one or two cells per lane divide, tiles one cell wide, seams inside a lane's cells."""
+import numpy as np
+import pytest
+
+from parity_util import random_padded
+from test_parity_gpu import check
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (interior dims, tiles, iterations, norm every)
+    ((513, 301), (1, 1), 37, 12), ((300, 1001), (3, 7), 40, 7), ((257, 770), (1, 5), 33, 33), ((1024, 1024), (4, 4), 60, 30),
+    ((701, 613), (1, 1), 41, 8), ((640, 300), (64, 300), 32, 16), ((512, 264), (512, 2), 24, 6), ((130, 514), (2, 1), 64, 1),
+    ((1500, 1110), (5, 3), 48, 25), ((66, 2600), (1, 13), 30, 10), ((2000, 258), (8, 3), 50, 0), ((1536, 1536), (2, 3), 20, 10),
+]
+
+
+def run_whole(H, a, tiles, iters, every, **opts):
+    r = H.JacobiRun([n - 2 for n in a.shape], tiles, a.dtype, **opts)
+    try:
+        r.load(a)
+        r.other().fill_(255)                    # NaN: the other grid's ring has to come from the run
+        res = r.run(iters, every, fuse_residual=True) if every else (r.sweep(iters) or [])
+        where = r.cur is r.a
+        return r.fetch(), res, where
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("dims,tiles,iters,every", CASES)
+def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype):
+    a = random_padded(dims, dtype=dtype, seed=sum(dims) + iters)
+    ref, ref_res = oracle_mod.run(a, iters, every)
+    out, res, in_a = run_whole(H, a, tiles, iters, every, resident=1)
+    check(out, res, ref, ref_res)
+    # the launch-per-iteration path: the same grid to the bit (fp32 too), the result in the same buffer
+    out0, res0, in_a0 = run_whole(H, a, tiles, iters, every, resident=0)
+    assert np.array_equal(out, out0) and in_a == in_a0
+    out2, res2, _ = run_whole(H, a, tiles, iters, every, resident=1)
+    assert np.array_equal(out2, out) and res2 == res                # and the same bits on every run
+
+
+@pytest.mark.parametrize("dims,tiles,dtype", [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32)])
+def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, tiles, dtype):
+    """resident_spin_limit = 1: the roll is called once, without waiting.  Some workgroups are then missing (or, if all
+    happen to be there, none): those present do the work along the plain path, with the same result; the next launch
+    finds the plan's words as it needs them."""
+    a = random_padded(dims, dtype=dtype, seed=77)
+    for iters, every in ((24, 8), (23, 0), (16, 16)):
+        ref, ref_res = oracle_mod.run(a, iters, every)
+        r = H.JacobiRun(dims, tiles, dtype, resident=1, resident_spin_limit=1)
+        try:
+            for limit in (1, 1, 0, 1, 0):
+                r.set_option("resident_spin_limit", limit)
+                r.load(a)
+                res = r.run(iters, every, fuse_residual=True) if every else (r.sweep(iters) or [])
+                check(r.fetch(), res, ref, ref_res)
+        finally:
+            r.close()
+
+
+def test_blocks_sweeps_keep_parity_and_residual_of_the_input(H, oracle_mod):
+    """jacobi_sweep ends in the buffer the schedule says, also with blocked passes asked for; jacobi_sweep_residual gives
+    the norm of the field that went in."""
+    import torch
+    a = random_padded((700, 900), seed=5)
+    for iters, opts in ((40, {}), (41, {}), (40, dict(tblock=8)), (39, dict(tblock=12)), (30, dict(fused=0)), (30, dict(profile=1))):
+        ref, _ = oracle_mod.run(a, iters)
+        r = H.JacobiRun((700, 900), (7, 3), resident=1, **opts)
+        try:
+            r.load(a)
+            passes = len(H.B.jacobi_pass_schedule(r.plan, iters))
+            r.sweep(iters)
+            assert (r.cur is r.a) == (passes % 2 == 0), (iters, opts)
+            assert np.array_equal(r.fetch(), ref), (iters, opts)
+            r.load(a)
+            norm = torch.zeros(1, dtype=torch.float64, device="cuda")
+            r.sweep_residual(iters, norm)
+            assert np.array_equal(r.fetch(), ref), (iters, opts)
+            want = oracle_mod.residual(a)
+            assert abs(norm.item() - want) <= 1e-12 * want
+            if opts.get("profile"):
+                ms, n = H.B.jacobi_profile_read(r.plan)
+                assert n == 2 and ms > 0.0
+        finally:
+            r.close()
+
+
+def test_blocks_special_values_and_many_norms(H, oracle_mod):
+    """Infinities and NaN in the field spread as on the other path; more norms than one launch delivers."""
+    a = random_padded((520, 640), seed=9)
+    a[100, 200] = np.inf
+    a[300, 0] = -np.inf
+    a[400, 641] = np.nan
+    got = [run_whole(H, a, (2, 4), 30, 10, resident=k) for k in (1, 0)]
+    assert np.array_equal(got[0][0], got[1][0], equal_nan=True)
+    assert np.array_equal(np.isnan(got[0][1]), np.isnan(got[1][1]))
+    b = random_padded((260, 300), seed=10)
+    ref, ref_res = oracle_mod.run(b, 300, 2)                       # 150 norms
+    out, res, _ = run_whole(H, b, (1, 1), 300, 2, resident=1)
+    check(out, res, ref, ref_res)
+
+
+def test_blocks_in_a_hip_graph_and_two_plans_on_two_streams(H, oracle_mod):
+    import torch
+    a = random_padded((512, 700), seed=12)
+    iters = 32
+    r = H.JacobiRun((512, 700), (4, 7), resident=1)
+    q = H.JacobiRun((1024, 1024), (1, 1), resident=1)
+    b = random_padded((1024, 1024), seed=13)
+    ref_b, _ = oracle_mod.run(b, 40)
+    try:
+        H.B.jacobi_prepare(r.plan)
+        g_dev = torch.from_numpy(a).cuda()
+        res = torch.zeros(2, dtype=torch.float64, device="cuda")
+        exp, exp_res = oracle_mod.run(a, iters, 16)
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            st = int(torch.cuda.current_stream().cuda_stream)
+            H.B.jacobi_scatter(r.plan, g_dev.data_ptr(), r.a.data_ptr(), st)
+            fin = H.B.jacobi_run(r.plan, r.a.data_ptr(), r.b.data_ptr(), iters, 16, res.data_ptr(), st)
+        for k in range(3):
+            res.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            r.cur = r.a if fin == r.a.data_ptr() else r.b
+            check(r.fetch(), res.cpu().tolist(), exp, exp_res)
+            r.load(a)
+            r.sweep(20 + k)                      # eager launches between the replays use up other tags
+            r.residual()
+        # two plans whose workgroups together are more than the chip has CUs, on two streams at once
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        for k in range(4):
+            r.load(a)
+            q.load(b)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s1):
+                r.sweep(iters)
+            with torch.cuda.stream(s2):
+                q.sweep(40)
+            torch.cuda.synchronize()
+            assert np.array_equal(r.fetch(), exp), k
+            assert np.array_equal(q.fetch(), ref_b), k
+    finally:
+        r.close()
+        q.close()
