@@ -384,7 +384,8 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    that "resident_depth" / "resident_rows" were not set for) run that way too, cut into blocks in
  *                    both directions: a workgroup keeps a block in registers and exchanges its border with the
  *                    neighbouring blocks alone, as messages in the plan's scratch (1024^2: 5.4 -> 1.2 us per
- *                    iteration); jacobi_run is then ONE launch, norms included (128 of them per launch).  There
+ *                    iteration), and so do 3-D grids of rows that fill at least half of one, two or (fp32) four
+ *                    cells per lane, up to about 100^3 (64^3: 6.0 -> 3.6 us); jacobi_run is then ONE launch, norms included (128 of them per launch).  There
  *                    jacobi_pass_schedule still lists the passes of the launch-per-pass path, as which the grids swap
  *                    roles.  If not all of the launch's workgroups start within a few milliseconds (other work holds
  *                    CUs), those that did do the work through memory: slower, the same result.  A call takes this path

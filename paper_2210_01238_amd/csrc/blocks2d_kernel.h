@@ -55,7 +55,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     // this lane's cells in a row of tiles, for rows found by a RowWalk
     long long co[C];
     bool seam = false;
-    auto find_cells = [&](int first_col) {
+    auto find_cells = [&](int first_col) JK_INLINE {
         const int tx = first_col / g.tw;
         int c = first_col - tx * g.tw;
         long long off = (long long)tx * g.tile_stride + c;
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         seam = co[C - 1] - co[0] != C - 1;
     };
     find_cells(col);
-    auto load_cells = [&](const T *rowp, T (&v)[C]) {
+    auto load_cells = [&](const T *rowp, T (&v)[C]) JK_INLINE {
         if (C > 1 && !seam) {
             const VU x = *(const VU *)(rowp + co[0]);
 #pragma unroll
@@ -135,8 +135,8 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
 #pragma unroll
     for (int j = 0; j < RW; ++j) {
 #pragma unroll
-        for (int e = 0; e < C; ++e) asm volatile("" : "+v"(a[j + 1][e]));
-        asm volatile("" : "+v"(ring[j]));
+        for (int e = 0; e < C; ++e) arrived(a[j + 1][e]);
+        arrived(ring[j]);
     }
     __syncthreads();
     unsigned ticket = 0;                           // looked at by thread 0 in the roll call, no sooner
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     int parity = 0;
     const bool at_north = north && wave == 0, at_south = south && wave == BLK_WAVES - 1;
     const int wave_up = max(wave - 1, 0), wave_dn = min(wave + 1, BLK_WAVES - 1);
-    auto publish = [&](auto slot0) {
+    auto publish = [&](auto slot0) JK_INLINE {
         constexpr int S = decltype(slot0)::value;
 #pragma unroll
         for (int e = 0; e < C; ++e) {
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         }
         __syncthreads();
     };
-    auto neighbours = [&](T (&above)[C], T (&below)[C]) {
+    auto neighbours = [&](T (&above)[C], T (&below)[C]) JK_INLINE {
         const T(*up)[WAVE] = at_north ? ring_row[0] : xch[parity][wave_up][1];
         const T(*dn)[WAVE] = at_south ? ring_row[1] : xch[parity][wave_dn][0];
 #pragma unroll
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
             below[e] = dn[e][lane];
         }
     };
-    auto step = [&](auto up_dir, auto edge) {
+    auto step = [&](auto up_dir, auto edge) JK_INLINE {
         constexpr int UP = decltype(up_dir)::value, EDGE = decltype(edge)::value, S = UP ? 0 : 1;
         publish(std::integral_constant<int, S>{});
         T above[C], below[C];
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         }
         parity ^= 1;
     };
-    auto iterate_edge = [&](int n, auto edge) {
+    auto iterate_edge = [&](int n, auto edge) JK_INLINE {
         for (int it = 0; it + 2 <= n; it += 2) {
             step(std::integral_constant<int, 0>{}, edge);
             step(std::integral_constant<int, 1>{}, edge);
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
                 for (int e = 0; e < C; ++e) a[j][e] = a[j - 1][e];
         }
     };
-    auto iterate = [&](int n) {
+    auto iterate = [&](int n) JK_INLINE {
         if (east) iterate_edge(n, std::integral_constant<int, 2>{});
         else iterate_edge(n, std::integral_constant<int, 1>{});
     };
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     }
     unsigned exchanges = 0;
     bool healthy = true;
-    auto exchange = [&]() {
+    auto exchange = [&]() JK_INLINE {
         ++exchanges;
         if (!healthy) return;
         const unsigned tag = epoch + exchanges;
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     };
 
     // ---- the norm of the grid as it is: the cells next to the owned ones are current
-    auto norm_sum = [&]() -> double {
+    auto norm_sum = [&]() JK_INLINE -> double {
         publish(std::integral_constant<int, 1>{});
         T above[C], below[C];
         neighbours(above, below);

@@ -24,6 +24,10 @@
 // leave.  Slower, but the same bits, and no launch depends on what else runs.
 #pragma once
 #include "launchers.h"
+#include <utility>
+
+// Lambdas that touch arrays kept in registers: one that the compiler does not inline puts them into memory.
+#define JK_INLINE __attribute__((always_inline))
 
 namespace jk {
 
@@ -64,6 +68,16 @@ __device__ __forceinline__ void roll_call(BlockSync *s, unsigned expected, unsig
     }
     *outcome = members == expected ? ALL_PRESENT : (int)ticket;
 }
+
+// A loaded value that has to be there before the program goes on.
+template <typename T> __device__ __forceinline__ void arrived(T &v) { asm volatile("" : "+v"(v)); }
+
+// f(0), f(1), ..., f(N-1) with compile-time indexes (integral_constant): arrays indexed by them stay in registers
+// however much code a turn is.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
 // ---- messages -------------------------------------------------------------------------------------------
 constexpr int AUX_AGENT = 16;               // sc1: agent scope, past the L2
@@ -201,7 +215,7 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
             const int x = (int)(w - row * xchunks) * (int)blockDim.x + (int)threadIdx.x;
             if (x >= Nx) continue;
             const int z = NDIM == 3 ? (int)(row / Ny) : 0, y = (int)(row - (long long)z * Ny);
-            auto at = [&](int dz, int dy, int dx) -> T {
+            auto at = [&](int dz, int dy, int dx) JK_INLINE -> T {
                 const int zz = z + dz, yy = y + dy, xx = x + dx;
                 const bool ring = (NDIM == 3 && (zz < 0 || zz >= Nz)) || yy < 0 || yy >= Ny || xx < 0 || xx >= Nx;
                 return (ring ? in : src)[domain_cell_off(g, zz, yy, xx)];

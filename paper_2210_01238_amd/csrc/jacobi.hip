@@ -64,8 +64,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // shape and type.
 struct BlockPlan {
     bool ok = false;
-    int cells_per_lane = 0, rows_per_wave = 0;
-    jk::BlockCut x, y;
+    int cells_per_lane = 0, rows_per_wave = 0, planes_per_wave = 0;
+    jk::BlockCut x, y, z;             // 2-D: x and y; 3-D: the padded rows in y and z
+    int frame_rows = 0;               // 3-D: rows of a block's message
     int workgroups = 0;
     int64_t msg_bytes = 0;            // of one of the two message areas
     int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
@@ -690,6 +691,60 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
     return best;
 }
 
+// 3-D: the same model, fitted to eight cuts of five grids between 48 x 40 x 60 and 128^3 (within 25 %); rows are whole, cut in
+// y and z.  The border rows go through LDS (128 bytes per clock), messages count written and read; the fp64 patch of 18 rows
+// takes 3 us more per exchange because the registers do not hold everything.
+double launch_us_3d(int64_t cell_bytes) { return 4.6 + 0.25e-6 * cell_bytes; }
+BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
+{
+    struct Variant { int c, rz, ry; bool f32_only; };
+    static const Variant variants[] = {
+#define JK_V(C_, RZ_, RY_) {C_, RZ_, RY_, false},
+        JK_BLOCKS3D_VARIANTS(JK_V)
+#undef JK_V
+#define JK_V(C_, RZ_, RY_) {C_, RZ_, RY_, true},
+        JK_BLOCKS3D_VARIANTS_F32(JK_V)
+#undef JK_V
+    };
+    BlockPlan best;
+    const bool f64 = dtype == JACOBI_F64;
+    const int64_t Nx = (int64_t)g.Tx * g.tw, Ny = (int64_t)g.Ty * g.th, Nz = (int64_t)g.Tz * g.td;
+    const int cell = f64 ? 8 : 4;
+    for (const Variant &v : variants) {
+        if (f64 && v.f32_only) continue;
+        const int width = jk::WAVE * v.c, HZ = 2 * v.rz, HY = 4 * v.ry;
+        if (Nx > width || 2 * Nx <= width) continue;            // at least half of the lanes have cells
+        for (int d = 1; d <= 3; ++d) {
+            jk::BlockCut y, z;
+            if (!cut_into_blocks(Ny + 2, HY, d, 1, 2 * d, &y) || !cut_into_blocks(Nz + 2, HZ, d, 1, 2 * d, &z)) continue;
+            const int64_t nb = (int64_t)y.nb * z.nb;
+            if (nb > num_cu) continue;
+            int ny = 0, nz = 0;
+            for (int b = 0; b < y.nb; ++b) ny = std::max(ny, y.own_hi(b) - y.own_lo(b));
+            for (int b = 0; b < z.nb; ++b) nz = std::max(nz, z.own_hi(b) - z.own_lo(b));
+            const int frame = 2 * d * ny + (nz - 2 * d) * 2 * d;
+            const double row_msg = (double)width * 2 * cell, msg = nb * frame * row_msg;
+            const double ghost = nb > 1 ? nb * ((double)(ny + 2 * d) * (nz + 2 * d) - (double)ny * nz) * row_msg : 0.0;
+            const double instr = 2.0 * v.rz * v.ry * (6 * v.c + (f64 ? 4 : 2) + (Nx < width ? v.c * (f64 ? 2 : 1) : 0));
+            const double lds = 8.0 * (2 * v.ry + 2 * (v.rz - 2) + 2 * (v.rz + v.ry)) * width * cell / 128 / 2200;
+            const double us = 0.1 + instr * 0.00205 + lds + (2.2 + 0.1e-6 * (msg + ghost) + (f64 && v.rz * v.ry > 12 ? 3.0 : 0.0)) / d;
+            if (best.ok && us >= best.us_per_iteration) continue;
+            best.ok = true;
+            best.us_per_iteration = us;
+            best.cells_per_lane = v.c;
+            best.rows_per_wave = v.ry;
+            best.planes_per_wave = v.rz;
+            best.y = y; best.z = z;
+            best.frame_rows = frame;
+            best.workgroups = (int)nb;
+            best.msg_bytes = round_up((int64_t)msg, 256);
+        }
+    }
+    if (best.ok && best.us_per_iteration > 0.8 * launch_us_3d(Nx * Ny * Nz * cell)) best.ok = false;
+    if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
+    return best;
+}
+
 // Whether a call of so many iterations runs that way: what it saves per iteration has to pay for the launch (1024^2:
 // 3 iterations 20 us by launches against 32, 8 iterations 48 against 19).  `row`: what the kernel for narrow grids
 // (resident2d_kernel) would do with them - if it can run, it takes 0.95 us per iteration and about 6 us less per launch, and it
@@ -704,7 +759,8 @@ bool blocks_usable(const jacobi_plan *p, int iters, const ResidentChoice &row)
         if (p->resident_depth > 0 || p->resident_rows > 0 || row.nwg == 1) return false;
         return iters * (0.95 - b.us_per_iteration) > 6.0;
     }
-    const double other = p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
+    const double other = L.ndim == 3 ? launch_us_3d(cells * (int64_t)p->esize)
+                         : p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
     return iters * (other - b.us_per_iteration) > BLOCK_LAUNCH_US;
 }
 
@@ -790,8 +846,14 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
     run.msg = p->block_scratch + p->blocks.scratch_bytes - 2 * p->blocks.msg_bytes;
     run.msg_bytes = (unsigned)p->blocks.msg_bytes;
     run.result = result;
-    jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, run}, in, out};
     const int c = p->blocks.cells_per_lane, rw = p->blocks.rows_per_wave;
+    if (p->geo.ndim == 3) {
+        const jk::Blocks3dLaunch a{st, p->geo, {p->blocks.z, p->blocks.y, (int)p->lay.dims[2], p->blocks.frame_rows, run}, in, out};
+        const int rz = p->blocks.planes_per_wave;
+        return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks3d_f64(c, rz, rw, a) : jk::launch_blocks3d_f32(c, rz, rw, a),
+                              "3-D block kernel launch");
+    }
+    const jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, run}, in, out};
     return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks2d_f64(c, rw, a) : jk::launch_blocks2d_f32(c, rw, a),
                           "block kernel launch");
 }
@@ -1159,7 +1221,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
     g.hpitch = L.xhalo_pitch;
     g.xsend = L.xsend_offset;
     g.tile_stride = L.tile_stride;
-    if (ndim == 2) p->blocks = plan_blocks2d(g, dtype, jk::NUM_CU);
+    p->blocks = ndim == 2 ? plan_blocks2d(g, dtype, jk::NUM_CU) : plan_blocks3d(g, dtype, jk::NUM_CU);
     *plan = p;
     return JACOBI_OK;
 }

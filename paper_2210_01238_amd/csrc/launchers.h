@@ -182,4 +182,23 @@ struct Blocks2dLaunch {
 hipError_t launch_blocks2d_f64(int c, int rw, const Blocks2dLaunch &a);
 hipError_t launch_blocks2d_f32(int c, int rw, const Blocks2dLaunch &a);
 
+// 3-D: cuts of the padded rows (n = N + 2) in z and y
+struct Blocks3d {
+    BlockCut z, y;
+    int nx;
+    int frame_rows;        // rows of a block's message at most
+    BlockRun run;
+};
+// Compiled variants: cells per lane, rows in z and y a wavefront keeps (larger patches do not fit the registers)
+#define JK_BLOCKS3D_VARIANTS(X) X(1, 4, 2) X(1, 6, 3) X(2, 4, 2) X(2, 5, 2)
+#define JK_BLOCKS3D_VARIANTS_F32(X) X(2, 6, 3) X(4, 4, 2) X(4, 5, 2)
+struct Blocks3dLaunch {
+    hipStream_t st;
+    Geo g;
+    Blocks3d p;
+    void *in, *out;
+};
+hipError_t launch_blocks3d_f64(int c, int rz, int ry, const Blocks3dLaunch &a);
+hipError_t launch_blocks3d_f32(int c, int rz, int ry, const Blocks3dLaunch &a);
+
 }  // namespace jk

@@ -30,8 +30,16 @@ def run_whole(H, a, tiles, iters, every, **opts):
         r.close()
 
 
+CASES_3D = [
+    # rows of exactly one and two lanes' cells, one cell fewer, odd rows, one and many blocks per direction
+    ((64, 64, 64), (2, 2, 2), 40, 20), ((64, 64, 64), (1, 1, 1), 33, 1), ((61, 53, 47), (1, 1, 1), 30, 7), ((48, 40, 60), (2, 2, 3), 41, 0),
+    ((40, 70, 63), (4, 7, 21), 36, 12), ((6, 40, 64), (2, 4, 8), 60, 15), ((128, 128, 128), (2, 2, 2), 30, 10), ((96, 96, 128), (3, 2, 1), 30, 10),
+    ((90, 100, 126), (1, 5, 9), 28, 14), ((70, 62, 256), (1, 2, 4), 32, 8), ((66, 60, 251), (2, 3, 1), 32, 8), ((30, 46, 33), (1, 1, 1), 40, 40),
+]
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
-@pytest.mark.parametrize("dims,tiles,iters,every", CASES)
+@pytest.mark.parametrize("dims,tiles,iters,every", CASES + CASES_3D)
 def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype):
     a = random_padded(dims, dtype=dtype, seed=sum(dims) + iters)
     ref, ref_res = oracle_mod.run(a, iters, every)
@@ -44,13 +52,14 @@ def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype
     assert np.array_equal(out2, out) and res2 == res                # and the same bits on every run
 
 
-@pytest.mark.parametrize("dims,tiles,dtype", [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32)])
+@pytest.mark.parametrize("dims,tiles,dtype", [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32),
+                                              ((64, 64, 64), (2, 2, 2), np.float64), ((61, 53, 47), (1, 1, 1), np.float32)])
 def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, tiles, dtype):
     """resident_spin_limit = 1: the roll is called once, without waiting.  Some workgroups are then missing (or, if all
     happen to be there, none): those present do the work along the plain path, with the same result; the next launch
     finds the plan's words as it needs them."""
     a = random_padded(dims, dtype=dtype, seed=77)
-    for iters, every in ((24, 8), (23, 0), (16, 16)):
+    for iters, every in ((24, 8), (23, 0), (26, 26)):
         ref, ref_res = oracle_mod.run(a, iters, every)
         r = H.JacobiRun(dims, tiles, dtype, resident=1, resident_spin_limit=1)
         try:
