@@ -48,6 +48,7 @@ constexpr int64_t LARGE_GRID_BYTES = 1LL << 30;   // grids from this size on get
 // cache) the outcome depends on where the two buffers happen to lie (42 - 48 us against 47.4 with streaming
 // stores), at 4224^2 (137 MiB) they are level, and from 256^3 (136 MiB: 53.7 -> 58.5) and 4352^2 on they lose.
 constexpr int64_t CACHED_GRID_BYTES = 124LL << 20;
+constexpr int64_t SPREAD_GRID_BYTES = 6LL << 20;    // 3-D updates of grids from this size on: 2048 wavefronts
 constexpr int64_t CACHED_CHUNK_BYTES = 24LL << 20;  // cache-resident 2-D grids from this size on: XCD chunks of 32
 
 // Scatter: consecutive workgroups one XCD takes (16384^2: 797 us in the hardware's order, 806 with 16, 765 with 32, 752
@@ -186,7 +187,9 @@ SweepConfig make_config(const jacobi_plan *p, int mode)
         // with 1024 strips of 2 planes x 2 rows; 128^3 in 64^3 tiles 18.9 -> 10.1); tiny grids go down to one row
         // per wavefront as well (32^3: 6.3 -> 4.0)
         R = 16;
-        while (R > 2 && (int64_t)ceil_div(extent, R) * lanes_of_work < 1024) R /= 2;
+        // (fp32 rows of at most 128 cells move half as much per wavefront and want twice as many: 210 x 198 x 250 in
+        // eight tiles 20.8 us with 1400, 18.9 with 2800; grids from 6 MiB on too: 128^3 8.6 with 1024, 7.5 with 2048)
+        while (R > 2 && (int64_t)ceil_div(extent, R) * lanes_of_work < (narrow_f32 || p->lay.grid_bytes >= SPREAD_GRID_BYTES ? 2048 : 1024)) R /= 2;
         if (p->rows_per_wave <= 0 && c.rows_per_wave > 1 && !narrow_f32 &&
             (int64_t)ceil_div(extent, R) * lanes_of_work < 512) {
             c.rows_per_wave = 1;
@@ -202,8 +205,12 @@ SweepConfig make_config(const jacobi_plan *p, int mode)
         // mid-sized 2-D grids: at 8 rows a 4096^2 grid gives each CU only ~3 rounds of workgroups
         // and the last round runs half empty; 4-row strips measure 8 % faster there
         if (!d3 && mode != jk::MODE_RESIDUAL && (int64_t)ceil_div(extent, R) * lanes_of_work < 24576) R = 4;
-        // (3-D: 16-plane strips until fewer than 512 strips would be left)
+        // (3-D: 16-plane strips until fewer than 512 strips would be left; the residual pass below 1 GiB goes on to 4 planes
+        // while there are fewer than 2048: 150^3 in fp32 14.9 us with 750, 11.4 with 2850, 128^3 12.8 -> 9.4; below 4 planes 100 x
+        // 90 x 110 in fp32 loses again, 8.9 -> 10.1)
         while (R > 1 && (int64_t)ceil_div(extent, R) * lanes_of_work < (d3 ? 512 : 4096)) R /= 2;
+        if (d3_small_residual)
+            while (R > 4 && (int64_t)ceil_div(extent, R) * lanes_of_work < 2048) R /= 2;
     }
     if (R > extent) R = extent;
     sp.R = R;
@@ -217,8 +224,10 @@ SweepConfig make_config(const jacobi_plan *p, int mode)
     c.whole_cu = d3 && mode != jk::MODE_RESIDUAL && p->esize == 8 && g.pitch >= jk::WAVE * nv &&
                  p->lay.grid_bytes >= LARGE_GRID_BYTES;
     sp.xcd_chunk = xcd_chunk_of(p, c.whole_cu);
-    // 3-D updates below 1 GiB: the hardware's own order on small grids (64^3 5.1 -> 4.5 us), runs of 16 from 24 MiB on
-    if (d3_small_update && p->xcd_chunk <= 0) sp.xcd_chunk = p->lay.grid_bytes < CACHED_CHUNK_BYTES ? 1 : 16;
+    // 3-D updates below 1 GiB: the hardware's own order on small grids (64^3 5.1 -> 4.5 us), runs of 32 from 6 MiB on (100 x 90
+    // x 110 in fp64 10.2 -> 8.6 us, 150^3 in fp32 9.5 -> 8.9, together with the shorter strips above), of 16 from 24 MiB on
+    if (d3_small_update && p->xcd_chunk <= 0)
+        sp.xcd_chunk = p->lay.grid_bytes < SPREAD_GRID_BYTES ? 1 : p->lay.grid_bytes < CACHED_CHUNK_BYTES ? 32 : 16;
     // 2-D updates of cache-resident grids: longer runs per XCD (2048^2: 11.8 -> 11.3 us, 3072^2: 24.6 -> 23.2;
     // below 2048^2 the hardware's own order is as good or better)
     if (!d3 && mode != jk::MODE_RESIDUAL && p->xcd_chunk <= 0 && store_flavour(p) == 0 &&
