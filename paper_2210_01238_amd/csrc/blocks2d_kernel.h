@@ -42,7 +42,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     const int lane = threadIdx.x % WAVE;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int nb = p.x.nb * p.y.nb;
-    const int blk = blockIdx.x, by = blk / p.x.nb, bx = blk - by * p.x.nb;
+    const int blk = block_of_workgroup(p.x.nb, p.y.nb, p.strip), by = blk / p.x.nb, bx = blk - by * p.x.nb;
     const unsigned epoch = agent_load(&br.sync->epoch);
     const unsigned max_exchanges = (unsigned)br.iters + (unsigned)br.norms + 2u;
     const int d = p.x.d;

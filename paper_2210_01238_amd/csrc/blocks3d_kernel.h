@@ -49,7 +49,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks3d_kernel(Geo g, Block
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int wz = wave / WY, wy = wave % WY;
     const int nb = p.y.nb * p.z.nb;
-    const int blk = blockIdx.x, bz = blk / p.y.nb, by = blk - bz * p.y.nb;
+    const int blk = block_of_workgroup(p.y.nb, p.z.nb, p.strip), bz = blk / p.y.nb, by = blk - bz * p.y.nb;
     const unsigned epoch = agent_load(&br.sync->epoch);
     const unsigned max_exchanges = (unsigned)br.iters + (unsigned)br.norms + 2u;
     const int d = p.y.d, Nx = p.nx;

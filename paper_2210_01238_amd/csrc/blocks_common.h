@@ -79,6 +79,20 @@ __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
+// Which block a workgroup takes.  The hardware deals workgroups out to the 8 XCDs in turn, and a message between two
+// workgroups of one XCD stays in its L2 (0.44 us against 0.75 us, and nothing on the way to memory), so each XCD gets a
+// compact patch of blocks: the blocks are numbered strip by strip (`strip` blocks wide, rows of a strip one after the other)
+// and every XCD takes a run of numbers.  strip = 0: as dealt.  Where a workgroup really runs does not matter for the result.
+__device__ __forceinline__ int block_of_workgroup(int nbx, int nby, int strip)
+{
+    const int nb = nbx * nby, wg = blockIdx.x, xcd = wg % NUM_XCD;
+    if (strip == 0) return wg;
+    const int n = xcd * (nb / NUM_XCD) + min(xcd, nb % NUM_XCD) + wg / NUM_XCD;
+    const int s = n / (strip * nby), in_strip = n - s * strip * nby, w = min(strip, nbx - s * strip);
+    const int y = in_strip / w;
+    return y * nbx + s * strip + in_strip - y * w;
+}
+
 // ---- messages -------------------------------------------------------------------------------------------
 constexpr int AUX_AGENT = 16;               // sc1: agent scope, past the L2
 constexpr int AUX_VOLATILE = (int)0x80000000u;

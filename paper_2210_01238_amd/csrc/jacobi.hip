@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -68,6 +69,7 @@ struct BlockPlan {
     int cells_per_lane = 0, rows_per_wave = 0, planes_per_wave = 0;
     jk::BlockCut x, y, z;             // 2-D: x and y; 3-D: the padded rows in y and z
     int frame_rows = 0;               // 3-D: rows of a block's message
+    int strip = 0;                    // blocks side by side in an XCD's patch (0: no patches)
     int workgroups = 0;
     int64_t msg_bytes = 0;            // of one of the two message areas
     int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
@@ -659,6 +661,17 @@ double blocked_us_2d(int64_t cells) { return 1.8 + 0.7e-6 * cells; }
 // 2400^2 (within 10 % of what they measured): 0.06 us for the border rows and the barrier, 2.05 ns for each of the
 // instructions a SIMD's two wavefronts issue (4 per cell, 4 or 2 lane shifts per row), and every d iterations an exchange of
 // 2.5 us plus 0.22 us per MB of messages.
+// Width in blocks of the patch an XCD gets, for the least traffic across its border: blocks of `w` x `h` cells, nbx side by
+// side, `n` in all.  (In 2-D only while the messages are small: patches run 512^2 in 0.58 us per iteration, workgroups dealt
+// out one by one in 0.62, 256^2 0.526 / 0.537; but 1024^2 with 18 MB of messages 1.05 / 1.01, 2048^2 in fp32 2.40 / 2.17 - all
+// neighbours then press on the same L2.  3-D: 64^3 3.42 / 3.63, 128^3 in fp32 4.23 / 4.37.)
+constexpr double PATCH_MESSAGES = 9e6;
+int strip_width(int n, int nbx, double w, double h)
+{
+    const int strip = (int)(std::sqrt(n / (double)jk::NUM_XCD * h / w) + 0.5);
+    return strip < 1 ? 1 : strip > nbx ? nbx : strip;
+}
+
 BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
 {
     struct Variant { int c, rw; double extra64, extra32; bool f32_only; };
@@ -691,6 +704,7 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
             best.rows_per_wave = v.rw;
             best.x = x; best.y = y;
             best.workgroups = x.nb * y.nb;
+            best.strip = msg < PATCH_MESSAGES ? strip_width(best.workgroups, x.nb, (double)Nx / x.nb, (double)Ny / y.nb) : 0;
             best.msg_bytes = round_up((int64_t)msg, 256);
         }
     }
@@ -703,7 +717,7 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
 // 3-D: the same model, fitted to eight cuts of five grids between 48 x 40 x 60 and 128^3 (within 25 %); rows are whole, cut in
 // y and z.  The border rows go through LDS (128 bytes per clock), messages count written and read; the fp64 patch of 18 rows
 // takes 3 us more per exchange because the registers do not hold everything.
-double launch_us_3d(int64_t cell_bytes) { return 4.6 + 0.25e-6 * cell_bytes; }
+double launch_us_3d(int64_t cell_bytes) { return 4.6 + 0.35e-6 * cell_bytes; }
 BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
 {
     struct Variant { int c, rz, ry; bool f32_only; };
@@ -745,6 +759,7 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
             best.planes_per_wave = v.rz;
             best.y = y; best.z = z;
             best.frame_rows = frame;
+            best.strip = strip_width((int)nb, y.nb, (double)Ny / y.nb, (double)Nz / z.nb);
             best.workgroups = (int)nb;
             best.msg_bytes = round_up((int64_t)msg, 256);
         }
@@ -857,12 +872,12 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
     run.result = result;
     const int c = p->blocks.cells_per_lane, rw = p->blocks.rows_per_wave;
     if (p->geo.ndim == 3) {
-        const jk::Blocks3dLaunch a{st, p->geo, {p->blocks.z, p->blocks.y, (int)p->lay.dims[2], p->blocks.frame_rows, run}, in, out};
+        const jk::Blocks3dLaunch a{st, p->geo, {p->blocks.z, p->blocks.y, (int)p->lay.dims[2], p->blocks.frame_rows, p->blocks.strip, run}, in, out};
         const int rz = p->blocks.planes_per_wave;
         return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks3d_f64(c, rz, rw, a) : jk::launch_blocks3d_f32(c, rz, rw, a),
                               "3-D block kernel launch");
     }
-    const jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, run}, in, out};
+    const jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, p->blocks.strip, run}, in, out};
     return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks2d_f64(c, rw, a) : jk::launch_blocks2d_f32(c, rw, a),
                           "block kernel launch");
 }

@@ -160,6 +160,7 @@ struct BlockCut {
 
 struct Blocks2d {
     BlockCut x, y;
+    int strip;             // width of the strips that the blocks are dealt out to the XCDs by
     BlockRun run;
 };
 
@@ -187,6 +188,7 @@ struct Blocks3d {
     BlockCut z, y;
     int nx;
     int frame_rows;        // rows of a block's message at most
+    int strip;
     BlockRun run;
 };
 // Compiled variants: cells per lane, rows in z and y a wavefront keeps (larger patches do not fit the registers)
