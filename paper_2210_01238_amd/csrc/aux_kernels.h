@@ -205,8 +205,11 @@ struct ScatterParams {
     unsigned vrow;             // vectors per row: ceil(tw / NV)
     unsigned nvec;             // vectors of a tile: nplanes * rows * vrow
     unsigned wg_per_tile;
-    FastDiv by_vrow, by_rows;
+    FastDiv by_vrow, by_rows, by_wg_per_tile, by_layer, by_Tx;
+    // workgroup order (see xcd_logical_wg; the host knows the sizes, so nothing is divided by a variable here)
     int xcd_chunk;
+    unsigned in_groups;        // workgroups that lie in whole groups of NUM_XCD * xcd_chunk
+    FastDiv by_group;
 };
 
 template <typename T, bool STREAM>
@@ -215,10 +218,15 @@ __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, co
     using V = typename Vec<T>::type;
     constexpr int NV = Vec<T>::N;
     typedef T VU __attribute__((ext_vector_type(NV), aligned(sizeof(T))));
-    const unsigned lwg = (unsigned)xcd_logical_wg(sp.xcd_chunk);
-    const int t = (int)(lwg / sp.wg_per_tile);
-    const unsigned v0 = (lwg - (unsigned)t * sp.wg_per_tile) * SG_UNIT;
-    const int tz = t / (g.Ty * g.Tx), ty = (t / g.Tx) % g.Ty, tx = t % g.Tx;
+    unsigned lwg = blockIdx.x;
+    if (lwg < sp.in_groups) {
+        const unsigned span = NUM_XCD * (unsigned)sp.xcd_chunk, first = sp.by_group(lwg) * span, within = lwg - first;
+        lwg = first + within % NUM_XCD * (unsigned)sp.xcd_chunk + within / NUM_XCD;
+    }
+    const unsigned t = sp.by_wg_per_tile(lwg);
+    const unsigned v0 = (lwg - t * sp.wg_per_tile) * SG_UNIT;
+    const unsigned tz = sp.by_layer(t), in_layer = t - tz * (unsigned)(g.Ty * g.Tx);
+    const unsigned ty = sp.by_Tx(in_layer), tx = in_layer - ty * (unsigned)g.Tx;
     // the padded cell (plane 0, row 0, column 0) of the tile; column 0 is the cell right of the x- halo
     const T *corner = from + ((long long)tz * g.td * sp.GQ + (long long)ty * g.th * sp.GP + (long long)tx * g.tw + 1);
     T *tile = to + (long long)t * g.tile_stride;

@@ -49,7 +49,7 @@ constexpr int64_t LARGE_GRID_BYTES = 1LL << 30;   // grids from this size on get
 // cache) the outcome depends on where the two buffers happen to lie (42 - 48 us against 47.4 with streaming
 // stores), at 4224^2 (137 MiB) they are level, and from 256^3 (136 MiB: 53.7 -> 58.5) and 4352^2 on they lose.
 constexpr int64_t CACHED_GRID_BYTES = 124LL << 20;
-constexpr int64_t SPREAD_GRID_BYTES = 6LL << 20;    // 3-D updates of grids from this size on: 2048 wavefronts
+constexpr int64_t SPREAD_GRID_BYTES = 6LL << 20;    // 3-D updates of grids from this size on: 1500 wavefronts
 constexpr int64_t CACHED_CHUNK_BYTES = 24LL << 20;  // cache-resident 2-D grids from this size on: XCD chunks of 32
 
 // Scatter: consecutive workgroups one XCD takes (16384^2: 797 us in the hardware's order, 806 with 16, 765 with 32, 752
@@ -73,7 +73,12 @@ struct BlockPlan {
     int workgroups = 0;
     int64_t msg_bytes = 0;            // of one of the two message areas
     int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
-    double us_per_iteration = 0;      // estimate
+    double us_iterate = 0, us_exchange = 0;     // estimates: of an iteration, of an exchange
+    double us_per_iteration(int every) const    // with an exchange every d iterations, or after each norm
+    {
+        const int d = y.d;
+        return us_iterate + us_exchange / (every > 0 && every < d ? every : d);
+    }
 };
 
 struct jacobi_plan {
@@ -189,9 +194,12 @@ SweepConfig make_config(const jacobi_plan *p, int mode)
         // with 1024 strips of 2 planes x 2 rows; 128^3 in 64^3 tiles 18.9 -> 10.1); tiny grids go down to one row
         // per wavefront as well (32^3: 6.3 -> 4.0)
         R = 16;
-        // (fp32 rows of at most 128 cells move half as much per wavefront and want twice as many: 210 x 198 x 250 in
-        // eight tiles 20.8 us with 1400, 18.9 with 2800; grids from 6 MiB on too: 128^3 8.6 with 1024, 7.5 with 2048)
-        while (R > 2 && (int64_t)ceil_div(extent, R) * lanes_of_work < (narrow_f32 || p->lay.grid_bytes >= SPREAD_GRID_BYTES ? 2048 : 1024)) R /= 2;
+        while (R > 2 && (int64_t)ceil_div(extent, R) * lanes_of_work < (narrow_f32 ? 2048 : 1024)) R /= 2;
+        // fp32 rows of at most 128 cells move half as much per wavefront and want twice as many (210 x 198 x 250 in eight
+        // tiles 20.8 us with 1400, 18.9 with 2800); grids of 6 to 64 MiB do with 1500 (128^3 8.5 us with 1024, 7.9 with 2048, in
+        // eight tiles 12.2 and 10.2, 100 x 90 x 110 10.3 with 1288, 9.5 with 2392; 90^3 in 27 tiles 10.9 with 1620, 11.2 with 3240)
+        if (p->lay.grid_bytes >= SPREAD_GRID_BYTES && p->lay.grid_bytes <= (64LL << 20))
+            while (R > 4 && (int64_t)ceil_div(extent, R) * lanes_of_work < 1536) R /= 2;
         if (p->rows_per_wave <= 0 && c.rows_per_wave > 1 && !narrow_f32 &&
             (int64_t)ceil_div(extent, R) * lanes_of_work < 512) {
             c.rows_per_wave = 1;
@@ -226,10 +234,8 @@ SweepConfig make_config(const jacobi_plan *p, int mode)
     c.whole_cu = d3 && mode != jk::MODE_RESIDUAL && p->esize == 8 && g.pitch >= jk::WAVE * nv &&
                  p->lay.grid_bytes >= LARGE_GRID_BYTES;
     sp.xcd_chunk = xcd_chunk_of(p, c.whole_cu);
-    // 3-D updates below 1 GiB: the hardware's own order on small grids (64^3 5.1 -> 4.5 us), runs of 32 from 6 MiB on (100 x 90
-    // x 110 in fp64 10.2 -> 8.6 us, 150^3 in fp32 9.5 -> 8.9, together with the shorter strips above), of 16 from 24 MiB on
-    if (d3_small_update && p->xcd_chunk <= 0)
-        sp.xcd_chunk = p->lay.grid_bytes < SPREAD_GRID_BYTES ? 1 : p->lay.grid_bytes < CACHED_CHUNK_BYTES ? 32 : 16;
+    // 3-D updates below 1 GiB: the hardware's own order on small grids (64^3 5.1 -> 4.5 us), runs of 16 from 24 MiB on
+    if (d3_small_update && p->xcd_chunk <= 0) sp.xcd_chunk = p->lay.grid_bytes < CACHED_CHUNK_BYTES ? 1 : 16;
     // 2-D updates of cache-resident grids: longer runs per XCD (2048^2: 11.8 -> 11.3 us, 3072^2: 24.6 -> 23.2;
     // below 2048^2 the hardware's own order is as good or better)
     if (!d3 && mode != jk::MODE_RESIDUAL && p->xcd_chunk <= 0 && store_flavour(p) == 0 &&
@@ -695,11 +701,12 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
             if (!cut_into_blocks(Nx, HW, d, v.c, 2 * d, &x) || !cut_into_blocks(Ny, HH, d, 1, 2 * d, &y)) continue;
             if (x.nb < 2 || (int64_t)x.nb * y.nb > num_cu) continue;
             const double msg = (double)x.nb * y.nb * jk::blocks2d_frame(x, y) * (f64 ? 16 : 8);
-            const double us = 0.06 + 2 * v.rw * (4 * v.c + (f64 ? 4 : 2)) * 0.00205 +
-                              (2.5 + 0.22e-6 * msg + (f64 ? v.extra64 : v.extra32)) / d;
-            if (best.ok && us >= best.us_per_iteration) continue;
+            const double iterate = 0.06 + 2 * v.rw * (4 * v.c + (f64 ? 4 : 2)) * 0.00205;
+            const double exchange = 2.5 + 0.22e-6 * msg + (f64 ? v.extra64 : v.extra32);
+            if (best.ok && iterate + exchange / d >= best.us_per_iteration(0)) continue;
             best.ok = true;
-            best.us_per_iteration = us;
+            best.us_iterate = iterate;
+            best.us_exchange = exchange;
             best.cells_per_lane = v.c;
             best.rows_per_wave = v.rw;
             best.x = x; best.y = y;
@@ -709,7 +716,7 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
         }
     }
     // not for grids that the other paths run as fast
-    if (best.ok && best.us_per_iteration > 0.8 * launch_us_2d(Nx * Ny * (f64 ? 8 : 4))) best.ok = false;
+    if (best.ok && best.us_per_iteration(0) > 0.8 * launch_us_2d(Nx * Ny * (f64 ? 8 : 4))) best.ok = false;
     if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
     return best;
 }
@@ -750,10 +757,12 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
             const double ghost = nb > 1 ? nb * ((double)(ny + 2 * d) * (nz + 2 * d) - (double)ny * nz) * row_msg : 0.0;
             const double instr = 2.0 * v.rz * v.ry * (6 * v.c + (f64 ? 4 : 2) + (Nx < width ? v.c * (f64 ? 2 : 1) : 0));
             const double lds = 8.0 * (2 * v.ry + 2 * (v.rz - 2) + 2 * (v.rz + v.ry)) * width * cell / 128 / 2200;
-            const double us = 0.1 + instr * 0.00205 + lds + (2.2 + 0.1e-6 * (msg + ghost) + (f64 && v.rz * v.ry > 12 ? 3.0 : 0.0)) / d;
-            if (best.ok && us >= best.us_per_iteration) continue;
+            const double iterate = 0.1 + instr * 0.00205 + lds;
+            const double exchange = 2.2 + 0.1e-6 * (msg + ghost) + (f64 && v.rz * v.ry > 12 ? 3.0 : 0.0);
+            if (best.ok && iterate + exchange / d >= best.us_per_iteration(0)) continue;
             best.ok = true;
-            best.us_per_iteration = us;
+            best.us_iterate = iterate;
+            best.us_exchange = exchange;
             best.cells_per_lane = v.c;
             best.rows_per_wave = v.ry;
             best.planes_per_wave = v.rz;
@@ -764,7 +773,7 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
             best.msg_bytes = round_up((int64_t)msg, 256);
         }
     }
-    if (best.ok && best.us_per_iteration > 0.8 * launch_us_3d(Nx * Ny * Nz * cell)) best.ok = false;
+    if (best.ok && best.us_per_iteration(0) > 0.8 * launch_us_3d(Nx * Ny * Nz * cell)) best.ok = false;
     if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
     return best;
 }
@@ -773,19 +782,20 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
 // 3 iterations 20 us by launches against 32, 8 iterations 48 against 19).  `row`: what the kernel for narrow grids
 // (resident2d_kernel) would do with them - if it can run, it takes 0.95 us per iteration and about 6 us less per launch, and it
 // runs where its geometry was asked for by option.
-bool blocks_usable(const jacobi_plan *p, int iters, const ResidentChoice &row)
+bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentChoice &row)
 {
     const BlockPlan &b = p->blocks;
     if (!p->resident || !b.ok || b.workgroups > p->num_cu || iters > BLOCK_MAX_ITERS) return false;
     const jacobi_layout &L = p->lay;
     const int64_t cells = L.dims[0] * L.dims[1] * L.dims[2];
+    const double us = b.us_per_iteration(every);
     if (row.ok) {
         if (p->resident_depth > 0 || p->resident_rows > 0 || row.nwg == 1) return false;
-        return iters * (0.95 - b.us_per_iteration) > 6.0;
+        return iters * (0.95 - us) > 6.0;
     }
     const double other = L.ndim == 3 ? launch_us_3d(cells * (int64_t)p->esize)
                          : p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
-    return iters * (other - b.us_per_iteration) > BLOCK_LAUNCH_US;
+    return iters * (other - us) > BLOCK_LAUNCH_US + b.us_exchange;
 }
 
 // What the next pass does with `left` iterations to go.  The iterations are spread evenly over
@@ -975,8 +985,14 @@ int launch_scatter_t(jacobi_plan *p, const T *from, T *grid, hipStream_t st)
     sp.wg_per_tile = (unsigned)ceil_div(sp.nvec, jk::SG_UNIT);
     sp.by_vrow.set(sp.vrow);
     sp.by_rows.set((unsigned)g.rows);
-    sp.xcd_chunk = SG_XCD_CHUNK;
+    sp.by_wg_per_tile.set(sp.wg_per_tile);
+    sp.by_layer.set((unsigned)(g.Ty * g.Tx));
+    sp.by_Tx.set((unsigned)g.Tx);
     const int64_t nwg = (int64_t)g.ntiles * sp.wg_per_tile;
+    const unsigned span = jk::NUM_XCD * SG_XCD_CHUNK;
+    sp.xcd_chunk = SG_XCD_CHUNK;
+    sp.in_groups = (unsigned)(nwg / span * span);
+    sp.by_group.set(span);
     if (nwg > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many workgroups for one scatter / gather launch");
     const dim3 blocks((unsigned)nwg), threads(jk::WG);
     if (store_flavour(p)) hipLaunchKernelGGL((jk::scatter_kernel<T, true>), blocks, threads, 0, st, g, sp, from, grid);
@@ -1348,7 +1364,7 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     ResidentChoice rc_res = resident_choice(plan, iters, residual_out_dev != nullptr);
     const bool norm_in_launch = rc_res.ok && residual_out_dev;
     if (!rc_res.ok && residual_out_dev) rc_res = resident_choice(plan, iters);
-    const bool blocks = blocks_usable(plan, iters, rc_res);
+    const bool blocks = blocks_usable(plan, iters, 0, rc_res);
     if (rc_res.ok && !blocks) {
         // small 2-D grid: every iteration inside one launch, which also carries the ring over and delivers the
         // residual of its result; the residual of `in`, if asked for, from the stand-alone reduction first
@@ -1622,7 +1638,7 @@ int jacobi_run(jacobi_plan *plan, void *in, void *out, int iters, int residual_e
     const int nres = residual_every > 0 ? iters / residual_every : 0;
     if (nres > 0 && !residuals_dev) return fail(JACOBI_EINVAL, "residuals_dev is NULL");
     hipStream_t st = (hipStream_t)stream;
-    if (iters > 0 && blocks_usable(plan, iters, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0))) {
+    if (iters > 0 && blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0))) {
         int rc = prepare_run(plan);
         if (rc) return rc;
         return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);
