@@ -389,7 +389,8 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    jacobi_pass_schedule still lists the passes of the launch-per-pass path, as which the grids swap
  *                    roles.  If not all of the launch's workgroups start within a few milliseconds (other work holds
  *                    CUs), those that did do the work through memory: slower, the same result.  A call takes this path
- *                    if a fixed estimate of both says it is faster (8 iterations and more of 1024^2).
+ *                    if a fixed estimate of both says it is faster (8 iterations and more of 1024^2) and it is not
+ *                    being recorded into a HIP graph; launches of one plan follow each other on whatever streams.
  *                    The launch is the whole call: it carries the Dirichlet ring over itself, and in
  *                    jacobi_run it also delivers the residual norm of the grid it produced (NaN if the
  *                    barrier gave up).  Two launches of one plan must not overlap in time: they share

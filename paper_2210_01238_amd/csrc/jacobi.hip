@@ -101,6 +101,7 @@ struct jacobi_plan {
     int64_t partial_cap = 0;
     BlockPlan blocks;
     char *block_scratch = nullptr;    // behind those
+    hipEvent_t block_done = nullptr;  // end of the last block launch: the next one, on whatever stream, waits for it
     unsigned *sync_words = nullptr;   // behind the partial sums: arrival counter and failure flag of the resident kernel
     // profiling events around update launches
     std::vector<hipEvent_t> ev;   // pairs: 2*i start, 2*i+1 stop
@@ -903,6 +904,9 @@ int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double
         const int64_t passes = every > 0 ? (int64_t)norms * count_passes(p, every) + count_passes(p, n % every) : count_passes(p, n);
         const bool to_other = (passes & 1) != 0;
         const bool timed = p->profile && p->ev_used < MAX_PROFILE_EVENTS;
+        // Launches of one plan share its messages and words, so they follow each other even if the caller puts calls with
+        // different grids on different streams (the launch-per-iteration path shares nothing and may overlap).
+        HIP_TRY(hipStreamWaitEvent(st, p->block_done, 0));
         if (timed) HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used], st));
         const int rc = launch_blocks(p, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
         if (rc) return rc;
@@ -910,11 +914,24 @@ int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double
             HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used + 1], st));
             ++p->ev_used;
         }
+        HIP_TRY(hipEventRecord(p->block_done, st));
         if (to_other) std::swap(cur, other);
         done += n;
     }
     if (final) *final = cur;
     return JACOBI_OK;
+}
+
+// Whether calls on `st` may run in blocks: not while they are recorded into a graph, whose replays nothing would keep apart
+// from the plan's other launches.
+bool may_run_blocks(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
 }
 
 template <typename T>
@@ -1114,6 +1131,15 @@ int prepare_plan(jacobi_plan *p)
         p->block_scratch = nullptr;
         return fail_hip(e, "hipMemset(barrier words)");
     }
+    if (p->blocks.ok) {
+        e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            (void)hipFree(p->partial);
+            p->partial = nullptr;
+            p->block_scratch = nullptr;
+            return fail_hip(e, "hipEventCreateWithFlags");
+        }
+    }
     p->prepared = true;
     return JACOBI_OK;
 }
@@ -1274,6 +1300,7 @@ int jacobi_destroy(jacobi_plan *plan)
         hipError_t e = hipDeviceSynchronize();
         if (e != hipSuccess) rc = fail_hip(e, "hipDeviceSynchronize");
         if (plan->partial) (void)hipFree(plan->partial);
+        if (plan->block_done) (void)hipEventDestroy(plan->block_done);
         for (hipEvent_t ev : plan->ev) (void)hipEventDestroy(ev);
         for (hipEvent_t ev : plan->task_events) (void)hipEventDestroy(ev);
         for (hipStream_t s : plan->task_streams) (void)hipStreamDestroy(s);
@@ -1364,7 +1391,7 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     ResidentChoice rc_res = resident_choice(plan, iters, residual_out_dev != nullptr);
     const bool norm_in_launch = rc_res.ok && residual_out_dev;
     if (!rc_res.ok && residual_out_dev) rc_res = resident_choice(plan, iters);
-    const bool blocks = blocks_usable(plan, iters, 0, rc_res);
+    const bool blocks = blocks_usable(plan, iters, 0, rc_res) && may_run_blocks(st);
     if (rc_res.ok && !blocks) {
         // small 2-D grid: every iteration inside one launch, which also carries the ring over and delivers the
         // residual of its result; the residual of `in`, if asked for, from the stand-alone reduction first
@@ -1638,7 +1665,8 @@ int jacobi_run(jacobi_plan *plan, void *in, void *out, int iters, int residual_e
     const int nres = residual_every > 0 ? iters / residual_every : 0;
     if (nres > 0 && !residuals_dev) return fail(JACOBI_EINVAL, "residuals_dev is NULL");
     hipStream_t st = (hipStream_t)stream;
-    if (iters > 0 && blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0))) {
+    if (iters > 0 && blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0)) &&
+        may_run_blocks(st)) {
         int rc = prepare_run(plan);
         if (rc) return rc;
         return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);

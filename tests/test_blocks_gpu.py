@@ -144,8 +144,26 @@ def test_blocks_in_a_hip_graph_and_two_plans_on_two_streams(H, oracle_mod):
             r.load(a)
             r.sweep(20 + k)                      # eager launches between the replays use up other tags
             r.residual()
+        # one plan, two pairs of grids, two streams at once: launches of one plan share its messages and follow each other
+        other = H.JacobiRun((512, 700), (4, 7), resident=1)
+        c = random_padded((512, 700), seed=14)
+        ref_c, _ = oracle_mod.run(c, 41)
+        try:
+            s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+            for k in range(4):
+                r.load(a)
+                other.load(c)
+                torch.cuda.synchronize()
+                f1 = H.B.jacobi_sweep(r.plan, r.a.data_ptr(), r.b.data_ptr(), iters, int(s1.cuda_stream))
+                f2 = H.B.jacobi_sweep(r.plan, other.a.data_ptr(), other.b.data_ptr(), 41, int(s2.cuda_stream))
+                torch.cuda.synchronize()
+                r.cur = r.a if f1 == r.a.data_ptr() else r.b
+                other.cur = other.a if f2 == other.a.data_ptr() else other.b
+                assert np.array_equal(r.fetch(), exp), k
+                assert np.array_equal(other.fetch(), ref_c), k
+        finally:
+            other.close()
         # two plans whose workgroups together are more than the chip has CUs, on two streams at once
-        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
         for k in range(4):
             r.load(a)
             q.load(b)
