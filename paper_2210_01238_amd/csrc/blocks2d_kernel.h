@@ -1,7 +1,7 @@
 // Mid-sized 2-D grids: a whole jacobi_run in one launch, the grid in the registers of the chip.
 //
-// The domain is cut into nbx x nby blocks, one workgroup (16 wavefronts) each, at most one per CU.  A workgroup HOLDS
-// 16*RW rows x 64*C columns: wavefront w rows [w*RW, (w+1)*RW), lane l columns [l*C, (l+1)*C).  The held ranges of
+// The domain is cut into nbx x nby blocks, one workgroup (8 wavefronts) each, at most one per CU.  A workgroup HOLDS
+// 8*RW rows x 64*C columns: wavefront w rows [w*RW, (w+1)*RW), lane l columns [l*C, (l+1)*C).  The held ranges of
 // neighbouring blocks overlap by 2d cells and more; each block OWNS the cells from d behind its held range's start to d
 // behind the next one's.  Held ranges lie inside the domain and the outermost ones end where it ends, so the Dirichlet
 // ring is never among the held cells: ring rows sit in LDS where the first / last wavefront finds the row next to its
@@ -14,12 +14,12 @@
 //
 // What bounds it: per iteration the vector unit (3 additions, 1 product and 4 / C lane shifts per cell in fp64; 8 wavefronts
 // of 8 rows x 128 columns 0.45 us, of which 0.39 are these instructions), per exchange the latency of a message between two
-// XCDs (0.75 us for one, 1.2 us for 16 in a row) and its bytes (2.5 us + 0.22 us per MB of all blocks' messages).  Eight
+// XCDs (0.5 - 0.6 us for one word per lane, 0.75 - 0.9 for 8 in a row, 1.1 - 1.2 for 16) and its bytes (2.5 us + 0.22 us per MB of all blocks' messages).  Eight
 // wavefronts of many rows rather than sixteen of few: half the border rows through LDS and room for the whole state (16
 // wavefronts of 4 rows: 0.93 against 0.74 us).  Measured, us per iteration, launches -> blocks, 100 iterations with the
 // launch: 300^2 3.10 -> 0.69, 512^2 3.60 -> 0.83, 768^2 4.96 -> 1.09, 1024^2 5.44 -> 1.19, 1536^2 7.6 -> 2.2, 2048^2 11.4 -> 6.0
 // (its registers do not hold a block any more: an exchange goes through scratch memory); fp32 1500 x 1110 5.36 -> 1.15, 2048^2
-// 6.7 -> 2.4.  256^2, 100 iterations and their norm: 106 -> 73 us against resident2d_kernel.
+// 6.7 -> 2.4.  256^2, 100 iterations and their norm: 107 -> 74 us against resident2d_kernel.
 #pragma once
 #include "blocks_common.h"
 

@@ -12,9 +12,9 @@
 // wavefront (EXACT); otherwise it sits in the lane cell behind the row's last one and keeps its value there.
 //
 // What bounds it: the exchange.  With few rows per block an iteration takes 0.6 us (64^3: 4 x 2 rows of 64 cells per
-// wavefront), a message 0.75 us from XCD to XCD, but every one or two iterations all border rows have to go out, arrive and be
-// taken apart.  Measured, us per iteration, launches -> blocks (plus about 20 us per launch): 64^3 in eight tiles 5.96 -> 3.6, in
-// fp32 5.3 -> 2.6, 96 x 96 x 128 7.95 -> 5.0, 128^3 in fp32 11.0 -> 4.3.  Larger cubes need patches that do not fit the registers
+// wavefront), a message 0.5 - 0.9 us from XCD to XCD, but every one or two iterations all border rows have to go out, arrive and be
+// taken apart.  Measured, us per iteration, launches -> blocks (plus about 20 us per launch): 64^3 in eight tiles 5.96 -> 3.4, in
+// fp32 5.3 -> 2.45, 128^3 in fp32 11.0 -> 4.3.  Larger cubes need patches that do not fit the registers
 // (7 x 4 rows of 256 fp32 cells: most of the state goes to scratch memory), so they stay with a launch per iteration.
 #pragma once
 #include "blocks_common.h"
