@@ -187,7 +187,7 @@ struct RowWalk {
 // Barrier of the plain path among `members` workgroups; every thread calls it.  Returns false if it was given up.
 __device__ __forceinline__ bool plain_barrier(const BlockRun &br, unsigned members, unsigned round, int *lds_flag)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    stores_arrived();                             // thread 0 then writes the L2 back for all of them
     __syncthreads();
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");

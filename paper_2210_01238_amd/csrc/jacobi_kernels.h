@@ -229,6 +229,11 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// All stores of the calling wavefront have arrived (in the L2; agent-scope ones beyond it).  __syncthreads() alone
+// does not wait for them: a workgroup's wavefronts share an L1, so only a workgroup that tells ANOTHER one about its
+// stores needs this, in every wavefront, before the barrier behind which one thread does the telling.
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Workgroup sum: wavefront shuffle tree -> one LDS slot per wavefront -> fixed-order add.
 // Every thread of the workgroup must call it; the result is valid in thread 0.
 __device__ __forceinline__ double wg_sum(double v, double *lds /* WAVES_PER_WG (or more) slots */)
