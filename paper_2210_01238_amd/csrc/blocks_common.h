@@ -251,9 +251,6 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
             __syncthreads();
             const double tot = wg_sum(acc, red);
             if (threadIdx.x == 0) __hip_atomic_store(&br.partial[(long long)norm * gridDim.x + me], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (me == 0)          // nobody writes the sums of the workgroups that are not there
-                for (unsigned w = members + threadIdx.x; w < gridDim.x; w += blockDim.x)
-                    __hip_atomic_store(&br.partial[(long long)norm * gridDim.x + w], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
             ++norm;
         }
@@ -271,23 +268,23 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
         }
 }
 
-// The end of a workgroup: the last one adds up the norms and leaves the words as the next launch has to find them.
+// The end of a workgroup: the last one adds up the norms - one sum per workgroup that did the work: all of them, or those that
+// were counted in when the roll was closed - and leaves the words as the next launch has to find them.
 // `exchanges`: how many tags the launch has used at most.  Every thread calls it.
 __device__ __forceinline__ void block_epilogue(const BlockRun &br, unsigned epoch, unsigned exchanges, double *red, int *lds_flag)
 {
+    // This workgroup's sums and its failure flag - any wavefront may have raised it - went out past the caches: they only have
+    // to have arrived.  (An agent-scope release here would have every workgroup write back its XCD's whole L2.)
+    stores_arrived();
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // This workgroup's sums went out past the caches: they only have to have arrived.  (An agent-scope release
-        // here would have every workgroup write back its XCD's whole L2.)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        *lds_flag = agent_add(&br.sync->done, 1u) == gridDim.x - 1 ? 1 : 0;
-    }
+    if (threadIdx.x == 0) *lds_flag = agent_add(&br.sync->done, 1u) == gridDim.x - 1 ? 1 : 0;
     __syncthreads();
     if (!*lds_flag) return;
     const bool failed = agent_load(&br.sync->failed) != 0u;
+    const unsigned counted = agent_load(&br.sync->participants), nsums = counted ? counted : gridDim.x;
     for (int k = 0; k < br.norms; ++k) {
         double v = 0.0;
-        for (unsigned i = threadIdx.x; i < gridDim.x; i += blockDim.x)
+        for (unsigned i = threadIdx.x; i < nsums; i += blockDim.x)
             v += __hip_atomic_load(&br.partial[(long long)k * gridDim.x + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const double sum = wg_sum(v, red);
         if (threadIdx.x == 0) br.result[k] = failed ? __builtin_nan("") : sqrt(sum);

@@ -19,6 +19,7 @@ template __global__ void jk::blocks3d_kernel<float, 2, 4, 2, true>(jk::Geo, jk::
 template __global__ void jk::resident2d_kernel<float, 1, 1>(jk::Geo, jk::ResidentParams, float *, float *);
 """
 STORE = re.compile(r"(global|buffer|flat)_(store|atomic)")
+EDGE = re.compile(r"label|s_c?branch")           # other ways lead here, or from here elsewhere
 VMCNT0 = re.compile(r"s_waitcnt .*vmcnt\(0\)")
 
 
@@ -40,6 +41,8 @@ def kernels(tmp_path_factory):
             found[name] = []
         elif line.startswith(".Lfunc_end"):
             name = None
+        elif name and line.startswith(".LBB"):
+            found[name].append("label")
         elif name and line.startswith("\t") and not line.lstrip().startswith((";", ".")):
             found[name].append(line.split(";")[0].strip())
     assert set(found) == {"blocks2d_kernel", "blocks3d_kernel", "resident2d_kernel"}
@@ -47,8 +50,9 @@ def kernels(tmp_path_factory):
 
 
 def unwaited(code, sites):
-    """Of the signals `sites` (indexes of instructions) those whose workgroup barrier some wavefront may pass with stores under way.
-    A signal with a store of its own behind the barrier publishes that one, not what the others stored."""
+    """Of the signals `sites` (indexes of instructions) those whose workgroup barrier some wavefront may pass with stores under way:
+    no wait right in front of it, on every way to it.  A signal with a store of its own behind the barrier publishes that
+    one, not what the others stored."""
     bad, looked_at = [], 0
     for i in sites:
         k = i - 1
@@ -58,7 +62,7 @@ def unwaited(code, sites):
             continue
         looked_at += 1
         k -= 1
-        while k >= 0 and not VMCNT0.match(code[k]) and not STORE.match(code[k]):
+        while k >= 0 and not VMCNT0.match(code[k]) and not STORE.match(code[k]) and not EDGE.match(code[k]):
             k -= 1
         if k < 0 or not VMCNT0.match(code[k]):
             bad.append(code[max(k, 0):i + 1])
@@ -70,4 +74,13 @@ def test_barrier_among_workgroups_waits_for_every_wavefront(kernels, name):
     """The write-back of the L2 comes after all stores of the workgroup."""
     code = kernels[name]
     bad, n = unwaited(code, [i for i, x in enumerate(code) if x.startswith("buffer_wbl2")])
+    assert n >= 1 and not bad, bad
+
+
+@pytest.mark.parametrize("name", ["blocks2d_kernel", "blocks3d_kernel"])
+def test_end_of_a_workgroup_waits_for_every_wavefront(kernels, name):
+    """Norms' sums and the failure flag come from any of them, and the workgroup that finishes last reads and clears them.  (The
+    count of finished workgroups is the third word of the plan's.)"""
+    code = kernels[name]
+    bad, n = unwaited(code, [i for i, x in enumerate(code) if re.match(r"global_atomic_add v.* offset:8 sc0", x)])
     assert n >= 1 and not bad, bad
