@@ -48,11 +48,11 @@ namespace jk {
 // this workgroup gave up waiting (or saw that another one had).  The cache maintenance that makes one XCD's
 // stores visible to the others (write back the L2's dirty lines before arriving, drop its clean lines after
 // the wait) is done ONCE per workgroup, by thread 0: the wavefronts of a workgroup share their CU's L1 and
-// their XCD's L2, every wavefront's stores have completed when it passes the first barrier below, and none
+// their XCD's L2, every wavefront waits for its stores before it passes the first barrier below, and none
 // of them loads before the second.  (All 16 wavefronts doing it cost 7 us per barrier.)
 __device__ __forceinline__ bool resident_grid_barrier(unsigned *sync, unsigned target, unsigned spin_limit, int *lds_flag)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // this wavefront's stores have completed
+    stores_arrived();
     __syncthreads();
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");

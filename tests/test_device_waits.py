@@ -69,7 +69,7 @@ def unwaited(code, sites):
     return bad, looked_at
 
 
-@pytest.mark.parametrize("name", ["blocks2d_kernel", "blocks3d_kernel"])
+@pytest.mark.parametrize("name", ["blocks2d_kernel", "blocks3d_kernel", "resident2d_kernel"])
 def test_barrier_among_workgroups_waits_for_every_wavefront(kernels, name):
     """The write-back of the L2 comes after all stores of the workgroup."""
     code = kernels[name]
