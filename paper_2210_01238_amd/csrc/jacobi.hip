@@ -1125,6 +1125,9 @@ int prepare_plan(jacobi_plan *p)
         clear = (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words);
     }
     e = hipMemset(p->sync_words, 0, clear);
+    // hipMemset returns before the memory is clear (2 us for 37 MB), and streams created as non-blocking, on which the first
+    // launch may come, do not wait for the default stream
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         (void)hipFree(p->partial);
         p->partial = nullptr;
