@@ -120,7 +120,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * to grow: 8 bytes per 4 one-row strips of about 100 cells at most, 5 MiB for 16384^2; behind
  * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
  * blocks, their messages and words (16 to 32 bytes per border cell: 2 MB for 256^2, 37 MB for 1024^2), set
- * to zero here once).
+ * to zero here once; where the device has no room for the messages, the plan does without them and runs launch by launch).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -128,12 +128,13 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * jacobi_sweep, jacobi_sweep_residual, jacobi_run, halo_exchange and residual_norm allocates,
  * frees or synchronises anything, whatever options are changed in between, so they can be recorded
  * into a HIP graph (the call that runs the set-up cannot: do it before the capture starts).
+ * Waits for the default stream (the scratch is cleared on it).
  * Idempotent.  Errors: EINVAL (NULL), ENOMEM, EHIP.
  */
 int jacobi_prepare(jacobi_plan *plan);
 
 /* Bytes of device scratch jacobi_prepare allocates for this plan (host-only: no device call;
- * independent of the current option values); 0 if plan is NULL. */
+ * independent of the current option values; once it has run, what it did allocate); 0 if plan is NULL. */
 size_t jacobi_scratch_bytes(const jacobi_plan *plan);
 
 /* Frees the plan and the device scratch it owns (synchronises the device first if it owns any).

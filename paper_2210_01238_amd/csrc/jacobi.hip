@@ -1108,8 +1108,15 @@ int prepare_plan(jacobi_plan *p)
     else (void)hipGetLastError();
     const int64_t need = max_partials(p) + 1;      // + the slot residual_norm_host reads back
     // behind them: two doubles' worth of words for the resident kernel's grid barrier
-    const size_t words_end = (size_t)round_up((need + 2) * (int64_t)sizeof(double), 256);
-    hipError_t e = hipMalloc((void **)&p->partial, p->blocks.ok ? words_end + (size_t)p->blocks.scratch_bytes : (size_t)(need + 2) * sizeof(double));
+    const size_t sums = (size_t)(need + 2) * sizeof(double), words_end = (size_t)round_up((int64_t)sums, 256);
+    bool blocks = p->blocks.ok;
+    hipError_t e = hipMalloc((void **)&p->partial, blocks ? words_end + (size_t)p->blocks.scratch_bytes : sums);
+    if (e == hipErrorOutOfMemory && blocks) {
+        // the messages are an extra (up to some 90 MB): without room for them the plan runs by launches
+        (void)hipGetLastError();
+        blocks = false;
+        e = hipMalloc((void **)&p->partial, sums);
+    }
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         return fail(JACOBI_ENOMEM, "device allocation of residual scratch failed");
@@ -1120,7 +1127,7 @@ int prepare_plan(jacobi_plan *p)
     // the resident kernel's barrier words are zero between launches: it clears them itself when it finishes
     // so are the block kernels' words, and no message carries a tag yet
     size_t clear = 2 * sizeof(double);
-    if (p->blocks.ok) {
+    if (blocks) {
         p->block_scratch = (char *)p->partial + words_end;
         clear = (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words);
     }
@@ -1134,7 +1141,7 @@ int prepare_plan(jacobi_plan *p)
         p->block_scratch = nullptr;
         return fail_hip(e, "hipMemset(barrier words)");
     }
-    if (p->blocks.ok) {
+    if (blocks) {
         e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
         if (e != hipSuccess) {
             (void)hipFree(p->partial);
@@ -1143,6 +1150,7 @@ int prepare_plan(jacobi_plan *p)
             return fail_hip(e, "hipEventCreateWithFlags");
         }
     }
+    p->blocks.ok = blocks;
     p->prepared = true;
     return JACOBI_OK;
 }
@@ -1668,11 +1676,10 @@ int jacobi_run(jacobi_plan *plan, void *in, void *out, int iters, int residual_e
     const int nres = residual_every > 0 ? iters / residual_every : 0;
     if (nres > 0 && !residuals_dev) return fail(JACOBI_EINVAL, "residuals_dev is NULL");
     hipStream_t st = (hipStream_t)stream;
-    if (iters > 0 && blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0)) &&
-        may_run_blocks(st)) {
-        int rc = prepare_run(plan);
-        if (rc) return rc;
-        return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);
+    if (iters > 0 && plan->blocks.ok && may_run_blocks(st)) {
+        if (int rc = prepare_run(plan)) return rc;       // may find no room for the messages
+        if (blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0)))
+            return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);
     }
     void *cur = in, *other = out;
     int done = 0, pending = -1;      // pending: index of a residual still owed for the grid in `cur`

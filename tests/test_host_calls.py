@@ -52,3 +52,39 @@ for dims in ((256, 256), (1024, 1024), (64, 64, 64), (4096, 4096)):
     assert "hipStreamSynchronize" in after or "hipDeviceSynchronize" in after, calls
     J.jacobi_destroy(p)
 """)
+
+
+def test_without_room_for_the_messages_a_plan_runs_by_launches(stub):
+    """The block kernels' messages are an extra: where the device has room for the partial sums only, the plan is set up and runs
+    launch by launch as without them; without room for those it is out of memory."""
+    run(stub, """
+for dims, tiles in (((1024, 1024), (4, 4)), ((64, 64, 64), (2, 2, 2))):
+    p = J.jacobi_create(dims, tiles, J.JACOBI_F64)
+    whole = J.jacobi_scratch_bytes(p)
+    stub.stub_malloc_limit(whole - 1)
+    J.jacobi_prepare(p)
+    sizes = [int(c[1]) for c in log() if c[0] == "hipMalloc"]
+    assert sizes[0] == whole and sizes[-1] < 1 << 20, sizes
+    assert J.jacobi_scratch_bytes(p) == sizes[-1]
+    a, b = GRIDS(p)
+    J.jacobi_sweep(p, a, b, 50)
+    assert sum(c[0] == "hipLaunchKernel" for c in log()) >= 50
+    J.jacobi_destroy(p)
+    p = J.jacobi_create(dims, tiles, J.JACOBI_F64)
+    J.jacobi_run(p, a, b, 50, 25, 1 << 16)           # which sets the plan up itself
+    assert sum(c[0] == "hipLaunchKernel" for c in log()) >= 50
+    J.jacobi_destroy(p)
+    p = J.jacobi_create(dims, tiles, J.JACOBI_F64)
+    stub.stub_malloc_limit(1000)
+    try:
+        J.jacobi_prepare(p)
+        raise SystemExit("prepared without memory")
+    except J.JacobiError as e:
+        assert e.code == J.binding.JACOBI_ENOMEM
+    stub.stub_malloc_limit(1 << 40)
+    J.jacobi_prepare(p)                              # and again, with room: in blocks after all
+    log()
+    J.jacobi_sweep(p, a, b, 50)
+    assert sum(c[0] == "hipLaunchKernel" for c in log()) == 1
+    J.jacobi_destroy(p)
+""")
