@@ -208,6 +208,7 @@ struct ScatterParams {
     FastDiv by_vrow, by_rows, by_wg_per_tile, by_layer, by_Tx;
     // workgroup order (see xcd_logical_wg; the host knows the sizes, so nothing is divided by a variable here)
     int xcd_chunk;
+    unsigned first;            // workgroups of earlier launches
     unsigned in_groups;        // workgroups that lie in whole groups of NUM_XCD * xcd_chunk
     FastDiv by_group;
 };
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, co
     using V = typename Vec<T>::type;
     constexpr int NV = Vec<T>::N;
     typedef T VU __attribute__((ext_vector_type(NV), aligned(sizeof(T))));
-    unsigned lwg = blockIdx.x;
+    unsigned lwg = blockIdx.x + sp.first;
     if (lwg < sp.in_groups) {
         const unsigned span = NUM_XCD * (unsigned)sp.xcd_chunk, first = sp.by_group(lwg) * span, within = lwg - first;
         lwg = first + within % NUM_XCD * (unsigned)sp.xcd_chunk + within / NUM_XCD;

@@ -1011,10 +1011,14 @@ int launch_scatter_t(jacobi_plan *p, const T *from, T *grid, hipStream_t st)
     sp.in_groups = (unsigned)(nwg / span * span);
     sp.by_group.set(span);
     if (nwg > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many workgroups for one scatter / gather launch");
-    const dim3 blocks((unsigned)nwg), threads(jk::WG);
-    if (store_flavour(p)) hipLaunchKernelGGL((jk::scatter_kernel<T, true>), blocks, threads, 0, st, g, sp, from, grid);
-    else hipLaunchKernelGGL((jk::scatter_kernel<T, false>), blocks, threads, 0, st, g, sp, from, grid);
-    HIP_TRY(hipGetLastError());
+    // a launch has fewer than 2^32 threads (2^24 one-row tiles and more need several launches); whole groups of the XCD order each
+    const unsigned most = 0xffffffffu / jk::WG / span * span;
+    for (sp.first = 0; sp.first < nwg; sp.first += most) {
+        const dim3 blocks(std::min((unsigned)nwg - sp.first, most)), threads(jk::WG);
+        if (store_flavour(p)) hipLaunchKernelGGL((jk::scatter_kernel<T, true>), blocks, threads, 0, st, g, sp, from, grid);
+        else hipLaunchKernelGGL((jk::scatter_kernel<T, false>), blocks, threads, 0, st, g, sp, from, grid);
+        HIP_TRY(hipGetLastError());
+    }
     return JACOBI_OK;
 }
 

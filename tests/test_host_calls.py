@@ -88,3 +88,19 @@ for dims, tiles in (((1024, 1024), (4, 4)), ((64, 64, 64), (2, 2, 2))):
     assert sum(c[0] == "hipLaunchKernel" for c in log()) == 1
     J.jacobi_destroy(p)
 """)
+
+
+def test_scatter_of_very_many_tiles_stays_within_what_one_launch_takes(stub):
+    """A launch of 2^32 threads and more is refused by the runtime; a workgroup per one-row tile gets there with 2^24 tiles."""
+    run(stub, """
+n = (1 << 24) + 300
+for tiles, dtype in ((n, J.JACOBI_F64), (1000, J.JACOBI_F32)):
+    p = J.jacobi_create((tiles, 3), (tiles, 1), dtype)
+    J.jacobi_prepare(p)
+    log()
+    J.jacobi_scatter(p, 1 << 20, 1 << 20)
+    launches = [(int(c[1]), int(c[2])) for c in log() if c[0] == "hipLaunchKernel"]
+    assert sum(g for g, b in launches) == tiles, launches
+    assert all(g * b < 1 << 32 for g, b in launches), launches
+    J.jacobi_destroy(p)
+""")

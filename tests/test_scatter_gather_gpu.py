@@ -85,3 +85,23 @@ def test_gather_ignores_the_copies_of_neighbours_cells(H):
             assert np.array_equal(r.fetch(), a)
         finally:
             r.close()
+
+
+def test_scatter_gather_of_more_tiles_than_one_launch_takes(H):
+    """2^24 one-row tiles and some (15 GB): the scatter runs as two launches.  Out and back again, and a row of cells in between."""
+    import torch
+    n = (1 << 24) + 300
+    r = H.JacobiRun((n, 3), (n, 1))
+    try:
+        stream = int(torch.cuda.current_stream().cuda_stream)
+        a = torch.arange((n + 2) * 5, dtype=torch.float64, device="cuda").reshape(n + 2, 5)
+        out = torch.zeros_like(a)
+        H.B.jacobi_scatter(r.plan, a.data_ptr(), r.a.data_ptr(), stream)
+        H.B.jacobi_gather(r.plan, r.a.data_ptr(), out.data_ptr(), stream)
+        assert torch.equal(out, a)
+        lay = H.B.jacobi_get_layout(r.plan)
+        tiles = r.a.view(torch.float64)[:n * lay.tile_stride].view(n, lay.tile_stride)
+        for k in range(3):                                   # the halo rows, too
+            assert torch.equal(tiles[:, k * lay.pitch:k * lay.pitch + 3], a[k:k + n, 1:4])
+    finally:
+        r.close()
