@@ -644,18 +644,19 @@ constexpr int64_t BLOCK_SYNC_BYTES = 256;
 constexpr unsigned ROLL_DEFAULT_LIMIT = 1u << 11;        // polls of about a microsecond each
 
 // Cuts n cells into held ranges of `held`, starts at multiples of `unit`, `d` ghost cells; false if that cannot be done
-// with owned ranges of at least `least` cells.
-bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, jk::BlockCut *c)
+// with owned ranges of at least `least` cells, or takes more than `most` blocks.
+bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, jk::BlockCut *c)
 {
     if (n < held || n % unit || held % unit || d % unit || held <= 2 * d) return false;
+    const int64_t units = (n - held) / unit, nb = 1 + ceil_div(units, (held - 2 * d) / unit);
+    if (nb > most) return false;
     c->n = (int)n; c->held = held; c->d = d; c->unit = unit;
-    const int units = (int)(n - held) / unit;
-    c->nb = 1 + (int)ceil_div(units, (held - 2 * d) / unit);
-    c->step = c->nb > 1 ? units / (c->nb - 1) : 0;
-    c->longer = c->nb > 1 ? units % (c->nb - 1) : 0;
-    for (int b = 0; b < c->nb; ++b)
-        if (c->nb > 1 && c->own_hi(b) - c->own_lo(b) < least) return false;
-    return true;
+    c->nb = (int)nb;
+    c->step = nb > 1 ? (int)(units / (nb - 1)) : 0;
+    c->longer = nb > 1 ? (int)(units % (nb - 1)) : 0;
+    // The last start is always `step` units behind the one before it.  What the blocks own: between starts the step; the first
+    // one d more, the last one what its held range holds behind its ghost cells.
+    return nb == 1 || (c->own_hi(0) >= least && held - d >= least && (nb == 2 || c->step * unit >= least));
 }
 
 // What the model below says a launch per iteration / passes of up to 12 iterations take (us per iteration), and what a
@@ -699,7 +700,7 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
         if (Nx <= HW || Ny < HH) continue;
         for (int d = 4; d <= 16; d += 4) {
             jk::BlockCut x, y;
-            if (!cut_into_blocks(Nx, HW, d, v.c, 2 * d, &x) || !cut_into_blocks(Ny, HH, d, 1, 2 * d, &y)) continue;
+            if (!cut_into_blocks(Nx, HW, d, v.c, 2 * d, num_cu, &x) || !cut_into_blocks(Ny, HH, d, 1, 2 * d, num_cu, &y)) continue;
             if (x.nb < 2 || (int64_t)x.nb * y.nb > num_cu) continue;
             const double msg = (double)x.nb * y.nb * jk::blocks2d_frame(x, y) * (f64 ? 16 : 8);
             const double iterate = 0.06 + 2 * v.rw * (4 * v.c + (f64 ? 4 : 2)) * 0.00205;
@@ -747,7 +748,7 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
         if (Nx > width || 2 * Nx <= width) continue;            // at least half of the lanes have cells
         for (int d = 1; d <= 3; ++d) {
             jk::BlockCut y, z;
-            if (!cut_into_blocks(Ny + 2, HY, d, 1, 2 * d, &y) || !cut_into_blocks(Nz + 2, HZ, d, 1, 2 * d, &z)) continue;
+            if (!cut_into_blocks(Ny + 2, HY, d, 1, 2 * d, num_cu, &y) || !cut_into_blocks(Nz + 2, HZ, d, 1, 2 * d, num_cu, &z)) continue;
             const int64_t nb = (int64_t)y.nb * z.nb;
             if (nb > num_cu) continue;
             int ny = 0, nz = 0;
