@@ -61,6 +61,7 @@ __device__ __forceinline__ void roll_call(BlockSync *s, unsigned expected, unsig
         if (!(before & ROLL_CLOSED)) {
             members = before;
             agent_store(&s->participants, members);
+            stores_arrived();                     // this workgroup's other wavefronts read it, too
         } else {
             // whoever closed it writes the number next: it runs, so this ends
             while ((members = agent_load(&s->participants)) == 0u) __builtin_amdgcn_s_sleep(1);

@@ -84,3 +84,21 @@ def test_end_of_a_workgroup_waits_for_every_wavefront(kernels, name):
     code = kernels[name]
     bad, n = unwaited(code, [i for i, x in enumerate(code) if re.match(r"global_atomic_add v.* offset:8 sc0", x)])
     assert n >= 1 and not bad, bad
+
+
+@pytest.mark.parametrize("name", ["blocks2d_kernel", "blocks3d_kernel"])
+def test_number_of_participants_is_there_before_other_wavefronts_read_it(kernels, name):
+    """The thread that closes the roll stores the number (the second word of the plan's), and the other wavefronts of its workgroup
+    step through the cells by it: read as zero, their loop would not end."""
+    code = kernels[name]
+    reset = re.compile(r"global_store_dword v\d+, v\d+, s\[[\d:]+\] offset:8 sc1")       # the end of a launch clears word after word
+    n = 0
+    for i, x in enumerate(code):
+        if not re.match(r"global_store_dword v\d+, v\d+, s\[[\d:]+\] offset:4 sc1", x) or reset.match(code[i + 1]):
+            continue
+        n += 1
+        k = i + 1
+        while not VMCNT0.match(code[k]) and not EDGE.match(code[k]) and not code[k].startswith("s_barrier"):
+            k += 1
+        assert VMCNT0.match(code[k]), code[i:k + 1]
+    assert n >= 1
