@@ -405,6 +405,10 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *   "resident_spin_limit"  0 | n  polls a workgroup waits at that barrier before giving up: n - 1
  *                    beyond the first (0 = default, about 4 million: seconds); with blocks: polls before the
  *                    workgroups that are there go on without the others (0 = default, 2048)
+ *   "resident_admitted"  0 | 1..65536  for tests of that case: with blocks, only so many workgroups do the work,
+ *                    through memory, as if the others had not started (0 = default: all)
+ *   "resident_epoch_limit"  0 | 1..3221225472  for tests: number of exchanges of a plan after which a launch with blocks
+ *                    clears the messages and counts from 0 again (0 = default, 3221225472)
  *   "stack"          0 | 1 | 4 | 8  2-D stand-alone residual pass: wavefronts of a workgroup stacked over
  *                    the same columns, 8 rows each, passing each other their border rows through LDS
  *                    instead of loading them again (0 = choose: 8 on tiles of 1024 rows and more, else
@@ -425,6 +429,8 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  * jacobi_get_option also reads these figures (not settable): "lds_limit_failed" (see "cu_lds"),
  * "lds_request_1" / "lds_request_2" (the LDS bytes requested to keep 1 / 2 workgroups per CU; 0 while
  * the LDS size is unknown), "num_cu" (compute units; 256 until jacobi_prepare has asked the device),
+ * how a plan is cut into the blocks that option "resident" keeps in registers (all 0: it is not): "block_workgroups",
+ * "block_cells_per_lane", "block_rows_per_wave", "block_planes_per_wave" (3-D), "block_depth" (iterations between exchanges),
  * and what a single-step launch will run with under the current options (host-only, the choices the
  * 0 = "choose" settings resolve to): "update_rows_per_strip", "update_rows_per_wave", "update_unroll",
  * "update_xcd_chunk", "update_strips" (wavefronts of work), "update_one_workgroup_per_cu",

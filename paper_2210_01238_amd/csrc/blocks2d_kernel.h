@@ -364,7 +364,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         stale = n;
         if (it == 0) {
             // is everybody there?  (the first exchange and the result wait for it)
-            if (threadIdx.x == 0) roll_call(br.sync, (unsigned)nb, ticket, br.roll_limit, &flag);
+            if (threadIdx.x == 0) roll_call(br.sync, (unsigned)nb, br.admitted, ticket, br.roll_limit, &flag);
             __syncthreads();
             if (flag != ALL_PRESENT) {
                 if (flag >= 0) plain_path<T, 2>(g, br, ga, gb, red, &flag);

@@ -32,7 +32,6 @@
 namespace jk {
 
 constexpr unsigned ROLL_CLOSED = 1u << 30;
-constexpr unsigned EPOCH_LIMIT = 0xc0000000u;    // beyond it the messages are cleared and the epoch starts at 0 again
 
 __device__ __forceinline__ unsigned agent_load(unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void agent_store(unsigned *p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -44,22 +43,26 @@ __device__ __forceinline__ int opaque(int uniform) { uniform = __builtin_amdgcn_
 __device__ __forceinline__ int opaque_lane(int v) { asm volatile("" : "+v"(v)); return v; }
 
 // Are all `expected` workgroups there?  *outcome: ALL_PRESENT, or TOO_LATE if the roll was closed before this workgroup
-// counted itself in (it got `ticket`), or else this workgroup's number on the plain path.  One thread calls it.
+// counted itself in (it got `ticket`), or else this workgroup's number on the plain path.  Only the first `admitted` workgroups
+// are let in: fewer than expected on request, as if the others had come too late.  One thread calls it.
 constexpr int ALL_PRESENT = -1, TOO_LATE = -2;
-__device__ __forceinline__ void roll_call(BlockSync *s, unsigned expected, unsigned ticket, unsigned limit, int *outcome)
+__device__ __forceinline__ void roll_call(BlockSync *s, unsigned expected, unsigned admitted, unsigned ticket, unsigned limit, int *outcome)
 {
-    if (ticket & ROLL_CLOSED) { *outcome = TOO_LATE; return; }
+    if (ticket >= admitted) { *outcome = TOO_LATE; return; }        // ROLL_CLOSED is beyond every number
     unsigned members = 0;
     for (unsigned n = 0; n <= limit; ++n) {
         const unsigned r = agent_load(&s->roll);
         if (r & ROLL_CLOSED) break;
-        if (r == expected) { members = expected; break; }
+        if (r >= admitted) {
+            if (admitted == expected) members = expected;
+            break;
+        }
         __builtin_amdgcn_s_sleep(2);
     }
     if (members == 0) {
         const unsigned before = __hip_atomic_fetch_or(&s->roll, ROLL_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (!(before & ROLL_CLOSED)) {
-            members = before;
+            members = min(before, admitted);
             agent_store(&s->participants, members);
             stores_arrived();                     // this workgroup's other wavefronts read it, too
         } else {
@@ -292,7 +295,7 @@ __device__ __forceinline__ void block_epilogue(const BlockRun &br, unsigned epoc
         __syncthreads();
     }
     unsigned next = epoch + exchanges;
-    if (next > EPOCH_LIMIT) {                    // once in 2^32 exchanges
+    if (next > br.epoch_limit) {                 // by default once in some 2^31 exchanges
         u32x4 *m = (u32x4 *)br.msg;
         for (unsigned i = threadIdx.x; i < 2u * (br.msg_bytes / 16u); i += blockDim.x) m[i] = u32x4{0u, 0u, 0u, 0u};
         next = 0;

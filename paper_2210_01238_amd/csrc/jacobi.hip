@@ -87,7 +87,7 @@ struct jacobi_plan {
     size_t esize;
     // options
     int64_t fused = 1, rows_per_strip = 0, nontemporal = 1, profile = 0, unroll = 0, xcd_chunk = 0, rows_per_wave = 0, tblock = 1, cooperative = 1;
-    int64_t resident = 1, resident_depth = 0, resident_rows = 0, resident_spin_limit = 0;
+    int64_t resident = 1, resident_depth = 0, resident_rows = 0, resident_spin_limit = 0, resident_admitted = 0, resident_epoch_limit = 0;
     int64_t stack = 0;                // 2-D residual pass: wavefronts per workgroup stacked over one column segment (0: choose, 1: off, 4, 8)
     int64_t cu_lds_option = 0;        // option "cu_lds": LDS bytes per CU to compute the workgroup limits from (0: the device's)
     int64_t lds_limit_failed = 0;     // read-only: a launch dropped its workgroup limit (the occupancy query did not confirm it)
@@ -642,6 +642,7 @@ constexpr int BLOCK_NORMS = 128;                 // norms of one launch
 constexpr int BLOCK_MAX_ITERS = 1 << 28;         // iterations of one call (the tags of a launch have to fit 32 bits)
 constexpr int64_t BLOCK_SYNC_BYTES = 256;
 constexpr unsigned ROLL_DEFAULT_LIMIT = 1u << 11;        // polls of about a microsecond each
+constexpr unsigned EPOCH_DEFAULT_LIMIT = 0xc0000000u;    // a launch adds less than 2^30 to the epoch: no tag repeats
 
 // Cuts n cells into held ranges of `held`, starts at multiples of `unit`, `d` ghost cells; false if that cannot be done
 // with owned ranges of at least `least` cells, or takes more than `most` blocks.
@@ -877,6 +878,8 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
     run.final_is_out = final_is_out ? 1 : 0;
     run.roll_limit = p->resident_spin_limit > 0 ? (unsigned)(p->resident_spin_limit - 1) : ROLL_DEFAULT_LIMIT;
     run.spin_limit = RESIDENT_DEFAULT_SPIN;
+    run.admitted = (unsigned)(p->resident_admitted > 0 ? std::min<int64_t>(p->resident_admitted, p->blocks.workgroups) : p->blocks.workgroups);
+    run.epoch_limit = p->resident_epoch_limit > 0 ? (unsigned)p->resident_epoch_limit : EPOCH_DEFAULT_LIMIT;
     run.sync = (jk::BlockSync *)p->block_scratch;
     run.partial = (double *)(p->block_scratch + BLOCK_SYNC_BYTES);
     run.msg = p->block_scratch + p->blocks.scratch_bytes - 2 * p->blocks.msg_bytes;
@@ -1223,6 +1226,8 @@ const OptionSpec OPTIONS[] = {
     {"resident_depth", &jacobi_plan::resident_depth, 0, 31, {}},
     {"resident_rows", &jacobi_plan::resident_rows, 0, jk::RES_MAX_RW, {}},
     {"resident_spin_limit", &jacobi_plan::resident_spin_limit, 0, 1LL << 31, {}},
+    {"resident_admitted", &jacobi_plan::resident_admitted, 0, 1 << 16, {}},
+    {"resident_epoch_limit", &jacobi_plan::resident_epoch_limit, 0, 0xc0000000LL, {}},
     {"cu_lds", &jacobi_plan::cu_lds_option, 0, 1LL << 20, {}},
     {"stack", &jacobi_plan::stack, 0, 8, {1, 4, 8}},
 };
@@ -1805,6 +1810,13 @@ int jacobi_get_option(const jacobi_plan *plan, const char *key, int64_t *value)
     if (!strcmp(key, "lds_request_1")) { *value = lds_to_limit_workgroups(plan, 1); return JACOBI_OK; }
     if (!strcmp(key, "lds_request_2")) { *value = lds_to_limit_workgroups(plan, 2); return JACOBI_OK; }
     if (!strcmp(key, "num_cu")) { *value = plan->num_cu; return JACOBI_OK; }
+    // how the plan is cut into the blocks of one launch (all 0: it is not)
+    const BlockPlan &b = plan->blocks;
+    if (!strcmp(key, "block_workgroups")) { *value = b.ok ? b.workgroups : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_cells_per_lane")) { *value = b.ok ? b.cells_per_lane : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_rows_per_wave")) { *value = b.ok ? b.rows_per_wave : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_planes_per_wave")) { *value = b.ok ? b.planes_per_wave : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_depth")) { *value = b.ok ? b.y.d : 0; return JACOBI_OK; }
     // what the single-step launches will run with under the current options: "update_..." for the update,
     // "residual_..." for the stand-alone residual pass (the strip-per-wavefront kernel)
     for (const char *prefix : {"update_", "residual_"}) {

@@ -142,6 +142,8 @@ struct BlockRun {
     int norms;             // how many of them (iters / every, or 0)
     int final_is_out;      // the result goes to the grid the launch does not start from
     unsigned roll_limit, spin_limit;   // polls before the roll is closed / before a wait is given up
+    unsigned admitted;     // workgroups that may be counted in (all of them, unless a test wants the plain path)
+    unsigned epoch_limit;  // an epoch beyond it has the messages cleared and starts at 0 again
     BlockSync *sync;
     void *msg;             // two message areas
     unsigned msg_bytes;    // of one of them

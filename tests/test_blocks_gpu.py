@@ -52,12 +52,38 @@ def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype
     assert np.array_equal(out2, out) and res2 == res                # and the same bits on every run
 
 
-@pytest.mark.parametrize("dims,tiles,dtype", [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32),
-                                              ((64, 64, 64), (2, 2, 2), np.float64), ((61, 53, 47), (1, 1, 1), np.float32)])
+PLAIN = [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32), ((64, 64, 64), (2, 2, 2), np.float64),
+         ((61, 53, 47), (1, 1, 1), np.float32)]
+
+
+@pytest.mark.parametrize("dims,tiles,dtype", PLAIN)
 def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, tiles, dtype):
-    """resident_spin_limit = 1: the roll is called once, without waiting.  Some workgroups are then missing (or, if all
-    happen to be there, none): those present do the work along the plain path, with the same result; the next launch
-    finds the plan's words as it needs them."""
+    """Some workgroups come too late (resident_admitted: as many as are let in): the others do the work along the plain path, one
+    iteration after the other through memory, with the same result; the next launch finds the plan's words as it needs
+    them.  The norms' last bits show that it was that path: other workgroups' sums, in another order."""
+    a = random_padded(dims, dtype=dtype, seed=77)
+    r = H.JacobiRun(dims, tiles, dtype, resident=1)
+    try:
+        n = H.B.jacobi_get_option(r.plan, "block_workgroups")
+        for iters, every in ((24, 2), (23, 0), (26, 26), (25, 6)):
+            ref, ref_res = oracle_mod.run(a, iters, every)
+            norms = {}
+            for admitted in (0, 1, n // 2, n - 1, 0, n - 1, n - 1, 0):
+                r.set_option("resident_admitted", admitted)
+                r.load(a)
+                r.other().fill_(255)
+                res = r.run(iters, every, fuse_residual=True) if every else (r.sweep(iters) or [])
+                check(r.fetch(), res, ref, ref_res)
+                assert norms.setdefault(admitted, res) == res, (iters, every, admitted)
+            if len(ref_res) == 12:
+                assert len({tuple(v) for v in norms.values()}) == 4, norms
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("dims,tiles,dtype", PLAIN)
+def test_blocks_that_do_not_wait_for_each_other_to_start(H, oracle_mod, dims, tiles, dtype):
+    """resident_spin_limit = 1: the roll is called once, without waiting; whoever is there does the work, whichever path it is."""
     a = random_padded(dims, dtype=dtype, seed=77)
     for iters, every in ((24, 8), (23, 0), (26, 26)):
         ref, ref_res = oracle_mod.run(a, iters, every)
@@ -70,6 +96,24 @@ def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, 
                 check(r.fetch(), res, ref, ref_res)
         finally:
             r.close()
+
+
+@pytest.mark.parametrize("dims,tiles,dtype", PLAIN)
+def test_blocks_count_exchanges_from_zero_again(H, oracle_mod, dims, tiles, dtype):
+    """Every launch (resident_epoch_limit = 1) and every third one clears the messages and starts with the same tags: other fields
+    each time, so that a message left over would show."""
+    r = H.JacobiRun(dims, tiles, dtype, resident=1)
+    try:
+        for limit in (1, 130):
+            r.set_option("resident_epoch_limit", limit)
+            for k in range(5):
+                a = random_padded(dims, dtype=dtype, seed=100 + k)
+                ref, ref_res = oracle_mod.run(a, 50, 25)
+                r.load(a)
+                res = r.run(50, 25, fuse_residual=True)
+                check(r.fetch(), res, ref, ref_res)
+    finally:
+        r.close()
 
 
 def test_blocks_sweeps_keep_parity_and_residual_of_the_input(H, oracle_mod):
