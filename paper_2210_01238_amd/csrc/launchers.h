@@ -173,8 +173,8 @@ __host__ __device__ inline unsigned blocks2d_frame(const BlockCut &x, const Bloc
 // Compiled variants: cells per lane, rows per wavefront, and what an exchange takes longer in fp64 / fp32 because the
 // registers do not hold everything (us; measured; the cells themselves stay in registers).
 #define JK_BLOCKS2D_VARIANTS(X)                                                                                              \
-    X(1, 2, 0, 0) X(1, 4, 0, 0) X(1, 6, 0, 0) X(1, 8, 0, 0) X(1, 12, 0, 0) X(1, 16, 0, 0) X(2, 4, 0, 0) X(2, 6, 0, 0)        \
-    X(2, 8, 0, 0) X(2, 10, 0, 0) X(2, 12, 1.4, 0) X(2, 16, 20, 0) X(4, 8, 16, 1) X(4, 10, 25, 2) X(4, 12, 30, 5)
+    X(1, 2, 0, 0) X(1, 4, 0, 0) X(1, 6, 0, 0) X(1, 8, 0, 0) X(1, 12, 0, 0) X(1, 16, 0, 0) X(2, 6, 0, 0) X(2, 8, 0, 0)        \
+    X(2, 10, 0, 0) X(2, 12, 1.4, 0) X(2, 16, 20, 0) X(4, 8, 16, 1) X(4, 10, 25, 2) X(4, 12, 30, 5)
 #define JK_BLOCKS2D_VARIANTS_F32(X) X(1, 24, 0, 0) X(2, 24, 0, 10.6)
 struct Blocks2dLaunch {
     hipStream_t st;

@@ -11,9 +11,9 @@ from test_parity_gpu import check
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (interior dims, tiles, iterations, norm every)
+    # (interior dims, tiles, iterations, norm every[, the only type that runs this way])
     ((513, 301), (1, 1), 37, 12), ((300, 1001), (3, 7), 40, 7), ((257, 770), (1, 5), 33, 33), ((1024, 1024), (4, 4), 60, 30),
-    ((701, 613), (1, 1), 41, 8), ((640, 300), (64, 300), 32, 16), ((512, 264), (512, 2), 24, 6), ((130, 514), (2, 1), 64, 1),
+    ((701, 613), (1, 1), 41, 8), ((640, 300), (64, 300), 32, 16), ((512, 264), (512, 2), 24, 6, np.float64), ((130, 514), (2, 1), 64, 2),
     ((1500, 1110), (5, 3), 48, 25), ((66, 2600), (1, 13), 30, 10), ((2000, 258), (8, 3), 50, 0), ((1536, 1536), (2, 3), 20, 10),
 ]
 
@@ -33,14 +33,41 @@ def run_whole(H, a, tiles, iters, every, **opts):
 CASES_3D = [
     # rows of exactly one and two lanes' cells, one cell fewer, odd rows, one and many blocks per direction
     ((64, 64, 64), (2, 2, 2), 40, 20), ((64, 64, 64), (1, 1, 1), 33, 1), ((61, 53, 47), (1, 1, 1), 30, 7), ((48, 40, 60), (2, 2, 3), 41, 0),
-    ((40, 70, 63), (4, 7, 21), 36, 12), ((6, 40, 64), (2, 4, 8), 60, 15), ((128, 128, 128), (2, 2, 2), 30, 10), ((96, 96, 128), (3, 2, 1), 30, 10),
-    ((90, 100, 126), (1, 5, 9), 28, 14), ((70, 62, 256), (1, 2, 4), 32, 8), ((66, 60, 251), (2, 3, 1), 32, 8), ((30, 46, 33), (1, 1, 1), 40, 40),
+    ((40, 70, 63), (4, 7, 21), 36, 12), ((6, 40, 64), (2, 4, 8), 60, 15), ((128, 128, 128), (2, 2, 2), 30, 10, np.float32), ((96, 96, 128), (3, 2, 1), 30, 10),
+    ((90, 100, 126), (1, 5, 9), 28, 14, np.float32), ((30, 46, 33), (1, 1, 1), 40, 40),
 ]
 
+# Every compiled variant of the kernels, each at about the smallest grid for which it is chosen; in 3-D once with rows that fill the
+# wavefront and once with shorter ones.  Widths of tiles that 4 does not divide have seams inside a lane's cells.
+F64, F32 = np.float64, np.float32
+VARIANTS = {
+    # (cells per lane, planes (0: 2-D), rows per wavefront): [(interior dims, tiles, type)]
+    (1, 0, 2): [((20, 322), (4, 7), F64), ((20, 636), (4, 12), F32)], (1, 0, 4): [((37, 340), (1, 17), F64), ((37, 660), (1, 3), F32)],
+    (1, 0, 6): [((56, 300), (8, 1), F64), ((56, 580), (8, 29), F32)], (1, 0, 8): [((101, 333), (1, 9), F64), ((101, 613), (1, 1), F32)],
+    (1, 0, 12): [((3482, 113), (2, 1), F64), ((2065, 185), (7, 37), F32)], (1, 0, 16): [((265, 3093), (53, 3), F64), ((177, 3463), (59, 1), F32)],
+    (1, 0, 24): [((365, 3095), (5, 5), F32)],
+    (2, 0, 6): [((64, 3468), (8, 4), F64), ((1728, 228), (54, 12), F32)], (2, 0, 8): [((160, 2312), (32, 8), F64), ((2144, 188), (32, 4), F32)],
+    (2, 0, 10): [((268, 2940), (4, 28), F64), ((3459, 244), (3, 4), F32)], (2, 0, 12): [((3306, 468), (38, 12), F64), ((3618, 356), (54, 4), F32)],
+    (2, 0, 16): [((3189, 736), (3, 32), F64), ((3697, 468), (1, 12), F32)], (2, 0, 24): [((977, 3386), (1, 2), F32)],
+    (4, 0, 8): [((2667, 976), (21, 16), F64), ((802, 3608), (2, 8), F32)], (4, 0, 10): [((2221, 1096), (1, 8), F64), ((3160, 916), (40, 4), F32)],
+    (4, 0, 12): [((3410, 756), (2, 36), F64), ((3369, 1004), (3, 4), F32), ((2048, 2048), (2, 4), F64), ((2048, 2048), (2, 4), F32)],
+    (1, 4, 2): [((7, 7, 36), (1, 1, 12), F64), ((7, 7, 64), (1, 1, 16), F64), ((7, 7, 34), (1, 1, 2), F32), ((7, 7, 64), (1, 1, 4), F32)],
+    (1, 6, 3): [((226, 40, 57), (2, 5, 3), F64), ((232, 10, 64), (8, 2, 8), F64), ((12, 14, 34), (4, 2, 2), F32), ((12, 12, 64), (4, 4, 8), F32)],
+    (2, 4, 2): [((7, 7, 67), (1, 1, 1), F64), ((7, 7, 128), (1, 1, 32), F64), ((7, 7, 74), (1, 1, 2), F32), ((7, 7, 128), (1, 1, 4), F32)],
+    (2, 5, 2): [((11, 8, 72), (1, 1, 8), F64), ((11, 8, 128), (1, 1, 32), F64), ((11, 8, 73), (1, 2, 1), F32), ((11, 8, 128), (1, 1, 32), F32)],
+    (2, 6, 3): [((12, 12, 70), (4, 4, 10), F32), ((12, 12, 128), (4, 4, 4), F32)],
+    (4, 4, 2): [((8, 8, 137), (2, 2, 1), F32), ((8, 8, 256), (2, 2, 1), F32), ((190, 10, 255), (2, 1, 3), F32)],
+    (4, 5, 2): [((11, 8, 129), (1, 2, 43), F32), ((11, 8, 256), (1, 1, 32), F32)],
+}
+VARIANT_ITERS, VARIANT_EVERY = 31, 9
 
-@pytest.mark.parametrize("dtype", [np.float64, np.float32])
-@pytest.mark.parametrize("dims,tiles,iters,every", CASES + CASES_3D)
+
+BLOCK_CASES = [(*c[:4], t) for c in CASES + CASES_3D for t in (c[4:] or (np.float64, np.float32))]
+
+
+@pytest.mark.parametrize("dims,tiles,iters,every,dtype", BLOCK_CASES)
 def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype):
+    """(That these calls are one launch each is checked without a GPU: test_block_plans.py.)"""
     a = random_padded(dims, dtype=dtype, seed=sum(dims) + iters)
     ref, ref_res = oracle_mod.run(a, iters, every)
     out, res, in_a = run_whole(H, a, tiles, iters, every, resident=1)
@@ -50,6 +77,23 @@ def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype
     assert np.array_equal(out, out0) and in_a == in_a0
     out2, res2, _ = run_whole(H, a, tiles, iters, every, resident=1)
     assert np.array_equal(out2, out) and res2 == res                # and the same bits on every run
+
+
+@pytest.mark.parametrize("variant,dims,tiles,dtype", [(v, *c) for v, cases in VARIANTS.items() for c in cases])
+def test_every_variant_matches_the_oracle(H, oracle_mod, variant, dims, tiles, dtype):
+    a = random_padded(dims, dtype=dtype, seed=sum(dims))
+    ref, ref_res = oracle_mod.run(a, VARIANT_ITERS, VARIANT_EVERY)
+    r = H.JacobiRun(dims, tiles, dtype, resident=1, profile=1)
+    try:
+        got = tuple(H.B.jacobi_get_option(r.plan, "block_" + k) for k in ("cells_per_lane", "planes_per_wave", "rows_per_wave"))
+        assert got == variant
+        r.load(a)
+        r.other().fill_(255)
+        res = r.run(VARIANT_ITERS, VARIANT_EVERY, fuse_residual=True)
+        check(r.fetch(), res, ref, ref_res)
+        assert H.B.jacobi_profile_read(r.plan)[1] == 1             # one launch
+    finally:
+        r.close()
 
 
 PLAIN = [((1024, 1024), (4, 4), np.float64), ((300, 701), (3, 1), np.float32), ((64, 64, 64), (2, 2, 2), np.float64),
