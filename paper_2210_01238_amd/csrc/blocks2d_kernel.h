@@ -382,25 +382,25 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         find_cells(first_col);
         RowWalk row(g, y0 + opaque(wave) * RW);
 #pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        const int y = row0 + j;
-        T *rowp = fin + (row.tile + row.i * (long long)g.pitch);
-        row.next(g);
-        if (y < ylo || y >= yhi || first_col < xlo || first_col >= xhi) continue;
-        T v[C];
+        for (int j = 0; j < RW; ++j) {
+            const int y = row0 + j;
+            T *rowp = fin + (row.tile + row.i * (long long)g.pitch);
+            row.next(g);
+            if (y < ylo || y >= yhi || first_col < xlo || first_col >= xhi) continue;
+            T v[C];
 #pragma unroll
-        for (int e = 0; e < C; ++e) v[e] = healthy ? a[j + 1][e] : T(__builtin_nan(""));
-        if (C > 1 && !seam) {
-            VU x;
+            for (int e = 0; e < C; ++e) v[e] = healthy ? a[j + 1][e] : T(__builtin_nan(""));
+            if (C > 1 && !seam) {
+                VU x;
 #pragma unroll
-            for (int e = 0; e < C; ++e) x[e] = v[e];
-            *(VU *)(rowp + co[0]) = x;
-        } else {
+                for (int e = 0; e < C; ++e) x[e] = v[e];
+                *(VU *)(rowp + co[0]) = x;
+            } else {
 #pragma unroll
-            for (int e = 0; e < C; ++e) rowp[co[e]] = v[e];
+                for (int e = 0; e < C; ++e) rowp[co[e]] = v[e];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-    }
     }
     block_epilogue(br, epoch, max_exchanges, red, &flag);
 }
