@@ -74,10 +74,11 @@ struct BlockPlan {
     int64_t msg_bytes = 0;            // of one of the two message areas
     int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
     double us_iterate = 0, us_exchange = 0;     // estimates: of an iteration, of an exchange
-    double us_per_iteration(int every) const    // with an exchange every d iterations, or after each norm
+    double us_launch = 0;                       // of a launch besides
+    double us_per_iteration(int every) const    // with as many exchanges as the stretches between norms need (next_stretch)
     {
-        const int d = y.d;
-        return us_iterate + us_exchange / (every > 0 && every < d ? every : d);
+        const int d = y.d, stretches = every > 0 ? (every + (d > 1 ? 1 : 0) + d - 1) / d : 1;
+        return us_iterate + us_exchange * stretches / (every > 0 ? every : d);
     }
 };
 
@@ -660,16 +661,10 @@ bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, 
     return nb == 1 || (c->own_hi(0) >= least && held - d >= least && (nb == 2 || c->step * unit >= least));
 }
 
-// What the model below says a launch per iteration / passes of up to 12 iterations take (us per iteration), and what a
-// launch of a block kernel takes besides its iterations.
-constexpr double BLOCK_LAUNCH_US = 20.0;
+// What a launch per iteration / passes of up to 12 iterations take (us per iteration, 2-D).
 double launch_us_2d(int64_t cell_bytes) { return 3.0 + 0.25e-6 * cell_bytes; }
 double blocked_us_2d(int64_t cells) { return 1.8 + 0.7e-6 * cells; }
 
-// The cut of a 2-D grid with the least time per iteration, by a model fitted to 30 cuts of twelve grids between 300^2 and
-// 2400^2 (within 10 % of what they measured): 0.06 us for the border rows and the barrier, 2.05 ns for each of the
-// instructions a SIMD's two wavefronts issue (4 per cell, 4 or 2 lane shifts per row), and every d iterations an exchange of
-// 2.5 us plus 0.22 us per MB of messages.
 // Width in blocks of the patch an XCD gets, for the least traffic across its border: blocks of `w` x `h` cells, nbx side by
 // side, `n` in all.  (In 2-D only while the messages are small: patches run 512^2 in 0.58 us per iteration, workgroups dealt
 // out one by one in 0.62, 256^2 0.526 / 0.537; but 1024^2 with 18 MB of messages 1.05 / 1.01, 2048^2 in fp32 2.40 / 2.17 - all
@@ -681,6 +676,11 @@ int strip_width(int n, int nbx, double w, double h)
     return strip < 1 ? 1 : strip > nbx ? nbx : strip;
 }
 
+// The cut of a 2-D grid with the least time per iteration, by a model fitted to 30 cuts of twelve grids between 300^2 and
+// 2400^2 (within 10 % of what they measured): 0.06 us for the border rows and the barrier, 2.05 ns for each of the
+// instructions a SIMD's two wavefronts issue (4 per cell, 4 or 2 lane shifts per row), and every d iterations an exchange of
+// 2.5 us plus 0.22 us per MB of messages.  A launch takes 7.5 us besides, 0.5 per cell that a lane holds and 0.005 per workgroup
+// (270 calls of 5 to 200 iterations: the sum within 30 %, 7 % on average).
 BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
 {
     struct Variant { int c, rw; double extra64, extra32; bool f32_only; };
@@ -710,6 +710,7 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
             best.ok = true;
             best.us_iterate = iterate;
             best.us_exchange = exchange;
+            best.us_launch = 7.5 + 0.5 * v.rw * v.c + 0.005 * x.nb * y.nb;
             best.cells_per_lane = v.c;
             best.rows_per_wave = v.rw;
             best.x = x; best.y = y;
@@ -724,29 +725,48 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
     return best;
 }
 
-// 3-D: the same model, fitted to eight cuts of five grids between 48 x 40 x 60 and 128^3 (within 25 %); rows are whole, cut in
-// y and z.  The border rows go through LDS (128 bytes per clock), messages count written and read; the fp64 patch of 18 rows
-// takes 3 us more per exchange because the registers do not hold everything.
-double launch_us_3d(int64_t cell_bytes) { return 4.6 + 0.35e-6 * cell_bytes; }
-BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
+// 3-D, us per iteration of a launch each: by the wavefronts there are and the bytes they move, both up to where it levels off, and
+// by long strips (200 grids of 8 x 11 x 256 to 169 x 148 x 128 in one tile, 3.6 - 10.3 us: within 25 %, 6 % on average; two of
+// narrow tiles with strips of 16 planes: 14.0 and 16.4).  Four rows per wavefront: the 8-byte lanes of narrow fp32 rows.  Blocked
+// passes take 1 - 3 us more on such small grids (64 x 7 x 14: 3.5 and 5.5; 64 x 34 x 41: 4.3 and 7.9).
+constexpr double BLOCKED_3D_US = 1.8;
+constexpr double WORTH_3D = 0.95;         // of that: what blocks may take
+double launch_us_3d(const jacobi_plan *p, bool blocked)
 {
-    struct Variant { int c, rz, ry; bool f32_only; };
+    const SweepConfig c = make_config(p, jk::MODE_UPDATE);
+    const jacobi_layout &L = p->lay;
+    const double mb = 1e-6 * (double)(L.dims[0] * L.dims[1] * L.dims[2] * (int64_t)p->esize);
+    const double us = (c.rows_per_wave == 4 ? 4.6 : 3.4) + 0.7e-3 * (double)std::min<int64_t>(c.sp.nstrips, 1600) + 0.57 * std::min(mb, 6.0) +
+                      0.6 * std::max(c.sp.R - 4, 0);
+    return blocked ? std::min(us, 8.5) + BLOCKED_3D_US : us;
+}
+
+// The cut of a 3-D grid with the least time per iteration; rows are whole, cut in y and z.  What an iteration, an exchange and a
+// launch take was fitted, for each variant, to 200 cuts of 1 to 256 blocks with d from 1 to 3, timed over 24 to 96
+// iterations (within 9 %): most of it does not depend on the number of blocks, only 0.03 us per MB of messages, written and read, does.
+BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
+{
+    struct Cost { double iterate, exchange, iterate_short, exchange_short, launch; };
+    struct Variant { int c, rz, ry; bool f32_only; Cost f64, f32; };
+#define JK_COST(...) {__VA_ARGS__}
     static const Variant variants[] = {
-#define JK_V(C_, RZ_, RY_) {C_, RZ_, RY_, false},
+#define JK_V(C_, RZ_, RY_, F64_, F32_) {C_, RZ_, RY_, false, JK_COST F64_, JK_COST F32_},
         JK_BLOCKS3D_VARIANTS(JK_V)
 #undef JK_V
-#define JK_V(C_, RZ_, RY_) {C_, RZ_, RY_, true},
+#define JK_V(C_, RZ_, RY_, F64_, F32_) {C_, RZ_, RY_, true, JK_COST F64_, JK_COST F32_},
         JK_BLOCKS3D_VARIANTS_F32(JK_V)
 #undef JK_V
+#undef JK_COST
     };
     BlockPlan best;
-    const bool f64 = dtype == JACOBI_F64;
-    const int64_t Nx = (int64_t)g.Tx * g.tw, Ny = (int64_t)g.Ty * g.th, Nz = (int64_t)g.Tz * g.td;
+    const bool f64 = p->lay.dtype == JACOBI_F64;
+    const int64_t Nx = p->lay.dims[2], Ny = p->lay.dims[1], Nz = p->lay.dims[0];
     const int cell = f64 ? 8 : 4;
     for (const Variant &v : variants) {
         if (f64 && v.f32_only) continue;
         const int width = jk::WAVE * v.c, HZ = 2 * v.rz, HY = 4 * v.ry;
         if (Nx > width || 2 * Nx <= width) continue;            // at least half of the lanes have cells
+        const Cost &cost = f64 ? v.f64 : v.f32;
         for (int d = 1; d <= 3; ++d) {
             jk::BlockCut y, z;
             if (!cut_into_blocks(Ny + 2, HY, d, 1, 2 * d, num_cu, &y) || !cut_into_blocks(Nz + 2, HZ, d, 1, 2 * d, num_cu, &z)) continue;
@@ -758,14 +778,13 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
             const int frame = 2 * d * ny + (nz - 2 * d) * 2 * d;
             const double row_msg = (double)width * 2 * cell, msg = nb * frame * row_msg;
             const double ghost = nb > 1 ? nb * ((double)(ny + 2 * d) * (nz + 2 * d) - (double)ny * nz) * row_msg : 0.0;
-            const double instr = 2.0 * v.rz * v.ry * (6 * v.c + (f64 ? 4 : 2) + (Nx < width ? v.c * (f64 ? 2 : 1) : 0));
-            const double lds = 8.0 * (2 * v.ry + 2 * (v.rz - 2) + 2 * (v.rz + v.ry)) * width * cell / 128 / 2200;
-            const double iterate = 0.1 + instr * 0.00205 + lds;
-            const double exchange = 2.2 + 0.1e-6 * (msg + ghost) + (f64 && v.rz * v.ry > 12 ? 3.0 : 0.0);
+            const double iterate = Nx < width ? cost.iterate_short : cost.iterate;
+            const double exchange = (Nx < width ? cost.exchange_short : cost.exchange) + 0.03e-6 * (msg + ghost);
             if (best.ok && iterate + exchange / d >= best.us_per_iteration(0)) continue;
             best.ok = true;
             best.us_iterate = iterate;
             best.us_exchange = exchange;
+            best.us_launch = cost.launch + 0.05 * (double)nb;
             best.cells_per_lane = v.c;
             best.rows_per_wave = v.ry;
             best.planes_per_wave = v.rz;
@@ -776,29 +795,10 @@ BlockPlan plan_blocks3d(const Geo &g, int dtype, int num_cu)
             best.msg_bytes = round_up((int64_t)msg, 256);
         }
     }
-    if (best.ok && best.us_per_iteration(0) > 0.8 * launch_us_3d(Nx * Ny * Nz * cell)) best.ok = false;
+    // (with blocked passes asked for, later, blocks pay sooner)
+    if (best.ok && best.us_per_iteration(0) > WORTH_3D * (launch_us_3d(p, false) + BLOCKED_3D_US)) best.ok = false;
     if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
     return best;
-}
-
-// Whether a call of so many iterations runs that way: what it saves per iteration has to pay for the launch (1024^2:
-// 3 iterations 20 us by launches against 32, 8 iterations 48 against 19).  `row`: what the kernel for narrow grids
-// (resident2d_kernel) would do with them - if it can run, it takes 0.95 us per iteration and about 6 us less per launch, and it
-// runs where its geometry was asked for by option.
-bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentChoice &row)
-{
-    const BlockPlan &b = p->blocks;
-    if (!p->resident || !b.ok || b.workgroups > p->num_cu || iters > BLOCK_MAX_ITERS) return false;
-    const jacobi_layout &L = p->lay;
-    const int64_t cells = L.dims[0] * L.dims[1] * L.dims[2];
-    const double us = b.us_per_iteration(every);
-    if (row.ok) {
-        if (p->resident_depth > 0 || p->resident_rows > 0 || row.nwg == 1) return false;
-        return iters * (0.95 - us) > 6.0;
-    }
-    const double other = L.ndim == 3 ? launch_us_3d(cells * (int64_t)p->esize)
-                         : p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
-    return iters * (other - us) > BLOCK_LAUNCH_US + b.us_exchange;
 }
 
 // What the next pass does with `left` iterations to go.  The iterations are spread evenly over
@@ -855,6 +855,43 @@ PassChoice choose_pass(const jacobi_plan *p, int left)
         if (t2_usable(p)) return {2, 1};
     }
     return {1, 0};
+}
+
+// Whether a call of so many iterations, with a norm every `every`-th, runs that way: what it saves per iteration has to pay for the
+// launch.  `row`: what the kernel for narrow
+// grids (resident2d_kernel) would do with them; it runs where its geometry was asked for by option.
+bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentChoice &row)
+{
+    const BlockPlan &b = p->blocks;
+    if (!p->resident || !b.ok || b.workgroups > p->num_cu || iters > BLOCK_MAX_ITERS) return false;
+    const jacobi_layout &L = p->lay;
+    const int norms = every > 0 ? iters / every : 0;
+    const double us = b.us_per_iteration(norms > 0 ? every : 0);
+    if (L.ndim == 3) {
+        // Calls by launches take 5.5 us besides the iterations, norms 3.5 each and 5 for the last one; in a block launch 2.7 each and 1 for
+        // the first with the small variants, 5.5 and 7 with the large ones.  (700 calls of 5 to 200 iterations, both ways: the
+        // slower one is chosen in 12, 0.3 % of the time in all.)
+        const double other = launch_us_3d(p, choose_pass(p, norms > 0 ? every : iters).depth > 1);
+        const double more = b.us_launch - 5.5 + (norms > 0 ? norms * (0.1 * b.us_launch - 3.0) + 0.3 * b.us_launch - 8.0 : 0.0);
+        return us <= WORTH_3D * other && iters * (other - us) > more;
+    }
+    const double here = b.us_launch + iters * us;
+    if (row.ok) {
+        if (p->resident_depth > 0 || p->resident_rows > 0 || row.nwg == 1) return false;
+        // A launch per norm and one for the rest.  With one and with two vectors of a row per lane, us: a launch, a norm, a phase, and that
+        // per workgroup, an iteration; 1.9 a norm in blocks.  (144 calls from the first iterations on, both ways: each side
+        // within 20 %, 5 % on average; the slower one chosen in 2.  96 x 84: 13 iterations 15 us against 18, 26: 25 and 24, 78:
+        // 65 and 48.)
+        const bool wide = row.nseg == 2;
+        const double launches = every > 0 ? norms + (iters % every != 0) : 1;
+        return launches * ((wide ? 1.9 : 3.5) + row.nphase * (wide ? 4.05 + 0.035 * row.nwg : 2.4 + 0.02 * row.nwg)) +
+                   norms * (wide ? 2.6 : 2.2) + iters * (wide ? 0.76 : 0.67) > here + 1.9 * norms;
+    }
+    // Against launches (110 calls: never the slower one where it chooses blocks; calls with a norm every 1 or 2 iterations and
+    // some with blocked passes would already pay in blocks).
+    const int64_t cells = L.dims[1] * L.dims[2];
+    const double other = p->tblock > 1 ? blocked_us_2d(cells) : launch_us_2d(cells * (int64_t)p->esize);
+    return 4.5 + iters * other > here;
 }
 
 // Passes jacobi_sweep makes of `iters` iterations: as many as jacobi_pass_schedule lists.
@@ -1308,7 +1345,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
     g.hpitch = L.xhalo_pitch;
     g.xsend = L.xsend_offset;
     g.tile_stride = L.tile_stride;
-    p->blocks = ndim == 2 ? plan_blocks2d(g, dtype, jk::NUM_CU) : plan_blocks3d(g, dtype, jk::NUM_CU);
+    p->blocks = ndim == 2 ? plan_blocks2d(g, dtype, jk::NUM_CU) : plan_blocks3d(p, jk::NUM_CU);
     *plan = p;
     return JACOBI_OK;
 }

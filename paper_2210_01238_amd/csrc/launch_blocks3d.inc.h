@@ -9,7 +9,7 @@ static hipError_t blocks3d_dispatch(int c, int rz, int ry, const Blocks3dLaunch 
 {
     const dim3 grid((unsigned)(a.p.z.nb * a.p.y.nb)), block(BLK_WAVES * WAVE);
     T *ga = (T *)a.in, *gb = (T *)a.out;
-#define JK_L(C_, RZ_, RY_)                                                                                                   \
+#define JK_L(C_, RZ_, RY_, ...)                                                                                              \
     if (c == C_ && rz == RZ_ && ry == RY_) {                                                                                 \
         if (a.p.nx == WAVE * C_)                                                                                             \
             hipLaunchKernelGGL((blocks3d_kernel<T, C_, RZ_, RY_, true>), grid, block, 0, a.st, a.g, a.p, ga, gb);            \

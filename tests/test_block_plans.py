@@ -43,10 +43,40 @@ for want, cases in {text(VARIANTS)}.items():
         J.jacobi_destroy(p)
 """)
     with open(os.path.join(ROOT, "paper_2210_01238_amd", "csrc", "launchers.h")) as f:
-        tables = {m.group(1): re.findall(r"X\(([\d., ]+)\)", m.group(2))
+        tables = {m.group(1): re.findall(r"X\((\d[\d., ]*)", m.group(2))
                   for m in re.finditer(r"#define JK_(BLOCKS\dD_VARIANTS\w*)\(X\)((?:.*\\\n)*.*)", f.read())}
-    numbers = {name: [tuple(int(float(n)) for n in v.split(",")) for v in vs] for name, vs in tables.items()}
-    both = {(c, 0, rw) for c, rw, *_ in numbers["BLOCKS2D_VARIANTS"]} | set(numbers["BLOCKS3D_VARIANTS"])
-    f32_only = {(c, 0, rw) for c, rw, *_ in numbers["BLOCKS2D_VARIANTS_F32"]} | set(numbers["BLOCKS3D_VARIANTS_F32"])
+    numbers = {name: [[int(n) for n in v.split(",")[:3] if n.strip().isdigit()] for v in vs] for name, vs in tables.items()}
+    both = {(c, 0, rw) for c, rw, *_ in numbers["BLOCKS2D_VARIANTS"]} | {tuple(v) for v in numbers["BLOCKS3D_VARIANTS"]}
+    f32_only = {(c, 0, rw) for c, rw, *_ in numbers["BLOCKS2D_VARIANTS_F32"]} | {tuple(v) for v in numbers["BLOCKS3D_VARIANTS_F32"]}
     compiled = {(v, t) for v in both for t in ("float64", "float32")} | {(v, "float32") for v in f32_only}
     assert compiled == {(v, c[2].__name__) for v, cases in VARIANTS.items() for c in cases}
+
+
+# Calls timed both ways (us, MI355X): the launch-per-iteration path or, for the narrow grids, resident2d_kernel, and in blocks.
+TIMED = [
+    # dims, tiles, type, tblock, iterations, norm every, other, blocks
+    ((27, 29, 119), (1, 1, 1), "float64", 1, 22, 0, 87.3, 116.2), ((27, 29, 119), (1, 1, 1), "float64", 1, 132, 0, 503.9, 603.5),
+    ((84, 126, 128), (3, 1, 1), "float64", 1, 15, 10, 115.6, 144.5), ((19, 20, 128), (1, 4, 1), "float64", 1, 20, 20, 85.4, 103.9),
+    ((14, 7, 64), (2, 1, 2), "float64", 4, 98, 98, 548.6, 335.7), ((51, 33, 256), (1, 3, 1), "float32", 12, 14, 0, 128.9, 78.2),
+    ((77, 50, 256), (1, 5, 1), "float32", 1, 132, 22, 891.4, 632.1), ((64, 64, 64), (2, 2, 2), "float64", 1, 100, 50, 605.1, 363.9),
+    ((29, 28, 128), (1, 4, 1), "float32", 1, 12, 10, 65.9, 56.6), ((23, 26, 64), (1, 2, 4), "float32", 1, 9, 4, 57.1, 43.4),
+    ((26, 35, 64), (2, 1, 1), "float32", 1, 9, 0, 48.0, 38.5),
+    ((96, 84), (3, 1), "float64", 1, 13, 0, 14.9, 18.3), ((76, 228), (1, 3), "float32", 8, 13, 0, 15.1, 18.9),
+    ((96, 84), (3, 1), "float64", 1, 78, 0, 65.8, 48.1), ((76, 248), (2, 4), "float64", 8, 18, 9, 32.0, 26.8),
+    ((352, 208), (1, 1), "float64", 1, 32, 0, 35.4, 26.5), ((256, 256), (1, 1), "float64", 1, 100, 100, 99.5, 66.4),
+    ((295, 460), (1, 1), "float32", 1, 127, 25, 170.0, 98.6), ((68, 148), (1, 2), "float32", 4, 64, 2, 318.8, 149.7),
+]
+
+
+def test_calls_take_the_faster_path(stub):  # noqa: F811
+    """(Block kernels are the launches of 512 threads.)"""
+    run(stub, HEAD + f"""
+for dims, tiles, dtype, tblock, iters, every, other, blocks in {TIMED!r}:
+    p = plan(dims, tiles, float64 if dtype == "float64" else float32)
+    J.jacobi_set_option(p, "tblock", tblock)
+    J.jacobi_prepare(p)
+    log()
+    J.jacobi_run(p, *GRIDS(p), iters, every, 1 << 16)
+    assert ("512" in [c[2] for c in log() if c[0] == "hipLaunchKernel"]) == (blocks < other), (dims, dtype, iters, other, blocks)
+    J.jacobi_destroy(p)
+""")

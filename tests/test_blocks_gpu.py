@@ -32,7 +32,7 @@ def run_whole(H, a, tiles, iters, every, **opts):
 
 CASES_3D = [
     # rows of exactly one and two lanes' cells, one cell fewer, odd rows, one and many blocks per direction
-    ((64, 64, 64), (2, 2, 2), 40, 20), ((64, 64, 64), (1, 1, 1), 33, 1), ((61, 53, 47), (1, 1, 1), 30, 7), ((48, 40, 60), (2, 2, 3), 41, 0),
+    ((64, 64, 64), (2, 2, 2), 40, 20), ((64, 64, 64), (1, 1, 1), 33, 1, np.float64), ((64, 64, 64), (1, 1, 1), 33, 5), ((61, 53, 47), (1, 1, 1), 30, 7), ((48, 40, 60), (2, 2, 3), 41, 0),
     ((40, 70, 63), (4, 7, 21), 36, 12), ((6, 40, 64), (2, 4, 8), 60, 15), ((128, 128, 128), (2, 2, 2), 30, 10, np.float32), ((96, 96, 128), (3, 2, 1), 30, 10),
     ((90, 100, 126), (1, 5, 9), 28, 14, np.float32), ((30, 46, 33), (1, 1, 1), 40, 40),
 ]
@@ -51,13 +51,13 @@ VARIANTS = {
     (2, 0, 16): [((3189, 736), (3, 32), F64), ((3697, 468), (1, 12), F32)], (2, 0, 24): [((977, 3386), (1, 2), F32)],
     (4, 0, 8): [((2667, 976), (21, 16), F64), ((802, 3608), (2, 8), F32)], (4, 0, 10): [((2221, 1096), (1, 8), F64), ((3160, 916), (40, 4), F32)],
     (4, 0, 12): [((3410, 756), (2, 36), F64), ((3369, 1004), (3, 4), F32), ((2048, 2048), (2, 4), F64), ((2048, 2048), (2, 4), F32)],
-    (1, 4, 2): [((7, 7, 36), (1, 1, 12), F64), ((7, 7, 64), (1, 1, 16), F64), ((7, 7, 34), (1, 1, 2), F32), ((7, 7, 64), (1, 1, 4), F32)],
-    (1, 6, 3): [((226, 40, 57), (2, 5, 3), F64), ((232, 10, 64), (8, 2, 8), F64), ((12, 14, 34), (4, 2, 2), F32), ((12, 12, 64), (4, 4, 8), F32)],
-    (2, 4, 2): [((7, 7, 67), (1, 1, 1), F64), ((7, 7, 128), (1, 1, 32), F64), ((7, 7, 74), (1, 1, 2), F32), ((7, 7, 128), (1, 1, 4), F32)],
-    (2, 5, 2): [((11, 8, 72), (1, 1, 8), F64), ((11, 8, 128), (1, 1, 32), F64), ((11, 8, 73), (1, 2, 1), F32), ((11, 8, 128), (1, 1, 32), F32)],
-    (2, 6, 3): [((12, 12, 70), (4, 4, 10), F32), ((12, 12, 128), (4, 4, 4), F32)],
-    (4, 4, 2): [((8, 8, 137), (2, 2, 1), F32), ((8, 8, 256), (2, 2, 1), F32), ((190, 10, 255), (2, 1, 3), F32)],
-    (4, 5, 2): [((11, 8, 129), (1, 2, 43), F32), ((11, 8, 256), (1, 1, 32), F32)],
+    (1, 4, 2): [((7, 7, 36), (1, 1, 12), F64), ((7, 7, 64), (1, 1, 8), F64), ((7, 7, 34), (1, 1, 2), F32), ((7, 7, 64), (1, 1, 4), F32)],
+    (1, 6, 3): [((15, 15, 51), (3, 5, 17), F64), ((37, 217, 64), (1, 31, 4), F64), ((200, 44, 33), (8, 4, 11), F32), ((13, 13, 64), (1, 1, 4), F32)],
+    (2, 4, 2): [((8, 8, 65), (1, 2, 13), F64), ((8, 8, 128), (1, 1, 8), F64), ((7, 7, 65), (1, 1, 13), F32), ((7, 7, 128), (1, 1, 32), F32)],
+    (2, 5, 2): [((36, 6, 102), (4, 2, 34), F64), ((21, 6, 128), (7, 2, 32), F64), ((11, 8, 128), (1, 1, 2), F32)],
+    (2, 6, 3): [((43, 193, 69), (1, 1, 23), F32), ((40, 220, 128), (8, 4, 8), F32)],
+    (4, 4, 2): [((8, 8, 147), (1, 1, 21), F32), ((7, 7, 256), (1, 1, 8), F32), ((190, 10, 255), (2, 1, 3), F32)],
+    (4, 5, 2): [((12, 10, 250), (4, 2, 50), F32), ((37, 217, 256), (1, 7, 16), F32)],
 }
 VARIANT_ITERS, VARIANT_EVERY = 31, 9
 
