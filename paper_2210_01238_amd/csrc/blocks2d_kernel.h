@@ -33,6 +33,9 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     typedef T VU __attribute__((ext_vector_type(C == 1 ? 2 : C), aligned(sizeof(T))));
     constexpr int HH = BLK_WAVES * RW, HW = WAVE * C;
     constexpr unsigned MB = MSG_BYTES<T>;
+    // The plain path's code lies behind the others': 1024^2 128 -> 125 us per 100 iterations, 256^2 66.4 -> 63.8, 1536^2 268 -> 223, all
+    // variants 0 to 15 % - but for fp32 with 4 x 12 cells per lane, which then spills elsewhere (2048^2 267 -> 380).
+    constexpr bool OUT_OF_THE_WAY = sizeof(T) == 8 || C != 4 || RW != 12;
     __shared__ T xch[2][BLK_WAVES][2][C][WAVE];    // [parity][wavefront][first / last row][component][lane]
     __shared__ T ring_row[2][C][WAVE];             // the Dirichlet rows above / below the domain
     __shared__ double red[BLK_WAVES];
@@ -366,7 +369,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
             // is everybody there?  (the first exchange and the result wait for it)
             if (threadIdx.x == 0) roll_call(br.sync, (unsigned)nb, br.admitted, ticket, br.roll_limit, &flag);
             __syncthreads();
-            if (flag != ALL_PRESENT) {
+            if (OUT_OF_THE_WAY ? __builtin_expect(flag != ALL_PRESENT, 0) : flag != ALL_PRESENT) {
                 if (flag >= 0) plain_path<T, 2>(g, br, ga, gb, red, &flag);
                 block_epilogue(br, epoch, max_exchanges, red, &flag);
                 return;

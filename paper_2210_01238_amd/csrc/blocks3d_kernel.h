@@ -349,7 +349,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks3d_kernel(Geo g, Block
             // is everybody there?  (the first exchange and the result wait for it)
             if (threadIdx.x == 0) roll_call(br.sync, (unsigned)nb, br.admitted, ticket, br.roll_limit, &flag);
             __syncthreads();
-            if (flag != ALL_PRESENT) {
+            if (__builtin_expect(flag != ALL_PRESENT, 0)) {          // (64^3 365 -> 347 us per 100 iterations)
                 if (flag >= 0) plain_path<T, 3>(g, br, ga, gb, red, &flag);
                 block_epilogue(br, epoch, max_exchanges, red, &flag);
                 return;

@@ -217,9 +217,8 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
 {
     const unsigned me = (unsigned)*lds_flag, members = agent_load(&br.sync->participants);
     __syncthreads();
-    const int Nz = NDIM == 3 ? g.Tz * g.td : 1, Ny = g.Ty * g.th, Nx = g.Tx * g.tw;
-    const long long rows = (long long)Nz * Ny;
-    const int xchunks = (Nx + (int)blockDim.x - 1) / (int)blockDim.x;
+    const unsigned Nz = NDIM == 3 ? g.Tz * g.td : 1, Ny = g.Ty * g.th, Nx = g.Tx * g.tw;
+    const unsigned cells = Nz * Ny * Nx, first = me * blockDim.x + threadIdx.x, step = members * blockDim.x;   // far below 2^31
     T *src = in, *dst = out;
     unsigned round = 0;
     bool healthy = true;
@@ -229,14 +228,11 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
         const bool copy_here = it == br.iters && (src != in) != (br.final_is_out != 0);    // the result lies in the other grid
         const bool update_here = it < br.iters;
         double acc = 0.0;
-        for (long long w = me; w < rows * xchunks; w += members) {
-            const long long row = w / xchunks;
-            const int x = (int)(w - row * xchunks) * (int)blockDim.x + (int)threadIdx.x;
-            if (x >= Nx) continue;
-            const int z = NDIM == 3 ? (int)(row / Ny) : 0, y = (int)(row - (long long)z * Ny);
+        for (unsigned w = first; w < cells; w += step) {
+            const int row = (int)(w / Nx), x = (int)(w - row * Nx), z = NDIM == 3 ? row / (int)Ny : 0, y = row - z * (int)Ny;
             auto at = [&](int dz, int dy, int dx) JK_INLINE -> T {
                 const int zz = z + dz, yy = y + dy, xx = x + dx;
-                const bool ring = (NDIM == 3 && (zz < 0 || zz >= Nz)) || yy < 0 || yy >= Ny || xx < 0 || xx >= Nx;
+                const bool ring = (NDIM == 3 && (unsigned)zz >= Nz) || (unsigned)yy >= Ny || (unsigned)xx >= Nx;
                 return (ring ? in : src)[domain_cell_off(g, zz, yy, xx)];
             };
             const T c = at(0, 0, 0);
@@ -264,11 +260,9 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
         T *t = src; src = dst; dst = t;
     }
     if (!healthy)                                   // given up: no plausible values
-        for (long long w = me; w < rows * xchunks; w += members) {
-            const long long row = w / xchunks;
-            const int x = (int)(w - row * xchunks) * (int)blockDim.x + (int)threadIdx.x;
-            const int z = NDIM == 3 ? (int)(row / Ny) : 0, y = (int)(row - (long long)z * Ny);
-            if (x < Nx) (br.final_is_out ? out : in)[domain_cell_off(g, z, y, x)] = T(__builtin_nan(""));
+        for (unsigned w = first; w < cells; w += step) {
+            const int row = (int)(w / Nx), z = NDIM == 3 ? row / (int)Ny : 0;
+            (br.final_is_out ? out : in)[domain_cell_off(g, z, row - z * (int)Ny, (int)(w - row * Nx))] = T(__builtin_nan(""));
         }
 }
 

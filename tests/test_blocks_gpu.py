@@ -109,7 +109,7 @@ def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, 
     r = H.JacobiRun(dims, tiles, dtype, resident=1)
     try:
         n = H.B.jacobi_get_option(r.plan, "block_workgroups")
-        for iters, every in ((24, 2), (23, 0), (26, 26), (25, 6)):
+        for iters, every in ((120, 2), (24, 2), (23, 0), (26, 26), (25, 6)):
             ref, ref_res = oracle_mod.run(a, iters, every)
             norms = {}
             for admitted in (0, 1, n // 2, n - 1, 0, n - 1, n - 1, 0):
@@ -119,8 +119,9 @@ def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, 
                 res = r.run(iters, every, fuse_residual=True) if every else (r.sweep(iters) or [])
                 check(r.fetch(), res, ref, ref_res)
                 assert norms.setdefault(admitted, res) == res, (iters, every, admitted)
-            if len(ref_res) == 12:
-                assert len({tuple(v) for v in norms.values()}) == 4, norms
+            if len(ref_res) == 60:
+                # one norm in three or so differs in its last bit; fp32: fewer (squares have 48 bits and are added up in 53)
+                assert len({tuple(v) for v in norms.values()}) >= (4 if dtype == np.float64 else 3), norms
     finally:
         r.close()
 
