@@ -741,9 +741,9 @@ double launch_us_3d(const jacobi_plan *p, bool blocked)
     return blocked ? std::min(us, 8.5) + BLOCKED_3D_US : us;
 }
 
-// The cut of a 3-D grid with the least time per iteration; rows are whole, cut in y and z.  What an iteration, an exchange and a
+// The cut of a 3-D grid with the least time for 100 iterations; rows are whole, cut in y and z.  What an iteration, an exchange and a
 // launch take was fitted, for each variant, to 200 cuts of 1 to 256 blocks with d from 1 to 3, timed over 24 to 96
-// iterations (within 9 %): most of it does not depend on the number of blocks, only 0.03 us per MB of messages, written and read, does.
+// iterations (within 10 %): most of it does not depend on the number of blocks, only 0.03 us per MB of messages, written and read, does.
 BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
 {
     struct Cost { double iterate, exchange, iterate_short, exchange_short, launch; };
@@ -759,6 +759,7 @@ BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
 #undef JK_COST
     };
     BlockPlan best;
+    double least = 0;
     const bool f64 = p->lay.dtype == JACOBI_F64;
     const int64_t Nx = p->lay.dims[2], Ny = p->lay.dims[1], Nz = p->lay.dims[0];
     const int cell = f64 ? 8 : 4;
@@ -780,11 +781,13 @@ BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
             const double ghost = nb > 1 ? nb * ((double)(ny + 2 * d) * (nz + 2 * d) - (double)ny * nz) * row_msg : 0.0;
             const double iterate = Nx < width ? cost.iterate_short : cost.iterate;
             const double exchange = (Nx < width ? cost.exchange_short : cost.exchange) + 0.03e-6 * (msg + ghost);
-            if (best.ok && iterate + exchange / d >= best.us_per_iteration(0)) continue;
+            const double launch = cost.launch + 0.05 * (double)nb, us = 100 * (iterate + exchange / d) + launch;
+            if (best.ok && us >= least) continue;
+            least = us;
             best.ok = true;
             best.us_iterate = iterate;
             best.us_exchange = exchange;
-            best.us_launch = cost.launch + 0.05 * (double)nb;
+            best.us_launch = launch;
             best.cells_per_lane = v.c;
             best.rows_per_wave = v.ry;
             best.planes_per_wave = v.rz;
@@ -869,8 +872,8 @@ bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentCho
     const double us = b.us_per_iteration(norms > 0 ? every : 0);
     if (L.ndim == 3) {
         // Calls by launches take 5.5 us besides the iterations, norms 3.5 each and 5 for the last one; in a block launch 2.7 each and 1 for
-        // the first with the small variants, 5.5 and 7 with the large ones.  (700 calls of 5 to 200 iterations, both ways: the
-        // slower one is chosen in 12, 0.3 % of the time in all.)
+        // the first with the small variants, 5.5 and 7 with the large ones.  (340 calls of 5 to 200 iterations, both ways: the
+        // slower one is chosen in 19, by more than 10 % in 10; 0.9 % of the time in all.)
         const double other = launch_us_3d(p, choose_pass(p, norms > 0 ? every : iters).depth > 1);
         const double more = b.us_launch - 5.5 + (norms > 0 ? norms * (0.1 * b.us_launch - 3.0) + 0.3 * b.us_launch - 8.0 : 0.0);
         return us <= WORTH_3D * other && iters * (other - us) > more;

@@ -197,14 +197,14 @@ struct Blocks3d {
 // they cost in fp64 / fp32 (us; measured, see plan_blocks3d): an iteration and an exchange where the rows fill the wavefront, the
 // same where they are shorter, and a launch besides its iterations.
 #define JK_BLOCKS3D_VARIANTS(X)                                                                                              \
-    X(1, 4, 2, (1.99, 1.29, 2.21, 1.24, 15), (0.71, 1.76, 0.60, 2.03, 16))                                                   \
-    X(1, 6, 3, (1.82, 4.60, 1.96, 3.72, 31), (1.24, 3.20, 1.65, 3.55, 30))                                                   \
-    X(2, 4, 2, (2.38, 1.71, 2.56, 1.71, 16), (1.06, 1.82, 1.22, 1.89, 18))                                                   \
-    X(2, 5, 2, (2.16, 3.49, 2.48, 3.41, 23), (1.15, 2.21, 1.73, 3.26, 23))
+    X(1, 4, 2, (2.02, 1.09, 2.19, 1.02, 11), (0.66, 1.64, 0.62, 1.77, 12))                                                   \
+    X(1, 6, 3, (1.36, 4.55, 1.85, 3.70, 36), (1.29, 2.98, 1.46, 3.54, 30))                                                   \
+    X(2, 4, 2, (2.40, 1.44, 2.55, 1.43, 13), (1.00, 1.66, 1.17, 1.62, 15))                                                   \
+    X(2, 5, 2, (3.14, 1.86, 2.32, 3.40, 19), (1.10, 2.04, 1.56, 3.27, 20))
 #define JK_BLOCKS3D_VARIANTS_F32(X)                                                                                          \
-    X(2, 6, 3, (0, 0, 0, 0, 0), (1.66, 4.55, 2.44, 4.07, 35))                                                                \
-    X(4, 4, 2, (0, 0, 0, 0, 0), (2.07, 1.94, 2.54, 3.38, 19))                                                                \
-    X(4, 5, 2, (0, 0, 0, 0, 0), (1.97, 4.44, 2.96, 4.12, 24))
+    X(2, 6, 3, (0, 0, 0, 0, 0), (1.71, 4.22, 2.29, 4.02, 36))                                                                \
+    X(4, 4, 2, (0, 0, 0, 0, 0), (2.11, 1.64, 2.44, 3.14, 19))                                                                \
+    X(4, 5, 2, (0, 0, 0, 0, 0), (2.18, 4.02, 2.96, 3.99, 26))
 struct Blocks3dLaunch {
     hipStream_t st;
     Geo g;

@@ -55,16 +55,15 @@ for want, cases in {text(VARIANTS)}.items():
 # Calls timed both ways (us, MI355X): the launch-per-iteration path or, for the narrow grids, resident2d_kernel, and in blocks.
 TIMED = [
     # dims, tiles, type, tblock, iterations, norm every, other, blocks
-    ((27, 29, 119), (1, 1, 1), "float64", 1, 22, 0, 87.3, 116.2), ((27, 29, 119), (1, 1, 1), "float64", 1, 132, 0, 503.9, 603.5),
-    ((84, 126, 128), (3, 1, 1), "float64", 1, 15, 10, 115.6, 144.5), ((19, 20, 128), (1, 4, 1), "float64", 1, 20, 20, 85.4, 103.9),
-    ((14, 7, 64), (2, 1, 2), "float64", 4, 98, 98, 548.6, 335.7), ((51, 33, 256), (1, 3, 1), "float32", 12, 14, 0, 128.9, 78.2),
-    ((77, 50, 256), (1, 5, 1), "float32", 1, 132, 22, 891.4, 632.1), ((64, 64, 64), (2, 2, 2), "float64", 1, 100, 50, 605.1, 363.9),
-    ((29, 28, 128), (1, 4, 1), "float32", 1, 12, 10, 65.9, 56.6), ((23, 26, 64), (1, 2, 4), "float32", 1, 9, 4, 57.1, 43.4),
-    ((26, 35, 64), (2, 1, 1), "float32", 1, 9, 0, 48.0, 38.5),
-    ((96, 84), (3, 1), "float64", 1, 13, 0, 14.9, 18.3), ((76, 228), (1, 3), "float32", 8, 13, 0, 15.1, 18.9),
-    ((96, 84), (3, 1), "float64", 1, 78, 0, 65.8, 48.1), ((76, 248), (2, 4), "float64", 8, 18, 9, 32.0, 26.8),
-    ((352, 208), (1, 1), "float64", 1, 32, 0, 35.4, 26.5), ((256, 256), (1, 1), "float64", 1, 100, 100, 99.5, 66.4),
-    ((295, 460), (1, 1), "float32", 1, 127, 25, 170.0, 98.6), ((68, 148), (1, 2), "float32", 4, 64, 2, 318.8, 149.7),
+    ((27, 29, 119), (1, 1, 1), "float64", 1, 22, 0, 87.9, 107.3), ((27, 29, 119), (1, 1, 1), "float64", 1, 132, 0, 506.8, 559.3),
+    ((19, 20, 128), (1, 4, 1), "float64", 1, 20, 20, 85.4, 98.0), ((14, 7, 64), (2, 1, 2), "float64", 4, 98, 98, 547.3, 312.1),
+    ((51, 33, 256), (1, 3, 1), "float32", 12, 14, 0, 129.0, 73.4), ((77, 50, 256), (1, 5, 1), "float32", 1, 132, 22, 891.1, 596.3),
+    ((64, 64, 64), (2, 2, 2), "float64", 1, 100, 50, 604.6, 345.4), ((29, 28, 128), (1, 4, 1), "float32", 1, 12, 10, 65.8, 52.3),
+    ((23, 26, 64), (1, 2, 4), "float32", 1, 9, 4, 57.0, 40.2), ((26, 35, 64), (2, 1, 1), "float32", 1, 9, 0, 47.9, 35.6),
+    ((96, 84), (3, 1), "float64", 1, 13, 0, 14.9, 17.4), ((76, 228), (1, 3), "float32", 8, 13, 0, 15.1, 17.3),
+    ((96, 84), (3, 1), "float64", 1, 78, 0, 65.6, 45.3), ((76, 248), (2, 4), "float64", 8, 18, 9, 32.1, 25.0),
+    ((352, 208), (1, 1), "float64", 1, 32, 0, 35.2, 25.5), ((256, 256), (1, 1), "float64", 1, 100, 100, 98.8, 63.7),
+    ((295, 460), (1, 1), "float32", 1, 127, 25, 169.0, 91.7), ((68, 148), (1, 2), "float32", 4, 64, 2, 320.1, 140.0),
 ]
 
 

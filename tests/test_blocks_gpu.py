@@ -51,13 +51,13 @@ VARIANTS = {
     (2, 0, 16): [((3189, 736), (3, 32), F64), ((3697, 468), (1, 12), F32)], (2, 0, 24): [((977, 3386), (1, 2), F32)],
     (4, 0, 8): [((2667, 976), (21, 16), F64), ((802, 3608), (2, 8), F32)], (4, 0, 10): [((2221, 1096), (1, 8), F64), ((3160, 916), (40, 4), F32)],
     (4, 0, 12): [((3410, 756), (2, 36), F64), ((3369, 1004), (3, 4), F32), ((2048, 2048), (2, 4), F64), ((2048, 2048), (2, 4), F32)],
-    (1, 4, 2): [((7, 7, 36), (1, 1, 12), F64), ((7, 7, 64), (1, 1, 8), F64), ((7, 7, 34), (1, 1, 2), F32), ((7, 7, 64), (1, 1, 4), F32)],
-    (1, 6, 3): [((15, 15, 51), (3, 5, 17), F64), ((37, 217, 64), (1, 31, 4), F64), ((200, 44, 33), (8, 4, 11), F32), ((13, 13, 64), (1, 1, 4), F32)],
-    (2, 4, 2): [((8, 8, 65), (1, 2, 13), F64), ((8, 8, 128), (1, 1, 8), F64), ((7, 7, 65), (1, 1, 13), F32), ((7, 7, 128), (1, 1, 32), F32)],
-    (2, 5, 2): [((36, 6, 102), (4, 2, 34), F64), ((21, 6, 128), (7, 2, 32), F64), ((11, 8, 128), (1, 1, 2), F32)],
-    (2, 6, 3): [((43, 193, 69), (1, 1, 23), F32), ((40, 220, 128), (8, 4, 8), F32)],
-    (4, 4, 2): [((8, 8, 147), (1, 1, 21), F32), ((7, 7, 256), (1, 1, 8), F32), ((190, 10, 255), (2, 1, 3), F32)],
-    (4, 5, 2): [((12, 10, 250), (4, 2, 50), F32), ((37, 217, 256), (1, 7, 16), F32)],
+    (1, 4, 2): [((7, 7, 36), (1, 1, 12), F64), ((7, 7, 64), (1, 1, 4), F64), ((7, 7, 34), (1, 1, 2), F32), ((7, 7, 64), (1, 1, 8), F32)],
+    (1, 6, 3): [((219, 38, 35), (3, 2, 7), F64), ((64, 10, 64), (16, 2, 16), F64), ((200, 44, 33), (8, 4, 11), F32), ((37, 217, 64), (1, 7, 4), F32)],
+    (2, 4, 2): [((8, 8, 65), (1, 2, 13), F64), ((8, 8, 128), (2, 2, 2), F64), ((7, 7, 65), (1, 1, 13), F32), ((7, 7, 128), (1, 1, 32), F32)],
+    (2, 5, 2): [((225, 37, 65), (25, 1, 13), F64), ((217, 37, 128), (31, 1, 2), F64), ((11, 8, 128), (1, 1, 16), F32)],
+    (2, 6, 3): [((38, 220, 67), (2, 4, 1), F32), ((49, 217, 128), (7, 7, 32), F32)],
+    (4, 4, 2): [((8, 8, 130), (2, 1, 10), F32), ((7, 7, 256), (1, 1, 8), F32), ((190, 10, 255), (2, 1, 3), F32)],
+    (4, 5, 2): [((45, 6, 159), (5, 2, 53), F32), ((37, 217, 256), (1, 7, 16), F32)],
 }
 VARIANT_ITERS, VARIANT_EVERY = 31, 9
 
