@@ -128,7 +128,8 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * jacobi_sweep, jacobi_sweep_residual, jacobi_run, halo_exchange and residual_norm allocates,
  * frees or synchronises anything, whatever options are changed in between, so they can be recorded
  * into a HIP graph (the call that runs the set-up cannot: do it before the capture starts).
- * Waits for the default stream (the scratch is cleared on it).
+ * Waits for the default stream where option "resident" may use its kernel for narrow grids (words in the scratch are
+ * cleared on that stream).
  * Idempotent.  Errors: EINVAL (NULL), ENOMEM, EHIP.
  */
 int jacobi_prepare(jacobi_plan *plan);

@@ -573,6 +573,14 @@ constexpr int RESIDENT_DEFAULT_DEPTH = 20;
 constexpr int RESIDENT_MAX_WORKGROUPS = 1024;           // the plan's scratch holds a partial sum for each
 constexpr unsigned RESIDENT_DEFAULT_SPIN = 1u << 22;    // polls of about a microsecond each: seconds
 
+// Whether resident2d_kernel can run a plan at all: 2-D, whole vectors in a row of a tile, rows that a wavefront holds.
+bool narrow_grid(const jacobi_plan *p)
+{
+    const Geo &g = p->geo;
+    const int nv = 16 / (int)p->esize;
+    return g.ndim == 2 && g.tw % nv == 0 && (int64_t)g.Tx * g.tw <= (int64_t)jk::RES_MAX_SEG * jk::WAVE * nv;
+}
+
 // with_residual: the kernel is also to deliver the residual norm of its result, for which the rows next to a
 // workgroup's own must still be exact after the deepest phase: one more ghost row per side.
 ResidentChoice resident_choice(const jacobi_plan *p, int iters, bool with_residual = false)
@@ -580,10 +588,9 @@ ResidentChoice resident_choice(const jacobi_plan *p, int iters, bool with_residu
     ResidentChoice c;
     const Geo &g = p->geo;
     const int nv = 16 / (int)p->esize;
-    if (!p->resident || g.ndim != 2 || iters < 1 || g.tw % nv) return c;
+    if (!p->resident || iters < 1 || !narrow_grid(p)) return c;
     const int64_t Nx = (int64_t)g.Tx * g.tw, Ny = (int64_t)g.Ty * g.th;
     const int nseg = (int)ceil_div(Nx, (int64_t)jk::WAVE * nv);
-    if (nseg > jk::RES_MAX_SEG) return c;
     // rows a wavefront can keep: two register sets of rows x vectors have to fit 128 registers
     const int max_rw = nseg == 2 ? jk::RES_MAX_RW - 1 : jk::RES_MAX_RW;
     int rw = (int)p->resident_rows;
@@ -1172,31 +1179,27 @@ int prepare_plan(jacobi_plan *p)
     if (e != hipSuccess) return fail_hip(e, "hipMalloc(residual scratch)");
     p->partial_cap = need;
     p->sync_words = (unsigned *)(p->partial + need);
-    // the resident kernel's barrier words are zero between launches: it clears them itself when it finishes
-    // so are the block kernels' words, and no message carries a tag yet
-    size_t clear = 2 * sizeof(double);
+    // The resident kernel's barrier words are zero between launches: it clears them itself when it finishes.  So are the block
+    // kernels' words, and no message carries a tag yet.
+    const bool narrow = narrow_grid(p);
     if (blocks) {
         p->block_scratch = (char *)p->partial + words_end;
-        clear = (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words);
+        e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
     }
-    e = hipMemset(p->sync_words, 0, clear);
+    if (e == hipSuccess && (blocks || narrow))
+        e = hipMemset(p->sync_words, 0, blocks ? (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words) : 2 * sizeof(double));
     // hipMemset returns before the memory is clear (2 us for 37 MB), and streams created as non-blocking, on which the first
-    // launch may come, do not wait for the default stream
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    // launch may come, do not wait for the default stream.  Block launches wait for the event before them; launches of
+    // the resident kernel for nothing.
+    if (e == hipSuccess && blocks) e = hipEventRecord(p->block_done, nullptr);
+    if (e == hipSuccess && narrow) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
+        if (p->block_done) (void)hipEventDestroy(p->block_done);
         (void)hipFree(p->partial);
+        p->block_done = nullptr;
         p->partial = nullptr;
         p->block_scratch = nullptr;
-        return fail_hip(e, "hipMemset(barrier words)");
-    }
-    if (blocks) {
-        e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            (void)hipFree(p->partial);
-            p->partial = nullptr;
-            p->block_scratch = nullptr;
-            return fail_hip(e, "hipEventCreateWithFlags");
-        }
+        return fail_hip(e, "clearing the residual scratch");
     }
     p->blocks.ok = blocks;
     p->prepared = true;

@@ -38,18 +38,27 @@ GRIDS = lambda p: (1 << 20, (1 << 20) + J.jacobi_grid_bytes(p))        # address
     return r.stdout
 
 
-def test_set_up_waits_for_the_clearing_of_its_scratch(stub):
+def test_first_launch_comes_after_the_clearing_of_the_scratch(stub):
     """hipMemset goes to the default stream, which streams created as non-blocking do not wait for: the first launch on one
-    must not meet words and messages that are cleared under it."""
+    must not meet words and messages that are cleared under it.  Set-up waits for it where resident2d_kernel may run; block
+    launches wait for an event recorded behind it; who uses neither has nothing cleared and waits for nothing."""
     run(stub, """
-for dims in ((256, 256), (1024, 1024), (64, 64, 64), (4096, 4096)):
+for dims, narrow, blocks in (((256, 256), 1, 1), ((256, 60), 1, 0), ((1024, 1024), 0, 1), ((64, 64, 64), 0, 1), ((4096, 4096), 0, 0), ((256, 256, 256), 0, 0)):
     p = J.jacobi_create(dims, (1,) * len(dims), J.JACOBI_F64)
     log()
     J.jacobi_prepare(p)
-    calls = [c[0] for c in log()]
-    assert "hipMemset" in calls, calls
-    after = calls[calls.index("hipMemset"):]
-    assert "hipStreamSynchronize" in after or "hipDeviceSynchronize" in after, calls
+    calls = log()
+    names = [c[0] for c in calls]
+    assert (J.jacobi_get_option(p, "block_workgroups") > 0) == bool(blocks)
+    assert ("hipMemset" in names) == bool(narrow or blocks), calls
+    assert ("hipStreamSynchronize" in names) == bool(narrow), calls
+    if narrow:
+        assert names.index("hipStreamSynchronize") > names.index("hipMemset"), calls
+    if blocks:
+        assert ["hipEventRecord", "(nil)"] in calls[names.index("hipMemset"):], calls
+        J.jacobi_sweep(p, *GRIDS(p), 100, 1 << 12)
+        names = [c[0] for c in log()]
+        assert names.count("hipLaunchKernel") == 1 and "hipStreamWaitEvent" in names[:names.index("hipLaunchKernel")], names
     J.jacobi_destroy(p)
 """)
 
