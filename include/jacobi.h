@@ -119,8 +119,8 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * double per workgroup of the largest launch ANY option setting can ask for, so it never has
  * to grow: 8 bytes per 4 one-row strips of about 100 cells at most, 5 MiB for 16384^2; behind
  * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
- * blocks, their messages and words (16 to 32 bytes per border cell: 2 MB for 256^2, 37 MB for 1024^2), set
- * to zero here once; where the device has no room for the messages, the plan does without them and runs launch by launch).
+ * blocks, their messages and words (two areas of 8 bytes per fp32, 16 per fp64 cell at a block's border: in fp64
+ * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once; where the device has no room for the messages, the plan does without them and runs launch by launch).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -372,7 +372,7 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    2 KiB (256 fp64 / 512 fp32 columns), the tile width is a multiple of 16 bytes, and
  *                    the rows fit one workgroup per CU (a workgroup owns what its 48 or 64 rows leave
  *                    after the ghost rows - 8 of 48 with 20 per side; taller grids get shallower phases,
- *                    up to ~12000 rows).
+ *                    up to ~12000 rows); many of these grids run faster in blocks, see below.
  *                    Such grids are updated in about a microsecond, so the launch-per-iteration sequence
  *                    is bound by launch latency (3.5 us per iteration); here the grid stays in registers,
  *                    the wavefronts of a workgroup pass each other their border rows through LDS, and
@@ -382,21 +382,25 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    swap the two grids like passes do (jacobi_pass_schedule lists them; read *final).
  *                    The narrow grids' barrier's wait is bounded: if the workgroups cannot all be resident (the device
  *                    is busy with other work for seconds) the launch still ends and writes NaN.
- *                    Mid-sized 2-D grids (wider than 64 cells, up to about 2000^2 in fp64, 2400^2 in fp32, also those above
- *                    that "resident_depth" / "resident_rows" were not set for) run that way too, cut into blocks in
- *                    both directions: a workgroup keeps a block in registers and exchanges its border with the
- *                    neighbouring blocks alone, as messages in the plan's scratch (1024^2: 5.4 -> 1.2 us per
- *                    iteration), and so do 3-D grids of rows that fill at least half of one, two or (fp32) four
- *                    cells per lane, up to about 100^3 (64^3: 6.0 -> 3.6 us); jacobi_run is then ONE launch, norms included (128 of them per launch).  There
+ *                    Mid-sized 2-D grids wider than 64 cells run that way too, cut into blocks in both directions: a workgroup
+ *                    keeps a block in registers and exchanges its border with the neighbouring blocks alone, as messages in
+ *                    the plan's scratch (1024^2: 5.4 -> 1.1 us per iteration in calls of 100).  Squares up to 2240^2 in fp64
+ *                    and 2288^2 in fp32 where 4 divides the width, up to 1926^2 and 2286^2 where 2 does, up to 1295^2 and
+ *                    1575^2 where it is odd; also the narrow grids above, unless "resident_depth" / "resident_rows" are set
+ *                    for them.  So do 3-D grids of rows of 33 to 128 cells (fp32: 256) as long as planes and rows
+ *                    are few enough: cubes up to 108^3 in fp64, 128^3 in fp32 (64^3: 5.9 -> 3.4 us).  jacobi_run is then ONE
+ *                    launch, norms included (128 of them per launch).  There
  *                    jacobi_pass_schedule still lists the passes of the launch-per-pass path, as which the grids swap
- *                    roles.  If not all of the launch's workgroups start within a few milliseconds (other work holds
- *                    CUs), those that did do the work through memory: slower, the same result.  A call takes this path
- *                    if a fixed estimate of both says it is faster (8 iterations and more of 1024^2) and it is not
+ *                    roles.  If not all of the launch's workgroups start within about 2 milliseconds (other work holds
+ *                    CUs), those that did do the work through memory: much slower - with half of the workgroups 256^2 takes
+ *                    11 us per iteration, 1024^2 34, 64^3 27 to 34 -, the same result.  A wait for a
+ *                    message is bounded as the barrier's is, with NaN for a result.  A call takes this path
+ *                    if a fixed estimate of both says it is faster (3 iterations and more of 1024^2) and it is not
  *                    being recorded into a HIP graph; launches of one plan follow each other on whatever streams.
- *                    The launch is the whole call: it carries the Dirichlet ring over itself, and in
+ *                    Either way the launch is the whole call: it carries the Dirichlet ring over itself, and in
  *                    jacobi_run it also delivers the residual norm of the grid it produced (NaN if the
- *                    barrier gave up).  Two launches of one plan must not overlap in time: they share
- *                    the barrier words in the plan's scratch.
+ *                    barrier gave up).  Two launches of the narrow grids' kernel on one plan must not overlap in
+ *                    time: they share the barrier words in the plan's scratch.
  *                    Ignores "tblock"; inter-tile halo cells of the result are left alone.
  *   "resident_depth" 0 | 1..31  iterations between two barriers of that kernel (0 = choose: 20, evened
  *                    out over the call)

@@ -17,9 +17,9 @@
 // XCDs (0.5 - 0.6 us for one word per lane, 0.75 - 0.9 for 8 in a row, 1.1 - 1.2 for 16) and its bytes (2.5 us + 0.22 us per MB of all blocks' messages).  Eight
 // wavefronts of many rows rather than sixteen of few: half the border rows through LDS and room for the whole state (16
 // wavefronts of 4 rows: 0.93 against 0.74 us).  Measured, us per iteration, launches -> blocks, 100 iterations with the
-// launch: 300^2 3.10 -> 0.69, 512^2 3.60 -> 0.83, 768^2 4.96 -> 1.09, 1024^2 5.44 -> 1.19, 1536^2 7.6 -> 2.2, 2048^2 11.4 -> 6.0
-// (its registers do not hold a block any more: an exchange goes through scratch memory); fp32 1500 x 1110 5.36 -> 1.15, 2048^2
-// 6.7 -> 2.4.  256^2, 100 iterations and their norm: 107 -> 74 us against resident2d_kernel.
+// launch: 300^2 3.10 -> 0.69, 512^2 3.71 -> 0.79, 768^2 5.10 -> 0.98, 1024^2 5.42 -> 1.14, 1536^2 7.44 -> 1.88, 2048^2 10.6 -> 5.9
+// (its registers do not hold a block any more: an exchange goes through scratch memory); fp32 1500 x 1110 5.27 -> 1.11, 2048^2
+// 6.08 -> 2.36.  256^2, 100 iterations and their norm: 99 -> 64 us against resident2d_kernel.
 #pragma once
 #include "blocks_common.h"
 

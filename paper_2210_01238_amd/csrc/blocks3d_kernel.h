@@ -11,10 +11,11 @@
 // the W ring cell enters lane 0 through the open end of the lane shift, the E ring cell lane 63 where a row fills the
 // wavefront (EXACT); otherwise it sits in the lane cell behind the row's last one and keeps its value there.
 //
-// What bounds it: the exchange.  With few rows per block an iteration takes 0.6 us (64^3: 4 x 2 rows of 64 cells per
-// wavefront), a message 0.5 - 0.9 us from XCD to XCD, but every one or two iterations all border rows have to go out, arrive and be
-// taken apart.  Measured, us per iteration, launches -> blocks (plus about 20 us per launch): 64^3 in eight tiles 5.96 -> 3.4, in
-// fp32 5.3 -> 2.45, 128^3 in fp32 11.0 -> 4.3.  Larger cubes need patches that do not fit the registers
+// What bounds it: latencies.  A message takes 0.5 - 0.9 us from XCD to XCD, and every one to three iterations all border rows
+// have to go out, arrive and be taken apart: in fp64 with 4 x 2 rows of 64 cells per wavefront 3.1 us per iteration with an exchange
+// after each, 2.6 with one after every second, whatever the number of blocks.  Measured, us per iteration, launches -> blocks, calls
+// of 100 iterations: 64^3 in eight tiles 5.91 -> 3.39, 96^3 8.01 -> 5.28, 108^3 7.31 -> 7.36; in fp32 64^3 5.78 -> 2.59, 96^3 7.97 ->
+// 3.67, 128^3 6.69 -> 4.77 and in eight tiles 10.3 -> 4.75.  Larger cubes need patches that do not fit the registers
 // (7 x 4 rows of 256 fp32 cells: most of the state goes to scratch memory), so they stay with a launch per iteration.
 #pragma once
 #include "blocks_common.h"
