@@ -1189,10 +1189,10 @@ int prepare_plan(jacobi_plan *p)
     if (e == hipSuccess && (blocks || narrow))
         e = hipMemset(p->sync_words, 0, blocks ? (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words) : 2 * sizeof(double));
     // hipMemset returns before the memory is clear (2 us for 37 MB), and streams created as non-blocking, on which the first
-    // launch may come, do not wait for the default stream.  Block launches wait for the event before them; launches of
-    // the resident kernel for nothing.
-    if (e == hipSuccess && blocks) e = hipEventRecord(p->block_done, nullptr);
+    // launch may come, do not wait for the default stream.  Block launches wait for the event before them (at first for this
+    // record, 5 - 9 us, of the clearing), launches of the resident kernel for nothing.
     if (e == hipSuccess && narrow) e = hipStreamSynchronize(nullptr);
+    else if (e == hipSuccess && blocks) e = hipEventRecord(p->block_done, nullptr);
     if (e != hipSuccess) {
         if (p->block_done) (void)hipEventDestroy(p->block_done);
         (void)hipFree(p->partial);
