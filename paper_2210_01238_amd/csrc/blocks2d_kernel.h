@@ -13,7 +13,8 @@
 // is, so RW + 1 rows of registers hold RW rows and nothing is copied.
 //
 // What bounds it: per iteration the vector unit (3 additions, 1 product and 4 / C lane shifts per cell in fp64; 8 wavefronts
-// of 8 rows x 128 columns 0.45 us, of which 0.39 are these instructions), per exchange the latency of a message between two
+// of 8 rows x 128 columns 0.45 us, of which 0.39 are these instructions by their number; the vector units of a whole 1024^2 call
+// are busy for 34 % of it), per exchange the latency of a message between two
 // XCDs (0.5 - 0.6 us for one word per lane, 0.75 - 0.9 for 8 in a row, 1.1 - 1.2 for 16) and its bytes (2.5 us + 0.22 us per MB of all blocks' messages).  Eight
 // wavefronts of many rows rather than sixteen of few: half the border rows through LDS and room for the whole state (16
 // wavefronts of 4 rows: 0.93 against 0.74 us).  Measured, us per iteration, launches -> blocks, 100 iterations with the
