@@ -18,9 +18,8 @@
 // XCDs (0.5 - 0.6 us for one word per lane, 0.75 - 0.9 for 8 in a row, 1.1 - 1.2 for 16) and its bytes (2.5 us + 0.22 us per MB of all blocks' messages).  Eight
 // wavefronts of many rows rather than sixteen of few: half the border rows through LDS and room for the whole state (16
 // wavefronts of 4 rows: 0.93 against 0.74 us).  Measured, us per iteration, launches -> blocks, 100 iterations with the
-// launch: 300^2 3.10 -> 0.69, 512^2 3.71 -> 0.79, 768^2 5.10 -> 0.98, 1024^2 5.42 -> 1.14, 1536^2 7.44 -> 1.88, 2048^2 10.6 -> 5.9
-// (its registers do not hold a block any more: an exchange goes through scratch memory); fp32 1500 x 1110 5.27 -> 1.11, 2048^2
-// 6.08 -> 2.36.  256^2, 100 iterations and their norm: 99 -> 64 us against resident2d_kernel.
+// launch: 300^2 3.10 -> 0.69, 512^2 3.71 -> 0.79, 768^2 5.10 -> 0.98, 1024^2 5.42 -> 1.14, 1536^2 7.44 -> 1.88, 2048^2 11.5 -> 2.4;
+// fp32 1500 x 1110 5.27 -> 1.11, 2048^2 6.08 -> 2.0.  256^2, 100 iterations and their norm: 99 -> 64 us against resident2d_kernel.
 #pragma once
 #include "blocks_common.h"
 
@@ -36,6 +35,11 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     constexpr unsigned MB = MSG_BYTES<T>;
     // The plain path's code lies behind the others': 1024^2 128 -> 125 us per 100 iterations, 256^2 66.4 -> 63.8, 1536^2 268 -> 223, all
     // variants 0 to 15 % - but for fp32 with 4 x 12 cells per lane, which then spills elsewhere (2048^2 267 -> 380).
+    // The rows' message offsets, constants of the run, take the registers of the grid (8 a row and more, in scratch memory where there
+    // is no room); computed anew in every exchange the large variants run without most of that: us per iteration 2048^2 5.1 -> 2.1,
+    // 2200^2 7.0 -> 3.2, 8000 x 500 6.0 -> 2.8, fp32 2048^2 2.1 -> 1.9, 2240^2 5.3 -> 4.1.  The others have the room, or lose more
+    // by computing: 1536^2 1.71 -> 1.83, in fp32 1.01 -> 1.04.
+    constexpr bool ANEW = C == 4 || (sizeof(T) == 8 && RW == 16);
     constexpr bool OUT_OF_THE_WAY = sizeof(T) == 8 || C != 4 || RW != 12;
     __shared__ T xch[2][BLK_WAVES][2][C][WAVE];    // [parity][wavefront][first / last row][component][lane]
     __shared__ T ring_row[2][C][WAVE];             // the Dirichlet rows above / below the domain
@@ -226,18 +230,18 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
     const unsigned frame = blocks2d_frame(p.x, p.y) * MB;
     const unsigned bottom_part = (unsigned)(d * HW) * MB, left_part = 2u * bottom_part, right_part = left_part + (unsigned)(HH * d) * MB;
     const unsigned row_step = (unsigned)(HW / C) * MB, side_step = (unsigned)(d / C) * MB;      // from component to component
-    unsigned send_row = MSG_SKIP, send_side = MSG_SKIP, recv_row = MSG_SKIP, recv_side = MSG_SKIP;
+    unsigned send_row_ = MSG_SKIP, send_side_ = MSG_SKIP, recv_row_ = MSG_SKIP, recv_side_ = MSG_SKIP;
     if (own_col) {
-        send_row = (unsigned)blk * frame + (unsigned)(col - xlo) / C * MB;
-        recv_row = (unsigned)bx * frame + (unsigned)(col - xlo) / C * MB;
-        if (!west && col < xlo + d) send_side = (unsigned)blk * frame + left_part + (unsigned)(col - xlo) / C * MB;
-        if (!east && col >= xhi - d) send_side = (unsigned)blk * frame + right_part + (unsigned)(col - (xhi - d)) / C * MB;
+        send_row_ = (unsigned)blk * frame + (unsigned)(col - xlo) / C * MB;
+        recv_row_ = (unsigned)bx * frame + (unsigned)(col - xlo) / C * MB;
+        if (!west && col < xlo + d) send_side_ = (unsigned)blk * frame + left_part + (unsigned)(col - xlo) / C * MB;
+        if (!east && col >= xhi - d) send_side_ = (unsigned)blk * frame + right_part + (unsigned)(col - (xhi - d)) / C * MB;
     } else if (ghost_w) {
-        recv_row = (unsigned)(bx - 1) * frame + (unsigned)(col - p.x.own_lo(bx - 1)) / C * MB;
-        recv_side = (unsigned)(blk - 1) * frame + right_part + (unsigned)(col - (xlo - d)) / C * MB;
+        recv_row_ = (unsigned)(bx - 1) * frame + (unsigned)(col - p.x.own_lo(bx - 1)) / C * MB;
+        recv_side_ = (unsigned)(blk - 1) * frame + right_part + (unsigned)(col - (xlo - d)) / C * MB;
     } else if (ghost_e) {
-        recv_row = (unsigned)(bx + 1) * frame + (unsigned)(col - xhi) / C * MB;
-        recv_side = (unsigned)(blk + 1) * frame + left_part + (unsigned)(col - xhi) / C * MB;
+        recv_row_ = (unsigned)(bx + 1) * frame + (unsigned)(col - xhi) / C * MB;
+        recv_side_ = (unsigned)(blk + 1) * frame + left_part + (unsigned)(col - xhi) / C * MB;
     }
     unsigned send_row_y[RW], send_side_y[RW], recv_y[RW], recv_is_row[RW];
 #pragma unroll
@@ -261,6 +265,8 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         if (!healthy) return;
         const unsigned tag = epoch + exchanges;
         const __amdgpu_buffer_rsrc_t buf = buffer_of((char *)br.msg + (size_t)(exchanges & 1u) * br.msg_bytes, br.msg_bytes);
+        const unsigned send_row = ANEW ? opaque_lane(send_row_) : send_row_, send_side = ANEW ? opaque_lane(send_side_) : send_side_;
+        const unsigned recv_row = ANEW ? opaque_lane(recv_row_) : recv_row_, recv_side = ANEW ? opaque_lane(recv_side_) : recv_side_;
 #pragma unroll
         for (int j = 0; j < RW; ++j) {
             if (send_row_y[j] != MSG_SKIP) {                         // wave-uniform

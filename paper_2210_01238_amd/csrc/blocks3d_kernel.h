@@ -12,11 +12,10 @@
 // wavefront (EXACT); otherwise it sits in the lane cell behind the row's last one and keeps its value there.
 //
 // What bounds it: latencies.  A message takes 0.5 - 0.9 us from XCD to XCD, and every one to three iterations all border rows
-// have to go out, arrive and be taken apart: in fp64 with 4 x 2 rows of 64 cells per wavefront 3.1 us per iteration with an exchange
-// after each, 2.6 with one after every second, whatever the number of blocks.  Measured, us per iteration, launches -> blocks, calls
-// of 100 iterations: 64^3 in eight tiles 5.91 -> 3.39, 96^3 8.01 -> 5.28, 108^3 7.31 -> 7.36; in fp32 64^3 5.78 -> 2.59, 96^3 7.97 ->
-// 3.67, 128^3 6.69 -> 4.77 and in eight tiles 10.3 -> 4.75.  Larger cubes need patches that do not fit the registers
-// (7 x 4 rows of 256 fp32 cells: most of the state goes to scratch memory), so they stay with a launch per iteration.
+// have to go out, arrive and be taken apart: in fp64 with 4 x 2 rows of 64 cells per wavefront 2.75 us per iteration with an exchange
+// after each, whatever the number of blocks.  Measured, us per iteration, launches -> blocks, calls
+// of 100 iterations: 64^3 in eight tiles 5.91 -> 2.95, 96^3 8.01 -> 5.28, 108^3 7.31 -> 6.9; in fp32 64^3 5.78 -> 2.52, 96^3 7.97 ->
+// 3.67, 128^3 6.69 -> 4.04.
 #pragma once
 #include "blocks_common.h"
 
@@ -257,7 +256,9 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks3d_kernel(Geo g, Block
         if (!healthy) return;
         const unsigned tag = epoch + exchanges;
         const __amdgpu_buffer_rsrc_t buf = buffer_of((char *)br.msg + (size_t)(exchanges & 1u) * br.msg_bytes, br.msg_bytes);
-        const unsigned lane_at = (unsigned)lane * MB;
+        // Computed anew in every exchange, but for patches that fit beside them: the rows' offsets take the registers of the grid (64^3 3.21
+        // -> 2.75 us per iteration, 108^3 6.81 -> 6.58 and 44 -> 28 a launch, 128^3 in fp32 4.12 -> 3.56; 96^3 4.89 -> 4.95).
+        const unsigned lane_at = (unsigned)(C == 2 && RZ == 4 ? lane : opaque_lane(lane)) * MB;
         static_for<RZ * RY>([&](auto j_) JK_INLINE {
             constexpr int J = decltype(j_)::value, z = J / RY, y = J % RY;
                 if (send_at[z * RY + y] != MSG_SKIP) {                  // wave-uniform
