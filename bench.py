@@ -338,7 +338,7 @@ def main() -> int:
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": ("blocks2d_kernel<double> or resident2d_kernel<double> (a block of iterations per launch: the grid stays in registers, so the "
+            "kernel": ("blocks2d_kernel<double>, chip2d_kernel<double> or resident2d_kernel<double> (a block of iterations per launch: the grid stays in registers, so the "
                        "bytes counted never cross the HBM interface)") if iters_per_launch > 1.5 else
                       (("sweep2d_kernel<double, update>" if len(w.dims) == 2 else "sweep3d_kernel<double, update>")
                        + " (the launches timed include the first update of the run, which reads the neighbouring tiles' edge "

@@ -120,7 +120,8 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * to grow: 8 bytes per 4 one-row strips of about 100 cells at most, 5 MiB for 16384^2; behind
  * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
  * blocks, their messages and words (two areas of 8 bytes per fp32, 16 per fp64 cell at a block's border: in fp64
- * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once; where the device has no room for the messages, the plan does without them and runs launch by launch).
+ * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once - or, for grids of 2000^2 and more in blocks without
+ * ghost cells, 17 MB at most, by the first call -; where the device has no room for the messages, the plan does without them and runs launch by launch).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -397,6 +398,10 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    message is bounded as the barrier's is, with NaN for a result.  A call takes this path
  *                    if a fixed estimate of both says it is faster (3 iterations and more of 1024^2) and it is not
  *                    being recorded into a HIP graph; launches of one plan follow each other on whatever streams.
+ *                    Larger 2-D grids, and those whose widths the cuts above cannot take, run the same way in blocks without ghost
+ *                    cells, in registers and LDS, the borders exchanged in every iteration: as many cells as ceil(Nx / w) *
+ *                    ceil(Ny / h) <= 256 blocks hold, w = 256 in fp64 and 512 in fp32, h at most 256 - 4096^2 in fp64, 4096 x 8192 or
+ *                    5632^2 in fp32 - and wider than one block (4096^2: 48 -> 5.9 us per iteration in calls of 100).
  *                    Either way the launch is the whole call: it carries the Dirichlet ring over itself, and in
  *                    jacobi_run it also delivers the residual norm of the grid it produced (NaN if the
  *                    barrier gave up).  Two launches of the narrow grids' kernel on one plan must not overlap in
@@ -436,6 +441,8 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  * the LDS size is unknown), "num_cu" (compute units; 256 until jacobi_prepare has asked the device),
  * how a plan is cut into the blocks that option "resident" keeps in registers (all 0: it is not): "block_workgroups",
  * "block_cells_per_lane", "block_rows_per_wave", "block_planes_per_wave" (3-D), "block_depth" (iterations between exchanges),
+ * the same for the larger 2-D grids that run in blocks without ghost cells: "chip_workgroups", "chip_cells_per_lane",
+ * "chip_rows_per_wave", "chip_rows_in_registers" (of those), "chip_even" (1: no blocks overlap by other than whole lanes),
  * and what a single-step launch will run with under the current options (host-only, the choices the
  * 0 = "choose" settings resolve to): "update_rows_per_strip", "update_rows_per_wave", "update_unroll",
  * "update_xcd_chunk", "update_strips" (wavefronts of work), "update_one_workgroup_per_cu",

@@ -377,4 +377,9 @@ __global__ __launch_bounds__(WG) void stream_copy_kernel(const uint4 *__restrict
     if (i < n16) dst[i] = src[i];
 }
 
+__global__ __launch_bounds__(WG) void clear_kernel(uint4 *p, long long n16)
+{
+    for (long long i = (long long)blockIdx.x * WG + threadIdx.x; i < n16; i += (long long)gridDim.x * WG) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 }  // namespace jk

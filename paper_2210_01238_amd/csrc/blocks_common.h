@@ -1,4 +1,4 @@
-// What the block kernels (blocks2d_kernel.h, blocks3d_kernel.h) share: how the workgroups of a launch find out
+// What the block kernels (blocks2d_kernel.h, blocks3d_kernel.h, chip2d_kernel.h) share: how the workgroups of a launch find out
 // that they are all there, the messages they pass each other, the plain path they take if they are not, and how
 // a launch ends.
 //
@@ -291,7 +291,7 @@ __device__ __forceinline__ void block_epilogue(const BlockRun &br, unsigned epoc
     unsigned next = epoch + exchanges;
     if (next > br.epoch_limit) {                 // by default once in some 2^31 exchanges
         u32x4 *m = (u32x4 *)br.msg;
-        for (unsigned i = threadIdx.x; i < 2u * (br.msg_bytes / 16u); i += blockDim.x) m[i] = u32x4{0u, 0u, 0u, 0u};
+        for (unsigned i = threadIdx.x; i < (unsigned)br.areas * (br.msg_bytes / 16u); i += blockDim.x) m[i] = u32x4{0u, 0u, 0u, 0u};
         next = 0;
     }
     __syncthreads();

@@ -66,18 +66,22 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // shape and type.
 struct BlockPlan {
     bool ok = false;
-    int cells_per_lane = 0, rows_per_wave = 0, planes_per_wave = 0;
+    bool chip = false;                // 2-D: chip2d_kernel, which holds no ghost cells
+    bool ragged = false;
+    int cells_per_lane = 0, rows_per_wave = 0, planes_per_wave = 0, rows_in_registers = 0;
     jk::BlockCut x, y, z;             // 2-D: x and y; 3-D: the padded rows in y and z
     int frame_rows = 0;               // 3-D: rows of a block's message
     int strip = 0;                    // blocks side by side in an XCD's patch (0: no patches)
     int workgroups = 0;
-    int64_t msg_bytes = 0;            // of one of the two message areas
+    int areas = 2;                    // message areas that take turns
+    int64_t msg_bytes = 0;            // of one of them
     int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
     double us_iterate = 0, us_exchange = 0;     // estimates: of an iteration, of an exchange
     double us_launch = 0;                       // of a launch besides
+    int depth() const { return y.d > 0 ? y.d : 1; }         // iterations between exchanges
     double us_per_iteration(int every) const    // with as many exchanges as the stretches between norms need (next_stretch)
     {
-        const int d = y.d, stretches = every > 0 ? (every + (d > 1 ? 1 : 0) + d - 1) / d : 1;
+        const int d = depth(), stretches = every > 0 ? (every + (d > 1 ? 1 : 0) + d - 1) / d : 1;
         return us_iterate + us_exchange * stretches / (every > 0 ? every : d);
     }
 };
@@ -102,6 +106,8 @@ struct jacobi_plan {
     int64_t partial_cap = 0;
     BlockPlan blocks;
     char *block_scratch = nullptr;    // behind those
+    bool chip_cleared = false;        // blocks.chip: a launch that clears it has been enqueued
+    std::mutex block_lock;            // launches of blocks are enqueued one after the other, whichever threads make the calls
     hipEvent_t block_done = nullptr;  // end of the last block launch: the next one, on whatever stream, waits for it
     unsigned *sync_words = nullptr;   // behind the partial sums: arrival counter and failure flag of the resident kernel
     // profiling events around update launches
@@ -668,6 +674,11 @@ bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, 
     return nb == 1 || (c->own_hi(0) >= least && held - d >= least && (nb == 2 || c->step * unit >= least));
 }
 
+int64_t scratch_of(const BlockPlan &b)
+{
+    return BLOCK_SYNC_BYTES + round_up((int64_t)b.workgroups * BLOCK_NORMS * 8, 256) + b.areas * b.msg_bytes;
+}
+
 // What a launch per iteration / passes of up to 12 iterations take (us per iteration, 2-D).
 double launch_us_2d(int64_t cell_bytes) { return 3.0 + 0.25e-6 * cell_bytes; }
 double blocked_us_2d(int64_t cells) { return 1.8 + 0.7e-6 * cells; }
@@ -728,7 +739,51 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
     }
     // not for grids that the other paths run as fast
     if (best.ok && best.us_per_iteration(0) > 0.8 * launch_us_2d(Nx * Ny * (f64 ? 8 : 4))) best.ok = false;
-    if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
+    if (best.ok) best.scratch_bytes = scratch_of(best);
+    return best;
+}
+
+// The cut of a 2-D grid that blocks2d_kernel does not take, into blocks without ghost cells, with the least time for 100 iterations.  What
+// an iteration takes was fitted to 25 grids from 2000^2 to 5600^2 with random cells: by the rows of a wavefront, 2.2 us with 8, 2.7
+// with 16, 3.3 with 24, 4.8 with 32 (nine of them in LDS); where the cut is not even - blocks overlap, or the width is no
+// multiple of a lane's cells - 2.6, 3.8, 5.0 and 6.4 (within 8 %).  A launch takes 16 us besides and 0.36 per MB of the grid, which it
+// reads and writes once.
+BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
+{
+    struct Variant { int rr, lt, lb; };
+    static const Variant variants[] = {
+#define JK_V(RR_, LT_, LB_) {RR_, LT_, LB_},
+        JK_CHIP2D_VARIANTS(JK_V)
+#undef JK_V
+    };
+    BlockPlan best;
+    const int esize = dtype == JACOBI_F64 ? 8 : 4, c = jk::CHIP2D_LANE_BYTES / esize, HW = jk::WAVE * c;
+    const int64_t Nx = (int64_t)g.Tx * g.tw, Ny = (int64_t)g.Ty * g.th;
+    for (const Variant &v : variants) {
+        const int rw = v.rr + v.lt + v.lb, HH = jk::BLK_WAVES * rw;
+        jk::BlockCut x, y;
+        if (!cut_into_blocks(Nx, HW, 0, Nx % c ? 1 : c, 1, num_cu, &x) || !cut_into_blocks(Ny, HH, 0, 1, 1, num_cu, &y)) continue;
+        if (x.nb < 2 || (int64_t)x.nb * y.nb > num_cu) continue;
+        const bool ragged = Nx % c != 0 || Ny != (int64_t)y.nb * HH;
+        if (!jk::chip2d_compiled(v.rr, esize == 8, ragged)) continue;
+        const double us = ragged ? 1.3 + 0.157 * rw : 1.5 + 0.078 * rw + (v.lt ? 0.7 : 0.0);
+        if (best.ok && us >= best.us_iterate) continue;
+        best.ok = best.chip = true;
+        best.us_iterate = us;
+        best.us_launch = 16 + 0.36e-6 * (double)(Nx * Ny * esize);
+        best.ragged = ragged;
+        best.cells_per_lane = c;
+        best.rows_per_wave = rw;
+        best.rows_in_registers = v.rr;
+        best.x = x; best.y = y;
+        best.workgroups = x.nb * y.nb;
+        best.strip = 0;
+        best.areas = 4;
+        best.msg_bytes = round_up((int64_t)best.workgroups * 2 * (HH + HW) * 2 * esize, 256);
+    }
+    // not for grids that the other paths run as fast
+    if (best.ok && best.us_iterate > 0.8 * launch_us_2d(Nx * Ny * esize)) best.ok = false;
+    if (best.ok) best.scratch_bytes = scratch_of(best);
     return best;
 }
 
@@ -807,7 +862,7 @@ BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
     }
     // (with blocked passes asked for, later, blocks pay sooner)
     if (best.ok && best.us_per_iteration(0) > WORTH_3D * (launch_us_3d(p, false) + BLOCKED_3D_US)) best.ok = false;
-    if (best.ok) best.scratch_bytes = BLOCK_SYNC_BYTES + round_up((int64_t)best.workgroups * BLOCK_NORMS * 8, 256) + 2 * best.msg_bytes;
+    if (best.ok) best.scratch_bytes = scratch_of(best);
     return best;
 }
 
@@ -929,7 +984,8 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
     run.epoch_limit = p->resident_epoch_limit > 0 ? (unsigned)p->resident_epoch_limit : EPOCH_DEFAULT_LIMIT;
     run.sync = (jk::BlockSync *)p->block_scratch;
     run.partial = (double *)(p->block_scratch + BLOCK_SYNC_BYTES);
-    run.msg = p->block_scratch + p->blocks.scratch_bytes - 2 * p->blocks.msg_bytes;
+    run.msg = p->block_scratch + p->blocks.scratch_bytes - p->blocks.areas * p->blocks.msg_bytes;
+    run.areas = p->blocks.areas;
     run.msg_bytes = (unsigned)p->blocks.msg_bytes;
     run.result = result;
     const int c = p->blocks.cells_per_lane, rw = p->blocks.rows_per_wave;
@@ -938,6 +994,14 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
         const int rz = p->blocks.planes_per_wave;
         return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks3d_f64(c, rz, rw, a) : jk::launch_blocks3d_f32(c, rz, rw, a),
                               "3-D block kernel launch");
+    }
+    if (p->blocks.chip) {
+        const jk::Chip2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, p->blocks.strip, run}, in, out};
+        const int rr = p->blocks.rows_in_registers;
+        const bool f64 = p->lay.dtype == JACOBI_F64;
+        return launch_checked(p->blocks.ragged ? f64 ? jk::launch_chip2d_ragged_f64(rr, a) : jk::launch_chip2d_ragged_f32(rr, a)
+                                               : f64 ? jk::launch_chip2d_even_f64(rr, a) : jk::launch_chip2d_even_f32(rr, a),
+                              "block kernel launch");
     }
     const jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, p->blocks.strip, run}, in, out};
     return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks2d_f64(c, rw, a) : jk::launch_blocks2d_f32(c, rw, a),
@@ -955,9 +1019,18 @@ int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double
         const int64_t passes = every > 0 ? (int64_t)norms * count_passes(p, every) + count_passes(p, n % every) : count_passes(p, n);
         const bool to_other = (passes & 1) != 0;
         const bool timed = p->profile && p->ev_used < MAX_PROFILE_EVENTS;
+        const std::lock_guard<std::mutex> hold(p->block_lock);
         // Launches of one plan share its messages and words, so they follow each other even if the caller puts calls with
         // different grids on different streams (the launch-per-iteration path shares nothing and may overlap).
         HIP_TRY(hipStreamWaitEvent(st, p->block_done, 0));
+        if (p->blocks.chip && !p->chip_cleared) {
+            // here and not in the set-up, which would clear on the default stream: the launch behind it is in order without an event
+            const int64_t n16 = p->blocks.scratch_bytes / 16;
+            hipLaunchKernelGGL(jk::clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(n16, jk::WG), 2048)), dim3(jk::WG), 0, st,
+                               (uint4 *)p->block_scratch, (long long)n16);
+            HIP_TRY(hipGetLastError());
+            p->chip_cleared = true;
+        }
         if (timed) HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used], st));
         const int rc = launch_blocks(p, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
         if (rc) return rc;
@@ -1186,13 +1259,14 @@ int prepare_plan(jacobi_plan *p)
         p->block_scratch = (char *)p->partial + words_end;
         e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
     }
-    if (e == hipSuccess && (blocks || narrow))
+    if (e == hipSuccess && ((blocks && !p->blocks.chip) || narrow))
         e = hipMemset(p->sync_words, 0, blocks ? (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words) : 2 * sizeof(double));
     // hipMemset returns before the memory is clear (2 us for 37 MB), and streams created as non-blocking, on which the first
     // launch may come, do not wait for the default stream.  Block launches wait for the event before them (at first for this
     // record, 5 - 9 us, of the clearing), launches of the resident kernel for nothing.
+    // (chip2d_kernel's words and messages: cleared by its first launch's stream, see run_blocks.)
     if (e == hipSuccess && narrow) e = hipStreamSynchronize(nullptr);
-    else if (e == hipSuccess && blocks) e = hipEventRecord(p->block_done, nullptr);
+    else if (e == hipSuccess && blocks && !p->blocks.chip) e = hipEventRecord(p->block_done, nullptr);
     if (e != hipSuccess) {
         if (p->block_done) (void)hipEventDestroy(p->block_done);
         (void)hipFree(p->partial);
@@ -1352,6 +1426,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
     g.xsend = L.xsend_offset;
     g.tile_stride = L.tile_stride;
     p->blocks = ndim == 2 ? plan_blocks2d(g, dtype, jk::NUM_CU) : plan_blocks3d(p, jk::NUM_CU);
+    if (ndim == 2 && !p->blocks.ok) p->blocks = plan_chip2d(g, dtype, jk::NUM_CU);
     *plan = p;
     return JACOBI_OK;
 }
@@ -1855,11 +1930,17 @@ int jacobi_get_option(const jacobi_plan *plan, const char *key, int64_t *value)
     if (!strcmp(key, "num_cu")) { *value = plan->num_cu; return JACOBI_OK; }
     // how the plan is cut into the blocks of one launch (all 0: it is not)
     const BlockPlan &b = plan->blocks;
-    if (!strcmp(key, "block_workgroups")) { *value = b.ok ? b.workgroups : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_cells_per_lane")) { *value = b.ok ? b.cells_per_lane : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_rows_per_wave")) { *value = b.ok ? b.rows_per_wave : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_planes_per_wave")) { *value = b.ok ? b.planes_per_wave : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_depth")) { *value = b.ok ? b.y.d : 0; return JACOBI_OK; }
+    const bool ghosts = b.ok && !b.chip, chip = b.ok && b.chip;
+    if (!strcmp(key, "block_workgroups")) { *value = ghosts ? b.workgroups : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_cells_per_lane")) { *value = ghosts ? b.cells_per_lane : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_rows_per_wave")) { *value = ghosts ? b.rows_per_wave : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_planes_per_wave")) { *value = ghosts ? b.planes_per_wave : 0; return JACOBI_OK; }
+    if (!strcmp(key, "block_depth")) { *value = ghosts ? b.depth() : 0; return JACOBI_OK; }
+    if (!strcmp(key, "chip_workgroups")) { *value = chip ? b.workgroups : 0; return JACOBI_OK; }
+    if (!strcmp(key, "chip_cells_per_lane")) { *value = chip ? b.cells_per_lane : 0; return JACOBI_OK; }
+    if (!strcmp(key, "chip_rows_per_wave")) { *value = chip ? b.rows_per_wave : 0; return JACOBI_OK; }
+    if (!strcmp(key, "chip_rows_in_registers")) { *value = chip ? b.rows_in_registers : 0; return JACOBI_OK; }
+    if (!strcmp(key, "chip_even")) { *value = chip && !b.ragged ? 1 : 0; return JACOBI_OK; }
     // what the single-step launches will run with under the current options: "update_..." for the update,
     // "residual_..." for the stand-alone residual pass (the strip-per-wavefront kernel)
     for (const char *prefix : {"update_", "residual_"}) {

@@ -1,0 +1,4 @@
+#include "launch_chip2d.inc.h"
+namespace jk {
+hipError_t launch_chip2d_even_f32(int rr, const Chip2dLaunch &a) { return chip2d_dispatch<float, false>(rr, a); }
+}

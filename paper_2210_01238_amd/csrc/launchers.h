@@ -145,7 +145,8 @@ struct BlockRun {
     unsigned admitted;     // workgroups that may be counted in (all of them, unless a test wants the plain path)
     unsigned epoch_limit;  // an epoch beyond it has the messages cleared and starts at 0 again
     BlockSync *sync;
-    void *msg;             // two message areas
+    void *msg;             // the message areas
+    int areas;
     unsigned msg_bytes;    // of one of them
     double *partial;       // one sum per norm and workgroup
     double *result;        // the norms
@@ -155,9 +156,9 @@ struct BlockRun {
 // the n cells; a block owns what lies d behind the start of its range up to d behind the start of the next one.
 struct BlockCut {
     int n, held, nb, d, unit, step, longer;        // steps between starts in units: the first `longer` ones step + 1
-    __host__ __device__ int start(int b) const { return (b * step + (b < longer ? b : longer)) * unit; }
-    __host__ __device__ int own_lo(int b) const { return b == 0 ? 0 : start(b) + d; }
-    __host__ __device__ int own_hi(int b) const { return b == nb - 1 ? n : start(b + 1) + d; }
+    __host__ __device__ __forceinline__ int start(int b) const { return (b * step + (b < longer ? b : longer)) * unit; }
+    __host__ __device__ __forceinline__ int own_lo(int b) const { return b == 0 ? 0 : start(b) + d; }
+    __host__ __device__ __forceinline__ int own_hi(int b) const { return b == nb - 1 ? n : start(b + 1) + d; }
 };
 
 struct Blocks2d {
@@ -184,6 +185,28 @@ struct Blocks2dLaunch {
 };
 hipError_t launch_blocks2d_f64(int c, int rw, const Blocks2dLaunch &a);
 hipError_t launch_blocks2d_f32(int c, int rw, const Blocks2dLaunch &a);
+
+// 2-D grids that fill the chip (chip2d_kernel.h): cuts without ghost cells (d = 0)
+struct Chip2d {
+    BlockCut x, y;
+    int strip;
+    BlockRun run;
+};
+constexpr int CHIP2D_LANE_BYTES = 32;          // of a row in a lane: 4 fp64, 8 fp32 cells
+// Compiled variants: rows per wavefront in registers, in LDS above those, in LDS below; each for cuts that are even - the blocks' widths
+// whole lanes, their heights not overlapping - and for the others.  Even fp64 cuts of 8 rows: blocks2d_kernel takes those grids.
+#define JK_CHIP2D_VARIANTS(X) X(8, 0, 0) X(12, 0, 0) X(16, 0, 0) X(20, 0, 0) X(24, 0, 0) X(23, 4, 5)
+__host__ __device__ constexpr bool chip2d_compiled(int rows_in_registers, bool f64, bool ragged) { return rows_in_registers != 8 || !f64 || ragged; }
+struct Chip2dLaunch {
+    hipStream_t st;
+    Geo g;
+    Chip2d p;
+    void *in, *out;
+};
+hipError_t launch_chip2d_even_f64(int rows_in_registers, const Chip2dLaunch &a);
+hipError_t launch_chip2d_even_f32(int rows_in_registers, const Chip2dLaunch &a);
+hipError_t launch_chip2d_ragged_f64(int rows_in_registers, const Chip2dLaunch &a);
+hipError_t launch_chip2d_ragged_f32(int rows_in_registers, const Chip2dLaunch &a);
 
 // 3-D: cuts of the padded rows (n = N + 2) in z and y
 struct Blocks3d {

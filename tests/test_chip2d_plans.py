@@ -1,0 +1,132 @@
+"""Which large 2-D grids run whole on the chip (chip2d_kernel), and as what: planned on the CPU, with a stand-in for the HIP runtime
+(hip_stub) that counts launches; and the waits in the generated code, as for the other block kernels."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import test_device_waits as waits
+from test_block_plans import text
+from test_chip2d_gpu import EVERY, ITERS, PLAIN, VARIANTS
+from test_host_calls import ROOT, run, stub  # noqa: F401  (stub: a fixture)
+
+HEAD = """
+from numpy import float64, float32
+def plan(dims, tiles, dtype):
+    return J.jacobi_create(dims, tiles, J.JACOBI_F64 if dtype is float64 else J.JACOBI_F32)
+def figures(p, *names):
+    return tuple(J.jacobi_get_option(p, "chip_" + n) for n in names)
+def launches(p, iters, every):
+    J.jacobi_prepare(p)
+    J.jacobi_sweep(p, *GRIDS(p), 50)                     # the first one also clears the plan's words
+    log()
+    J.jacobi_run(p, *GRIDS(p), iters, every, 1 << 16) if every else J.jacobi_sweep(p, *GRIDS(p), iters)
+    return sum(c[0] == "hipLaunchKernel" for c in log())
+"""
+
+
+def test_every_compiled_variant_is_reached(stub):  # noqa: F811
+    run(stub, HEAD + f"""
+for want, cases in {text(VARIANTS)}.items():
+    for dims, tiles, dtype in cases:
+        p = plan(dims, tiles, dtype)
+        assert figures(p, "rows_in_registers", "even") == want and launches(p, {ITERS}, {EVERY}) == 1, (dims, dtype, want)
+        assert J.jacobi_get_option(p, "block_workgroups") == 0
+        J.jacobi_destroy(p)
+for dims, tiles, dtype in {text(PLAIN)}:
+    p = plan(dims, tiles, dtype)
+    assert launches(p, 9, 3) == launches(p, 8, 0) == 1, (dims, dtype)
+    J.jacobi_destroy(p)
+""")
+    with open(os.path.join(ROOT, "paper_2210_01238_amd", "csrc", "launchers.h")) as f:
+        rows = {int(n) for n in re.findall(r"X\((\d+),", re.search(r"#define JK_CHIP2D_VARIANTS\(X\)(.*)", f.read()).group(1))}
+    compiled = {((n, even), t) for n in rows for even in (0, 1) for t in ("float64", "float32")} - {((8, 1), "float64")}
+    assert compiled == {(v, c[2].__name__) for v, cases in VARIANTS.items() for c in cases}
+
+
+def test_cuts_cover_the_grid(stub):  # noqa: F811
+    """Blocks of lanes x cells by wavefronts x rows, as few as cover the grid, at most one per CU; larger grids, narrow ones and those
+    the other block kernel takes have none."""
+    run(stub, HEAD + """
+import random
+rng = random.Random(7)
+seen = 0
+for _ in range(3000):
+    dtype = rng.choice((float64, float32))
+    ny, nx = (int(2 ** rng.uniform(6, 13.3)) for _ in range(2))
+    p = plan((ny, nx), (1, 1), dtype)
+    wg, cells, rows, regs, even = figures(p, "workgroups", "cells_per_lane", "rows_per_wave", "rows_in_registers", "even")
+    if wg:
+        seen += 1
+        w, h = 64 * cells, 8 * rows
+        assert cells * (8 if dtype is float64 else 4) == 32 and w < nx and h <= ny
+        assert wg == -(-nx // w) * -(-ny // h) <= 256 and regs <= rows
+        assert bool(even) == (nx % cells == 0 and ny % h == 0)
+        assert J.jacobi_get_option(p, "block_workgroups") == 0
+    J.jacobi_destroy(p)
+assert seen > 300, seen
+for dims in ((4096, 4100), (8192, 8192), (20000, 200), (1024, 1024), (2048, 2048)):
+    p = plan(dims, (1, 1), float64)
+    assert figures(p, "workgroups") == (0,), dims
+    J.jacobi_destroy(p)
+""")
+
+
+def test_set_up_words_and_scratch(stub):  # noqa: F811
+    """The plan's words are cleared by a kernel on the stream of the first launch, once; without room for the messages the plan runs by
+    launches; calls of one or two iterations take the path that is faster for them."""
+    run(stub, HEAD + """
+p = plan((4096, 4096), (4, 4), float64)
+J.jacobi_prepare(p)
+assert "hipMemset" not in [c[0] for c in log()]
+counts = []
+for _ in range(3):
+    J.jacobi_sweep(p, *GRIDS(p), 100, 1 << 12)
+    counts.append(sum(c[0] == "hipLaunchKernel" for c in log()))
+assert counts == [2, 1, 1], counts
+J.jacobi_sweep(p, *GRIDS(p), 1)
+assert ["512"] != [c[2] for c in log() if c[0] == "hipLaunchKernel"]
+whole = J.jacobi_scratch_bytes(p)
+J.jacobi_destroy(p)
+p = plan((4096, 4096), (4, 4), float64)
+stub.stub_malloc_limit(whole - 1)
+J.jacobi_prepare(p)
+assert J.jacobi_scratch_bytes(p) < whole
+log()
+J.jacobi_sweep(p, *GRIDS(p), 50)
+assert sum(c[0] == "hipLaunchKernel" for c in log()) >= 50
+J.jacobi_destroy(p)
+""")
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """The instructions of one variant, in the order of the text."""
+    from paper_2210_01238_amd import build
+    d = tmp_path_factory.mktemp("asm")
+    src, out = str(d / "one.hip"), str(d / "one.s")
+    with open(src, "w") as f:
+        f.write('#include "chip2d_kernel.h"\n'
+                "template __global__ void jk::chip2d_kernel<float, 8, 0, 0, true>(jk::Geo, jk::Chip2d, float *, float *);\n")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.FLAGS, "-I", build.CSRC, "-I", os.path.join(ROOT, "include"),
+                    "--cuda-device-only", "-S", src, "-o", out], check=True, stdout=subprocess.DEVNULL, stderr=subprocess.STDOUT)
+    found, inside = [], False
+    for line in open(out):
+        if re.match(r"_ZN2jk\d+chip2d_kernelI.*:", line):
+            inside = True
+        elif line.startswith(".Lfunc_end"):
+            inside = False
+        elif inside and line.startswith(".LBB"):
+            found.append("label")
+        elif inside and line.startswith("\t") and not line.lstrip().startswith((";", ".")):
+            found.append(line.split(";")[0].strip())
+    assert found
+    return found
+
+
+def test_end_of_a_workgroup_and_its_barriers_wait_for_every_wavefront(code):
+    for pattern in (r"buffer_wbl2", r"global_atomic_add v.* offset:8 sc0"):
+        bad, n = waits.unwaited(code, [i for i, x in enumerate(code) if re.match(pattern, x)])
+        assert n >= 1 and not bad, (pattern, bad)
+
