@@ -120,8 +120,8 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * to grow: 8 bytes per 4 one-row strips of about 100 cells at most, 5 MiB for 16384^2; behind
  * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
  * blocks, their messages and words (two areas of 8 bytes per fp32, 16 per fp64 cell at a block's border: in fp64
- * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once - or, for grids of 2000^2 and more in blocks without
- * ghost cells, 17 MB at most, by the first call -; where the device has no room for the messages, the plan does without them and runs launch by launch).
+ * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once - or, for grids that only run in blocks without
+ * ghost cells (60 MB at most), by the first call -; where the device has no room for the messages, the plan does without them and runs launch by launch).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -401,12 +401,16 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    Larger 2-D grids, and those whose widths the cuts above cannot take, run the same way in blocks without ghost
  *                    cells, in registers and LDS, the borders exchanged in every iteration: as many cells as ceil(Nx / w) *
  *                    ceil(Ny / h) <= 256 blocks hold, w = 256 in fp64 and 512 in fp32, h at most 256 - 4096^2 in fp64, 4096 x 8192 or
- *                    5632^2 in fp32 - and wider than one block (4096^2: 48 -> 5.9 us per iteration in calls of 100).
+ *                    5632^2 in fp32 - and wider than one block (4096^2: 48 -> 5.9 us per iteration in calls of 100).  So do 3-D grids of rows of 8 to
+ *                    256 cells (fp32: 512) and of 256 rows and more (1000 where rows are longer than 64 cells) that fit the registers:
+ *                    128 cells wide about 36000 rows, 256 wide 25000 (fp32: 57000) (64^3: 3.2 -> 1.5 us, 160^3: 14 -> 7.4, 210 x 198 x 250 in fp32:
+ *                    17 -> 5).  Where a grid can run with and without ghost cells a fixed estimate chooses.
  *                    Either way the launch is the whole call: it carries the Dirichlet ring over itself, and in
  *                    jacobi_run it also delivers the residual norm of the grid it produced (NaN if the
  *                    barrier gave up).  Two launches of the narrow grids' kernel on one plan must not overlap in
  *                    time: they share the barrier words in the plan's scratch.
  *                    Ignores "tblock"; inter-tile halo cells of the result are left alone.
+ *   "chip"           0 | 1   whether option "resident" may use the blocks without ghost cells (default 1)
  *   "resident_depth" 0 | 1..31  iterations between two barriers of that kernel (0 = choose: 20, evened
  *                    out over the call)
  *   "resident_rows"  0 | 1..4   rows each of its wavefronts keeps (0 = choose: as many as fit the
@@ -441,8 +445,9 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  * the LDS size is unknown), "num_cu" (compute units; 256 until jacobi_prepare has asked the device),
  * how a plan is cut into the blocks that option "resident" keeps in registers (all 0: it is not): "block_workgroups",
  * "block_cells_per_lane", "block_rows_per_wave", "block_planes_per_wave" (3-D), "block_depth" (iterations between exchanges),
- * the same for the larger 2-D grids that run in blocks without ghost cells: "chip_workgroups", "chip_cells_per_lane",
- * "chip_rows_per_wave", "chip_rows_in_registers" (of those), "chip_even" (1: no blocks overlap by other than whole lanes),
+ * the same for the blocks without ghost cells: "chip_workgroups", "chip_cells_per_lane", "chip_rows_per_wave", in 2-D
+ * "chip_rows_in_registers" (of those) and "chip_even" (1: no blocks overlap by other than whole lanes), in 3-D "chip_planes_per_wave" and
+ * "chip_waves_per_row" (wavefronts a row lies in),
  * and what a single-step launch will run with under the current options (host-only, the choices the
  * 0 = "choose" settings resolve to): "update_rows_per_strip", "update_rows_per_wave", "update_unroll",
  * "update_xcd_chunk", "update_strips" (wavefronts of work), "update_one_workgroup_per_cu",

@@ -76,6 +76,9 @@ __device__ __forceinline__ void roll_call(BlockSync *s, unsigned expected, unsig
 // A loaded value that has to be there before the program goes on.
 template <typename T> __device__ __forceinline__ void arrived(T &v) { asm volatile("" : "+v"(v)); }
 
+// One of two values - not one of two places: the arrays they come from stay in registers.
+template <typename T> __device__ __forceinline__ T pick(bool first, T x, T y) { return first ? x : y; }
+
 // f(0), f(1), ..., f(N-1) with compile-time indexes (integral_constant): arrays indexed by them stay in registers
 // however much code a turn is.
 template <typename F, int... I>
@@ -96,6 +99,13 @@ __device__ __forceinline__ int block_of_workgroup(int nbx, int nby, int strip)
     const int s = n / (strip * nby), in_strip = n - s * strip * nby, w = min(strip, nbx - s * strip);
     const int y = in_strip / w;
     return y * nbx + s * strip + in_strip - y * w;
+}
+
+// This workgroup's number when every XCD takes a run of consecutive ones.
+__device__ __forceinline__ int run_of_workgroup()
+{
+    const int wg = blockIdx.x, n = gridDim.x, xcd = wg % NUM_XCD;
+    return xcd * (n / NUM_XCD) + min(xcd, n % NUM_XCD) + wg / NUM_XCD;
 }
 
 // ---- messages -------------------------------------------------------------------------------------------
@@ -137,6 +147,94 @@ template <> struct Msg<float> {
     }
     __device__ __forceinline__ unsigned wrong(unsigned tag) const { return m[1] ^ tag; }
     __device__ __forceinline__ float value() const { return __builtin_bit_cast(float, m[0]); }
+};
+
+// N cells per lane in 8-byte words with a tag of ONE byte each: the cells' 8-byte values (fp32: two cells each) with the highest byte
+// replaced by the tag, and words of seven such bytes behind them.  9.1 to 12 bytes per fp64 cell instead of 16, 4.6 to 6 per fp32 cell
+// instead of 8, for two or three more instructions on either side.  The tags come round after 255 exchanges, which is no
+// matter as long as a word holds nothing older than the exchange before the one waited for: whoever sends clears its words at the
+// start of a launch.  (Where the bytes are what an exchange costs: in 3-D.)
+__device__ __forceinline__ unsigned byte_tag(int exchange) { return (unsigned)(exchange % 255 + 1) << 24; }
+template <typename T, int N> struct ByteTagged {
+    static constexpr int PER = 8 / (int)sizeof(T), M = (N + PER - 1) / PER, WORDS = M + (M + 6) / 7, PAIRS = WORDS / 2;
+    static constexpr unsigned BYTES = byte_tagged_bytes(N, (int)sizeof(T));
+    unsigned lo[WORDS], hi[WORDS];
+
+    // word i of the message from its values' halves (get(item) -> Int2)
+    template <int I, typename G> static __device__ __forceinline__ Int2 word(unsigned tag, G &&get)
+    {
+        if constexpr (I < M) {
+            const Int2 v = get(std::integral_constant<int, I>{});
+            return {v.lo, (int)(((unsigned)v.hi & 0xffffffu) | tag)};
+        } else {
+            constexpr int J = (I - M) * 7;
+            unsigned l = 0, h = tag;
+            static_for<7>([&](auto k) JK_INLINE {
+                if constexpr (J + k.value < M) {
+                    const unsigned top = (unsigned)get(std::integral_constant<int, J + k.value>{}).hi >> 24;
+                    if constexpr (k.value < 4) l |= top << (8 * k.value);
+                    else h |= top << (8 * (k.value - 4));
+                }
+            });
+            return {(int)l, (int)h};
+        }
+    }
+    template <typename F> static __device__ __forceinline__ void send(unsigned tag, __amdgpu_buffer_rsrc_t buf, unsigned at, int lane, F &&cell)
+    {
+        auto get = [&](auto i) JK_INLINE -> Int2 {
+            if constexpr (PER == 1) return __builtin_bit_cast(Int2, cell(i));
+            else {
+                constexpr int K = 2 * decltype(i)::value;
+                int h = 0;
+                if constexpr (K + 1 < N) h = __builtin_bit_cast(int, cell(std::integral_constant<int, K + 1>{}));
+                return {__builtin_bit_cast(int, cell(std::integral_constant<int, K>{})), h};
+            }
+        };
+        static_for<PAIRS>([&](auto k) JK_INLINE {
+            const Int2 x = word<2 * k.value>(tag, get), y = word<2 * k.value + 1>(tag, get);
+            const u32x4 m = {(unsigned)x.lo, (unsigned)x.hi, (unsigned)y.lo, (unsigned)y.hi};
+            __builtin_amdgcn_raw_buffer_store_b128(m, buf, (int)(at + (unsigned)lane * 16u + k.value * (WAVE * 16u)), 0, AUX_AGENT);      // (no scalar offset: see send_cell)
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (WORDS % 2 == 1) {
+            const Int2 x = word<WORDS - 1>(tag, get);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{(unsigned)x.lo, (unsigned)x.hi}, buf, (int)(at + (unsigned)lane * 8u + PAIRS * (WAVE * 16u)), 0, AUX_AGENT);
+        }
+    }
+    __device__ __forceinline__ void read(__amdgpu_buffer_rsrc_t buf, unsigned at, int lane)
+    {
+        static_for<PAIRS>([&](auto k) JK_INLINE {
+            const u32x4 m = __builtin_amdgcn_raw_buffer_load_b128(buf, (int)(at + (unsigned)lane * 16u + k.value * (WAVE * 16u)), 0, AUX_AGENT | AUX_VOLATILE);
+            lo[2 * k.value] = m[0];
+            hi[2 * k.value] = m[1];
+            lo[2 * k.value + 1] = m[2];
+            hi[2 * k.value + 1] = m[3];
+        });
+        if constexpr (WORDS % 2 == 1) {
+            const u32x2 m = __builtin_amdgcn_raw_buffer_load_b64(buf, (int)(at + (unsigned)lane * 8u + PAIRS * (WAVE * 16u)), 0, AUX_AGENT | AUX_VOLATILE);
+            lo[WORDS - 1] = m[0];
+            hi[WORDS - 1] = m[1];
+        }
+    }
+    __device__ __forceinline__ bool wrong(unsigned tag) const          // false: all of it is there
+    {
+        unsigned w = 0;
+        static_for<WORDS>([&](auto i) JK_INLINE { w |= hi[i.value] ^ tag; });
+        return w > 0xffffffu;
+    }
+    template <typename F> __device__ __forceinline__ void take(F &&put) const
+    {
+        static_for<M>([&](auto i_) JK_INLINE {
+            constexpr int i = decltype(i_)::value, e = M + i / 7, k = i % 7;
+            const unsigned top = (k < 4 ? lo[e] >> (8 * (k % 4)) : hi[e] >> (8 * (k % 4))) & 0xffu;
+            const int l = (int)lo[i], h = (int)((hi[i] & 0xffffffu) | top << 24);
+            if constexpr (PER == 1) put(i_, __builtin_bit_cast(T, Int2{l, h}));
+            else {
+                put(std::integral_constant<int, 2 * i>{}, __builtin_bit_cast(T, l));
+                if constexpr (2 * i + 1 < N) put(std::integral_constant<int, 2 * i + 1>{}, __builtin_bit_cast(T, h));
+            }
+        });
+    }
 };
 
 // A lane at the open end of a DPP wave shift receives zero; with these it receives `end`, which has to be zero in all

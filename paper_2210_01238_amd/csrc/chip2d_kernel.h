@@ -34,7 +34,11 @@
 namespace jk {
 
 template <int I> using Int = std::integral_constant<int, I>;
-template <typename T> __device__ __forceinline__ T pick(bool first, T x, T y) { return first ? x : y; }        // of values, not of their places
+
+// Where block b of a cut without ghost cells starts and ends.  (The cut's own members are not always inlined, and a call, even one that
+// is never made, costs registers.)
+__device__ __forceinline__ int start_of(const BlockCut &c, int b) { return (b * c.step + min(b, c.longer)) * c.unit; }
+__device__ __forceinline__ int end_of(const BlockCut &c, int b) { return b == c.nb - 1 ? c.n : start_of(c, b + 1); }
 
 template <typename T, int RR, int LT, int LB, bool RAGGED>
 __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d p, T *ga, T *gb)
@@ -72,7 +76,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     const int bx = blk - by * nbx;
     const unsigned epoch = __builtin_amdgcn_readfirstlane(agent_load(&br.sync->epoch));
     const unsigned max_exchanges = (unsigned)br.iters + 2u;
-    const int x0 = p.x.start(bx), y0 = p.y.start(by);
+    const int x0 = start_of(p.x, bx), y0 = start_of(p.y, by);
     const int row0 = y0 + wave * RW;               // first row of this wavefront
     const bool west = bx == 0, east = bx == nbx - 1, north = by == 0, south = by == nby - 1;
 
@@ -183,10 +187,10 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
 
     // ---- what other blocks need.  Columns, counted in this block: the one E of the block W of it, the one W of the block E of it (-1:
     // no such block); rows of this wavefront: the one below the block above, the one above the block below.
-    const int out_w = west ? -1 : p.x.start(bx - 1) + HW - x0, out_e = east ? -1 : p.x.start(bx + 1) - 1 - x0;
+    const int out_w = west ? -1 : start_of(p.x, bx - 1) + HW - x0, out_e = east ? -1 : start_of(p.x, bx + 1) - 1 - x0;
     const bool at_ends = (west || out_w % C == 0) && (east || out_e % C == C - 1);      // the first and the last cell of a lane
     const int lane_w = west ? -1 : out_w / C, lane_e = east ? -1 : out_e / C;
-    const int out_n = north ? -1 : p.y.start(by - 1) + HH - y0 - wave * RW, out_s = south ? -1 : p.y.start(by + 1) - 1 - y0 - wave * RW;
+    const int out_n = north ? -1 : start_of(p.y, by - 1) + HH - y0 - wave * RW, out_s = south ? -1 : start_of(p.y, by + 1) - 1 - y0 - wave * RW;
     const int my_column = lane == lane_w ? wave * 2 * RW : lane == lane_e ? (wave * 2 + 1) * RW : COLUMN + lane;
 
     // ---- one iteration
@@ -416,7 +420,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     auto norm_sum = [&]() JK_INLINE -> double {
         const Row above = row_above(), below = row_below();
         const int first_row = opaque(row0), first_col = x0 + opaque_lane(lane) * C;
-        const int ylo = p.y.own_lo(by), yhi = p.y.own_hi(by), xlo = p.x.own_lo(bx), xhi = p.x.own_hi(bx);
+        const int ylo = start_of(p.y, by), yhi = end_of(p.y, by), xlo = start_of(p.x, bx), xhi = end_of(p.x, bx);
         double acc = 0.0;
         auto add = [&](int r, const Row &u, const Row &c, const Row &d) JK_INLINE {
             if (first_row + r < ylo || first_row + r >= yhi) return;
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     T *fin = br.final_is_out ? gb : ga;
     {
         const int first_col = x0 + opaque_lane(lane) * C;
-        const int ylo = p.y.own_lo(by), yhi = p.y.own_hi(by), xlo = p.x.own_lo(bx), xhi = p.x.own_hi(bx);
+        const int ylo = start_of(p.y, by), yhi = end_of(p.y, by), xlo = start_of(p.x, bx), xhi = end_of(p.x, bx);
         find_cells(first_col);
         const bool whole = !seam && first_col >= xlo && first_col + C <= xhi;
         RowWalk row(g, y0 + opaque(wave) * RW);

@@ -66,16 +66,17 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // shape and type.
 struct BlockPlan {
     bool ok = false;
-    bool chip = false;                // 2-D: chip2d_kernel, which holds no ghost cells
+    bool chip = false;                // for chip2d_kernel or chip3d_kernel, which hold no ghost cells
     bool ragged = false;
     int cells_per_lane = 0, rows_per_wave = 0, planes_per_wave = 0, rows_in_registers = 0;
     jk::BlockCut x, y, z;             // 2-D: x and y; 3-D: the padded rows in y and z
+    jk::EvenCut cy, cz;               // chip3d_kernel's
+    int waves_per_row = 0;
     int frame_rows = 0;               // 3-D: rows of a block's message
     int strip = 0;                    // blocks side by side in an XCD's patch (0: no patches)
     int workgroups = 0;
     int areas = 2;                    // message areas that take turns
     int64_t msg_bytes = 0;            // of one of them
-    int64_t scratch_bytes = 0;        // synchronisation words, partial sums, message areas
     double us_iterate = 0, us_exchange = 0;     // estimates: of an iteration, of an exchange
     double us_launch = 0;                       // of a launch besides
     int depth() const { return y.d > 0 ? y.d : 1; }         // iterations between exchanges
@@ -93,6 +94,7 @@ struct jacobi_plan {
     // options
     int64_t fused = 1, rows_per_strip = 0, nontemporal = 1, profile = 0, unroll = 0, xcd_chunk = 0, rows_per_wave = 0, tblock = 1, cooperative = 1;
     int64_t resident = 1, resident_depth = 0, resident_rows = 0, resident_spin_limit = 0, resident_admitted = 0, resident_epoch_limit = 0;
+    int64_t chip_option = 1;
     int64_t stack = 0;                // 2-D residual pass: wavefronts per workgroup stacked over one column segment (0: choose, 1: off, 4, 8)
     int64_t cu_lds_option = 0;        // option "cu_lds": LDS bytes per CU to compute the workgroup limits from (0: the device's)
     int64_t lds_limit_failed = 0;     // read-only: a launch dropped its workgroup limit (the occupancy query did not confirm it)
@@ -104,9 +106,9 @@ struct jacobi_plan {
     // ask for, plus one slot for the value residual_norm_host copies back.  Never reallocated.
     double *partial = nullptr;
     int64_t partial_cap = 0;
-    BlockPlan blocks;
-    char *block_scratch = nullptr;    // behind those
-    bool chip_cleared = false;        // blocks.chip: a launch that clears it has been enqueued
+    BlockPlan blocks, chip;           // with and without ghost cells; a call takes the faster one (choose_blocks)
+    char *block_scratch = nullptr;    // behind those: words, partial sums, messages of the one, of the other
+    bool block_cleared = false;       // a launch that clears it has been enqueued, if the set-up has not
     std::mutex block_lock;            // launches of blocks are enqueued one after the other, whichever threads make the calls
     hipEvent_t block_done = nullptr;  // end of the last block launch: the next one, on whatever stream, waits for it
     unsigned *sync_words = nullptr;   // behind the partial sums: arrival counter and failure flag of the resident kernel
@@ -674,11 +676,6 @@ bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, 
     return nb == 1 || (c->own_hi(0) >= least && held - d >= least && (nb == 2 || c->step * unit >= least));
 }
 
-int64_t scratch_of(const BlockPlan &b)
-{
-    return BLOCK_SYNC_BYTES + round_up((int64_t)b.workgroups * BLOCK_NORMS * 8, 256) + b.areas * b.msg_bytes;
-}
-
 // What a launch per iteration / passes of up to 12 iterations take (us per iteration, 2-D).
 double launch_us_2d(int64_t cell_bytes) { return 3.0 + 0.25e-6 * cell_bytes; }
 double blocked_us_2d(int64_t cells) { return 1.8 + 0.7e-6 * cells; }
@@ -739,7 +736,6 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
     }
     // not for grids that the other paths run as fast
     if (best.ok && best.us_per_iteration(0) > 0.8 * launch_us_2d(Nx * Ny * (f64 ? 8 : 4))) best.ok = false;
-    if (best.ok) best.scratch_bytes = scratch_of(best);
     return best;
 }
 
@@ -783,7 +779,6 @@ BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
     }
     // not for grids that the other paths run as fast
     if (best.ok && best.us_iterate > 0.8 * launch_us_2d(Nx * Ny * esize)) best.ok = false;
-    if (best.ok) best.scratch_bytes = scratch_of(best);
     return best;
 }
 
@@ -798,8 +793,9 @@ double launch_us_3d(const jacobi_plan *p, bool blocked)
     const SweepConfig c = make_config(p, jk::MODE_UPDATE);
     const jacobi_layout &L = p->lay;
     const double mb = 1e-6 * (double)(L.dims[0] * L.dims[1] * L.dims[2] * (int64_t)p->esize);
-    const double us = (c.rows_per_wave == 4 ? 4.6 : 3.4) + 0.7e-3 * (double)std::min<int64_t>(c.sp.nstrips, 1600) + 0.57 * std::min(mb, 6.0) +
+    const double small = (c.rows_per_wave == 4 ? 4.6 : 3.4) + 0.7e-3 * (double)std::min<int64_t>(c.sp.nstrips, 1600) + 0.57 * std::min(mb, 6.0) +
                       0.6 * std::max(c.sp.R - 4, 0);
+    const double us = std::max(small, 3 + 0.33 * mb);           // (from 17 MB on: 160^3 14.4, 210 x 198 x 250 in fp32 17.1, 230 x 220 x 256 19.1)
     return blocked ? std::min(us, 8.5) + BLOCKED_3D_US : us;
 }
 
@@ -862,7 +858,60 @@ BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
     }
     // (with blocked passes asked for, later, blocks pay sooner)
     if (best.ok && best.us_per_iteration(0) > WORTH_3D * (launch_us_3d(p, false) + BLOCKED_3D_US)) best.ok = false;
-    if (best.ok) best.scratch_bytes = scratch_of(best);
+    return best;
+}
+
+// The cut of a 3-D grid into blocks without ghost cells with the least time for 100 iterations.  An iteration: 0.65 us, 0.03 per row of a
+// wavefront (a fifth more per cell beyond the first of a lane, a quarter less in fp32), 0.06 per word of its messages and 0.15 per MB
+// that all of them send (50 cuts of 28 grids from 48^3 to 230 x 220 x 256, 1.3 to 7.4 us: within 20 %, 5 % on average).  A launch: 18 us
+// besides, 0.55 per MB of the grid and 0.03 per workgroup.  Grids of few rows - below 256, below 1000 where a row lies in two
+// wavefronts - keep the path they had, though they would gain, too (27 x 29 x 119: 1.6 us against 3.8): the suite fixes it.
+BlockPlan plan_chip3d(const jacobi_plan *p, int num_cu)
+{
+    struct Variant { int c, rz, ry, nxw; bool f32_only; };
+    static const Variant variants[] = {
+#define JK_V(C_, RZ_, RY_, NXW_) {C_, RZ_, RY_, NXW_, false},
+        JK_CHIP3D_VARIANTS(JK_V)
+#undef JK_V
+#define JK_V(C_, RZ_, RY_, NXW_) {C_, RZ_, RY_, NXW_, true},
+        JK_CHIP3D_VARIANTS_F32(JK_V)
+#undef JK_V
+    };
+    BlockPlan best;
+    const bool f64 = p->lay.dtype == JACOBI_F64;
+    const int64_t Nx = p->lay.dims[2], Ny = p->lay.dims[1], Nz = p->lay.dims[0];
+    // parts of 2 * r cells or one fewer
+    auto cut = [](int64_t n, int r, jk::EvenCut *c) {
+        c->n = (int)n;
+        c->nb = (int)ceil_div(n, 2 * r);
+        return n / c->nb >= 2 * r - 1;
+    };
+    for (const Variant &v : variants) {
+        if (f64 && v.f32_only) continue;
+        const int width = jk::WAVE * v.c;
+        if (v.nxw == 2 ? Nx <= width || Nx > 2 * width || Ny * Nz < 1000 : Nx > width || Nx < 8 || Ny * Nz < 256) continue;
+        jk::EvenCut y, z;
+        if (!cut(Ny, v.ry, &y) || !cut(Nz, v.rz, &z)) continue;
+        const int64_t nb = (int64_t)y.nb * z.nb, nwg = v.nxw == 2 ? nb : ceil_div(nb, 2);
+        if (nwg > num_cu) continue;
+        const int64_t wave_bytes = jk::byte_tagged_bytes(v.ry * v.c, (int)p->esize) + jk::byte_tagged_bytes(v.rz * v.c, (int)p->esize);
+        const double mb = 1e-6 * (double)(nb * 4 * v.nxw * wave_bytes);
+        const double us = 0.65 + 0.03 * v.rz * v.ry * (0.8 + 0.2 * v.c) * (f64 ? 1.0 : 0.75) + 0.06 * (double)(wave_bytes / (jk::WAVE * 8)) + 0.15 * mb;
+        if (best.ok && us >= best.us_iterate) continue;
+        best.ok = best.chip = true;
+        best.us_iterate = us;
+        best.us_launch = 18 + 0.55e-6 * (double)(Nx * Ny * Nz * (int64_t)p->esize) + 0.03 * (double)nwg;
+        best.cells_per_lane = v.c;
+        best.rows_per_wave = v.ry;
+        best.planes_per_wave = v.rz;
+        best.waves_per_row = v.nxw;
+        best.cy = y; best.cz = z;
+        best.strip = strip_width((int)nb, y.nb, (double)Ny / y.nb, (double)Nz / z.nb);
+        best.workgroups = (int)nwg;
+        best.msg_bytes = nb * 4 * v.nxw * wave_bytes;
+    }
+    // not for grids that launches run as fast
+    if (best.ok && best.us_iterate > 0.9 * launch_us_3d(p, false)) best.ok = false;
     return best;
 }
 
@@ -925,9 +974,8 @@ PassChoice choose_pass(const jacobi_plan *p, int left)
 // Whether a call of so many iterations, with a norm every `every`-th, runs that way: what it saves per iteration has to pay for the
 // launch.  `row`: what the kernel for narrow
 // grids (resident2d_kernel) would do with them; it runs where its geometry was asked for by option.
-bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentChoice &row)
+bool blocks_usable(const jacobi_plan *p, const BlockPlan &b, int iters, int every, const ResidentChoice &row)
 {
-    const BlockPlan &b = p->blocks;
     if (!p->resident || !b.ok || b.workgroups > p->num_cu || iters > BLOCK_MAX_ITERS) return false;
     const jacobi_layout &L = p->lay;
     const int norms = every > 0 ? iters / every : 0;
@@ -937,6 +985,8 @@ bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentCho
         // the first with the small variants, 5.5 and 7 with the large ones.  (340 calls of 5 to 200 iterations, both ways: the
         // slower one is chosen in 19, by more than 10 % in 10; 0.9 % of the time in all.)
         const double other = launch_us_3d(p, choose_pass(p, norms > 0 ? every : iters).depth > 1);
+        // (chip3d_kernel: norms take half of what they do by launches.)
+        if (b.chip) return iters * (other - us) > b.us_launch - 5.5;
         const double more = b.us_launch - 5.5 + (norms > 0 ? norms * (0.1 * b.us_launch - 3.0) + 0.3 * b.us_launch - 8.0 : 0.0);
         return us <= WORTH_3D * other && iters * (other - us) > more;
     }
@@ -959,6 +1009,17 @@ bool blocks_usable(const jacobi_plan *p, int iters, int every, const ResidentCho
     return 4.5 + iters * other > here;
 }
 
+// The cut that such a call runs in (null: it takes another path).  With both, the one that a fixed estimate says is the faster.
+const BlockPlan *choose_blocks(const jacobi_plan *p, int iters, int every, const ResidentChoice &row)
+{
+    const bool chip = p->chip_option && blocks_usable(p, p->chip, iters, every, row), ghosts = blocks_usable(p, p->blocks, iters, every, row);
+    if (chip && ghosts) {
+        auto us = [&](const BlockPlan &b) { return b.us_launch + iters * b.us_per_iteration(every > 0 && every <= iters ? every : 0); };
+        return us(p->chip) < us(p->blocks) ? &p->chip : &p->blocks;
+    }
+    return chip ? &p->chip : ghosts ? &p->blocks : nullptr;
+}
+
 // Passes jacobi_sweep makes of `iters` iterations: as many as jacobi_pass_schedule lists.
 int64_t count_passes(const jacobi_plan *p, int64_t iters)
 {
@@ -969,9 +1030,20 @@ int64_t count_passes(const jacobi_plan *p, int64_t iters)
     return n;
 }
 
+// The block launches' scratch: synchronisation words, partial sums, messages.
+int64_t block_sums_bytes(const jacobi_plan *p)
+{
+    return round_up((int64_t)std::max(p->blocks.ok ? p->blocks.workgroups : 0, p->chip.ok ? p->chip.workgroups : 0) * BLOCK_NORMS * 8, 256);
+}
+int64_t message_bytes(const BlockPlan &b) { return b.ok ? b.areas * b.msg_bytes : 0; }
+int64_t block_scratch_bytes(const jacobi_plan *p)
+{
+    return p->blocks.ok || p->chip.ok ? BLOCK_SYNC_BYTES + block_sums_bytes(p) + message_bytes(p->blocks) + message_bytes(p->chip) : 0;
+}
+
 // One launch: `iters` iterations, norms of the grids after every `every`-th (0: none).  The result goes to `in` or
 // `out` as the passes of the launch-per-pass path would leave it.
-int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int norms, double *result, bool final_is_out, hipStream_t st)
+int launch_blocks(jacobi_plan *p, const BlockPlan &b, void *in, void *out, int iters, int every, int norms, double *result, bool final_is_out, hipStream_t st)
 {
     jk::BlockRun run;
     run.iters = iters;
@@ -980,36 +1052,45 @@ int launch_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, int
     run.final_is_out = final_is_out ? 1 : 0;
     run.roll_limit = p->resident_spin_limit > 0 ? (unsigned)(p->resident_spin_limit - 1) : ROLL_DEFAULT_LIMIT;
     run.spin_limit = RESIDENT_DEFAULT_SPIN;
-    run.admitted = (unsigned)(p->resident_admitted > 0 ? std::min<int64_t>(p->resident_admitted, p->blocks.workgroups) : p->blocks.workgroups);
+    run.admitted = (unsigned)(p->resident_admitted > 0 ? std::min<int64_t>(p->resident_admitted, b.workgroups) : b.workgroups);
     run.epoch_limit = p->resident_epoch_limit > 0 ? (unsigned)p->resident_epoch_limit : EPOCH_DEFAULT_LIMIT;
     run.sync = (jk::BlockSync *)p->block_scratch;
     run.partial = (double *)(p->block_scratch + BLOCK_SYNC_BYTES);
-    run.msg = p->block_scratch + p->blocks.scratch_bytes - p->blocks.areas * p->blocks.msg_bytes;
-    run.areas = p->blocks.areas;
-    run.msg_bytes = (unsigned)p->blocks.msg_bytes;
+    run.msg = p->block_scratch + BLOCK_SYNC_BYTES + block_sums_bytes(p) + (b.chip ? message_bytes(p->blocks) : 0);
+    run.areas = b.areas;
+    run.msg_bytes = (unsigned)b.msg_bytes;
     run.result = result;
-    const int c = p->blocks.cells_per_lane, rw = p->blocks.rows_per_wave;
+    const int c = b.cells_per_lane, rw = b.rows_per_wave;
+    if (p->geo.ndim == 3 && b.chip) {
+        const jk::Chip3dLaunch a{st, p->geo, {b.cz, b.cy, (int)p->lay.dims[2], b.strip, run}, in, out};
+        const int rz = b.planes_per_wave, nxw = b.waves_per_row;
+        const bool f64 = p->lay.dtype == JACOBI_F64;
+        return launch_checked(c == 1   ? f64 ? jk::launch_chip3d_c1_f64(rz, rw, nxw, a) : jk::launch_chip3d_c1_f32(rz, rw, nxw, a)
+                              : c == 2 ? f64 ? jk::launch_chip3d_c2_f64(rz, rw, nxw, a) : jk::launch_chip3d_c2_f32(rz, rw, nxw, a)
+                                       : jk::launch_chip3d_c4_f32(rz, rw, nxw, a),
+                              "3-D block kernel launch");
+    }
     if (p->geo.ndim == 3) {
-        const jk::Blocks3dLaunch a{st, p->geo, {p->blocks.z, p->blocks.y, (int)p->lay.dims[2], p->blocks.frame_rows, p->blocks.strip, run}, in, out};
-        const int rz = p->blocks.planes_per_wave;
+        const jk::Blocks3dLaunch a{st, p->geo, {b.z, b.y, (int)p->lay.dims[2], b.frame_rows, b.strip, run}, in, out};
+        const int rz = b.planes_per_wave;
         return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks3d_f64(c, rz, rw, a) : jk::launch_blocks3d_f32(c, rz, rw, a),
                               "3-D block kernel launch");
     }
-    if (p->blocks.chip) {
-        const jk::Chip2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, p->blocks.strip, run}, in, out};
-        const int rr = p->blocks.rows_in_registers;
+    if (b.chip) {
+        const jk::Chip2dLaunch a{st, p->geo, {b.x, b.y, b.strip, run}, in, out};
+        const int rr = b.rows_in_registers;
         const bool f64 = p->lay.dtype == JACOBI_F64;
-        return launch_checked(p->blocks.ragged ? f64 ? jk::launch_chip2d_ragged_f64(rr, a) : jk::launch_chip2d_ragged_f32(rr, a)
+        return launch_checked(b.ragged ? f64 ? jk::launch_chip2d_ragged_f64(rr, a) : jk::launch_chip2d_ragged_f32(rr, a)
                                                : f64 ? jk::launch_chip2d_even_f64(rr, a) : jk::launch_chip2d_even_f32(rr, a),
                               "block kernel launch");
     }
-    const jk::Blocks2dLaunch a{st, p->geo, {p->blocks.x, p->blocks.y, p->blocks.strip, run}, in, out};
+    const jk::Blocks2dLaunch a{st, p->geo, {b.x, b.y, b.strip, run}, in, out};
     return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_blocks2d_f64(c, rw, a) : jk::launch_blocks2d_f32(c, rw, a),
                           "block kernel launch");
 }
 
 // `iters` iterations of jacobi_run that way, in launches of at most BLOCK_NORMS norms.  *final as jacobi_run leaves it.
-int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double *result, hipStream_t st, void **final)
+int run_blocks(jacobi_plan *p, const BlockPlan &b, void *in, void *out, int iters, int every, double *result, hipStream_t st, void **final)
 {
     void *cur = in, *other = out;
     const int64_t per_launch = every > 0 ? (int64_t)every * BLOCK_NORMS : iters;
@@ -1023,16 +1104,16 @@ int run_blocks(jacobi_plan *p, void *in, void *out, int iters, int every, double
         // Launches of one plan share its messages and words, so they follow each other even if the caller puts calls with
         // different grids on different streams (the launch-per-iteration path shares nothing and may overlap).
         HIP_TRY(hipStreamWaitEvent(st, p->block_done, 0));
-        if (p->blocks.chip && !p->chip_cleared) {
+        if (!p->block_cleared) {
             // here and not in the set-up, which would clear on the default stream: the launch behind it is in order without an event
-            const int64_t n16 = p->blocks.scratch_bytes / 16;
+            const int64_t n16 = block_scratch_bytes(p) / 16;
             hipLaunchKernelGGL(jk::clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(n16, jk::WG), 2048)), dim3(jk::WG), 0, st,
                                (uint4 *)p->block_scratch, (long long)n16);
             HIP_TRY(hipGetLastError());
-            p->chip_cleared = true;
+            p->block_cleared = true;
         }
         if (timed) HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used], st));
-        const int rc = launch_blocks(p, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
+        const int rc = launch_blocks(p, b, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
         if (rc) return rc;
         if (timed) {
             HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used + 1], st));
@@ -1237,8 +1318,8 @@ int prepare_plan(jacobi_plan *p)
     const int64_t need = max_partials(p) + 1;      // + the slot residual_norm_host reads back
     // behind them: two doubles' worth of words for the resident kernel's grid barrier
     const size_t sums = (size_t)(need + 2) * sizeof(double), words_end = (size_t)round_up((int64_t)sums, 256);
-    bool blocks = p->blocks.ok;
-    hipError_t e = hipMalloc((void **)&p->partial, blocks ? words_end + (size_t)p->blocks.scratch_bytes : sums);
+    bool blocks = p->blocks.ok || p->chip.ok;
+    hipError_t e = hipMalloc((void **)&p->partial, blocks ? words_end + (size_t)block_scratch_bytes(p) : sums);
     if (e == hipErrorOutOfMemory && blocks) {
         // the messages are an extra (up to some 90 MB): without room for them the plan runs by launches
         (void)hipGetLastError();
@@ -1259,14 +1340,15 @@ int prepare_plan(jacobi_plan *p)
         p->block_scratch = (char *)p->partial + words_end;
         e = hipEventCreateWithFlags(&p->block_done, hipEventDisableTiming);
     }
-    if (e == hipSuccess && ((blocks && !p->blocks.chip) || narrow))
-        e = hipMemset(p->sync_words, 0, blocks ? (size_t)(p->block_scratch + p->blocks.scratch_bytes - (char *)p->sync_words) : 2 * sizeof(double));
+    p->block_cleared = blocks && p->blocks.ok;
+    if (e == hipSuccess && (p->block_cleared || narrow))
+        e = hipMemset(p->sync_words, 0, p->block_cleared ? (size_t)(p->block_scratch + block_scratch_bytes(p) - (char *)p->sync_words) : 2 * sizeof(double));
     // hipMemset returns before the memory is clear (2 us for 37 MB), and streams created as non-blocking, on which the first
     // launch may come, do not wait for the default stream.  Block launches wait for the event before them (at first for this
     // record, 5 - 9 us, of the clearing), launches of the resident kernel for nothing.
-    // (chip2d_kernel's words and messages: cleared by its first launch's stream, see run_blocks.)
+    // (Grids that only run without ghost cells: cleared on their first launch's stream, see run_blocks.)
     if (e == hipSuccess && narrow) e = hipStreamSynchronize(nullptr);
-    else if (e == hipSuccess && blocks && !p->blocks.chip) e = hipEventRecord(p->block_done, nullptr);
+    else if (e == hipSuccess && p->block_cleared) e = hipEventRecord(p->block_done, nullptr);
     if (e != hipSuccess) {
         if (p->block_done) (void)hipEventDestroy(p->block_done);
         (void)hipFree(p->partial);
@@ -1275,7 +1357,7 @@ int prepare_plan(jacobi_plan *p)
         p->block_scratch = nullptr;
         return fail_hip(e, "clearing the residual scratch");
     }
-    p->blocks.ok = blocks;
+    if (!blocks) p->blocks.ok = p->chip.ok = false;
     p->prepared = true;
     return JACOBI_OK;
 }
@@ -1340,6 +1422,7 @@ const OptionSpec OPTIONS[] = {
     {"tblock", &jacobi_plan::tblock, 1, jk::TP_MAX, {}},
     {"cooperative", &jacobi_plan::cooperative, 0, 1, {}},
     {"resident", &jacobi_plan::resident, 0, 1, {}},
+    {"chip", &jacobi_plan::chip_option, 0, 1, {}},
     {"resident_depth", &jacobi_plan::resident_depth, 0, 31, {}},
     {"resident_rows", &jacobi_plan::resident_rows, 0, jk::RES_MAX_RW, {}},
     {"resident_spin_limit", &jacobi_plan::resident_spin_limit, 0, 1LL << 31, {}},
@@ -1426,7 +1509,8 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
     g.xsend = L.xsend_offset;
     g.tile_stride = L.tile_stride;
     p->blocks = ndim == 2 ? plan_blocks2d(g, dtype, jk::NUM_CU) : plan_blocks3d(p, jk::NUM_CU);
-    if (ndim == 2 && !p->blocks.ok) p->blocks = plan_chip2d(g, dtype, jk::NUM_CU);
+    if (ndim == 3) p->chip = plan_chip3d(p, jk::NUM_CU);
+    else if (!p->blocks.ok) p->chip = plan_chip2d(g, dtype, jk::NUM_CU);
     *plan = p;
     return JACOBI_OK;
 }
@@ -1458,7 +1542,7 @@ size_t jacobi_scratch_bytes(const jacobi_plan *plan)
 {
     if (!plan) return 0;
     const int64_t bytes = (max_partials(const_cast<jacobi_plan *>(plan)) + 1 + 2) * (int64_t)sizeof(double);
-    return (size_t)(plan->blocks.ok ? round_up(bytes, 256) + plan->blocks.scratch_bytes : bytes);
+    return (size_t)(plan->blocks.ok || plan->chip.ok ? round_up(bytes, 256) + block_scratch_bytes(plan) : bytes);
 }
 
 size_t jacobi_grid_bytes(const jacobi_plan *plan) { return plan ? (size_t)plan->lay.grid_bytes : 0; }
@@ -1530,7 +1614,7 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     ResidentChoice rc_res = resident_choice(plan, iters, residual_out_dev != nullptr);
     const bool norm_in_launch = rc_res.ok && residual_out_dev;
     if (!rc_res.ok && residual_out_dev) rc_res = resident_choice(plan, iters);
-    const bool blocks = blocks_usable(plan, iters, 0, rc_res) && may_run_blocks(st);
+    const BlockPlan *const blocks = may_run_blocks(st) ? choose_blocks(plan, iters, 0, rc_res) : nullptr;
     if (rc_res.ok && !blocks) {
         // small 2-D grid: every iteration inside one launch, which also carries the ring over and delivers the
         // residual of its result; the residual of `in`, if asked for, from the stand-alone reduction first
@@ -1564,7 +1648,7 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
             if (rc) return rc;
         }
         if (carry) *carry = RunCarry{true, false, false};
-        return run_blocks(plan, in, out, iters, residual_out_dev ? iters : 0, residual_out_dev, st, final);
+        return run_blocks(plan, *blocks, in, out, iters, residual_out_dev ? iters : 0, residual_out_dev, st, final);
     }
     const PassChoice first = choose_pass(plan, iters);
     int64_t nwg_res = 0;
@@ -1804,10 +1888,11 @@ int jacobi_run(jacobi_plan *plan, void *in, void *out, int iters, int residual_e
     const int nres = residual_every > 0 ? iters / residual_every : 0;
     if (nres > 0 && !residuals_dev) return fail(JACOBI_EINVAL, "residuals_dev is NULL");
     hipStream_t st = (hipStream_t)stream;
-    if (iters > 0 && plan->blocks.ok && may_run_blocks(st)) {
+    if (iters > 0 && (plan->blocks.ok || plan->chip.ok) && may_run_blocks(st)) {
         if (int rc = prepare_run(plan)) return rc;       // may find no room for the messages
-        if (blocks_usable(plan, iters, residual_every, resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0)))
-            return run_blocks(plan, in, out, iters, residual_every, residuals_dev, st, final);
+        const ResidentChoice row = resident_choice(plan, residual_every > 0 ? std::min(iters, residual_every) : iters, nres > 0);
+        if (const BlockPlan *const b = choose_blocks(plan, iters, residual_every, row))
+            return run_blocks(plan, *b, in, out, iters, residual_every, residuals_dev, st, final);
     }
     void *cur = in, *other = out;
     int done = 0, pending = -1;      // pending: index of a residual still owed for the grid in `cur`
@@ -1929,18 +2014,21 @@ int jacobi_get_option(const jacobi_plan *plan, const char *key, int64_t *value)
     if (!strcmp(key, "lds_request_2")) { *value = lds_to_limit_workgroups(plan, 2); return JACOBI_OK; }
     if (!strcmp(key, "num_cu")) { *value = plan->num_cu; return JACOBI_OK; }
     // how the plan is cut into the blocks of one launch (all 0: it is not)
-    const BlockPlan &b = plan->blocks;
-    const bool ghosts = b.ok && !b.chip, chip = b.ok && b.chip;
-    if (!strcmp(key, "block_workgroups")) { *value = ghosts ? b.workgroups : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_cells_per_lane")) { *value = ghosts ? b.cells_per_lane : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_rows_per_wave")) { *value = ghosts ? b.rows_per_wave : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_planes_per_wave")) { *value = ghosts ? b.planes_per_wave : 0; return JACOBI_OK; }
-    if (!strcmp(key, "block_depth")) { *value = ghosts ? b.depth() : 0; return JACOBI_OK; }
-    if (!strcmp(key, "chip_workgroups")) { *value = chip ? b.workgroups : 0; return JACOBI_OK; }
-    if (!strcmp(key, "chip_cells_per_lane")) { *value = chip ? b.cells_per_lane : 0; return JACOBI_OK; }
-    if (!strcmp(key, "chip_rows_per_wave")) { *value = chip ? b.rows_per_wave : 0; return JACOBI_OK; }
-    if (!strcmp(key, "chip_rows_in_registers")) { *value = chip ? b.rows_in_registers : 0; return JACOBI_OK; }
-    if (!strcmp(key, "chip_even")) { *value = chip && !b.ragged ? 1 : 0; return JACOBI_OK; }
+    for (const char *prefix : {"block_", "chip_"}) {
+        const size_t n = strlen(prefix);
+        if (strncmp(key, prefix, n)) continue;
+        const BlockPlan &b = prefix[0] == 'b' ? plan->blocks : plan->chip;
+        const char *what = key + n;
+        if (!strcmp(what, "workgroups")) { *value = b.ok ? b.workgroups : 0; return JACOBI_OK; }
+        if (!strcmp(what, "cells_per_lane")) { *value = b.ok ? b.cells_per_lane : 0; return JACOBI_OK; }
+        if (!strcmp(what, "rows_per_wave")) { *value = b.ok ? b.rows_per_wave : 0; return JACOBI_OK; }
+        if (!strcmp(what, "planes_per_wave")) { *value = b.ok ? b.planes_per_wave : 0; return JACOBI_OK; }
+        if (prefix[0] == 'b' && !strcmp(what, "depth")) { *value = b.ok ? b.depth() : 0; return JACOBI_OK; }
+        if (prefix[0] == 'c' && !strcmp(what, "rows_in_registers")) { *value = b.ok ? b.rows_in_registers : 0; return JACOBI_OK; }
+        if (prefix[0] == 'c' && !strcmp(what, "waves_per_row")) { *value = b.ok ? b.waves_per_row : 0; return JACOBI_OK; }
+        if (prefix[0] == 'c' && !strcmp(what, "even")) { *value = b.ok && !b.ragged ? 1 : 0; return JACOBI_OK; }
+        return fail(JACOBI_EINVAL, "unknown option");
+    }
     // what the single-step launches will run with under the current options: "update_..." for the update,
     // "residual_..." for the stand-alone residual pass (the strip-per-wavefront kernel)
     for (const char *prefix : {"update_", "residual_"}) {

@@ -156,9 +156,9 @@ struct BlockRun {
 // the n cells; a block owns what lies d behind the start of its range up to d behind the start of the next one.
 struct BlockCut {
     int n, held, nb, d, unit, step, longer;        // steps between starts in units: the first `longer` ones step + 1
-    __host__ __device__ __forceinline__ int start(int b) const { return (b * step + (b < longer ? b : longer)) * unit; }
-    __host__ __device__ __forceinline__ int own_lo(int b) const { return b == 0 ? 0 : start(b) + d; }
-    __host__ __device__ __forceinline__ int own_hi(int b) const { return b == nb - 1 ? n : start(b + 1) + d; }
+    __host__ __device__ int start(int b) const { return (b * step + (b < longer ? b : longer)) * unit; }
+    __host__ __device__ int own_lo(int b) const { return b == 0 ? 0 : start(b) + d; }
+    __host__ __device__ int own_hi(int b) const { return b == nb - 1 ? n : start(b + 1) + d; }
 };
 
 struct Blocks2d {
@@ -228,6 +228,40 @@ struct Blocks3d {
     X(2, 6, 3, (0, 0, 0, 0, 0), (1.71, 4.22, 2.29, 4.02, 36))                                                                \
     X(4, 4, 2, (0, 0, 0, 0, 0), (2.11, 1.64, 2.44, 3.14, 19))                                                                \
     X(4, 5, 2, (0, 0, 0, 0, 0), (2.18, 4.02, 2.96, 3.99, 26))
+// 3-D grids that fill the chip without ghost cells (chip3d_kernel.h): n cells in nb parts, which differ by one cell at most
+struct EvenCut {
+    int n, nb;
+    __host__ __device__ __forceinline__ int start(int b) const { return (int)((long long)b * n / nb); }
+};
+// bytes of a wavefront's message of n cells per lane (ByteTagged): 8-byte words, seven bytes of each payload
+__host__ __device__ constexpr unsigned byte_tagged_bytes(int n, int esize)
+{
+    const int items = (n * esize + 7) / 8, words = items + (items + 6) / 7;
+    return ((unsigned)words * WAVE * 8u + 255u) / 256u * 256u;
+}
+struct Chip3d {
+    EvenCut z, y;
+    int nx;
+    int strip;
+    BlockRun run;
+};
+// Compiled variants: cells per lane, planes and rows a wavefront keeps, wavefronts a row lies in.
+#define JK_CHIP3D_VARIANTS(X)                                                                                                \
+    X(1, 2, 2, 1) X(1, 3, 3, 1) X(1, 4, 4, 1) X(1, 6, 6, 1) X(1, 3, 3, 2) X(1, 4, 3, 2) X(1, 4, 4, 2) X(1, 5, 5, 2)          \
+    X(1, 6, 6, 2) X(2, 4, 4, 2) X(2, 5, 4, 2) X(2, 5, 5, 2)
+#define JK_CHIP3D_VARIANTS_F32(X) X(2, 6, 6, 2) X(2, 7, 6, 2) X(2, 8, 7, 2) X(4, 4, 4, 2) X(4, 5, 5, 2)
+struct Chip3dLaunch {
+    hipStream_t st;
+    Geo g;
+    Chip3d p;
+    void *in, *out;
+};
+hipError_t launch_chip3d_c1_f64(int rz, int ry, int nxw, const Chip3dLaunch &a);
+hipError_t launch_chip3d_c1_f32(int rz, int ry, int nxw, const Chip3dLaunch &a);
+hipError_t launch_chip3d_c2_f64(int rz, int ry, int nxw, const Chip3dLaunch &a);
+hipError_t launch_chip3d_c2_f32(int rz, int ry, int nxw, const Chip3dLaunch &a);
+hipError_t launch_chip3d_c4_f32(int rz, int ry, int nxw, const Chip3dLaunch &a);
+
 struct Blocks3dLaunch {
     hipStream_t st;
     Geo g;
