@@ -181,7 +181,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     __syncthreads();
     if (__builtin_expect(flag != ALL_PRESENT, 0)) {
         if (flag >= 0) plain_path<T, 2>(g, br, ga, gb, red, &flag);
-        block_epilogue(br, epoch, max_exchanges, red, &flag);
+        block_epilogue(br, epoch, max_exchanges, red, &flag, CHIP2D_AREAS);
         return;
     }
 
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     constexpr unsigned FRAME = (2u * HH + 2u * HW) * MB, E_PART = HH * MB, N_PART = 2u * HH * MB, S_PART = N_PART + HW * MB;
     bool healthy = true;
     auto area = [&](int exchange) JK_INLINE {
-        return buffer_of((char *)br.msg + (size_t)(exchange & 3) * br.msg_bytes, br.msg_bytes);
+        return buffer_of((char *)br.msg + (size_t)(exchange & (CHIP2D_AREAS - 1)) * br.msg_bytes, br.msg_bytes);
     };
     auto send = [&](int exchange, auto slot0) JK_INLINE {
         constexpr int S = decltype(slot0)::value;
@@ -501,7 +501,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    block_epilogue(br, epoch, max_exchanges, red, &flag);
+    block_epilogue(br, epoch, max_exchanges, red, &flag, CHIP2D_AREAS);
 }
 
 }  // namespace jk

@@ -774,7 +774,7 @@ BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
         best.x = x; best.y = y;
         best.workgroups = x.nb * y.nb;
         best.strip = 0;
-        best.areas = 4;
+        best.areas = jk::CHIP2D_AREAS;
         best.msg_bytes = round_up((int64_t)best.workgroups * 2 * (HH + HW) * 2 * esize, 256);
     }
     // not for grids that the other paths run as fast
@@ -1057,7 +1057,6 @@ int launch_blocks(jacobi_plan *p, const BlockPlan &b, void *in, void *out, int i
     run.sync = (jk::BlockSync *)p->block_scratch;
     run.partial = (double *)(p->block_scratch + BLOCK_SYNC_BYTES);
     run.msg = p->block_scratch + BLOCK_SYNC_BYTES + block_sums_bytes(p) + (b.chip ? message_bytes(p->blocks) : 0);
-    run.areas = b.areas;
     run.msg_bytes = (unsigned)b.msg_bytes;
     run.result = result;
     const int c = b.cells_per_lane, rw = b.rows_per_wave;

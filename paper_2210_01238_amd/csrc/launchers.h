@@ -146,7 +146,6 @@ struct BlockRun {
     unsigned epoch_limit;  // an epoch beyond it has the messages cleared and starts at 0 again
     BlockSync *sync;
     void *msg;             // the message areas
-    int areas;
     unsigned msg_bytes;    // of one of them
     double *partial;       // one sum per norm and workgroup
     double *result;        // the norms
@@ -192,6 +191,7 @@ struct Chip2d {
     int strip;
     BlockRun run;
 };
+constexpr int CHIP2D_AREAS = 4;                // message areas that take turns
 constexpr int CHIP2D_LANE_BYTES = 32;          // of a row in a lane: 4 fp64, 8 fp32 cells
 // Compiled variants: rows per wavefront in registers, in LDS above those, in LDS below; each for cuts that are even - the blocks' widths
 // whole lanes, their heights not overlapping - and for the others.  Even fp64 cuts of 8 rows: blocks2d_kernel takes those grids.
