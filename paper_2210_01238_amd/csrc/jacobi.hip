@@ -434,12 +434,13 @@ StripParams tp_strips(const jacobi_plan *p, int depth)
     return sp;
 }
 
-int launch_tp(jacobi_plan *p, int depth, const void *src, void *dst, bool with_residual, hipStream_t st)
+// levels: iterations of the pass, and one more where `mode` has it form the norm of its result
+int launch_tp(jacobi_plan *p, int levels, const void *src, void *dst, int mode, hipStream_t st)
 {
-    const StripParams sp = tp_strips(p, depth);
+    const StripParams sp = tp_strips(p, levels);
     const int64_t nwg = ceil_div(sp.nstrips, jk::WAVES_PER_WG);
     if (nwg <= 0 || nwg > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many workgroups for one launch");
-    jk::LaunchArgs a{(unsigned)nwg, st, p->geo, sp, src, dst, with_residual ? p->partial : nullptr};
+    jk::LaunchArgs a{(unsigned)nwg, st, p->geo, sp, src, dst, mode != jk::MODE_UPDATE ? p->partial : nullptr};
     // On a grid much larger than the caches a blocked pass streams best with at most 2 workgroups on a CU
     // (more wavefronts marching through memory at once slow the memory system down: 16384^2 at depth 4 takes
     // 0.86 ms per pass with the 5 that fit, 0.83 with 3, 0.80 with 2, 0.85 with 1), so half of the CU's LDS,
@@ -449,8 +450,10 @@ int launch_tp(jacobi_plan *p, int depth, const void *src, void *dst, bool with_r
     a.lds = p->lay.grid_bytes >= LARGE_GRID_BYTES ? lds_to_limit_workgroups(p, 2) : 0;
     a.per_cu = 2;
     a.limit_failed = &p->lds_limit_failed;
-    const int mode = with_residual ? jk::MODE_BOTH : jk::MODE_UPDATE;
-    return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_tp_f64(depth, mode, a) : jk::launch_tp_f32(depth, mode, a),
+    const bool f64 = p->lay.dtype == JACOBI_F64;
+    const bool after = mode == jk::MODE_AFTER || mode == jk::MODE_BOTH_AFTER;
+    return launch_checked(after ? (f64 ? jk::launch_tp_after_f64(levels, mode, a) : jk::launch_tp_after_f32(levels, mode, a))
+                                : (f64 ? jk::launch_tp_f64(levels, mode, a) : jk::launch_tp_f32(levels, mode, a)),
                           "pipelined blocked-pass kernel launch");
 }
 
@@ -1603,6 +1606,21 @@ static int prepare_run(jacobi_plan *plan)
     return JACOBI_OK;
 }
 
+// Whether the last pass of a run delivers the norm of its result itself, by one more level of its pipeline that stores nothing,
+// instead of a stand-alone pass over the new grid: up to 8 levels, which one more of them hardly slows (3, 4 and 6 iterations and
+// their norm on 4096^2 fp64 in 59, 66, 76 us instead of 84, 88, 94; 1024^2 16.5, 19, 25 / 21, 21, 25), and, where the grid is no
+// longer in the last-level cache and the stand-alone pass dear, up to 12.  On smaller grids the ninth level's additional ghost
+// lanes and registers cost more than that pass (8 iterations: 4096^2 fp32 84 us against 71, 5000^2 109 against 91; 8192^2, 256 MiB,
+// 172 against 192; fp64 16384^2 927 against 1193, 10 there 1025 against 1289; 11 1083 against 1337).
+// with_in: it delivers its source's norm too, and both need a partial sum per workgroup.
+constexpr int64_t UNCACHED_GRID_BYTES = 240LL << 20;
+static bool norm_after(const jacobi_plan *p, const PassChoice &pc, bool with_in)
+{
+    if (pc.kernel != 2 || pc.depth >= (p->lay.grid_bytes >= UNCACHED_GRID_BYTES ? jk::TP_MAX : 8) || !tp_usable(p, pc.depth + 1)) return false;
+    const int64_t nwg = ceil_div(tp_strips(p, pc.depth + 1).nstrips, jk::WAVES_PER_WG);
+    return (with_in ? 2 : 1) * nwg + 1 <= p->partial_cap;
+}
+
 // residual_in_dev: if not null, also the residual norm of `in`; residual_out_dev: if not null, also that of the
 // grid the iterations produce.
 static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipStream_t st, void **final,
@@ -1668,11 +1686,14 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     }
     void *src = in, *dst = out;
     int k = 0;
+    bool norm_done = false;
     bool halos_current = carry && carry->halos_current;     // inter-tile halos of src hold src's own edge cells
     bool x_packed = carry && carry->x_packed;   // src's x send arrays hold its first / last columns (the last pass packed them)
     while (k < iters) {
         const PassChoice pc = choose_pass(plan, iters - k);
         const bool with_res = k == 0 && residual_in_dev;
+        const bool after = residual_out_dev && k + pc.depth >= iters && norm_after(plan, pc, with_res);
+        const int64_t nwg_after = after ? ceil_div(tp_strips(plan, pc.depth + 1).nstrips, jk::WAVES_PER_WG) : 0;
         // A single-step update needs the cells beyond each tile (blocked passes fetch theirs themselves).  With the
         // fused push they are in src's halo cells from the second update of a run on; the first one PULLS them
         // from the neighbouring tiles' edges instead of waiting for an exchange kernel.  With fused = 0 the exchange
@@ -1686,7 +1707,8 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
         if (timed) HIP_TRY(hipEventRecord(plan->ev[2 * plan->ev_used], st));
         if (pc.kernel == 0)      rc = with_res ? launch_update_with_residual(plan, src, dst, st, pull) : launch_update(plan, src, dst, st, pull);
         else if (pc.kernel == 1) rc = launch_t2(plan, src, dst, with_res, st);
-        else if (pc.kernel == 2) rc = launch_tp(plan, pc.depth, src, dst, with_res, st);
+        else if (pc.kernel == 2)
+            rc = launch_tp(plan, pc.depth + after, src, dst, after ? (with_res ? jk::MODE_BOTH_AFTER : jk::MODE_AFTER) : with_res ? jk::MODE_BOTH : jk::MODE_UPDATE, st);
         else if (pc.kernel == 3) rc = launch_tp3d(plan, pc.depth, src, dst, with_res, st);
         else                     rc = launch_tc3d(plan, pc.depth, src, dst, with_res, st);
         if (rc) return rc;
@@ -1696,8 +1718,14 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
         }
         if (with_res) {
             hipLaunchKernelGGL(jk::residual_final_kernel, dim3(1), dim3(1024), 0, st, plan->partial,
-                               (long long)nwg_res, residual_in_dev);
+                               (long long)(after ? nwg_after : nwg_res), residual_in_dev);
             HIP_TRY(hipGetLastError());
+        }
+        if (after) {
+            hipLaunchKernelGGL(jk::residual_final_kernel, dim3(1), dim3(1024), 0, st, plan->partial + (with_res ? nwg_after : 0),
+                               (long long)nwg_after, residual_out_dev);
+            HIP_TRY(hipGetLastError());
+            norm_done = true;
         }
         // a single-step update with the fused push leaves dst's halos current; without it, dst's x send arrays
         halos_current = pc.depth == 1 && plan->fused;
@@ -1707,7 +1735,7 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     }
     if (carry) *carry = RunCarry{true, halos_current, x_packed};
     if (final) *final = src;
-    if (residual_out_dev) return residual_common(plan, src, residual_out_dev, st);
+    if (residual_out_dev && !norm_done) return residual_common(plan, src, residual_out_dev, st);
     return JACOBI_OK;
 }
 

@@ -252,7 +252,9 @@ __device__ __forceinline__ double wg_sum(double v, double *lds /* WAVES_PER_WG (
 
 // MODE_BOTH: update, and in the same pass the residual of the SOURCE grid (its terms need
 // exactly the values the update already holds in registers).
-enum Mode { MODE_UPDATE = 0, MODE_RESIDUAL = 1, MODE_BOTH = 2 };
+// MODE_AFTER: update, and the residual of the grid the pass PRODUCES; MODE_BOTH_AFTER: of both grids
+// (sweep2d_tp_kernel only).
+enum Mode { MODE_UPDATE = 0, MODE_RESIDUAL = 1, MODE_BOTH = 2, MODE_AFTER = 3, MODE_BOTH_AFTER = 4 };
 
 // What an update does with a tile's fresh edge cells besides storing them in place.  PUSH: writes them into the
 // face neighbours' halo cells of the destination grid (pack, transfer and unpack in the update's epilogue).
@@ -723,6 +725,9 @@ __global__ __launch_bounds__(WG) void sweep2d_t2_kernel(Geo g, StripParams sp,
 // Memory operations in the loop are unconditional and counted: one load per row PF rows ahead
 // and one buffer store per row (see buffer_store_stream), so the only wait of a trip is for
 // its own loads and a trip's stores stay in flight during the next one.
+// MODE_AFTER, MODE_BOTH_AFTER: level TB only forms the residual terms of level TB - 1's rows, which are what is stored: the norm
+// of the result without another pass over it (16384^2 fp64: 343 us; the additional level takes 20 - 80, 150 where the
+// source's norm is due as well).
 // Needs tw a multiple of the vector width, th >= TB, and a row of tiles smaller than 2 GiB.
 // ------------------------------------------------------------------------------------
 // Column geometry of a blocked pass of depth TB: every level loses one ghost column per side,
@@ -814,13 +819,16 @@ __global__ __launch_bounds__(WG, MINW) void sweep2d_tp_kernel(Geo g, StripParams
     constexpr int SEGW = TpGeometry<T, TB, 2>::SEGW;
     static_assert(PF >= 2 && PF % 2 == 0, "the two-row windows swap roles every step");
     static_assert(MODE != MODE_RESIDUAL, "stand-alone residual uses the single-step kernel");
-    __shared__ double red[WAVES_PER_WG];
+    // With the residual of the result the last of the TB levels only forms its terms: the pass makes STEPS iterations.
+    constexpr bool IN_NORM = MODE == MODE_BOTH || MODE == MODE_BOTH_AFTER, OUT_NORM = MODE == MODE_AFTER || MODE == MODE_BOTH_AFTER;
+    constexpr int STEPS = OUT_NORM ? TB - 1 : TB;
+    __shared__ double red[WAVES_PER_WG], red_out[WAVES_PER_WG];
 
     const int lane = threadIdx.x % WAVE;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // uniform: keeps row math scalar
     const long long lwg = xcd_logical_wg(sp.xcd_chunk);
     const long long s = lwg * WAVES_PER_WG + wave;
-    double acc = 0.0;
+    double acc = 0.0, acc_out = 0.0;
 
     if (s < sp.nstrips) {
         // strip = (row of tiles ty, row block rb, column segment seg); the segments run across the
@@ -888,11 +896,12 @@ __global__ __launch_bounds__(WG, MINW) void sweep2d_tp_kernel(Geo g, StripParams
                     const int q = b * PF + u;
                     const int rho = r0 - TB + q;             // row of u(t) entering the pipeline
                     const int p = u & 1;                     // slot holding the OLDER row of every level
-                    V down = cur[u];
+                    V down = cur[u], result = V(0);
 #pragma unroll
                     for (int l = 1; l <= TB; ++l) {
                         const V up = w[l - 1][p], c = w[l - 1][1 - p];
                         const int row = rho - l;             // the row this level produces
+                        if constexpr (OUT_NORM) if (l == TB) result = down;
                         // Dirichlet cells keep their value: whole rows (wave-uniform) and the one component of
                         // a ring lane that is the ring column.  Selects, not branches: with branches the
                         // compiler copied the whole vector around at every level (9 moves per level and row).
@@ -906,29 +915,37 @@ __global__ __launch_bounds__(WG, MINW) void sweep2d_tp_kernel(Geo g, StripParams
                             const T sn = up[j] + down[j];
                             const bool frozen = frozen_all || (j == NV - 1 && kind == 1) || (j == 0 && kind == 2);
                             nw[j] = FREEZE && frozen ? c[j] : Coef<T>::quarter * (we + sn);
-                            if constexpr (MODE == MODE_BOTH) {
+                            if constexpr (IN_NORM) {
                                 if (l == 1 && row >= r0 && row <= r1 && owner) {
                                     const T res = (we + sn) - Coef<T>::four * c[j];
                                     const double rd = (double)res;
                                     acc += rd * rd;
                                 }
                             }
+                            if constexpr (OUT_NORM) {
+                                if (l == TB && row >= r0 && row <= r1 && owner) {
+                                    const T res = (we + sn) - Coef<T>::four * c[j];
+                                    const double rd = (double)res;
+                                    acc_out += rd * rd;
+                                }
+                            }
                         }
                         w[l - 1][p] = down;                  // the older row is dead: its slot takes the newest
                         down = nw;
                     }
-                    const int orow = rho - TB;               // `down` is now u(t+TB) of this row
-                    const bool stores = q >= 2 * TB && orow <= r1;
+                    if constexpr (!OUT_NORM) result = down;
+                    const int orow = rho - STEPS;            // `result` is now u(t+STEPS) of this row
+                    const bool stores = q >= TB + STEPS && orow <= r1;
                     const unsigned row_bytes = (unsigned)orow * (unsigned)(g.pitch * (int)sizeof(T));
                     if constexpr (decltype(storing)::value)
-                        buffer_store_stream(down, out_rows, stores && owner ? lane_bytes + row_bytes : BUF_SKIP);
+                        buffer_store_stream(result, out_rows, stores && owner ? lane_bytes + row_bytes : BUF_SKIP);
                 }
 #pragma unroll
                 for (int u = 0; u < PF; ++u) cur[u] = nxt[u];
             };
             // the run-in blocks (rows that only fill the pipeline) issue no stores at all; every later block
             // issues exactly PF, so that they can be counted
-            const int run_in = min(2 * TB / PF, nblocks);
+            const int run_in = min((TB + STEPS) / PF, nblocks);
             for (int b = 0; b < run_in; ++b) block(b, std::false_type{});
             for (int b = run_in; b < nblocks; ++b) block(b, std::true_type{});
         };
@@ -936,9 +953,13 @@ __global__ __launch_bounds__(WG, MINW) void sweep2d_tp_kernel(Geo g, StripParams
         if (reaches_ring) run_strip(std::true_type{});
         else run_strip(std::false_type{});
     }
-    if constexpr (MODE == MODE_BOTH) {
+    if constexpr (IN_NORM) {
         const double tot = wg_sum(acc, red);
         if (threadIdx.x == 0) partial[lwg] = tot;
+    }
+    if constexpr (OUT_NORM) {
+        const double tot = wg_sum(acc_out, red_out);
+        if (threadIdx.x == 0) partial[(IN_NORM ? (long long)gridDim.x : 0) + lwg] = tot;      // behind the others
     }
 }
 

@@ -1,10 +1,11 @@
 // Dispatch over the depths of the pipelined temporal-blocking kernel (sweep2d_tp_kernel) for
-// one element type.  Included by launch_tp_f64.hip and launch_tp_f32.hip.
+// one element type.  Included by launch_tp_{f64,f32}.hip and launch_tp_after_{f64,f32}.hip.
 #include "launchers.h"
 
 namespace jk {
 
-template <typename T>
+// OUT_NORM: the variants that also deliver the norm of their result, `depth` counting the level that forms it
+template <typename T, bool OUT_NORM>
 static hipError_t tp_dispatch(int depth, int mode, const LaunchArgs &a)
 {
     const dim3 grid(a.nwg), block(WG);
@@ -26,7 +27,10 @@ static hipError_t tp_dispatch(int depth, int mode, const LaunchArgs &a)
     } while (0)
 #define JK_D(MODE_)                         \
     switch (depth) {                        \
-    case 3: JK_L(MODE_, 3); break;          \
+    case 3:                                 \
+        if constexpr (OUT_NORM) return hipErrorInvalidValue;    /* two iterations: sweep2d_t2_kernel */ \
+        else JK_L(MODE_, 3);                \
+        break;                              \
     case 4: JK_L(MODE_, 4); break;          \
     case 5: JK_L(MODE_, 5); break;          \
     case 6: JK_L(MODE_, 6); break;          \
@@ -38,9 +42,15 @@ static hipError_t tp_dispatch(int depth, int mode, const LaunchArgs &a)
     case 12: JK_L(MODE_, 12); break;        \
     default: return hipErrorInvalidValue;   \
     }
-    if (mode == MODE_UPDATE) { JK_D(MODE_UPDATE) }
-    else if (mode == MODE_BOTH) { JK_D(MODE_BOTH) }
-    else return hipErrorInvalidValue;
+    if constexpr (OUT_NORM) {
+        if (mode == MODE_AFTER) { JK_D(MODE_AFTER) }
+        else if (mode == MODE_BOTH_AFTER) { JK_D(MODE_BOTH_AFTER) }
+        else return hipErrorInvalidValue;
+    } else {
+        if (mode == MODE_UPDATE) { JK_D(MODE_UPDATE) }
+        else if (mode == MODE_BOTH) { JK_D(MODE_BOTH) }
+        else return hipErrorInvalidValue;
+    }
 #undef JK_D
 #undef JK_L
 #undef JK_MINW

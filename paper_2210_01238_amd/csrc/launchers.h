@@ -83,6 +83,9 @@ hipError_t launch_t2(bool f64, int mode, const LaunchArgs &a);
 constexpr int TP_MIN = 3, TP_MAX = 12;
 hipError_t launch_tp_f64(int depth, int mode, const LaunchArgs &a);
 hipError_t launch_tp_f32(int depth, int mode, const LaunchArgs &a);
+// levels - 1 iterations and the norm of their result (MODE_AFTER, MODE_BOTH_AFTER); levels in TP_MIN+1..TP_MAX
+hipError_t launch_tp_after_f64(int levels, int mode, const LaunchArgs &a);
+hipError_t launch_tp_after_f32(int levels, int mode, const LaunchArgs &a);
 
 // 3-D: passes of depth 2 (2 or 4 rows per wavefront) or 3 (2 rows), pipelined along z
 constexpr int TP3D_MIN = 2, TP3D_MAX = 3;
