@@ -558,17 +558,18 @@ StripParams tc3d_strips(const jacobi_plan *p, int depth, int *nyg_out)
     return sp;
 }
 
-int launch_tc3d(jacobi_plan *p, int depth, const void *src, void *dst, bool with_residual, hipStream_t st)
+// levels: as for launch_tp
+int launch_tc3d(jacobi_plan *p, int levels, const void *src, void *dst, int mode, hipStream_t st)
 {
     int nyg = 0;
-    const StripParams sp = tc3d_strips(p, depth, &nyg);
+    const StripParams sp = tc3d_strips(p, levels, &nyg);
     const int64_t nwg = sp.nstrips / jk::WAVES_PER_WG;      // exactly one workgroup per unit: all of them have work
     if (nwg <= 0 || nwg > 0x7fffffffLL) return fail(JACOBI_EINVAL, "too many workgroups for one launch");
-    jk::LaunchArgs a{(unsigned)nwg, st, p->geo, sp, src, dst, with_residual ? p->partial : nullptr};
+    jk::LaunchArgs a{(unsigned)nwg, st, p->geo, sp, src, dst, mode != jk::MODE_UPDATE ? p->partial : nullptr};
     a.aux = nyg;
-    const int mode = with_residual ? jk::MODE_BOTH : jk::MODE_UPDATE;
-    return launch_checked(p->lay.dtype == JACOBI_F64 ? jk::launch_tc3d_f64(depth, mode, a)
-                                                     : jk::launch_tc3d_f32(depth, mode, a),
+    return launch_checked(mode == jk::MODE_AFTER ? jk::launch_tc3d_after_f64(a)
+                          : p->lay.dtype == JACOBI_F64 ? jk::launch_tc3d_f64(levels, mode, a)
+                                                       : jk::launch_tc3d_f32(levels, mode, a),
                           "3-D cooperative blocked-pass kernel launch");
 }
 
@@ -1607,18 +1608,29 @@ static int prepare_run(jacobi_plan *plan)
 }
 
 // Whether the last pass of a run delivers the norm of its result itself, by one more level of its pipeline that stores nothing,
-// instead of a stand-alone pass over the new grid: up to 8 levels, which one more of them hardly slows (3, 4 and 6 iterations and
-// their norm on 4096^2 fp64 in 59, 66, 76 us instead of 84, 88, 94; 1024^2 16.5, 19, 25 / 21, 21, 25), and, where the grid is no
-// longer in the last-level cache and the stand-alone pass dear, up to 12.  On smaller grids the ninth level's additional ghost
-// lanes and registers cost more than that pass (8 iterations: 4096^2 fp32 84 us against 71, 5000^2 109 against 91; 8192^2, 256 MiB,
-// 172 against 192; fp64 16384^2 927 against 1193, 10 there 1025 against 1289; 11 1083 against 1337).
+// instead of a stand-alone pass over the new grid.  The workgroups of such a launch, 0 if it does not.
 // with_in: it delivers its source's norm too, and both need a partial sum per workgroup.
+// 2-D: up to 8 levels, which one more of them hardly slows (3, 4 and 6 iterations and their norm on 4096^2 fp64 in 59, 66, 76 us
+// instead of 84, 88, 94; 1024^2 16.5, 19, 25 / 21, 21, 25), and, where the grid is no longer in the last-level cache and the
+// stand-alone pass dear, up to 12.  On smaller grids the ninth level's additional ghost lanes and registers cost more than that
+// pass (8 iterations: 4096^2 fp32 84 us against 71, 5000^2 109 against 91; 8192^2, 256 MiB, 172 against 192; fp64 16384^2 927
+// against 1193, 10 there 1025 against 1289; 11 1083 against 1337).
+// 3-D: fp64 passes of 3 iterations with a fourth level (3 iterations and their norm: 200^3 63 us instead of 71, 256^3 100 / 124, 512^3 620 /
+// 740, 768 x 1024 x 1024 3017 / 3953; 128^3, 16 MB, 51.0 / 50.7).  With their source's norm as well they lose (256^3 two such blocks
+// 235 us instead of 209, 512^3 1374 / 1315); a fifth level does not fit the registers, and fp32 passes stop at 3 levels.
 constexpr int64_t UNCACHED_GRID_BYTES = 240LL << 20;
-static bool norm_after(const jacobi_plan *p, const PassChoice &pc, bool with_in)
+static int64_t norm_after(const jacobi_plan *p, const PassChoice &pc, bool with_in)
 {
-    if (pc.kernel != 2 || pc.depth >= (p->lay.grid_bytes >= UNCACHED_GRID_BYTES ? jk::TP_MAX : 8) || !tp_usable(p, pc.depth + 1)) return false;
-    const int64_t nwg = ceil_div(tp_strips(p, pc.depth + 1).nstrips, jk::WAVES_PER_WG);
-    return (with_in ? 2 : 1) * nwg + 1 <= p->partial_cap;
+    const int levels = pc.depth + 1;
+    int64_t nwg = 0;
+    if (pc.kernel == 2) {
+        if (levels <= (p->lay.grid_bytes >= UNCACHED_GRID_BYTES ? jk::TP_MAX : 8) && tp_usable(p, levels))
+            nwg = ceil_div(tp_strips(p, levels).nstrips, jk::WAVES_PER_WG);
+    } else if (pc.kernel == 4) {
+        if (levels == jk::TC3D_MAX && p->lay.dtype == JACOBI_F64 && !with_in && tc3d_usable(p, levels) && p->lay.grid_bytes >= CACHED_CHUNK_BYTES)
+            nwg = tc3d_strips(p, levels, nullptr).nstrips / jk::WAVES_PER_WG;
+    }
+    return (with_in ? 2 : 1) * nwg + 1 <= p->partial_cap ? nwg : 0;
 }
 
 // residual_in_dev: if not null, also the residual norm of `in`; residual_out_dev: if not null, also that of the
@@ -1692,8 +1704,9 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     while (k < iters) {
         const PassChoice pc = choose_pass(plan, iters - k);
         const bool with_res = k == 0 && residual_in_dev;
-        const bool after = residual_out_dev && k + pc.depth >= iters && norm_after(plan, pc, with_res);
-        const int64_t nwg_after = after ? ceil_div(tp_strips(plan, pc.depth + 1).nstrips, jk::WAVES_PER_WG) : 0;
+        const int64_t nwg_after = residual_out_dev && k + pc.depth >= iters ? norm_after(plan, pc, with_res) : 0;
+        const bool after = nwg_after > 0;
+        const int mode = after ? (with_res ? jk::MODE_BOTH_AFTER : jk::MODE_AFTER) : with_res ? jk::MODE_BOTH : jk::MODE_UPDATE;
         // A single-step update needs the cells beyond each tile (blocked passes fetch theirs themselves).  With the
         // fused push they are in src's halo cells from the second update of a run on; the first one PULLS them
         // from the neighbouring tiles' edges instead of waiting for an exchange kernel.  With fused = 0 the exchange
@@ -1707,10 +1720,9 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
         if (timed) HIP_TRY(hipEventRecord(plan->ev[2 * plan->ev_used], st));
         if (pc.kernel == 0)      rc = with_res ? launch_update_with_residual(plan, src, dst, st, pull) : launch_update(plan, src, dst, st, pull);
         else if (pc.kernel == 1) rc = launch_t2(plan, src, dst, with_res, st);
-        else if (pc.kernel == 2)
-            rc = launch_tp(plan, pc.depth + after, src, dst, after ? (with_res ? jk::MODE_BOTH_AFTER : jk::MODE_AFTER) : with_res ? jk::MODE_BOTH : jk::MODE_UPDATE, st);
+        else if (pc.kernel == 2) rc = launch_tp(plan, pc.depth + after, src, dst, mode, st);
         else if (pc.kernel == 3) rc = launch_tp3d(plan, pc.depth, src, dst, with_res, st);
-        else                     rc = launch_tc3d(plan, pc.depth, src, dst, with_res, st);
+        else                     rc = launch_tc3d(plan, pc.depth + after, src, dst, mode, st);
         if (rc) return rc;
         if (timed) {
             HIP_TRY(hipEventRecord(plan->ev[2 * plan->ev_used + 1], st));

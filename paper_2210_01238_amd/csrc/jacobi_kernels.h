@@ -253,7 +253,7 @@ __device__ __forceinline__ double wg_sum(double v, double *lds /* WAVES_PER_WG (
 // MODE_BOTH: update, and in the same pass the residual of the SOURCE grid (its terms need
 // exactly the values the update already holds in registers).
 // MODE_AFTER: update, and the residual of the grid the pass PRODUCES; MODE_BOTH_AFTER: of both grids
-// (sweep2d_tp_kernel only).
+// (sweep2d_tp_kernel; MODE_AFTER: sweep3d_tc_kernel, too).
 enum Mode { MODE_UPDATE = 0, MODE_RESIDUAL = 1, MODE_BOTH = 2, MODE_AFTER = 3, MODE_BOTH_AFTER = 4 };
 
 // What an update does with a tile's fresh edge cells besides storing them in place.  PUSH: writes them into the
@@ -1415,6 +1415,10 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     constexpr int OWN = WROWS - 2 * TB;          // rows it stores
     static_assert(OWN >= 1, "ghost rows must leave something to own");
     static_assert(MODE != MODE_RESIDUAL, "stand-alone residual uses the single-step kernel");
+    static_assert(MODE != MODE_BOTH_AFTER, "slower than a pass for the second norm");
+    // as in sweep2d_tp_kernel: with the residual of the result the last level only forms its terms
+    constexpr bool IN_NORM = MODE == MODE_BOTH, OUT_NORM = MODE == MODE_AFTER;
+    constexpr int STEPS = OUT_NORM ? TB - 1 : TB;
     __shared__ V xch[2][TB][WPG][2][WAVE];   // [step parity][level][wavefront][first / last row][lane]
     __shared__ double red[WPG];
 
@@ -1511,15 +1515,16 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
 #pragma unroll
                 for (int l = 1; l <= TB; ++l)
                     ring_plane[l] = (z_lo_ring && kappa - l == 0) || (z_hi_ring && kappa - l == g.td + 1);
-                const int oplane = kappa - TB;
-                const bool store_plane = q >= 2 * TB && oplane <= k1;
+                const int oplane = kappa - STEPS;
+                const bool store_plane = q >= TB + STEPS && oplane <= k1;
                 const long long out_plane = out_layer + (long long)oplane * g.plane;
 #pragma unroll
                 for (int j = 0; j < NR; ++j) {
-                    V d = ld[j];                                 // newest plane of the level below, row j
+                    V d = ld[j], result = V(0);                  // newest plane of the level below, row j
                     ld[j] = load_row(j);                         // same row of the next plane, for the next step
 #pragma unroll
                     for (int l = 1; l <= TB; ++l) {
+                        if constexpr (OUT_NORM) if (l == TB) result = d;
                         const V zm = st[l - 1][p][j];
                         st[l - 1][p][j] = d;                     // the older plane is dead: its slot takes the newest
                         // the neighbouring wavefronts need this plane of our first and last row in the next step
@@ -1544,9 +1549,10 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
                             const T sum = (xx + yy) + zz;
                             const bool frozen = frozen_all || (e == NV - 1 && kind == 1) || (e == 0 && kind == 2);
                             nw[e] = FREEZE && frozen ? c[e] : Coef<T>::sixth * sum;
-                            if constexpr (MODE == MODE_BOTH) {
-                                const int plane = kappa - 1;
-                                if (l == 1 && plane >= k0 && plane <= k1 && own_row[j] && owner) {
+                            if constexpr (IN_NORM || OUT_NORM) {
+                                constexpr int OF = IN_NORM ? 1 : TB;
+                                const int plane = kappa - OF;
+                                if (l == OF && plane >= k0 && plane <= k1 && own_row[j] && owner) {
                                     const T res = sum - Coef<T>::six * c[e];
                                     const double rd = (double)res;
                                     acc += rd * rd;
@@ -1556,9 +1562,10 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
                         d = nw;
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    // after TB levels `d` is u(t+TB) of plane kappa-TB: one counted store per row, dropped where
+                    if constexpr (!OUT_NORM) result = d;
+                    // `result` is u(t+STEPS) of plane kappa-STEPS: one counted store per row, dropped where
                     // there is nothing to store (see buffer_store_stream)
-                    buffer_store_stream(d, buffer_of(dst + (out_plane + row_base[j]), tilerow_bytes),
+                    buffer_store_stream(result, buffer_of(dst + (out_plane + row_base[j]), tilerow_bytes),
                                         store_plane && own_row[j] && owner ? lane_bytes : BUF_SKIP);
                     // keep the rows in program order: hoisting later rows' loads and LDS reads costs registers
                     __builtin_amdgcn_sched_barrier(0);
@@ -1572,7 +1579,7 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     for (int j = 0; j < NR; ++j) reaches_ring = reaches_ring || ring_row[j];
     if (reaches_ring) run_unit(std::true_type{});
     else run_unit(std::false_type{});
-    if constexpr (MODE == MODE_BOTH) {
+    if constexpr (IN_NORM || OUT_NORM) {
         const double tot = wg_sum(acc, red);
         if (threadIdx.x == 0) partial[lwg] = tot;
     }

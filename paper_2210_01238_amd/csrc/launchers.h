@@ -99,6 +99,8 @@ constexpr int TC3D_WAVES = 8;   // wavefronts per workgroup (one workgroup per C
 constexpr int tc3d_rows_per_wave(int depth) { return depth == 2 ? 8 : depth == 3 ? 6 : 5; }
 hipError_t launch_tc3d_f64(int depth, int mode, const LaunchArgs &a);
 hipError_t launch_tc3d_f32(int depth, int mode, const LaunchArgs &a);
+// TC3D_MAX - 1 iterations and the norm of their result
+hipError_t launch_tc3d_after_f64(const LaunchArgs &a);
 
 // All iterations of a call in one launch (small 2-D grids; resident_kernel.h).  nseg 1 or 2 column segments per
 // wavefront, 1..4 rows per wavefront.  With more than one workgroup a one-wavefront kernel that zeroes the

@@ -56,3 +56,25 @@ def test_deep_last_passes(H, dims, tiles, dtype, depth):
             r.close()
     assert np.array_equal(results[0][0], results[1][0])
     np.testing.assert_allclose(results[1][1], results[0][1], rtol=1e-12 if dtype == F64 else 1e-5)
+
+
+# the three-dimensional passes of 3 iterations, taken from grids of 24 MiB on: planes, rows and columns at the ends of what a workgroup and
+# a wavefront own; the last ones with a norm of the source due from the same pass, which keeps the pass of its own
+SHAPES_3D = [((64, 65, 800), (1, 1, 1)), ((3, 1030, 1130), (1, 1, 5)), ((126, 161, 226), (9, 7, 1)), ((33, 352, 366), (11, 11, 61)), ((120, 97, 360), (24, 1, 3))]
+
+
+@pytest.mark.parametrize("dims,tiles", SHAPES_3D)
+def test_last_norm_from_the_last_3d_pass(H, oracle_mod, dims, tiles):
+    a = random_padded(dims, dtype=F64, seed=sum(dims))
+    for iters, every, tblock, strip in ((3, 3, 3, 0), (3, 3, 3, 1), (10, 10, 4, 0), (10, 10, 4, 3), (6, 3, 3, 0)):
+        ref, ref_res = oracle_mod.run(a, iters, every)
+        r = H.JacobiRun(dims, tiles, F64, tblock=tblock, resident=0)
+        try:
+            assert r.nbytes >= 24 << 20
+            r.set_option("rows_per_strip", strip)
+            r.load(a)
+            r.other().fill_(255)        # NaN
+            res = r.run(iters, every, fuse_residual=True)
+            check(r.fetch(), res, ref, ref_res)
+        finally:
+            r.close()
