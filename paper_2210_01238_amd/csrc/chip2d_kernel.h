@@ -186,7 +186,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
     }
 
     // ---- what other blocks need.  Columns, counted in this block: the one E of the block W of it, the one W of the block E of it (-1:
-    // no such block); rows of this wavefront: the one below the block above, the one above the block below.
+    // no such block; they lie in two lanes: plan_chip2d); rows of this wavefront: the one below the block above, the one above the block below.
     const int out_w = west ? -1 : start_of(p.x, bx - 1) + HW - x0, out_e = east ? -1 : start_of(p.x, bx + 1) - 1 - x0;
     const bool at_ends = (west || out_w % C == 0) && (east || out_e % C == C - 1);      // the first and the last cell of a lane
     const int lane_w = west ? -1 : out_w / C, lane_e = east ? -1 : out_e / C;

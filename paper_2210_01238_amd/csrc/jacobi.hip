@@ -664,6 +664,15 @@ constexpr int64_t BLOCK_SYNC_BYTES = 256;
 constexpr unsigned ROLL_DEFAULT_LIMIT = 1u << 11;        // polls of about a microsecond each
 constexpr unsigned EPOCH_DEFAULT_LIMIT = 0xc0000000u;    // a launch adds less than 2^30 to the epoch: no tag repeats
 
+// The starts of nb held ranges, evenly.
+void spread_starts(jk::BlockCut *c, int nb)
+{
+    const int units = (c->n - c->held) / c->unit;
+    c->nb = nb;
+    c->step = nb > 1 ? units / (nb - 1) : 0;
+    c->longer = nb > 1 ? units % (nb - 1) : 0;
+}
+
 // Cuts n cells into held ranges of `held`, starts at multiples of `unit`, `d` ghost cells; false if that cannot be done
 // with owned ranges of at least `least` cells, or takes more than `most` blocks.
 bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, jk::BlockCut *c)
@@ -672,9 +681,7 @@ bool cut_into_blocks(int64_t n, int held, int d, int unit, int least, int most, 
     const int64_t units = (n - held) / unit, nb = 1 + ceil_div(units, (held - 2 * d) / unit);
     if (nb > most) return false;
     c->n = (int)n; c->held = held; c->d = d; c->unit = unit;
-    c->nb = (int)nb;
-    c->step = nb > 1 ? (int)(units / (nb - 1)) : 0;
-    c->longer = nb > 1 ? (int)(units % (nb - 1)) : 0;
+    spread_starts(c, (int)nb);
     // The last start is always `step` units behind the one before it.  What the blocks own: between starts the step; the first
     // one d more, the last one what its held range holds behind its ghost cells.
     return nb == 1 || (c->own_hi(0) >= least && held - d >= least && (nb == 2 || c->step * unit >= least));
@@ -743,6 +750,14 @@ BlockPlan plan_blocks2d(const Geo &g, int dtype, int num_cu)
     return best;
 }
 
+// Whether a lane has both the cell that the block W of its own needs and the one that the block E of it needs.
+bool lanes_send_both_ways(const jk::BlockCut &x, int cells_per_lane)
+{
+    for (int b = 1; b + 1 < x.nb; ++b)
+        if ((x.start(b - 1) + x.held - x.start(b)) / cells_per_lane == (x.start(b + 1) - 1 - x.start(b)) / cells_per_lane) return true;
+    return false;
+}
+
 // The cut of a 2-D grid that blocks2d_kernel does not take, into blocks without ghost cells, with the least time for 100 iterations.  What
 // an iteration takes was fitted to 25 grids from 2000^2 to 5600^2 with random cells: by the rows of a wavefront, 2.2 us with 8, 2.7
 // with 16, 3.3 with 24, 4.8 with 32 (nine of them in LDS); where the cut is not even - blocks overlap, or the width is no
@@ -763,6 +778,9 @@ BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
         const int rw = v.rr + v.lt + v.lb, HH = jk::BLK_WAVES * rw;
         jk::BlockCut x, y;
         if (!cut_into_blocks(Nx, HW, 0, Nx % c ? 1 : c, 1, num_cu, &x) || !cut_into_blocks(Ny, HH, 0, 1, 1, num_cu, &y)) continue;
+        // A lane of chip2d_kernel sends one column.  Three blocks that hold hardly more than two would (513 and 516 fp64 cells, 1025 and 1032
+        // fp32) overlap by half, the middle one's lane in the middle with both columns: one block more, then.
+        if (lanes_send_both_ways(x, c)) spread_starts(&x, x.nb + 1);
         if (x.nb < 2 || (int64_t)x.nb * y.nb > num_cu) continue;
         const bool ragged = Nx % c != 0 || Ny != (int64_t)y.nb * HH;
         if (!jk::chip2d_compiled(v.rr, esize == 8, ragged)) continue;

@@ -53,6 +53,33 @@ def test_every_variant_matches_the_oracle(H, oracle_mod, variant, dims, tiles, d
         r.close()
 
 
+# Widths at which the middle one of three columns of blocks would have, in one lane, the cell that the block W of it needs and the one the
+# block E of it needs: by launches (False) where four columns are more blocks than CUs
+BOTH_WAYS = [((8160, 516), (5, 3), F64, True), ((8192, 516), (1, 1), F64, True), ((9000, 513), (9, 19), F64, True),
+             ((14000, 513), (1, 1), F64, True), ((16384, 516), (1, 129), F64, True), ((17000, 513), (17, 1), F64, False),
+             ((5250, 1032), (1, 1), F32, True), ((8160, 1032), (8, 4), F32, True), ((9000, 1032), (1, 43), F32, True),
+             ((4096, 1025), (1, 5), F32, True), ((6000, 1025), (3, 1), F32, True), ((17000, 1032), (1, 1), F32, False)]
+
+
+@pytest.mark.parametrize("dims,tiles,dtype,whole", BOTH_WAYS)
+def test_widths_just_over_two_blocks(H, oracle_mod, dims, tiles, dtype, whole):
+    a = random_padded(dims, dtype=dtype, seed=sum(dims))
+    ref, ref_res = oracle_mod.run(a, ITERS, EVERY)
+    outs = []
+    for resident in (1, 0):
+        r = H.JacobiRun(dims, tiles, dtype, resident=resident, profile=1)
+        try:
+            r.load(a)
+            r.other().fill_(255)
+            res = r.run(ITERS, EVERY, fuse_residual=True)
+            assert (H.B.jacobi_profile_read(r.plan)[1] == 1) == (bool(resident) and whole)
+            outs.append(r.fetch())
+            check(outs[-1], res, ref, ref_res)
+        finally:
+            r.close()
+    assert np.array_equal(*outs)
+
+
 PLAIN = [((2304, 2304), (8, 8), F64), ((1601, 1607), (1, 1), F32)]
 
 

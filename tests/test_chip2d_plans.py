@@ -73,6 +73,39 @@ for dims in ((4096, 4100), (8192, 8192), (20000, 200), (1024, 1024), (2048, 2048
 """)
 
 
+def test_no_lane_sends_both_ways(stub):  # noqa: F811
+    """A lane has one column to send.  Every width up to 64 blocks side by side, at heights that blocks divide: the starts of the columns are
+    spread evenly, in whole lanes (in cells where a lane's cells do not divide the width), the first steps one longer; where the fewest
+    columns would leave a lane with two, there is one column more."""
+    seen = run(stub, HEAD + """
+seen = set()
+def both(nx, HW, C, nb):
+    unit = C if nx % C == 0 else 1
+    step, longer = divmod((nx - HW) // unit, nb - 1)
+    start = [(b * step + min(b, longer)) * unit for b in range(nb)]
+    assert start[-1] + HW == nx
+    return any((start[b - 1] + HW - start[b]) // C == (start[b + 1] - 1 - start[b]) // C for b in range(1, nb - 1))
+for dtype, C in ((float64, 4), (float32, 8)):
+    HW = 64 * C
+    for nx in range(HW + 1, 64 * HW + 1):
+        nb = -(-nx // HW)
+        shared = both(nx, HW, C, nb)
+        if not shared and nx % 97:
+            continue                                      # (a sample of the others)
+        for rows in (8, 12, 16, 20, 24, 32):
+            ny = 256 // nb // 2 * 8 * rows
+            p = plan((ny, nx), (1, 1), dtype)
+            wg, held = figures(p, "workgroups", "rows_per_wave")
+            J.jacobi_destroy(p)
+            if wg:
+                seen.add((nx, C))
+                columns = wg // -(-ny // (8 * held))
+                assert columns == nb + shared and not both(nx, HW, C, columns), (nx, rows, wg)
+print(sorted(s for s in seen if both(s[0], 64 * s[1], s[1], -(-s[0] // (64 * s[1])))), len(seen))
+""")
+    assert seen.strip().startswith("[(513, 4), (516, 4), (1025, 8), (1032, 8)]"), seen
+
+
 def test_set_up_words_and_scratch(stub):  # noqa: F811
     """The plan's words are cleared by a kernel on the stream of the first launch, once; without room for the messages the plan runs by
     launches; calls of one or two iterations take the path that is faster for them."""
