@@ -129,6 +129,26 @@ def test_tags_that_come_round(H, oracle_mod, dims, tiles, dtype):
         r.close()
 
 
+@pytest.mark.parametrize("dims", [(26, 78, 58), (66, 30, 33), (38, 62, 54)])
+def test_a_launch_without_ghost_cells_leaves_the_epoch_alone(H, oracle_mod, dims):
+    """Both kinds of launch share the epoch, not the messages: one without ghost cells, however low the limit is set for it, must not have
+    those with ghost cells count through tags again that their messages still carry.  Calls of one exchange, whose words nothing has
+    overwritten when the tag would come again; other fields each time, so that one of those words would show."""
+    r = H.JacobiRun(dims, (1, 1, 1), F32, resident=1, profile=1)
+    try:
+        assert H.B.jacobi_get_option(r.plan, "block_depth") == 2
+        for k, (chip, limit, iters) in enumerate([(0, 0, 4), (1, 1, 40), (0, 0, 4), (1, 1, 40), (0, 0, 4), (0, 0, 30), (1, 1, 40), (0, 0, 30)]):
+            a = random_padded(dims, dtype=F32, seed=200 + k)
+            r.set_option("chip", chip)
+            r.set_option("resident_epoch_limit", limit)
+            r.load(a)
+            r.sweep(iters)
+            check(r.fetch(), [], oracle_mod.run(a, iters)[0], [])
+            assert H.B.jacobi_profile_read(r.plan)[1] == 1
+    finally:
+        r.close()
+
+
 @pytest.mark.parametrize("iters,every,opts", [(9, 0, {}), (10, 1, {}), (20, 3, dict(tblock=4)), (21, 21, dict(fused=0)), (300, 2, {})])
 def test_short_calls_parity_of_the_buffers_and_many_norms(H, oracle_mod, iters, every, opts):
     dims, tiles = (61, 53, 47), (1, 1, 1)
