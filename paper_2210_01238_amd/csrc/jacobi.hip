@@ -79,6 +79,7 @@ struct BlockPlan {
     int64_t msg_bytes = 0;            // of one of them
     double us_iterate = 0, us_exchange = 0;     // estimates: of an iteration, of an exchange
     double us_launch = 0;                       // of a launch besides
+    double us_norm = 0, us_odd = 0;             // chip2d_kernel: of a norm, of a stretch of an odd number of iterations besides
     int depth() const { return y.d > 0 ? y.d : 1; }         // iterations between exchanges
     double us_per_iteration(int every) const    // with as many exchanges as the stretches between norms need (next_stretch)
     {
@@ -762,7 +763,8 @@ bool lanes_send_both_ways(const jk::BlockCut &x, int cells_per_lane)
 // an iteration takes was fitted to 25 grids from 2000^2 to 5600^2 with random cells: by the rows of a wavefront, 2.2 us with 8, 2.7
 // with 16, 3.3 with 24, 4.8 with 32 (nine of them in LDS); where the cut is not even - blocks overlap, or the width is no
 // multiple of a lane's cells - 2.6, 3.8, 5.0 and 6.4 (within 8 %).  A launch takes 16 us besides and 0.36 per MB of the grid, which it
-// reads and writes once.
+// reads and writes once, a norm 1.6 and 0.23 per row of a wavefront (fp32 1.5 and 0.35).  The largest ragged fp32 variants
+// spill where a stretch ends after an odd number of iterations: 8 us, 27 with 24 rows.
 BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
 {
     struct Variant { int rr, lt, lb; };
@@ -789,6 +791,8 @@ BlockPlan plan_chip2d(const Geo &g, int dtype, int num_cu)
         best.ok = best.chip = true;
         best.us_iterate = us;
         best.us_launch = 16 + 0.36e-6 * (double)(Nx * Ny * esize);
+        best.us_norm = esize == 8 ? 1.6 + 0.23 * rw : 1.5 + 0.35 * rw;
+        best.us_odd = esize == 8 || !ragged || v.rr < 20 ? 0 : v.rr == 24 ? 27 : 8;
         best.ragged = ragged;
         best.cells_per_lane = c;
         best.rows_per_wave = rw;
@@ -993,6 +997,27 @@ PassChoice choose_pass(const jacobi_plan *p, int left)
     return {1, 0};
 }
 
+// What the launches of a call take (us, 2-D grids of some MB and more): 5, and per launch 2.7 and 0.275 per MB for an iteration, 0.28 per MB
+// and for each iteration 2.7 and 0.1 per million cells for a blocked pass, 1.6 times the latter for one of 9 and more iterations, which
+// arithmetic bounds; 4 and 0.05 per MB for a norm.  (1309 calls of 1 to 200 iterations on grids of 10 to 125 MB: within 20 %, 5 % on average.)
+double launches_us_2d(const jacobi_plan *p, int iters, int every)
+{
+    const double mb = 1e-6 * (double)(p->lay.dims[1] * p->lay.dims[2] * (int64_t)p->esize), mc = mb / (double)p->esize;
+    auto stretch = [&](int n) {
+        constexpr int ENOUGH = 240;                // iterations to look at: longer stretches repeat them
+        double us = 0;
+        const int some = std::min(n, ENOUGH);
+        for (int left = some; left > 0;) {
+            const int d = choose_pass(p, left).depth;
+            us += d == 1 ? 2.7 + 0.275 * mb : 0.28 * mb + d * (2.7 + 0.1 * mc) * (d >= 9 ? 1.6 : 1.0);
+            left -= d;
+        }
+        return some > 0 ? us * n / some : 0.0;
+    };
+    const int norms = every > 0 ? iters / every : 0;
+    return 5 + norms * (stretch(every) + 4 + 0.05 * mb) + stretch(iters - norms * every);
+}
+
 // Whether a call of so many iterations, with a norm every `every`-th, runs that way: what it saves per iteration has to pay for the
 // launch.  `row`: what the kernel for narrow
 // grids (resident2d_kernel) would do with them; it runs where its geometry was asked for by option.
@@ -1006,9 +1031,15 @@ bool blocks_usable(const jacobi_plan *p, const BlockPlan &b, int iters, int ever
         // Calls by launches take 5.5 us besides the iterations, norms 3.5 each and 5 for the last one; in a block launch 2.7 each and 1 for
         // the first with the small variants, 5.5 and 7 with the large ones.  (340 calls of 5 to 200 iterations, both ways: the
         // slower one is chosen in 19, by more than 10 % in 10; 0.9 % of the time in all.)
-        const double other = launch_us_3d(p, choose_pass(p, norms > 0 ? every : iters).depth > 1);
-        // (chip3d_kernel: norms take half of what they do by launches.)
-        if (b.chip) return iters * (other - us) > b.us_launch - 5.5;
+        const int depth = choose_pass(p, norms > 0 ? every : iters).depth;
+        const double other = launch_us_3d(p, depth > 1);
+        if (b.chip) {
+            // (chip3d_kernel: norms take half of what they do by launches.  Passes of 2 are cheaper than deeper ones: 5.7 us per iteration of 7 MB,
+            // 7.2 of 10 MB.)
+            const double mb = 1e-6 * (double)(L.dims[0] * L.dims[1] * L.dims[2] * (int64_t)p->esize);
+            const double passes = depth == 2 ? std::min(launch_us_3d(p, false), 4.5 + 0.2 * mb) + 0.5 : other;
+            return iters * (passes - us) > b.us_launch - 5.5;
+        }
         const double more = b.us_launch - 5.5 + (norms > 0 ? norms * (0.1 * b.us_launch - 3.0) + 0.3 * b.us_launch - 8.0 : 0.0);
         return us <= WORTH_3D * other && iters * (other - us) > more;
     }
@@ -1023,6 +1054,12 @@ bool blocks_usable(const jacobi_plan *p, const BlockPlan &b, int iters, int ever
         const double launches = every > 0 ? norms + (iters % every != 0) : 1;
         return launches * ((wide ? 1.9 : 3.5) + row.nphase * (wide ? 4.05 + 0.035 * row.nwg : 2.4 + 0.02 * row.nwg)) +
                    norms * (wide ? 2.6 : 2.2) + iters * (wide ? 0.76 : 0.67) > here + 1.9 * norms;
+    }
+    if (b.chip) {
+        // (1074 calls of 1 to 200 iterations that run on the chip by this, measured both ways: three would be faster by launches by more than 5 %,
+        // at most 19 %.)
+        const int odd = norms * (every & 1) + ((iters - norms * every) & 1);
+        return launches_us_2d(p, iters, every) > 1.05 * (here + norms * b.us_norm + odd * b.us_odd);
     }
     // Against launches (110 calls: never the slower one where it chooses blocks; calls with a norm every 1 or 2 iterations and
     // some with blocked passes would already pay in blocks).
@@ -1661,7 +1698,8 @@ static int sweep_common(jacobi_plan *plan, void *in, void *out, int iters, hipSt
     ResidentChoice rc_res = resident_choice(plan, iters, residual_out_dev != nullptr);
     const bool norm_in_launch = rc_res.ok && residual_out_dev;
     if (!rc_res.ok && residual_out_dev) rc_res = resident_choice(plan, iters);
-    const BlockPlan *const blocks = may_run_blocks(st) ? choose_blocks(plan, iters, 0, rc_res) : nullptr;
+    const BlockPlan *blocks = may_run_blocks(st) ? choose_blocks(plan, iters, 0, rc_res) : nullptr;
+    if (blocks && blocks->chip && carry) blocks = nullptr;         // jacobi_run has weighed that for the whole call, norms included
     if (rc_res.ok && !blocks) {
         // small 2-D grid: every iteration inside one launch, which also carries the ring over and delivers the
         // residual of its result; the residual of `in`, if asked for, from the stand-alone reduction first

@@ -106,6 +106,33 @@ print(sorted(s for s in seen if both(s[0], 64 * s[1], s[1], -(-s[0] // (64 * s[1
     assert seen.strip().startswith("[(513, 4), (516, 4), (1025, 8), (1032, 8)]"), seen
 
 
+# Calls timed both ways (us, MI355X), chip = 0 and chip = 1 forced: short ones near the line, with norms, with blocked passes
+TIMED = [
+    # dims, type, tblock, iterations, norm every, by launches, on the chip
+    ((4672, 4836), "float32", 4, 4, 3, 80.5, 127.6), ((3968, 4172), "float32", 8, 4, 3, 64.4, 83.5), ((4224, 5780), "float32", 12, 5, 3, 95.1, 110.8),
+    ((3568, 6300), "float32", 1, 4, 3, 122.4, 135.2), ((4999, 4318), "float32", 12, 9, 1, 304.5, 443.2), ((4999, 4318), "float32", 8, 3, 0, 64.0, 89.9),
+    ((4208, 5082), "float32", 8, 23, 1, 743.0, 1027.0), ((4672, 5036), "float32", 4, 7, 0, 92.7, 112.9),
+    ((5832, 3452), "float32", 4, 100, 3, 1490.3, 1812.6), ((2187, 3092), "float32", 4, 8, 0, 40.5, 49.7), ((2595, 2096), "float32", 1, 3, 2, 34.2, 37.0),
+    ((1565, 1577), "float64", 8, 6, 6, 49.1, 40.3), ((2496, 3568), "float64", 4, 5, 0, 68.8, 56.0), ((3480, 3960), "float32", 4, 11, 11, 98.4, 80.0),
+    ((4224, 5248), "float32", 8, 5, 3, 87.9, 76.6), ((4032, 4115), "float32", 12, 12, 1, 332.0, 293.5), ((5015, 3392), "float32", 1, 3, 0, 68.5, 55.5),
+    ((3072, 2392), "float64", 8, 10, 10, 82.1, 69.0), ((3004, 2112), "float64", 8, 11, 5, 96.9, 78.0), ((2816, 4008), "float64", 8, 29, 0, 234.9, 188.5),
+]
+
+
+def test_calls_take_the_faster_path(stub):  # noqa: F811
+    """(A call on the chip is one launch.)"""
+    run(stub, HEAD + f"""
+wrong = []
+for dims, dtype, tblock, iters, every, other, chip in {TIMED!r}:
+    p = plan(dims, (1, 1), float64 if dtype == "float64" else float32)
+    J.jacobi_set_option(p, "tblock", tblock)
+    if (launches(p, iters, every) == 1) != (chip < other):
+        wrong.append((dims, dtype, tblock, iters, every, other, chip))
+    J.jacobi_destroy(p)
+assert not wrong, wrong
+""")
+
+
 def test_set_up_words_and_scratch(stub):  # noqa: F811
     """The plan's words are cleared by a kernel on the stream of the first launch, once; without room for the messages the plan runs by
     launches; calls of one or two iterations take the path that is faster for them."""

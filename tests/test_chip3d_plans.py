@@ -78,6 +78,29 @@ for dims in ((256, 256, 256), (7, 7, 64), (27, 29, 119), (512, 512, 512), (300, 
 """)
 
 
+# Calls timed both ways (us, MI355X), chip = 0 (which run by launches: these grids have no cut with ghost cells) and chip = 1 forced
+TIMED = [
+    # dims, type, tblock, iterations, norm every, by launches, on the chip
+    ((158, 82, 136), "float32", 4, 4, 0, 28.3, 39.2), ((124, 138, 152), "float32", 8, 4, 0, 34.4, 42.4),
+    ((75, 156, 168), "float32", 8, 4, 4, 37.8, 43.0), ((145, 121, 176), "float32", 12, 5, 2, 49.4, 55.0), ((92, 164, 134), "float32", 4, 8, 0, 66.6, 55.6),
+    ((120, 112, 184), "float64", 12, 10, 2, 111.3, 101.9), ((181, 196, 142), "float32", 1, 7, 2, 106.3, 91.2), ((181, 219, 172), "float32", 1, 7, 2, 114.7, 95.0),
+]
+
+
+def test_calls_take_the_faster_path(stub):  # noqa: F811
+    """(A call on the chip is one launch.)"""
+    run(stub, HEAD + f"""
+wrong = []
+for dims, dtype, tblock, iters, every, other, chip in {TIMED!r}:
+    p = plan(dims, (1, 1, 1), float64 if dtype == "float64" else float32)
+    J.jacobi_set_option(p, "tblock", tblock)
+    if (len(grids(p, iters, every)) == 1) != (chip < other) or J.jacobi_get_option(p, "block_workgroups"):
+        wrong.append((dims, dtype, tblock, iters, every, other, chip, J.jacobi_get_option(p, "block_workgroups")))
+    J.jacobi_destroy(p)
+assert not wrong, wrong
+""")
+
+
 PACKING = r"""
 #include <cstdio>
 #include <cstring>
