@@ -139,8 +139,8 @@ int jacobi_prepare(jacobi_plan *plan);
  * independent of the current option values; once it has run, what it did allocate); 0 if plan is NULL. */
 size_t jacobi_scratch_bytes(const jacobi_plan *plan);
 
-/* Frees the plan and the device scratch it owns (synchronises the device first if it owns any).
- * NULL is accepted. */
+/* Frees the plan and the device scratch, streams and events it owns (synchronises the device first if it owns any).
+ * NULL is accepted.  Error: EHIP (the first of its steps that failed; the others are done all the same). */
 int jacobi_destroy(jacobi_plan *plan);
 
 /* Bytes the caller must allocate (device memory) for one grid; 0 if plan is NULL. */

@@ -1578,13 +1578,16 @@ int jacobi_destroy(jacobi_plan *plan)
     if (!plan) return JACOBI_OK;
     int rc = JACOBI_OK;
     if (plan->partial || !plan->ev.empty() || !plan->task_streams.empty() || !plan->task_events.empty()) {
-        hipError_t e = hipDeviceSynchronize();
-        if (e != hipSuccess) rc = fail_hip(e, "hipDeviceSynchronize");
-        if (plan->partial) (void)hipFree(plan->partial);
-        if (plan->block_done) (void)hipEventDestroy(plan->block_done);
-        for (hipEvent_t ev : plan->ev) (void)hipEventDestroy(ev);
-        for (hipEvent_t ev : plan->task_events) (void)hipEventDestroy(ev);
-        for (hipStream_t s : plan->task_streams) (void)hipStreamDestroy(s);
+        // the first failure is reported, the rest goes on
+        auto done = [&](hipError_t e, const char *what) {
+            if (e != hipSuccess && rc == JACOBI_OK) rc = fail_hip(e, what);
+        };
+        done(hipDeviceSynchronize(), "hipDeviceSynchronize");
+        if (plan->partial) done(hipFree(plan->partial), "hipFree");
+        if (plan->block_done) done(hipEventDestroy(plan->block_done), "hipEventDestroy");
+        for (hipEvent_t ev : plan->ev) done(hipEventDestroy(ev), "hipEventDestroy");
+        for (hipEvent_t ev : plan->task_events) done(hipEventDestroy(ev), "hipEventDestroy");
+        for (hipStream_t s : plan->task_streams) done(hipStreamDestroy(s), "hipStreamDestroy");
     }
     delete plan;
     return rc;

@@ -25,6 +25,7 @@ sys.path.insert(0, {ROOT!r})
 stub = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
 stub.stub_log.restype = ctypes.c_char_p
 stub.stub_malloc_limit.argtypes = [ctypes.c_size_t]
+stub.stub_live.restype = stub.stub_misuses.restype = ctypes.c_long
 import paper_2210_01238_amd as J
 assert "torch" not in sys.modules                    # whose own HIP calls would come to the stand-in, too
 def log():
@@ -112,4 +113,55 @@ for tiles, dtype in ((n, J.JACOBI_F64), (1000, J.JACOBI_F32)):
     assert sum(g for g, b in launches) == tiles, launches
     assert all(g * b < 1 << 32 for g, b in launches), launches
     J.jacobi_destroy(p)
+""")
+
+
+PLANS = [((96, 200), (3, 2)), ((48, 48), (48, 48)), ((512, 512), (4, 4)), ((24, 20, 36), (2, 2, 3)), ((8, 8, 8), (8, 8, 8)), ((256, 256), (1, 1)),
+         ((2304, 2304), (8, 8)), ((64, 64, 64), (2, 2, 2))]
+
+
+def test_streams_events_and_memory_live_as_long_as_their_plan(stub):
+    """Every stream, event and block of memory that a plan's calls make is destroyed exactly once, by jacobi_destroy, after it has waited for the
+    device; nothing is used before it is made or after it is gone.  Plans that run tasks over their own streams, with task sizes and numbers
+    of streams that change from call to call, in blocks with and without ghost cells, with profiling, and plans that never run."""
+    run(stub, f"""
+for dims, tiles in {PLANS!r}:
+    for dtype in (J.JACOBI_F64, J.JACOBI_F32):
+        for profile in (0, 1):
+            p = J.jacobi_create(dims, tiles, dtype)
+            J.jacobi_set_option(p, "profile", profile)
+            J.jacobi_scatter(p, 1 << 40, 1 << 20)
+            for iters, group, streams in ((7, 1, 4), (3, 1, 4), (8, 2, 3), (5, 100, 1), (6, 37, 16), (4, 1, 2)):
+                J.jacobi_sweep_tasks(p, *GRIDS(p), iters, group, streams, 1 << 40)
+            J.jacobi_run(p, *GRIDS(p), 60, 20, 1 << 16, 1 << 40)
+            J.jacobi_sweep(p, *GRIDS(p), 60)
+            if profile:
+                J.jacobi_profile_read(p)
+            log()
+            J.jacobi_destroy(p)
+            names = [c[0] for c in log()]
+            assert names[0] == "hipDeviceSynchronize" and names.count("hipFree") == 1, names[:5]
+            assert [stub.stub_live(k) for k in (0, 1, 2)] == [0, 0, 0] and stub.stub_misuses() == 0, (dims, dtype)
+    p = J.jacobi_create(dims, tiles, J.JACOBI_F64)
+    J.jacobi_prepare(p)
+    J.jacobi_destroy(p)
+    p = J.jacobi_create(dims, tiles, J.JACOBI_F64)
+    J.jacobi_destroy(p)
+    assert [stub.stub_live(k) for k in (0, 1, 2)] == [0, 0, 0] and stub.stub_misuses() == 0, dims
+""")
+
+
+def test_destroying_a_plan_reports_what_failed(stub):
+    """The rest is destroyed all the same."""
+    run(stub, """
+for call in ("hipFree", "hipEventDestroy", "hipStreamDestroy"):
+    p = J.jacobi_create((512, 512), (4, 4), J.JACOBI_F64)
+    J.jacobi_sweep_tasks(p, *GRIDS(p), 3, 3, 5)
+    stub.stub_fail(call.encode())
+    try:
+        J.jacobi_destroy(p)
+        raise SystemExit(call + " failed unnoticed")
+    except J.JacobiError as e:
+        assert e.code == J.binding.JACOBI_EHIP and call in str(e), e
+    assert [stub.stub_live(k) for k in (0, 1, 2)] == [0, 0, 0]
 """)
