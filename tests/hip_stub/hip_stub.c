@@ -1,7 +1,7 @@
 /* The part of the HIP host API that the library's host code calls, without a GPU: memory is host memory, launches do
  * nothing, and every call leaves a line in a log.  Loaded with RTLD_GLOBAL in front of the library, so that the library's
  * calls come here; tests then look at what it allocates, clears, waits for and launches.  (Registration of the device
- * code still goes to the HIP runtime, which needs no GPU for it.) */
+ * code still goes to the HIP runtime, which needs no GPU for it; the kernels' names come here.) */
 #define _GNU_SOURCE
 #include <stdarg.h>
 #include <stddef.h>
@@ -115,10 +115,25 @@ int __hipPopCallConfiguration(dim3_t *grid, dim3_t *block, size_t *lds, void **s
     *grid = pending.grid; *block = pending.block; *lds = pending.lds; *st = pending.st;
     return SUCCESS;
 }
+static struct { const void *f; const char *name; } kernels[8192];
+static int nkernels;
+void __hipRegisterFunction(void **m, const void *f, char *df, const char *name, unsigned threads, void *tid, void *bid, void *bd, void *gd, int *ws)
+{
+    (void)m; (void)df; (void)threads; (void)tid; (void)bid; (void)bd; (void)gd; (void)ws;
+    if (nkernels == sizeof kernels / sizeof *kernels) abort();
+    kernels[nkernels].f = f;
+    kernels[nkernels++].name = name;
+}
+static const char *name_of(const void *f)
+{
+    for (int i = 0; i < nkernels; ++i)
+        if (kernels[i].f == f) return kernels[i].name;
+    return "?";
+}
 int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_t lds, void *st)
 {
-    (void)f; (void)args; (void)lds;
+    (void)args; (void)lds;
     on_stream(st);
-    note("hipLaunchKernel %llu %llu %p\n", (unsigned long long)grid.x * grid.y * grid.z, (unsigned long long)block.x * block.y * block.z, st);
+    note("hipLaunchKernel %llu %llu %p %s\n", (unsigned long long)grid.x * grid.y * grid.z, (unsigned long long)block.x * block.y * block.z, st, name_of(f));
     return SUCCESS;
 }
