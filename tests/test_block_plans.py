@@ -30,6 +30,8 @@ def test_calls_of_the_block_tests_run_in_blocks(stub):  # noqa: F811
 for dims, tiles, iters, every, dtype in {text(BLOCK_CASES + [(*c[:2], 24, 2, c[2]) for c in PLAIN])}:
     p = plan(dims, tiles, dtype)
     assert variant(p)[0] and launches(p, iters, every) == 1, (dims, tiles, iters, every, dtype)
+    J.jacobi_set_option(p, "chip", 0)
+    assert launches(p, iters, every) == 1, (dims, tiles, iters, every, dtype)
     J.jacobi_destroy(p)
 """)
 
@@ -39,6 +41,7 @@ def test_every_compiled_variant_is_reached(stub):  # noqa: F811
 for want, cases in {text(VARIANTS)}.items():
     for dims, tiles, dtype in cases:
         p = plan(dims, tiles, dtype)
+        J.jacobi_set_option(p, "chip", 0)
         assert variant(p) == want and launches(p, {VARIANT_ITERS}, {VARIANT_EVERY}) == 1, (dims, tiles, dtype, variant(p), want)
         J.jacobi_destroy(p)
 """)

@@ -60,6 +60,7 @@ VARIANTS = {
     (4, 5, 2): [((45, 6, 159), (5, 2, 53), F32), ((37, 217, 256), (1, 7, 16), F32)],
 }
 VARIANT_ITERS, VARIANT_EVERY = 31, 9
+# (Option chip = 0 in the tests below: blocks with ghost cells also where a call would run in those without.)
 
 
 BLOCK_CASES = [(*c[:4], t) for c in CASES + CASES_3D for t in (c[4:] or (np.float64, np.float32))]
@@ -77,13 +78,17 @@ def test_blocks_match_the_oracle(H, oracle_mod, dims, tiles, iters, every, dtype
     assert np.array_equal(out, out0) and in_a == in_a0
     out2, res2, _ = run_whole(H, a, tiles, iters, every, resident=1)
     assert np.array_equal(out2, out) and res2 == res                # and the same bits on every run
+    if len(dims) == 3:                                              # which may have been without ghost cells: with them
+        out3, res3, in_a3 = run_whole(H, a, tiles, iters, every, resident=1, chip=0)
+        check(out3, res3, ref, ref_res)
+        assert np.array_equal(out3, out) and in_a3 == in_a
 
 
 @pytest.mark.parametrize("variant,dims,tiles,dtype", [(v, *c) for v, cases in VARIANTS.items() for c in cases])
 def test_every_variant_matches_the_oracle(H, oracle_mod, variant, dims, tiles, dtype):
     a = random_padded(dims, dtype=dtype, seed=sum(dims))
     ref, ref_res = oracle_mod.run(a, VARIANT_ITERS, VARIANT_EVERY)
-    r = H.JacobiRun(dims, tiles, dtype, resident=1, profile=1)
+    r = H.JacobiRun(dims, tiles, dtype, resident=1, chip=0, profile=1)
     try:
         got = tuple(H.B.jacobi_get_option(r.plan, "block_" + k) for k in ("cells_per_lane", "planes_per_wave", "rows_per_wave"))
         assert got == variant
@@ -106,7 +111,7 @@ def test_blocks_without_all_workgroups_take_the_plain_path(H, oracle_mod, dims, 
     iteration after the other through memory, with the same result; the next launch finds the plan's words as it needs
     them.  The norms' last bits show that it was that path: other workgroups' sums, in another order."""
     a = random_padded(dims, dtype=dtype, seed=77)
-    r = H.JacobiRun(dims, tiles, dtype, resident=1)
+    r = H.JacobiRun(dims, tiles, dtype, resident=1, chip=0)
     try:
         n = H.B.jacobi_get_option(r.plan, "block_workgroups")
         for iters, every in ((120, 2), (24, 2), (23, 0), (26, 26), (25, 6)):
@@ -132,7 +137,7 @@ def test_blocks_that_do_not_wait_for_each_other_to_start(H, oracle_mod, dims, ti
     a = random_padded(dims, dtype=dtype, seed=77)
     for iters, every in ((24, 8), (23, 0), (26, 26)):
         ref, ref_res = oracle_mod.run(a, iters, every)
-        r = H.JacobiRun(dims, tiles, dtype, resident=1, resident_spin_limit=1)
+        r = H.JacobiRun(dims, tiles, dtype, resident=1, chip=0, resident_spin_limit=1)
         try:
             for limit in (1, 1, 0, 1, 0):
                 r.set_option("resident_spin_limit", limit)
@@ -147,7 +152,7 @@ def test_blocks_that_do_not_wait_for_each_other_to_start(H, oracle_mod, dims, ti
 def test_blocks_count_exchanges_from_zero_again(H, oracle_mod, dims, tiles, dtype):
     """Every launch (resident_epoch_limit = 1) and every third one clears the messages and starts with the same tags: other fields
     each time, so that a message left over would show."""
-    r = H.JacobiRun(dims, tiles, dtype, resident=1)
+    r = H.JacobiRun(dims, tiles, dtype, resident=1, chip=0)
     try:
         for limit in (1, 130):
             r.set_option("resident_epoch_limit", limit)
