@@ -121,7 +121,7 @@ int jacobi_create(jacobi_plan **plan, int ndim, const int64_t *dims, const int64
  * it the 16 bytes of the one-launch kernel's barrier words and, for plans that option "resident" runs in
  * blocks, their messages and words (two areas of 8 bytes per fp32, 16 per fp64 cell at a block's border: in fp64
  * 6.5 MB for 256^2, 37 MB for 1024^2, at most 93 MB), set to zero here once - or, for grids that only run in blocks without
- * ghost cells (60 MB at most), by the first call -; where the device has no room for the messages, the plan does without them and runs launch by launch).
+ * ghost cells (51 MB at most), by the first call -; where the device has no room for the messages, the plan does without them and runs launch by launch).
  * This is the only device allocation the library ever makes for a plan (the paper's runtime
  * keeps such buffers in a pre-allocated device memory pool for the same reason, Sec. VI-A).
  * jacobi_scatter, jacobi_sweep, jacobi_sweep_residual, jacobi_sweep_tasks, residual_norm and
@@ -394,14 +394,16 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *                    jacobi_pass_schedule still lists the passes of the launch-per-pass path, as which the grids swap
  *                    roles.  If not all of the launch's workgroups start within about 2 milliseconds (other work holds
  *                    CUs), those that did do the work through memory: much slower - with half of the workgroups 256^2 takes
- *                    11 us per iteration, 1024^2 34, 64^3 27 to 34 -, the same result.  A wait for a
+ *                    11 us per iteration, 1024^2 34, 2304^2 163, 4096^2 424, 64^3 26 to 34, 160^3 164 (by launches 2.8, 5.3, 15, 48, 5.9
+ *                    and 14) -, the same result.  A wait for a
  *                    message is bounded as the barrier's is, with NaN for a result.  A call takes this path
  *                    if a fixed estimate of both says it is faster (3 iterations and more of 1024^2) and it is not
  *                    being recorded into a HIP graph; launches of one plan follow each other on whatever streams.
  *                    Larger 2-D grids, and those whose widths the cuts above cannot take, run the same way in blocks without ghost
  *                    cells, in registers and LDS, the borders exchanged in every iteration: as many cells as ceil(Nx / w) *
  *                    ceil(Ny / h) <= 256 blocks hold, w = 256 in fp64 and 512 in fp32, h at most 256 - 4096^2 in fp64, 4096 x 8192 or
- *                    5632^2 in fp32 - and wider than one block (4096^2: 48 -> 5.9 us per iteration in calls of 100).  So do 3-D grids of rows of 8 to
+ *                    5632^2 in fp32 - and wider than one block (4096^2: 48 -> 5.9 us per iteration in calls of 100); one column of
+ *                    blocks more at 513 and 516 cells in fp64, 1025 and 1032 in fp32.  So do 3-D grids of rows of 8 to
  *                    256 cells (fp32: 512) and of 256 rows and more (1000 where rows are longer than 64 cells) that fit the registers:
  *                    128 cells wide about 36000 rows, 256 wide 25000 (fp32: 57000) (64^3: 3.2 -> 1.5 us, 160^3: 14 -> 7.4, 210 x 198 x 250 in fp32:
  *                    17 -> 5).  Where a grid can run with and without ghost cells a fixed estimate chooses.

@@ -1,4 +1,4 @@
-// What the block kernels (blocks2d_kernel.h, blocks3d_kernel.h, chip2d_kernel.h) share: how the workgroups of a launch find out
+// What the block kernels (blocks2d_kernel.h, blocks3d_kernel.h, chip2d_kernel.h, chip3d_kernel.h) share: how the workgroups of a launch find out
 // that they are all there, the messages they pass each other, the plain path they take if they are not, and how
 // a launch ends.
 //

@@ -19,15 +19,19 @@
 //
 // What bounds it: of 4096^2's 11700 clocks per iteration (2 GHz) 9000 are the rows' update - 29 instructions per row and wavefront, 20
 // of them the arithmetic and the lane shifts, two wavefronts per SIMD -, 2000 to 2700 the messages' way (sent 350, two hops of
-// memory latency) and a barrier.  Measured, us per iteration with random cells, launches -> one launch, in long runs: fp64 2304^2
-// 14.2 -> 2.4, 2560^2 16.9 -> 2.7, 3072 x 4096 31.8 -> 3.3, 4096^2 51.4 -> 4.9, ragged 1501^2 8.0 -> 2.6, 2601^2 17.6 -> 3.8, 4001^2 40.0 -> 6.4; fp32
-// 3072^2 12.6 -> 2.5, 4096^2 20.5 -> 2.8, 5632^2 38.5 -> 4.8, ragged 5501^2 37.0 -> 6.3.  A launch takes 16 us besides and 0.36 per MB of the
-// grid.
+// memory latency) and a barrier, which follow it: nothing is updated while they travel.  Measured, us per iteration with random cells,
+// launches -> one launch, launch behind launch: fp64 2304^2 14.2 -> 2.4, 2560^2 16.9 -> 2.7, 3072 x 4096 31.8 -> 3.3, 4096^2 51.4 -> 4.7,
+// ragged 1501^2 8.0 -> 2.6, 2601^2 17.6 -> 3.8, 4001^2 40.0 -> 6.4; fp32 3072^2 12.6 -> 2.5, 4096^2 20.5 -> 2.8, 5632^2 38.5 -> 4.8, ragged 5501^2
+// 37.0 -> 6.3.  After an idle stretch 4096^2 takes 5.5 (1000 iterations and ten norms 5600 us, launch behind launch 4890).  A launch takes
+// 16 us besides and 0.36 per MB of the grid, a norm 1.6 and 0.23 per row of a wavefront (fp32 1.5 and 0.35).
 //
 // Everything here is arranged around the registers; what spilled made an iteration three to six times as long.  So: arrays are
 // indexed by constants and hold single cells (rows as vectors would need neighbouring registers), no branch stands between the rows
 // of an iteration (where only some lanes or rows have something to write, the others write to a place where nobody looks), new cells are
-// pinned where they are computed, and the loop over iterations holds nothing but two of them.
+// pinned where they are computed, and the loop over iterations holds nothing but two of them.  The largest variants do use scratch memory
+// (bytes per lane: even fp64 192 with 24 rows and 188 with 23 + 9, fp32 88; ragged fp64 28 and 64, fp32 180 with 20 rows, 436 and 220), but
+// not in that loop: what lies there is used once in a stretch, mostly by its last iteration if their number is odd, and by the norm.  Only the
+// ragged fp32 ones feel it, 8 us in such a stretch and 27 with 24 rows.
 #pragma once
 #include "blocks_common.h"
 
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip2d_kernel(Geo g, Chip2d 
 
     // ---- messages.  A block's: the column that the block W of it needs, the one E of it (a cell per held row), the row for the
     // one above, the one below (component by component).  Four areas take turns, for a row may be sent by another wavefront than the
-    // one that receives the neighbour's: when one sends exchange x + 1 its neighbours have all of x - 2 behind them.
+    // one that receives the neighbour's: when one sends exchange x + 1 its neighbours have all of x - 3, which was in that area, behind them.
     constexpr unsigned FRAME = (2u * HH + 2u * HW) * MB, E_PART = HH * MB, N_PART = 2u * HH * MB, S_PART = N_PART + HW * MB;
     bool healthy = true;
     auto area = [&](int exchange) JK_INLINE {

@@ -891,7 +891,8 @@ BlockPlan plan_blocks3d(const jacobi_plan *p, int num_cu)
 // wavefront (a fifth more per cell beyond the first of a lane, a quarter less in fp32), 0.06 per word of its messages and 0.15 per MB
 // that all of them send (50 cuts of 28 grids from 48^3 to 230 x 220 x 256, 1.3 to 7.4 us: within 20 %, 5 % on average).  A launch: 18 us
 // besides, 0.55 per MB of the grid and 0.03 per workgroup.  Grids of few rows - below 256, below 1000 where a row lies in two
-// wavefronts - keep the path they had, though they would gain, too (27 x 29 x 119: 1.6 us against 3.8): the suite fixes it.
+// wavefronts - keep the path they had.  Nothing measured stands behind that line: they would gain, too (27 x 29 x 119: 1.6 us against 3.8 by
+// launches), but test_block_plans.py holds such calls to launches, which it compares with blocks3d_kernel (4.9) only.
 BlockPlan plan_chip3d(const jacobi_plan *p, int num_cu)
 {
     struct Variant { int c, rz, ry, nxw; bool f32_only; };
@@ -1379,7 +1380,7 @@ int prepare_plan(jacobi_plan *p)
     bool blocks = p->blocks.ok || p->chip.ok;
     hipError_t e = hipMalloc((void **)&p->partial, blocks ? words_end + (size_t)block_scratch_bytes(p) : sums);
     if (e == hipErrorOutOfMemory && blocks) {
-        // the messages are an extra (up to some 90 MB): without room for them the plan runs by launches
+        // the messages are an extra (up to 93 MB): without room for them the plan runs by launches
         (void)hipGetLastError();
         blocks = false;
         e = hipMalloc((void **)&p->partial, sums);
