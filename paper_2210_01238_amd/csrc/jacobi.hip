@@ -1173,7 +1173,10 @@ int run_blocks(jacobi_plan *p, const BlockPlan &b, void *in, void *out, int iter
         }
         if (timed) HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used], st));
         const int rc = launch_blocks(p, b, cur, other, n, every, norms, norms ? result + done / every : nullptr, to_other, st);
-        if (rc) return rc;
+        if (rc) {
+            (void)hipEventRecord(p->block_done, st);       // the clearing may be under way, which the next launch has to wait for, too
+            return rc;
+        }
         if (timed) {
             HIP_TRY(hipEventRecord(p->ev[2 * p->ev_used + 1], st));
             ++p->ev_used;

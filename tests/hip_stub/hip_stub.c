@@ -101,7 +101,9 @@ int hipEventSynchronize(void *ev) { known(ev, EVENT); return SUCCESS; }
 int hipEventElapsedTime(float *ms, void *a, void *b) { known(a, EVENT); known(b, EVENT); *ms = 1.0f; return SUCCESS; }
 int hipFuncSetAttribute(const void *f, int attr, int v) { (void)f; (void)attr; (void)v; return SUCCESS; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int block, size_t lds) { (void)f; (void)block; (void)lds; *n = 1; return SUCCESS; }
-int hipGetLastError(void) { return SUCCESS; }
+static int last_error, launches_until_one_fails = -1;
+void stub_fail_launch(int n) { launches_until_one_fails = n; }       /* after n that do not */
+int hipGetLastError(void) { const int e = last_error; last_error = SUCCESS; return e; }
 const char *hipGetErrorString(int e) { return e == OUT_OF_MEMORY ? "out of memory" : "error"; }
 
 static struct { dim3_t grid, block; size_t lds; void *st; } pending;
@@ -134,6 +136,7 @@ int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_
 {
     (void)args; (void)lds;
     on_stream(st);
+    if (launches_until_one_fails >= 0 && launches_until_one_fails-- == 0) return last_error = 719;
     note("hipLaunchKernel %llu %llu %p %s\n", (unsigned long long)grid.x * grid.y * grid.z, (unsigned long long)block.x * block.y * block.z, st, name_of(f));
     return SUCCESS;
 }

@@ -160,6 +160,27 @@ J.jacobi_destroy(p)
 """)
 
 
+def test_a_launch_that_fails_leaves_its_clearing_waited_for(stub):  # noqa: F811
+    """The first launch fails, the kernel that clears the words is on its way: the next launch, on whatever stream, waits for it."""
+    run(stub, HEAD + """
+p = plan((4096, 4096), (4, 4), float64)
+J.jacobi_prepare(p)
+log()
+stub.stub_fail_launch(1)
+try:
+    J.jacobi_sweep(p, *GRIDS(p), 100, 1 << 40)
+    raise SystemExit("the launch did not fail")
+except J.JacobiError as e:
+    assert e.code == J.binding.JACOBI_EHIP
+calls = [c[0] for c in log()]
+assert calls.index("hipEventRecord") > calls.index("hipLaunchKernel") and calls.count("hipLaunchKernel") == 1, calls
+J.jacobi_sweep(p, *GRIDS(p), 100, 1 << 41)
+calls = [c[0] for c in log()]
+assert calls == ["hipStreamWaitEvent", "hipLaunchKernel", "hipEventRecord"], calls
+J.jacobi_destroy(p)
+""")
+
+
 @pytest.fixture(scope="module")
 def code(tmp_path_factory):
     """The instructions of one variant, in the order of the text."""
