@@ -366,8 +366,7 @@ __device__ __forceinline__ void plain_path(const Geo &g, const BlockRun &br, T *
 
 // The end of a workgroup: the last one adds up the norms - one sum per workgroup that did the work: all of them, or those that
 // were counted in when the roll was closed - and leaves the words as the next launch has to find them.
-// `exchanges`: how many tags the launch has used at most; `areas`: of messages.  (0: none of the epoch's.  Such a launch leaves the epoch alone: it
-// would start it again without clearing the messages of the plan's other cut, which carry its tags.)  Every thread calls it.
+// `exchanges`: how many tags the launch has used at most; `areas`: of messages.  Every thread calls it.
 __device__ __forceinline__ void block_epilogue(const BlockRun &br, unsigned epoch, unsigned exchanges, double *red, int *lds_flag, unsigned areas = 2u)
 {
     // This workgroup's sums and its failure flag - any wavefront may have raised it - went out past the caches: they only have
@@ -388,7 +387,7 @@ __device__ __forceinline__ void block_epilogue(const BlockRun &br, unsigned epoc
         __syncthreads();
     }
     unsigned next = epoch + exchanges;
-    if (exchanges != 0u && next > br.epoch_limit) {                 // by default once in some 2^31 exchanges
+    if (next > br.epoch_limit) {                 // by default once in some 2^31 exchanges
         u32x4 *m = (u32x4 *)br.msg;
         for (unsigned i = threadIdx.x; i < areas * (br.msg_bytes / 16u); i += blockDim.x) m[i] = u32x4{0u, 0u, 0u, 0u};
         next = 0;
