@@ -522,7 +522,7 @@ bool tc3d_usable(const jacobi_plan *p, int depth)
     const Geo &g = p->geo;
     const int nv = 16 / (int)p->esize;
     return p->cooperative && g.ndim == 3 && depth >= jk::TC3D_MIN && depth <= jk::TC3D_MAX && g.tw % nv == 0 &&
-           g.td >= depth && (int64_t)g.Ty * g.th < 0x7fffffffLL - 64 &&
+           g.td >= depth && (int64_t)g.Ty * g.th < 0x7fffffffLL - 64 && (int64_t)g.Tz * g.td < 0x7fffffffLL - 64 &&
            (int64_t)g.Tx * g.tile_stride * (int64_t)p->esize < 0x7fffffffLL;   // per-lane byte offsets are 32-bit
 }
 
@@ -534,25 +534,35 @@ StripParams tc3d_strips(const jacobi_plan *p, int depth, int *nyg_out)
     const int own = jk::TC3D_WAVES * jk::tc3d_rows_per_wave(depth) - 2 * depth;
     const int nyg = (int)ceil_div((int64_t)g.Ty * g.th, own);
     sp.nseg = (int)ceil_div((int64_t)g.Tx * g.tw, tp_segment_width(p, depth));
+    const int nz = (int)std::min<int64_t>((int64_t)g.Tz * g.td, 0x7fffffff);
     int R = (int)p->rows_per_strip;
     if (R <= 0) {
         // One workgroup runs per CU and all units of a launch take the same time (R + 2*depth plane
-        // steps), so the launch takes about ceil(units / CUs) rounds of that: pick the split of the tile
-        // depth that minimises rounds x steps (deep units amortise the run-in, more units fill the last round).
+        // steps), so the launch takes about ceil(units / CUs) rounds of that: split the planes of the whole column of
+        // tiles so that rounds x steps is least (deep units amortise the run-in, more units fill the last round).  Up to
+        // depth 3 memory decides, which shorter blocks suit better (the planes of the run-in have just been read
+        // by the block before): the shortest within a sixteenth of the least (768 x 1024 x 1024, depth 3: 2690 us with 9
+        // blocks, the least, 2659 with the 17 this takes, 2650 with 23; at depth 4 2817 with the 8 that are the least, 2840 with 6, 2880 with 15).
         int64_t best = -1;
-        R = g.td;
-        for (int nblk = 1; nblk <= 16 && nblk <= g.td; ++nblk) {
-            const int r = (int)ceil_div(g.td, nblk);
-            if ((int)ceil_div(g.td, r) != nblk) continue;
-            const int64_t units = (int64_t)g.Tz * nyg * sp.nseg * nblk;
-            const int64_t cost = ceil_div(units, p->num_cu) * (r + 2 * depth);
+        auto cost_of = [&](int r) { return ceil_div((int64_t)nyg * sp.nseg * ceil_div(nz, r), p->num_cu) * (r + 2 * depth); };
+        R = nz;
+        const int most = (int)std::max<int64_t>(16, ceil_div(24 * (int64_t)p->num_cu, (int64_t)nyg * sp.nseg));     // 24 rounds are plenty
+        for (int nblk = 1; nblk <= most && nblk <= nz; ++nblk) {
+            const int r = (int)ceil_div(nz, nblk);
+            const int64_t cost = cost_of(r);
             if (best < 0 || cost < best) { best = cost; R = r; }
         }
-    }
-    if (R > g.td) R = g.td;
+        if (depth <= 3)
+            for (int r = (int)ceil_div(nz, most); r < R; ++r)
+                if (cost_of(r) * 16 <= best * 17) R = r;
+    } else if (R > g.td) R = g.td;
     sp.R = R;
-    sp.nblk = (int)ceil_div(g.td, R);
-    sp.nstrips = (int64_t)g.Tz * sp.nblk * sp.nseg * nyg * jk::WAVES_PER_WG;   // partial sums: one per unit
+    sp.nblk = (int)ceil_div(nz, R);
+    sp.nstrips = (int64_t)sp.nblk * sp.nseg * nyg * jk::WAVES_PER_WG;   // partial sums: one per unit
+    // Row groups that follow each other on an XCD: four in y, then the next column segment, so that they find each other's
+    // ghost rows and lines cut by a segment in its L2 (768 x 1024 x 1024, all row groups first -> four: depth 3 2735 -> 2690 us,
+    // depth 4 2845 -> 2830; 2 or 8: 2727, 2705)
+    sp.band = std::min(nyg, 4);
     sp.fused = 0;
     sp.xcd_chunk = xcd_chunk_of(p);
     if (nyg_out) *nyg_out = nyg;

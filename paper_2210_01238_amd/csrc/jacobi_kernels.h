@@ -271,6 +271,7 @@ struct StripParams {
     int fused;           // update mode: 1 = push edge cells into the neighbours' halo cells of dst (FUSED_PUSH),
                          // 2 = pack the x edge cells into the tile's own send arrays of dst (FUSED_PACK)
     int xcd_chunk;       // G of xcd_logical_wg(): consecutive workgroups one XCD takes
+    int band = 1;         // sweep3d_tc_kernel: row groups side by side in y before the next column segment follows
     int rows_fastest = 0; // 3-D blocked passes: consecutive strips are neighbours in y (else in x)
     int tile0 = 0;        // single-step kernels: first tile this launch covers (a task = a range of tiles)
     int pull = 0;         // single-step kernels: run the variant that reads the cells beyond a tile from the neighbouring
@@ -1395,10 +1396,14 @@ __global__ __launch_bounds__(WG, MINW) void sweep3d_tp_kernel(Geo g, StripParams
 // row of every level's newest plane in LDS each step (double-buffered: one barrier per step).
 // Only the workgroup as a whole carries TB ghost rows per side, so WPG*NR rows are loaded per
 // WPG*NR - 2*TB rows stored.  Rows are counted along the whole column of tiles (a workgroup's rows
-// may lie in two tiles).  Columns, planes, ring handling and addressing as in sweep3d_tp_kernel.
+// may lie in two tiles), planes along the whole column of tiles as well, so a block of planes may begin and end anywhere.
+// Columns, ring handling and addressing as in sweep3d_tp_kernel.
+// Bound by how memory takes these accesses: 768 x 1024 x 1024 in fp64, depth 3, reads 8.7 GB (grid 6.4; ghost rows, cut lines and
+// run-in planes that miss the L2) and writes 6.4 in 2.65 ms; without any arithmetic it takes as long, without stores 1.7, with
+// all loads from the L2 1.7 (depth 4: 2.83, 2.36, 2.27 ms).  Loads fewer rows ahead, other store flavours: no faster.
 // Rows outside the shrinking range of a level are computed anyway (nothing valid reads them).
 // Every workgroup of the grid has work and all its wavefronts take the same number of steps.
-// Bit-identical to TB single steps.  Needs tw a multiple of the vector width and td >= TB.
+// Bit-identical to TB single steps.  Needs tw a multiple of the vector width.
 // ------------------------------------------------------------------------------------
 template <typename T, int MODE, int TB, int NR, int WPG, int MINW>
 __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, StripParams sp, int nyg,
@@ -1427,14 +1432,15 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     const long long lwg = xcd_logical_wg(sp.xcd_chunk);     // a work unit: the grid has exactly one workgroup each
     double acc = 0.0;
 
-    // unit = z-layer of tiles -> plane block -> column segment -> row group
-    const int per_layer = sp.nblk * sp.nseg * nyg;
-    const int tz = (int)(lwg / per_layer);
-    int rem = (int)(lwg - (long long)tz * per_layer);
-    const int kb = rem / (sp.nseg * nyg);
-    rem -= kb * sp.nseg * nyg;
-    const int seg = rem / nyg, yg = rem - seg * nyg;
-    const int k0 = 1 + kb * sp.R, k1 = min(g.td, k0 + sp.R - 1);
+    // unit = plane block -> band of row groups -> column segment -> row group of the band
+    const int kb = (int)(lwg / (sp.nseg * nyg));
+    int rem = (int)(lwg - (long long)kb * (sp.nseg * nyg));
+    const int bnd = rem / (sp.band * sp.nseg);
+    rem -= bnd * (sp.band * sp.nseg);
+    const int band_groups = min(sp.band, nyg - bnd * sp.band);
+    const int seg = rem / band_groups, yg = bnd * sp.band + (rem - seg * band_groups);
+    const int nz = g.Tz * g.td;                  // planes 1..nz along the column of tiles; 0 and nz+1: ring
+    const int k0 = 1 + kb * sp.R, k1 = min(nz, k0 + sp.R - 1);
     const int nrows = g.Ty * g.th;               // rows 1..nrows along the column of tiles; 0 and nrows+1: ring
     const int y0 = 1 + yg * OWN;                 // first row this workgroup stores
     const long long tilerow = (long long)g.Tx * g.tile_stride;
@@ -1443,7 +1449,6 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     const int kind = L.kind;
     const unsigned lane_bytes = L.bytes;
     const bool ring_lane = L.ring_lane, wave_has_ring = L.wave_has_ring, owner = L.owner;
-    const bool z_lo_ring = tz == 0, z_hi_ring = tz == g.Tz - 1;
 
     // ---- this wavefront's rows j = 0..NR-1: row y0 - TB + wave*NR + j of the column of tiles
     long long row_base[NR];      // element offset of the row inside a z-layer of tiles
@@ -1462,12 +1467,20 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
         row_base[j] = (long long)tyy * tilerow + (long long)rr * g.pitch;
         row_to_halo[j] = rr - rr * g.pitch;
     }
+    // ---- the plane being loaded, as (z-layer of tiles, plane in it); clamped onto the Dirichlet planes
+    const long long layer = g.Ty * tilerow;
+    int in_tz = 0, in_k = 0;
     long long pl_cells;
     int pl_to_halo;
-    auto locate_plane = [&](int kappa) {
-        const TpPlane P = tp_locate_plane(g, tz, z_lo_ring, z_hi_ring, g.Ty * tilerow, kappa, TB);
-        pl_cells = P.cells;
-        pl_to_halo = P.to_halo;
+    auto place_plane = [&]() {
+        pl_cells = in_tz * layer + (long long)in_k * g.plane;
+        pl_to_halo = in_k * g.rows - (int)((long long)in_k * g.plane);
+    };
+    auto next_plane = [&](int kappa) {           // kappa: the plane to load now, one beyond the last
+        if (kappa < 1 || kappa > nz + 1) return;
+        ++in_k;
+        if (in_k > g.td && in_tz < g.Tz - 1) { ++in_tz; in_k = 1; }
+        place_plane();
     };
     auto load_row = [&](int j) -> V {
         const T *rowp = src + (pl_cells + row_base[j]);
@@ -1492,7 +1505,8 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
         // The plane entering the pipeline, loaded one step ahead: as soon as a row has been taken, the load
         // of the same row of the next plane is issued in its place, so only ONE plane of loads is live.
         V ld[NR];
-        locate_plane(k0 - TB);
+        if (k0 - TB > 0) { in_tz = (k0 - TB - 1) / g.td; in_k = k0 - TB - in_tz * g.td; }
+        place_plane();
 #pragma unroll
         for (int j = 0; j < NR; ++j) ld[j] = load_row(j);
 
@@ -1500,7 +1514,7 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
 #pragma unroll
         for (int j = 0; j < NR; ++j) asm volatile("" : "+v"(ld[j]));
 
-        const long long out_layer = (long long)tz * g.Ty * tilerow;
+        int out_tz = (k0 - 1) / g.td, out_k = k0 - out_tz * g.td;        // the next plane to be stored
         const unsigned tilerow_bytes = (unsigned)(tilerow * (long long)sizeof(T));      // below 2 GiB
         const int wave_up = max(wave - 1, 0), wave_dn = min(wave + 1, WPG - 1);
 
@@ -1510,14 +1524,18 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
                 const int q = q0 + p;
                 if (q >= nsteps) break;
                 const int kappa = k0 - TB + q;                   // plane of u(t) entering the pipeline
-                locate_plane(kappa + 1);
+                next_plane(kappa + 1);
                 bool ring_plane[TB + 1];
 #pragma unroll
                 for (int l = 1; l <= TB; ++l)
-                    ring_plane[l] = (z_lo_ring && kappa - l == 0) || (z_hi_ring && kappa - l == g.td + 1);
+                    ring_plane[l] = kappa - l == 0 || kappa - l == nz + 1;
                 const int oplane = kappa - STEPS;
                 const bool store_plane = q >= TB + STEPS && oplane <= k1;
-                const long long out_plane = out_layer + (long long)oplane * g.plane;
+                const long long out_plane = out_tz * layer + (long long)out_k * g.plane;
+                if (store_plane) {
+                    ++out_k;
+                    if (out_k > g.td && out_tz < g.Tz - 1) { ++out_tz; out_k = 1; }
+                }
 #pragma unroll
                 for (int j = 0; j < NR; ++j) {
                     V d = ld[j], result = V(0);                  // newest plane of the level below, row j
@@ -1574,7 +1592,7 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
             }
         }
     };
-    bool reaches_ring = wave_has_ring || (z_lo_ring && k0 <= 2 * TB) || (z_hi_ring && k1 + 2 * TB > g.td);
+    bool reaches_ring = wave_has_ring || k0 <= 2 * TB || k1 + 2 * TB > nz;
 #pragma unroll
     for (int j = 0; j < NR; ++j) reaches_ring = reaches_ring || ring_row[j];
     if (reaches_ring) run_unit(std::true_type{});
