@@ -1424,6 +1424,9 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     // as in sweep2d_tp_kernel: with the residual of the result the last level only forms its terms
     constexpr bool IN_NORM = MODE == MODE_BOTH, OUT_NORM = MODE == MODE_AFTER;
     constexpr int STEPS = OUT_NORM ? TB - 1 : TB;
+    // Rows loaded ahead: a whole plane's, 3 where the result's norm needs their registers (all 5: some spill, 3.10 ms a pass of
+    // 768 x 1024 x 1024 with its norm; 3: 2.97)
+    constexpr int AHEAD = OUT_NORM && NR > 3 ? 3 : NR;
     __shared__ V xch[2][TB][WPG][2][WAVE];   // [step parity][level][wavefront][first / last row][lane]
     __shared__ double red[WPG];
 
@@ -1502,17 +1505,17 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
             for (int j = 0; j < NR; ++j) st[l][0][j] = st[l][1][j] = V(0);
 
         const int nsteps = (k1 - k0 + 1) + 2 * TB;              // planes kappa = k0-TB .. k1+TB
-        // The plane entering the pipeline, loaded one step ahead: as soon as a row has been taken, the load
-        // of the same row of the next plane is issued in its place, so only ONE plane of loads is live.
+        // The rows entering the pipeline, loaded AHEAD rows before they are needed - at most one plane: as soon as a row has
+        // been taken, the load of the same row of the next plane is issued in its place.
         V ld[NR];
         if (k0 - TB > 0) { in_tz = (k0 - TB - 1) / g.td; in_k = k0 - TB - in_tz * g.td; }
         place_plane();
 #pragma unroll
-        for (int j = 0; j < NR; ++j) ld[j] = load_row(j);
+        for (int j = 0; j < AHEAD; ++j) ld[j] = load_row(j);
 
-        // the first plane has to have arrived before the loop (its waits are placed for the longer-waiting entry)
+        // the first rows have to have arrived before the loop (its waits are placed for the longer-waiting entry)
 #pragma unroll
-        for (int j = 0; j < NR; ++j) asm volatile("" : "+v"(ld[j]));
+        for (int j = 0; j < AHEAD; ++j) asm volatile("" : "+v"(ld[j]));
 
         int out_tz = (k0 - 1) / g.td, out_k = k0 - out_tz * g.td;        // the next plane to be stored
         const unsigned tilerow_bytes = (unsigned)(tilerow * (long long)sizeof(T));      // below 2 GiB
@@ -1524,7 +1527,6 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
                 const int q = q0 + p;
                 if (q >= nsteps) break;
                 const int kappa = k0 - TB + q;                   // plane of u(t) entering the pipeline
-                next_plane(kappa + 1);
                 bool ring_plane[TB + 1];
 #pragma unroll
                 for (int l = 1; l <= TB; ++l)
@@ -1539,7 +1541,8 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
 #pragma unroll
                 for (int j = 0; j < NR; ++j) {
                     V d = ld[j], result = V(0);                  // newest plane of the level below, row j
-                    ld[j] = load_row(j);                         // same row of the next plane, for the next step
+                    if (j + AHEAD == NR) next_plane(kappa + 1);
+                    ld[(j + AHEAD) % NR] = load_row((j + AHEAD) % NR);
 #pragma unroll
                     for (int l = 1; l <= TB; ++l) {
                         if constexpr (OUT_NORM) if (l == TB) result = d;
