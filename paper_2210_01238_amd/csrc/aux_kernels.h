@@ -166,18 +166,22 @@ __global__ __launch_bounds__(WG) void halo_exchange_kernel(Geo g, T *grid, int c
 // Scatter / gather between a padded global array and the tile-major grid.  Both are plain copies, so what counts
 // is that every lane moves 16 bytes and that whole cache lines are written: each kernel walks its DESTINATION in
 // vectors that are 16-byte aligned there, and reads the source with 16-byte loads that are only element-aligned
-// (the tiles' rows start on cache lines, the global array's rows one ring cell off them).  Bound by HBM.  Moving one
-// cell per lane and load, with 64-bit addresses formed per cell, they ran at 2.4 - 4.9 TB/s; now (us, before -> after)
-//   16384^2 in 8 x 8 tiles:    scatter  893 ->  765 (5.6 TB/s)   gather  870 ->  778 (5.5 TB/s)
-//   8192^2 in 64 x 64 tiles:            220 ->  183                      246 ->  176
-//   1024 x 1024 x 768, 6x8x8:          3033 -> 2396 (5.4)               3179 -> 2336 (5.5)
-//   512^3, 4x4x4, fp32:                 431 ->  197 (5.5)                460 ->  192 (5.7)
-//   300^3, 30x30x30, fp32:             1059 ->  154                     1064 ->   90
+// (the tiles' rows start on cache lines, the global array's rows one ring cell off them).  Bound by HBM, which takes
+// many short wavefronts best: a lane of a large grid moves ONE vector, so that a wavefront reads 1 KiB, writes it and is gone
+// (four per lane, read then written: 5.4 - 5.6 TB/s; one: 5.7 - 6.4, and 1.25 to 1.3 ns per workgroup, about what it takes to start
+// them).  us, one cell per lane and load -> four vectors -> now:
+//   16384^2 in 8 x 8 tiles:    scatter  893 ->  765 ->  720       gather  870 ->  776 ->  676
+//   8192^2 in 64 x 64 tiles:            220 ->  178 ->  171               246 ->  176 ->  172
+//   1024 x 1024 x 768, 6x8x8:          3033 -> 2330 -> 2210              3179 -> 2320 (four vectors still)
+//   512^3, 4x4x4, fp32:                 431 ->  198 ->  186                460 ->  190 (three)
+//   300^3, 30x30x30, fp32:             1059 ->  154 ->  156               1064 ->   90 (two)
 // ------------------------------------------------------------------------------------
-constexpr int SG_VECS = 4;                    // vectors per thread, all loaded before the first is stored (one per thread, for
-                                              // more workgroups on small grids: 256^2 and 64^3 the same, 128^3 6.7 -> 9.8 us)
-constexpr int SG_UNIT = SG_VECS * WG;         // vectors a workgroup of the scatter copies (16 KiB)
+// Vectors per thread of the scatter, all loaded before the first is stored.  Grids that stay in the caches take two: 128^3 in one
+// tile 6.9 us against 8.0 with one, larger ones the same.
+template <bool STREAM> constexpr int SC_VECS = STREAM ? 1 : 2;
+constexpr int sc_unit(bool stream) { return (stream ? SC_VECS<true> : SC_VECS<false>) * WG; }      // vectors a workgroup copies (4 or 8 KiB)
 constexpr int LINE_BYTES = 128;               // a cache line
+constexpr int GATHER_VECS = 4;                // vectors per lane of the gather, at most
 
 // Division of a 32-bit number by a divisor the host knows: a multiplication and two shifts (Granlund and
 // Montgomery, "Division by invariant integers using multiplication", 1994).  Exact for every n.
@@ -198,7 +202,7 @@ struct FastDiv {
     }
 };
 
-// Scatter: a workgroup fills SG_UNIT consecutive vectors of one tile's rows - all padded rows, halo rows included -
+// Scatter: a workgroup fills sc_unit() consecutive vectors of one tile's rows - all padded rows, halo rows included -
 // and the two x halo cells of the rows that begin among them (a run of consecutive entries of the dense arrays).
 struct ScatterParams {
     long long GP, GQ;          // elements between rows / planes of the global array
@@ -217,7 +221,7 @@ template <typename T, bool STREAM>
 __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, const T *__restrict__ from, T *__restrict__ to)
 {
     using V = typename Vec<T>::type;
-    constexpr int NV = Vec<T>::N;
+    constexpr int NV = Vec<T>::N, VECS = SC_VECS<STREAM>, UNIT = sc_unit(STREAM);
     typedef T VU __attribute__((ext_vector_type(NV), aligned(sizeof(T))));
     unsigned lwg = blockIdx.x + sp.first;
     if (lwg < sp.in_groups) {
@@ -225,16 +229,16 @@ __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, co
         lwg = first + within % NUM_XCD * (unsigned)sp.xcd_chunk + within / NUM_XCD;
     }
     const unsigned t = sp.by_wg_per_tile(lwg);
-    const unsigned v0 = (lwg - t * sp.wg_per_tile) * SG_UNIT;
+    const unsigned v0 = (lwg - t * sp.wg_per_tile) * UNIT;
     const unsigned tz = sp.by_layer(t), in_layer = t - tz * (unsigned)(g.Ty * g.Tx);
     const unsigned ty = sp.by_Tx(in_layer), tx = in_layer - ty * (unsigned)g.Tx;
     // the padded cell (plane 0, row 0, column 0) of the tile; column 0 is the cell right of the x- halo
     const T *corner = from + ((long long)tz * g.td * sp.GQ + (long long)ty * g.th * sp.GP + (long long)tx * g.tw + 1);
     T *tile = to + (long long)t * g.tile_stride;
-    V v[SG_VECS];
-    unsigned dst[SG_VECS];
+    V v[VECS];
+    unsigned dst[VECS];
 #pragma unroll
-    for (int q = 0; q < SG_VECS; ++q) {
+    for (int q = 0; q < VECS; ++q) {
         const unsigned j = v0 + q * WG + threadIdx.x;
         v[q] = V(0);
         if (j >= sp.nvec) continue;
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, co
                 if (c + e < (unsigned)g.tw) v[q][e] = src[e];
         }
     }
-    const unsigned v1 = min(v0 + SG_UNIT, sp.nvec);
+    const unsigned v1 = min(v0 + UNIT, sp.nvec);
     const unsigned r0 = sp.by_vrow(v0 + sp.vrow - 1), r1 = sp.by_vrow(v1 + sp.vrow - 1);
     for (unsigned r = r0 + threadIdx.x; r < r1; r += WG) {
         const unsigned k = sp.by_rows(r), i = r - k * (unsigned)g.rows;
@@ -259,7 +263,7 @@ __global__ __launch_bounds__(WG) void scatter_kernel(Geo g, ScatterParams sp, co
         tile[g.xoff + g.hpitch + r] = xp;
     }
 #pragma unroll
-    for (int q = 0; q < SG_VECS; ++q)
+    for (int q = 0; q < VECS; ++q)
         if (v0 + q * WG + threadIdx.x < sp.nvec) stv<STREAM>((V *)(tile + dst[q]), v[q]);
 }
 
@@ -273,7 +277,6 @@ struct GatherParams {
     unsigned GP, plane_rows;   // cells per padded row; padded rows per plane
     unsigned shift;            // elements the array's first cell lies beyond a cache line
     unsigned nchunks, nitems;  // wavefronts per row; wavefronts in all
-    unsigned together;         // wavefronts whose vectors alternate: 1, or a whole workgroup's on long rows
     FastDiv by_chunks, by_rows, by_td, by_th, by_tw;
 };
 
@@ -305,13 +308,11 @@ __global__ __launch_bounds__(WG) void gather_kernel(Geo g, GatherParams gp, cons
     // a wavefront's vectors start on a cache line: cells of the row's first line that belong to the row before
     const int lead = (int)((unsigned)(lin + gp.shift) % (LINE_BYTES / sizeof(T)));
     const int GP = (int)gp.GP;
-    const unsigned step = gp.together * WAVE;
-    const unsigned first_vec = gp.together == 1 ? chunk * (Q * WAVE) + lane
-                                                : (chunk / WAVES_PER_WG * Q * WAVES_PER_WG + chunk % WAVES_PER_WG) * WAVE + lane;
+    const unsigned first_vec = chunk * (Q * WAVE) + lane;
     V v[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const long long at = (long long)(first_vec + q * step) * NV - lead;  // first cell: padded column
+        const long long at = (long long)(first_vec + q * WAVE) * NV - lead;  // first cell: padded column
         v[q] = V(0);
         if (at >= GP || at + NV <= 0) continue;
         const int gc = (int)max(at, 0ll);
@@ -357,7 +358,7 @@ __global__ __launch_bounds__(WG) void gather_kernel(Geo g, GatherParams gp, cons
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const long long at = (long long)(first_vec + q * step) * NV - lead;
+        const long long at = (long long)(first_vec + q * WAVE) * NV - lead;
         if (at >= 0 && at + NV <= GP) stv<STREAM>((V *)(to + (lin + at)), v[q]);
         else {
 #pragma unroll

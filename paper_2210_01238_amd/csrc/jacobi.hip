@@ -52,10 +52,10 @@ constexpr int64_t CACHED_GRID_BYTES = 124LL << 20;
 constexpr int64_t SPREAD_GRID_BYTES = 6LL << 20;    // 3-D updates of grids from this size on: 1500 wavefronts
 constexpr int64_t CACHED_CHUNK_BYTES = 24LL << 20;  // cache-resident 2-D grids from this size on: XCD chunks of 32
 
-// Scatter: consecutive workgroups one XCD takes (16384^2: 797 us in the hardware's order, 806 with 16, 765 with 32, 752
-// with 64; 1024 x 1024 x 768: 2463, 2382, 2399, 2422; small grids the same with all).  The x halo arrays fill in runs of
-// 16 cells and less per workgroup, which then meet in one L2.
-constexpr int SG_XCD_CHUNK = 32;
+// Scatter: consecutive workgroups one XCD takes (1024 x 1024 x 768: 2401 us with 8, 2319 with 16, 2219 with 32, 2209 with 64, 2221
+// with 128; 512^3 381, 380, 375, 368, 368; 16384^2 698, 686, 718, 717, 706; small grids the same with all).  The x halo arrays
+// fill in runs of a few cells per workgroup, which then meet in one L2.
+constexpr int SG_XCD_CHUNK = 64;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -1278,7 +1278,7 @@ int launch_scatter_t(jacobi_plan *p, const T *from, T *grid, hipStream_t st)
     sp.GQ = (p->lay.dims[1] + 2) * sp.GP;
     sp.vrow = (unsigned)ceil_div(g.tw, nv);
     sp.nvec = (unsigned)g.nplanes * (unsigned)g.rows * sp.vrow;
-    sp.wg_per_tile = (unsigned)ceil_div(sp.nvec, jk::SG_UNIT);
+    sp.wg_per_tile = (unsigned)ceil_div(sp.nvec, jk::sc_unit(store_flavour(p) != 0));
     sp.by_vrow.set(sp.vrow);
     sp.by_rows.set((unsigned)g.rows);
     sp.by_wg_per_tile.set(sp.wg_per_tile);
@@ -1312,15 +1312,16 @@ int launch_gather_t(jacobi_plan *p, const T *grid, T *to, hipStream_t st)
     gp.plane_rows = (unsigned)(p->lay.dims[1] + 2);
     const int line = jk::LINE_BYTES / (int)sizeof(T);
     gp.shift = (unsigned)((uintptr_t)to / sizeof(T) % line);
-    // a wavefront per row, up to four vectors per lane; several wavefronts for a longer row.  From 8 on the vectors
-    // of a workgroup's wavefronts alternate (16384^2: 834 us with 4 KiB per wavefront, 778 with 4 KiB per workgroup
-    // and step; shorter rows would leave more lanes without work).
+    // a wavefront per row, up to four vectors per lane; several wavefronts for a longer row.  In fp64, on grids that do not stay in the
+    // caches, a lane takes one from 16 times 64 vectors on (1 -> 4 vectors: 16384^2 676 -> 776 us, 8000^2 in one tile 158 -> 182,
+    // 8190 x 9001 181 -> 215, 12000 x 2100 49.2 -> 49.9); the last wavefront of a row, mostly idle, costs as much as the others, which
+    // shorter rows would feel (1024 x 1024 x 768: 2337 -> 2321, 512^3 410 -> 392).  Cached: 2000 x 4200 19.6 -> 19.2; fp32, where a
+    // wavefront has more instructions for its seams: 8000 x 12000 132 -> 131, 4096^2 21.4 -> 19.2.
+    const bool stream = store_flavour(p) != 0;
     const int64_t nrows = (int64_t)gp.plane_rows * (g.ndim == 3 ? p->lay.dims[0] + 2 : 1);
     const int64_t vecs = ceil_div((int64_t)gp.GP + line - 1, nv);
-    const int q = (int)std::min<int64_t>(jk::SG_VECS, ceil_div(vecs, jk::WAVE));
+    const int q = sizeof(T) == 8 && stream && vecs >= 16 * jk::WAVE ? 1 : (int)std::min<int64_t>(jk::GATHER_VECS, ceil_div(vecs, jk::WAVE));
     gp.nchunks = (unsigned)ceil_div(vecs, q * jk::WAVE);
-    gp.together = gp.nchunks >= 2 * jk::WAVES_PER_WG ? jk::WAVES_PER_WG : 1;
-    if (gp.together > 1) gp.nchunks = (unsigned)round_up(gp.nchunks, jk::WAVES_PER_WG);
     if (nrows * gp.nchunks > 0xfffffff0LL) return fail(JACOBI_EINVAL, "too many row chunks for one scatter / gather launch");
     gp.nitems = (unsigned)(nrows * gp.nchunks);
     gp.by_chunks.set(gp.nchunks);
@@ -1329,7 +1330,6 @@ int launch_gather_t(jacobi_plan *p, const T *grid, T *to, hipStream_t st)
     gp.by_th.set((unsigned)g.th);
     gp.by_tw.set((unsigned)g.tw);
     const dim3 blocks((unsigned)ceil_div(gp.nitems, jk::WAVES_PER_WG)), threads(jk::WG);
-    const bool stream = store_flavour(p) != 0;
 #define JK_GATHER(Q_)                                                                                                        \
     do {                                                                                                                     \
         if (stream) hipLaunchKernelGGL((jk::gather_kernel<T, true, Q_>), blocks, threads, 0, st, g, gp, grid, to);           \
