@@ -259,6 +259,15 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip3d_kernel(Geo g, Chip3d 
         const __amdgpu_buffer_rsrc_t buf = area(exchange);
         const int l = opaque_lane(lane);
         bool want_z = z_out, want_y = y_out;       // wave-uniform
+        // Blocks run level with each other, so asked at once the first question would come just too early and the answer to the second
+        // one a way to memory and back later.  Us per 100 iterations with scatter and gather, at once -> after this wait (of 64 clocks
+        // each; 3 less or more: the same within 2 %): one wavefront per row, one cell per lane 64^3 180.1 -> 172.2, 56^3 166.1 -> 158, fp32
+        // 64^3 153.6 -> 144.  With more to a row the blocks run less level: from 176 workgroups on only (one cell per lane and two wavefronts
+        // 182 workgroups 138.8 -> 131.3, 128 135 -> 138, 132 279 -> 285, fp32 80 149 -> 158; fp32 128^3 281 -> 258, 72^3 190 -> 202),
+        // and not in fp64 with two cells (128^3 391 -> 378, but 196 x 115 x 140 792 -> 801).
+        if constexpr (C == 1 && NXW == 1) __builtin_amdgcn_s_sleep(sizeof(T) == 8 ? 5 : 9);
+        else if constexpr (C == 1 || sizeof(T) == 4)
+            if (gridDim.x >= 176) __builtin_amdgcn_s_sleep(sizeof(T) == 8 ? 5 : 8);
         for (unsigned n = 0; want_z || want_y;) {
             ByteTagged<T, NZ> mz;
             ByteTagged<T, NY> my;
