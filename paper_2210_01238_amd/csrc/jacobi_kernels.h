@@ -1425,7 +1425,7 @@ __global__ __launch_bounds__(WPG * WAVE, MINW) void sweep3d_tc_kernel(Geo g, Str
     constexpr bool IN_NORM = MODE == MODE_BOTH, OUT_NORM = MODE == MODE_AFTER;
     constexpr int STEPS = OUT_NORM ? TB - 1 : TB;
     // Rows loaded ahead: a whole plane's, 3 where the result's norm needs their registers (all 5: some spill, 3.10 ms a pass of
-    // 768 x 1024 x 1024 with its norm; 3: 2.97)
+    // 768 x 1024 x 1024 with its norm; 3: 2.83)
     constexpr int AHEAD = OUT_NORM && NR > 3 ? 3 : NR;
     __shared__ V xch[2][TB][WPG][2][WAVE];   // [step parity][level][wavefront][first / last row][lane]
     __shared__ double red[WPG];
