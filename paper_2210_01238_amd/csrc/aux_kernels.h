@@ -277,6 +277,7 @@ struct GatherParams {
     unsigned GP, plane_rows;   // cells per padded row; padded rows per plane
     unsigned shift;            // elements the array's first cell lies beyond a cache line
     unsigned nchunks, nitems;  // wavefronts per row; wavefronts in all
+    unsigned first;            // workgroups of earlier launches
     FastDiv by_chunks, by_rows, by_td, by_th, by_tw;
 };
 
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(WG) void gather_kernel(Geo g, GatherParams gp, cons
     constexpr int NV = Vec<T>::N;
     typedef T VU __attribute__((ext_vector_type(NV), aligned(sizeof(T))));
     const int lane = threadIdx.x % WAVE;
-    const unsigned item = __builtin_amdgcn_readfirstlane(blockIdx.x * WAVES_PER_WG + threadIdx.x / WAVE);
+    const unsigned item = __builtin_amdgcn_readfirstlane((blockIdx.x + gp.first) * WAVES_PER_WG + threadIdx.x / WAVE);
     if (item >= gp.nitems) return;
     const unsigned row = gp.by_chunks(item), chunk = item - row * gp.nchunks;
     unsigned gk = 0, gi = row;

@@ -1329,20 +1329,24 @@ int launch_gather_t(jacobi_plan *p, const T *grid, T *to, hipStream_t st)
     gp.by_td.set((unsigned)g.td);
     gp.by_th.set((unsigned)g.th);
     gp.by_tw.set((unsigned)g.tw);
-    const dim3 blocks((unsigned)ceil_div(gp.nitems, jk::WAVES_PER_WG)), threads(jk::WG);
+    // as for the scatter: 2^32 threads are 2^26 wavefronts - as many rows, or 64 GiB of long fp64 ones
+    const unsigned nwg = (unsigned)ceil_div(gp.nitems, jk::WAVES_PER_WG), most = 0xffffffffu / jk::WG;
+    for (gp.first = 0; gp.first < nwg; gp.first += most) {
+        const dim3 blocks(std::min(nwg - gp.first, most)), threads(jk::WG);
 #define JK_GATHER(Q_)                                                                                                        \
     do {                                                                                                                     \
         if (stream) hipLaunchKernelGGL((jk::gather_kernel<T, true, Q_>), blocks, threads, 0, st, g, gp, grid, to);           \
         else hipLaunchKernelGGL((jk::gather_kernel<T, false, Q_>), blocks, threads, 0, st, g, gp, grid, to);                 \
     } while (0)
-    switch (q) {
-    case 1: JK_GATHER(1); break;
-    case 2: JK_GATHER(2); break;
-    case 3: JK_GATHER(3); break;
-    default: JK_GATHER(4); break;
-    }
+        switch (q) {
+        case 1: JK_GATHER(1); break;
+        case 2: JK_GATHER(2); break;
+        case 3: JK_GATHER(3); break;
+        default: JK_GATHER(4); break;
+        }
 #undef JK_GATHER
-    HIP_TRY(hipGetLastError());
+        HIP_TRY(hipGetLastError());
+    }
     return JACOBI_OK;
 }
 

@@ -116,6 +116,31 @@ for tiles, dtype in ((n, J.JACOBI_F64), (1000, J.JACOBI_F32)):
 """)
 
 
+def test_gather_of_very_large_grids_stays_within_what_one_launch_takes(stub):
+    """A wavefront takes 1 to 4 KiB of a row, so that 2^32 threads are reached by fp64 fields of 64 GiB with long rows, and by 2^26 short rows.  Every
+    wavefront is launched once: the launches cover what the rows need, and no workgroup more than the last one's rest."""
+    run(stub, """
+def waves(dims, dtype):
+    size, line = (8, 16) if dtype == J.JACOBI_F64 else (4, 32)
+    vecs = -(-(dims[-1] + 2 + line - 1) * size // 16)
+    rows = 1
+    for n in dims[:-1]: rows *= n + 2
+    grid = J.jacobi_grid_bytes(p)
+    q = 1 if size == 8 and grid > 124 << 20 and vecs >= 16 * 64 else min(4, -(-vecs // 64))
+    return rows * -(-vecs // (64 * q))
+for dims, tiles, dtype, pieces in (((93000, 93000), (8, 8), J.JACOBI_F64, 2), ((2100, 2080, 2080), (10, 10, 10), J.JACOBI_F64, 2), ((67108900, 3), (100, 1), J.JACOBI_F64, 2),
+                                   ((140000000, 2), (1000, 1), J.JACOBI_F32, 3), ((92000, 92000), (8, 8), J.JACOBI_F64, 1), ((1000, 300), (2, 2), J.JACOBI_F32, 1)):
+    p = J.jacobi_create(dims, tiles, dtype)
+    J.jacobi_prepare(p)
+    log()
+    J.jacobi_gather(p, 1 << 20, 1 << 20)
+    launches = [(int(c[1]), int(c[2])) for c in log() if c[0] == "hipLaunchKernel"]
+    assert all(g * b < 1 << 32 for g, b in launches), (dims, launches)
+    assert len(launches) == pieces and sum(g for g, b in launches) == -(-waves(dims, dtype) // 4), (dims, launches, waves(dims, dtype))
+    J.jacobi_destroy(p)
+""")
+
+
 PLANS = [((96, 200), (3, 2)), ((48, 48), (48, 48)), ((512, 512), (4, 4)), ((24, 20, 36), (2, 2, 3)), ((8, 8, 8), (8, 8, 8)), ((256, 256), (1, 1)),
          ((2304, 2304), (8, 8)), ((64, 64, 64), (2, 2, 2))]
 

@@ -105,3 +105,19 @@ def test_scatter_gather_of_more_tiles_than_one_launch_takes(H):
             assert torch.equal(tiles[:, k * lay.pitch:k * lay.pitch + 3], a[k:k + n, 1:4])
     finally:
         r.close()
+
+
+def test_gather_of_more_rows_than_one_launch_takes(H):
+    """2^26 rows and some, a wavefront each (grid 8.7 GB): the gather runs as two launches, and rows on both sides of their seam arrive."""
+    import torch
+    n = (1 << 26) + 136
+    r = H.JacobiRun((n, 3), (1000, 1))
+    try:
+        stream = int(torch.cuda.current_stream().cuda_stream)
+        a = torch.arange((n + 2) * 5, dtype=torch.float64, device="cuda").reshape(n + 2, 5)
+        out = torch.zeros_like(a)
+        H.B.jacobi_scatter(r.plan, a.data_ptr(), r.a.data_ptr(), stream)
+        H.B.jacobi_gather(r.plan, r.a.data_ptr(), out.data_ptr(), stream)
+        assert torch.equal(out, a)
+    finally:
+        r.close()
