@@ -526,6 +526,34 @@ bool tc3d_usable(const jacobi_plan *p, int depth)
            (int64_t)g.Tx * g.tile_stride * (int64_t)p->esize < 0x7fffffffLL;   // per-lane byte offsets are 32-bit
 }
 
+// Planes per block of the cooperative passes, with nz planes along the column of tiles and `across` units in each block.  One workgroup
+// runs per CU and all units of a launch take the same time (R + 2*depth plane steps), so the launch takes about ceil(units / CUs) rounds of that:
+// split the planes of the whole column of tiles so that rounds x steps is least (deep units amortise the run-in, more units fill the last
+// round).  Up to depth 3 memory decides, which shorter blocks suit better (the planes of the run-in have just been read
+// by the block before): the shortest within a sixteenth of the least (768 x 1024 x 1024, depth 3: 2690 us with 9
+// blocks, the least, 2659 with the 17 this takes, 2650 with 23; at depth 4 2817 with the 8 that are the least, 2840 with 6, 2880 with 15).
+// Only the splits that can be the answer are looked at, about two for each number of rounds: this is asked for with every launch.
+int tc3d_planes(int nz, int64_t across, int num_cu, int depth)
+{
+    const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(16, ceil_div(24 * (int64_t)num_cu, across)));     // 24 rounds are plenty
+    auto rounds_of = [&](int64_t blocks) { return ceil_div(across * blocks, num_cu); };
+    auto cost_of = [&](int64_t r) { return rounds_of(ceil_div(nz, r)) * (r + 2 * depth); };
+    int64_t best = -1, R = nz;
+    for (int64_t blocks = 1; blocks <= most; ++blocks) {
+        blocks = std::min(most, rounds_of(blocks) * num_cu / across);      // the most that take as many rounds
+        const int64_t r = ceil_div(nz, blocks), cost = cost_of(r);
+        if (best < 0 || cost < best) { best = cost; R = r; }
+    }
+    if (depth <= 3)
+        for (int64_t r = ceil_div(nz, most); r < R;) {
+            if (cost_of(r) * 16 <= best * 17) return (int)r;
+            const int64_t fewer = (rounds_of(ceil_div(nz, r)) - 1) * num_cu / across;      // blocks that take a round less
+            if (fewer < 1) break;
+            r = ceil_div(nz, fewer);
+        }
+    return (int)R;
+}
+
 // sp.nstrips = 4 per work unit (one partial sum per unit); *nyg_out = row groups along the whole column of tiles
 StripParams tc3d_strips(const jacobi_plan *p, int depth, int *nyg_out)
 {
@@ -536,26 +564,8 @@ StripParams tc3d_strips(const jacobi_plan *p, int depth, int *nyg_out)
     sp.nseg = (int)ceil_div((int64_t)g.Tx * g.tw, tp_segment_width(p, depth));
     const int nz = (int)std::min<int64_t>((int64_t)g.Tz * g.td, 0x7fffffff);
     int R = (int)p->rows_per_strip;
-    if (R <= 0) {
-        // One workgroup runs per CU and all units of a launch take the same time (R + 2*depth plane
-        // steps), so the launch takes about ceil(units / CUs) rounds of that: split the planes of the whole column of
-        // tiles so that rounds x steps is least (deep units amortise the run-in, more units fill the last round).  Up to
-        // depth 3 memory decides, which shorter blocks suit better (the planes of the run-in have just been read
-        // by the block before): the shortest within a sixteenth of the least (768 x 1024 x 1024, depth 3: 2690 us with 9
-        // blocks, the least, 2659 with the 17 this takes, 2650 with 23; at depth 4 2817 with the 8 that are the least, 2840 with 6, 2880 with 15).
-        int64_t best = -1;
-        auto cost_of = [&](int r) { return ceil_div((int64_t)nyg * sp.nseg * ceil_div(nz, r), p->num_cu) * (r + 2 * depth); };
-        R = nz;
-        const int most = (int)std::max<int64_t>(16, ceil_div(24 * (int64_t)p->num_cu, (int64_t)nyg * sp.nseg));     // 24 rounds are plenty
-        for (int nblk = 1; nblk <= most && nblk <= nz; ++nblk) {
-            const int r = (int)ceil_div(nz, nblk);
-            const int64_t cost = cost_of(r);
-            if (best < 0 || cost < best) { best = cost; R = r; }
-        }
-        if (depth <= 3)
-            for (int r = (int)ceil_div(nz, most); r < R; ++r)
-                if (cost_of(r) * 16 <= best * 17) R = r;
-    } else if (R > g.td) R = g.td;
+    if (R <= 0) R = tc3d_planes(nz, (int64_t)nyg * sp.nseg, p->num_cu, depth);
+    else if (R > g.td) R = g.td;
     sp.R = R;
     sp.nblk = (int)ceil_div(nz, R);
     sp.nstrips = (int64_t)sp.nblk * sp.nseg * nyg * jk::WAVES_PER_WG;   // partial sums: one per unit

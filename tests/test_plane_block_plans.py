@@ -1,0 +1,69 @@
+"""How the cooperative 3-D blocked passes split their planes into blocks: the workgroups of a launch, seen through a stand-in for the HIP runtime
+(hip_stub), against a search of all splits.  (test_plane_blocks_gpu.py compares the results of such passes with the oracle's.)"""
+from test_host_calls import run, stub  # noqa: F401  (stub: a fixture)
+
+HEAD = """
+import random
+CUS = 256
+def up(a, b): return -(-a // b)
+def units(dims, dtype, depth):
+    "units of a pass per block of planes: row groups x column segments"
+    own = 8 * {2: 8, 3: 6, 4: 5}[depth] - 2 * depth
+    return up(dims[1], own) * up(dims[2], 120 if dtype == J.JACOBI_F64 else 240)
+def plan(dims, tiles, dtype, depth, **options):
+    p = J.jacobi_create(dims, tiles, dtype)
+    for k, v in {"tblock": depth, "resident": 0, **options}.items(): J.jacobi_set_option(p, k, v)
+    J.jacobi_prepare(p)
+    return p
+def blocks(dims, tiles, dtype, depth, **options):
+    "blocks of planes in a cooperative pass of this depth"
+    p = plan(dims, tiles, dtype, depth, **options)
+    log()
+    J.jacobi_sweep(p, *GRIDS(p), depth)
+    n = [int(c[1]) for c in log() if c[0] == "hipLaunchKernel" and "sweep3d_tc_kernel" in c[4]]
+    J.jacobi_destroy(p)
+    assert len(n) == 1 and n[0] % units(dims, dtype, depth) == 0, (dims, n)
+    return n[0] // units(dims, dtype, depth)
+def searched(nz, across, depth):
+    "the rule, every split looked at: planes per block"
+    def cost(r): return up(across * up(nz, r), CUS) * (r + 2 * depth)
+    most = min(nz, max(16, up(24 * CUS, across)))
+    R = min((up(nz, n) for n in range(1, most + 1)), key=lambda r: (cost(r), -r))
+    if depth <= 3:
+        R = next(r for r in range(up(nz, most), R + 1) if r == R or cost(r) * 16 <= cost(R) * 17)
+    return R
+"""
+
+
+def test_the_split_is_the_best_of_all(stub):  # noqa: F811
+    run(stub, HEAD + """
+rng = random.Random(12)
+for _ in range(1500):
+    dtype, depth = rng.choice(((J.JACOBI_F64, 3), (J.JACOBI_F64, 4), (J.JACOBI_F32, 3)))
+    td, tz = rng.choice((4, 5, 7, 16, 33, 64, 100)), rng.choice((1, 1, 2, 3, 7, 20))
+    dims = (td * tz, int(2 ** rng.uniform(2, 10)), 4 * int(2 ** rng.uniform(1, 9)))
+    nz, across = dims[0], units(dims, dtype, depth)
+    assert blocks(dims, (tz, 1, 1), dtype, depth) == up(nz, searched(nz, across, depth)), (dims, tz, dtype, depth)
+""")
+
+
+def test_planning_takes_no_longer_than_a_launch(stub):  # noqa: F811
+    """The split is asked for with every pass: host time of a pass with the library's choice and with one that is given.  (A search of all
+    splits takes 15 to 60 us here, as long as the pass itself.)"""
+    run(stub, HEAD + """
+for dims in ((2048, 64, 64), (4096, 30, 60), (16384, 30, 60), (768, 1024, 1024)):
+    def per_pass(strip):
+        p = plan(dims, (1, 1, 1), J.JACOBI_F64, 3, rows_per_strip=strip)
+        a, b = GRIDS(p)
+        best = 1e9
+        for _ in range(9):
+            stub.stub_clear_log()
+            t = time.perf_counter()
+            J.jacobi_sweep(p, a, b, 600)
+            best = min(best, (time.perf_counter() - t) / 200)
+        J.jacobi_destroy(p)
+        return best
+    given, chosen = per_pass(64), per_pass(0)
+    print(dims, "us per pass, planes given %.2f, chosen %.2f" % (given * 1e6, chosen * 1e6))
+    assert chosen < given + 6e-6, (dims, given, chosen)
+""")
