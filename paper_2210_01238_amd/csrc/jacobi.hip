@@ -532,23 +532,34 @@ bool tc3d_usable(const jacobi_plan *p, int depth)
 // round).  Up to depth 3 memory decides, which shorter blocks suit better (the planes of the run-in have just been read
 // by the block before): the shortest within a sixteenth of the least (768 x 1024 x 1024, depth 3: 2690 us with 9
 // blocks, the least, 2659 with the 17 this takes, 2650 with 23; at depth 4 2817 with the 8 that are the least, 2840 with 6, 2880 with 15).
+// Where one round of blocks of 8 planes and more and up to 21 steps does, the last block, whose workgroups start last, had better be shorter than
+// the others, if that costs no more than a plane (us a pass with the last block full, 1, 2, 3 planes shorter: 32 blocks of 8 across 150 x 180, depth 3,
+// 48.0, 44.5, 41.6, 41.0; 21 of 14 across 250 x 230 72.8, 71.2, 69.5, 72.2; 16 of 9 there, depth 4, 55.3, 50.3, 48.3, 47.8; so 200^3 takes 23
+// blocks of 9, 44 - 46.5 us, and not 25 of 8, 48 - 50).  Thin blocks lose more with a plane more than they gain (128^3 in 32 blocks of 4 31.6 us, in 26
+// of 5 33.8), and so do deep ones (96 x 292 x 384, depth 4, 6 of 16 68.4, of 17 69.9; 384^3, fp32, 12 of 32 124, of 33 129).
 // Only the splits that can be the answer are looked at, about two for each number of rounds: this is asked for with every launch.
 int tc3d_planes(int nz, int64_t across, int num_cu, int depth)
 {
     const int64_t most = std::min<int64_t>(nz, std::max<int64_t>(16, ceil_div(24 * (int64_t)num_cu, across)));     // 24 rounds are plenty
     auto rounds_of = [&](int64_t blocks) { return ceil_div(across * blocks, num_cu); };
-    auto cost_of = [&](int64_t r) { return rounds_of(ceil_div(nz, r)) * (r + 2 * depth); };
+    auto cost_of = [&](int64_t r) {
+        const int64_t blocks = ceil_div(nz, r), rounds = rounds_of(blocks);
+        const bool full_last = rounds == 1 && r >= 8 && r + 2 * depth <= 21 && r < nz && nz % r == 0;
+        return rounds * (r + 2 * depth + full_last);
+    };
     int64_t best = -1, R = nz;
     for (int64_t blocks = 1; blocks <= most; ++blocks) {
-        blocks = std::min(most, rounds_of(blocks) * num_cu / across);      // the most that take as many rounds
-        const int64_t r = ceil_div(nz, blocks), cost = cost_of(r);
+        const int64_t rounds = rounds_of(blocks);
+        blocks = std::min(most, rounds * num_cu / across);                 // the most that take as many rounds
+        const int64_t least = ceil_div(nz, blocks);
+        const int64_t r = rounds == 1 && cost_of(least + 1) <= cost_of(least) ? least + 1 : least, cost = cost_of(r);
         if (best < 0 || cost < best) { best = cost; R = r; }
     }
     if (depth <= 3)
         for (int64_t r = ceil_div(nz, most); r < R;) {
-            if (cost_of(r) * 16 <= best * 17) return (int)r;
             const int64_t fewer = (rounds_of(ceil_div(nz, r)) - 1) * num_cu / across;      // blocks that take a round less
             if (fewer < 1) break;
+            if (cost_of(r) * 16 <= best * 17) return (int)r;
             r = ceil_div(nz, fewer);
         }
     return (int)R;

@@ -26,11 +26,13 @@ def blocks(dims, tiles, dtype, depth, **options):
     return n[0] // units(dims, dtype, depth)
 def searched(nz, across, depth):
     "the rule, every split looked at: planes per block"
-    def cost(r): return up(across * up(nz, r), CUS) * (r + 2 * depth)
-    most = min(nz, max(16, up(24 * CUS, across)))
-    R = min((up(nz, n) for n in range(1, most + 1)), key=lambda r: (cost(r), -r))
+    def rounds(r): return up(across * up(nz, r), CUS)
+    def cost(r):
+        return rounds(r) * (r + 2 * depth) + (rounds(r) == 1 and 8 <= r <= 21 - 2 * depth and r < nz and nz % r == 0)
+    least = up(nz, max(16, up(24 * CUS, across)))
+    R = min(range(least, nz + 1), key=lambda r: (cost(r), rounds(r), -r if rounds(r) == 1 else r))
     if depth <= 3:
-        R = next(r for r in range(up(nz, most), R + 1) if r == R or cost(r) * 16 <= cost(R) * 17)
+        R = next(r for r in range(least, R + 1) if r == R or up(nz, r) > CUS // across and cost(r) * 16 <= cost(R) * 17)
     return R
 """
 
@@ -44,6 +46,10 @@ for _ in range(1500):
     dims = (td * tz, int(2 ** rng.uniform(2, 10)), 4 * int(2 ** rng.uniform(1, 9)))
     nz, across = dims[0], units(dims, dtype, depth)
     assert blocks(dims, (tz, 1, 1), dtype, depth) == up(nz, searched(nz, across, depth)), (dims, tz, dtype, depth)
+# one round, ten units to a block: 25 blocks of 8 planes are all full, 23 of 9 end with one of 2; thin and thick blocks stay full
+assert blocks((200, 200, 200), (2, 2, 2), J.JACOBI_F64, 3) == 23 and blocks((198, 200, 200), (2, 2, 2), J.JACOBI_F64, 3) == 25
+assert blocks((128, 128, 128), (1, 1, 1), J.JACOBI_F64, 3) == 32 and blocks((384, 384, 384), (4, 4, 4), J.JACOBI_F32, 3) == 12
+assert blocks((96, 292, 384), (1, 1, 1), J.JACOBI_F64, 4) == 6
 """)
 
 
