@@ -326,7 +326,9 @@ int residual_norm_noalloc(jacobi_plan *plan, void *grid, double *result_dev, voi
  *   "rows_per_strip" 0 | 1..4096  rows (2-D) or planes (3-D) one wavefront marches
  *                    through; 0 = choose from the shape: 8 rows / 16 planes for single steps
  *                    (fewer on small grids, so that there are about a thousand wavefronts),
- *                    up to 128 rows / the tile depth for blocked passes (default 0)
+ *                    up to 128 rows / the tile depth for blocked passes - for the cooperative 3-D ones, whose
+ *                    strips cross from tile to tile, up to the planes of the whole grid (default 0).  A strip
+ *                    ends where its tile (there: the grid) ends, whatever the value
  *   "nontemporal"    0 | 1 | 2   how single-step updates store their results: 2 = streaming
  *                    (non-temporal) stores, 0 = plain stores, 1 = choose (default): plain when both
  *                    grids fit the Infinity Cache (grids of at most 124 MiB: the next iteration then

@@ -576,7 +576,7 @@ StripParams tc3d_strips(const jacobi_plan *p, int depth, int *nyg_out)
     const int nz = (int)std::min<int64_t>((int64_t)g.Tz * g.td, 0x7fffffff);
     int R = (int)p->rows_per_strip;
     if (R <= 0) R = tc3d_planes(nz, (int64_t)nyg * sp.nseg, p->num_cu, depth);
-    else if (R > g.td) R = g.td;
+    else if (R > nz) R = nz;
     sp.R = R;
     sp.nblk = (int)ceil_div(nz, R);
     sp.nstrips = (int64_t)sp.nblk * sp.nseg * nyg * jk::WAVES_PER_WG;   // partial sums: one per unit

@@ -53,6 +53,19 @@ assert blocks((96, 292, 384), (1, 1, 1), J.JACOBI_F64, 4) == 6
 """)
 
 
+def test_planes_that_are_given_are_taken_up_to_the_whole_column(stub):  # noqa: F811
+    """Blocks may cross from tile to tile, and those that the library chooses do: the option can ask for the same ones, and for deeper."""
+    run(stub, HEAD + """
+for dims, tiles, dtype, depth in (((36, 200, 720), (9, 1, 1), J.JACOBI_F64, 4), ((33, 352, 366), (11, 11, 61), J.JACOBI_F64, 3), ((512, 512, 512), (4, 4, 4), J.JACOBI_F64, 4)):
+    nz, td = dims[0], dims[0] // tiles[0]
+    chosen = blocks(dims, tiles, dtype, depth)
+    planes = searched(nz, units(dims, dtype, depth), depth)
+    assert planes > td and chosen == up(nz, planes), (dims, planes)
+    for given in (1, td - 1, td, td + 1, planes, nz - 1, nz, 4096):
+        assert blocks(dims, tiles, dtype, depth, rows_per_strip=given) == up(nz, min(nz, given)), (dims, given)
+""")
+
+
 def test_planning_takes_no_longer_than_a_launch(stub):  # noqa: F811
     """The split is asked for with every pass: host time of a pass with the library's choice and with one that is given.  (A search of all
     splits takes 15 to 60 us here, as long as the pass itself.)"""
