@@ -260,14 +260,25 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void chip3d_kernel(Geo g, Chip3d 
         const int l = opaque_lane(lane);
         bool want_z = z_out, want_y = y_out;       // wave-uniform
         // Blocks run level with each other, so asked at once the first question would come just too early and the answer to the second
-        // one a way to memory and back later.  Us per 100 iterations with scatter and gather, at once -> after this wait (of 64 clocks
-        // each; 3 less or more: the same within 2 %): one wavefront per row, one cell per lane 64^3 180.1 -> 172.2, 56^3 166.1 -> 158, fp32
-        // 64^3 153.6 -> 144.  With more to a row the blocks run less level: from 176 workgroups on only (one cell per lane and two wavefronts
-        // 182 workgroups 138.8 -> 131.3, 128 135 -> 138, 132 279 -> 285, fp32 80 149 -> 158; fp32 128^3 281 -> 258, 72^3 190 -> 202),
-        // and not in fp64 with two cells (128^3 391 -> 378, but 196 x 115 x 140 792 -> 801).
-        if constexpr (C == 1 && NXW == 1) __builtin_amdgcn_s_sleep(sizeof(T) == 8 ? 5 : 9);
-        else if constexpr (C == 1 || sizeof(T) == 4)
-            if (gridDim.x >= 176) __builtin_amdgcn_s_sleep(sizeof(T) == 8 ? 5 : 8);
+        // one a way to memory and back later.  A launch of few workgroups, and one whose wavefronts have many rows, ends an exchange sooner than
+        // the wait does, or runs less level, and loses by it: so it depends on the rows, and on the workgroups from which on it measured faster.  Us per
+        // 100 iterations with scatter and gather, at once -> after this wait (5 to 9 times 64 clocks; 3 more or less are up to 3 % slower or, 64^3 with
+        // 8, 2 % faster):
+        //   one cell, one wavefront to a row: 2 x 2 rows, 121 workgroups 180 -> 172, fp32 203 182 -> 167 (8: 123 -> 128, not told apart: the
+        //     branch would cost the others as much); 3 x 3, 111: 210 -> 199 (63: 184 -> 189); 4 x 4, 115: 269 -> 261 (98: 248 -> 253, but 120: 249
+        //     -> 255, too), fp32 209: 256 -> 241 (96: 197 -> 204); 6 x 6, 176: 470 -> 446 (120: 394 -> 399), fp32 181: 353 -> 323 (111: 283 -> 289)
+        //   two wavefronts, fp64: 3 x 3 and 4 x 3, 176 to 255 workgroups 2 to 7 % faster (128: 135 -> 138); 4 x 4, 204 to 253 2 to 4 (182: 298 ->
+        //     302); 5 x 5 from 0.8 % faster to 1.6 slower; 6 x 6 up to 2 % slower up to 208, then the same.  Two cells: 128^3 391 -> 378, but
+        //     196 x 115 x 140 792 -> 801
+        //   fp32, two wavefronts or more cells: up to 5 x 5, 176 to 256 1 to 9 % faster (80: 149 -> 158); more rows, 200 to 256 the same to 2 % faster
+        //     (6 x 6, 176: 418 -> 426)
+        constexpr bool F64 = sizeof(T) == 8;
+        constexpr unsigned NEVER = ~0u, ROWS = RZ * RY;
+        constexpr unsigned WAIT_FROM = C == 1 && NXW == 1 ? (RZ <= 2 || (RZ == 3 && !F64) ? 0 : RZ == 3 ? 70 : RZ == 4 || !F64 ? 112 : 176)
+                                       : F64              ? (C > 1 || ROWS >= 25 ? NEVER : ROWS >= 16 ? 200 : 176)
+                                                          : (ROWS > 25 ? 200 : 176);
+        if constexpr (WAIT_FROM != NEVER)
+            if (WAIT_FROM == 0 || gridDim.x >= WAIT_FROM) __builtin_amdgcn_s_sleep(F64 ? 5 : NXW == 1 && C == 1 ? 9 : 8);
         for (unsigned n = 0; want_z || want_y;) {
             ByteTagged<T, NZ> mz;
             ByteTagged<T, NY> my;
