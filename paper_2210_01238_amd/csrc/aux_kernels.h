@@ -168,8 +168,8 @@ __global__ __launch_bounds__(WG) void halo_exchange_kernel(Geo g, T *grid, int c
 // vectors that are 16-byte aligned there, and reads the source with 16-byte loads that are only element-aligned
 // (the tiles' rows start on cache lines, the global array's rows one ring cell off them).  Bound by HBM, which takes
 // many short wavefronts best: a lane of a large grid moves ONE vector, so that a wavefront reads 1 KiB, writes it and is gone
-// (four per lane, read then written: 5.4 - 5.6 TB/s; one: 5.7 - 6.4, and 1.25 to 1.3 ns per workgroup, about what it takes to start
-// them).  us, one cell per lane and load -> four vectors -> now:
+// (four per lane, read then written: 5.4 - 5.6 TB/s; one: 5.7 - 6.4, 1.27 to 1.38 ns per workgroup).
+// us, one cell per lane and load -> four vectors -> now:
 //   16384^2 in 8 x 8 tiles:    scatter  893 ->  765 ->  720       gather  870 ->  776 ->  676
 //   8192^2 in 64 x 64 tiles:            220 ->  178 ->  171               246 ->  176 ->  172
 //   1024 x 1024 x 768, 6x8x8:          3033 -> 2330 -> 2210              3179 -> 2320 (four vectors still)
@@ -177,7 +177,9 @@ __global__ __launch_bounds__(WG) void halo_exchange_kernel(Geo g, T *grid, int c
 //   300^3, 30x30x30, fp32:             1059 ->  154 ->  156               1064 ->   90 (two)
 // ------------------------------------------------------------------------------------
 // Vectors per thread of the scatter, all loaded before the first is stored.  Grids that stay in the caches take two: 128^3 in one
-// tile 6.9 us against 8.0 with one, larger ones the same.
+// tile 6.9 us against 8.0 with one, larger ones the same.  Grids of 135 to 270 MB, which just do not, take one for what else is done with them: 256^3,
+// fp64, 43.1 us with four, 42.2 with two, 46.5 with one if nothing but the scatter runs, again and again; 98.8, 97.8 and 101.9 with a gather between,
+// 160.5, 159.3 and 158.5 with two updates; 300^3 62.9, 62.4, 67.0; 154, 148, 144; 271, 264, 260.
 template <bool STREAM> constexpr int SC_VECS = STREAM ? 1 : 2;
 constexpr int sc_unit(bool stream) { return (stream ? SC_VECS<true> : SC_VECS<false>) * WG; }      // vectors a workgroup copies (4 or 8 KiB)
 constexpr int LINE_BYTES = 128;               // a cache line

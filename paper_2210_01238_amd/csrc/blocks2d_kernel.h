@@ -281,10 +281,12 @@ __global__ __launch_bounds__(BLK_WAVES * WAVE) void blocks2d_kernel(Geo g, Block
         }
         // ghost cells: a few rows at a time, each lane's until all of their words carry the tag
         // Blocks run level with each other, so asked at once the first question comes just too early and the answer to the second
-        // one a way to memory and back later: 900 clocks first.  Us per 100 iterations with scatter and gather, at once -> so (12 to
-        // 20 times 64 clocks: the same within 2 %): 256^2 68.6 -> 65.5, 420^2 79.7 -> 73, 650^2 99.5 -> 95, fp32 420^2 64.7 -> 59, 650^2 79.6 -> 73;
-        // 808 x 444 with a norm every 4 iterations 56.9 -> 57.6, of 40 random calls the only one longer.  With more cells per lane the rows are asked for in portions, one after the other, and a wait gives nothing (1024^2 129.2 ->
-        // 130.7 with 8, 1536^2 207.5 -> 206.1, 2048^2 the same).
+        // one a way to memory and back later: 900 clocks first.  Us per 100 iterations with scatter and gather, at once -> so: 256^2 68.6
+        // -> 65.5, 420^2 79.7 -> 71.2, 650^2 99.5 -> 93.7, fp32 420^2 64.7 -> 59.1, 650^2 79.6 -> 73.8; of 148 grids of one cell per lane none more than
+        // 1 % longer, 20 % shorter at most.  One wait for all: 51 workgroups and fewer are 2 % slower with 20, from 180
+        // on more would be better for some (of 64 clocks each, 14, 20, 24: 150 x 1800 77.5, 75.6, 75.2, fp32 650^2 73.8, 68.6, 67.5, but fp32 512^2
+        // 58.5, 58.4, 59.2, 150 x 1800 61.4, 62.4, 63.4).  With more cells per lane the rows are asked for in portions, one after the
+        // other, and a wait gives nothing (1024^2 129.2 -> 130.7 with 8, 1536^2 207.5 -> 206.1, 2048^2 the same).
         if constexpr (C == 1) __builtin_amdgcn_s_sleep(14);
         constexpr int CELLS = sizeof(T) == 8 ? 8 : 16, RB = C >= CELLS ? 1 : CELLS / C < RW ? CELLS / C : RW;
 #pragma unroll

@@ -522,7 +522,8 @@ bool tc3d_usable(const jacobi_plan *p, int depth)
     const Geo &g = p->geo;
     const int nv = 16 / (int)p->esize;
     return p->cooperative && g.ndim == 3 && depth >= jk::TC3D_MIN && depth <= jk::TC3D_MAX && g.tw % nv == 0 &&
-           g.td >= depth && (int64_t)g.Ty * g.th < 0x7fffffffLL - 64 && (int64_t)g.Tz * g.td < 0x7fffffffLL - 64 &&
+           g.td >= depth &&      // the kernel would take thinner tiles; they keep their shallower schedule, no other has been measured
+           (int64_t)g.Ty * g.th < 0x7fffffffLL - 64 && (int64_t)g.Tz * g.td < 0x7fffffffLL - 64 &&
            (int64_t)g.Tx * g.tile_stride * (int64_t)p->esize < 0x7fffffffLL;   // per-lane byte offsets are 32-bit
 }
 
@@ -1337,7 +1338,10 @@ int launch_gather_t(jacobi_plan *p, const T *grid, T *to, hipStream_t st)
     // caches, a lane takes one from 16 times 64 vectors on (1 -> 4 vectors: 16384^2 676 -> 776 us, 8000^2 in one tile 158 -> 182,
     // 8190 x 9001 181 -> 215, 12000 x 2100 49.2 -> 49.9); the last wavefront of a row, mostly idle, costs as much as the others, which
     // shorter rows would feel (1024 x 1024 x 768: 2337 -> 2321, 512^3 410 -> 392).  Cached: 2000 x 4200 19.6 -> 19.2; fp32, where a
-    // wavefront has more instructions for its seams: 8000 x 12000 132 -> 131, 4096^2 21.4 -> 19.2.
+    // wavefront has more instructions for its seams: 8000 x 12000 132 -> 130, 5000 x 8000 46.2 -> 47.4, 4096^2 21.4 -> 19.2 (but 16384^2 in one tile 330 ->
+    // 366).  A wavefront's vectors follow each other.  Where they alternate with those of its workgroup's other wavefronts, in fp32: 16384^2 in 8 x 8
+    // tiles 364 -> 362 us, in one 366 -> 378, 12000 x 16000 275 -> 273, 2000 x 30000 70.6 -> 75.9, 40 x 700 x 9000 356 -> 368; fp64, cached, 900 x 16000
+    // and 2500 x 6000 the same.
     const bool stream = store_flavour(p) != 0;
     const int64_t nrows = (int64_t)gp.plane_rows * (g.ndim == 3 ? p->lay.dims[0] + 2 : 1);
     const int64_t vecs = ceil_div((int64_t)gp.GP + line - 1, nv);
